@@ -123,6 +123,8 @@ typedef struct lce_adamw {
  * 160 MiB / (2*D) rounded down to 6144), or, where it gives the dW launches fewer
  * workgroup rounds, another multiple of 768 between max(8192, 4*D) and
  * min(24576, 160 MiB / (2*D)) (lce_plan_info reports the width): never O(N*V).
+ * Calls of few tokens (a slab of that width times the tokens is at most 1024 tiles of
+ * 384 x 256) take the fewest equal slabs that keep the [N, V_slab] bf16 block within 1.25 GiB.
  * The backward's size does not depend on V; the forward's vocabulary partials
  * take at most 2*D bytes per token. Either output pointer may be NULL.
  */

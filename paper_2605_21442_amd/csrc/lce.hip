@@ -1950,6 +1950,28 @@ int64_t whole_round_slab(int64_t v, int64_t d, int64_t vc) {
   return best * 384;
 }
 
+// Few tokens: at the width vc chosen above a slab's G launch is then only a few workgroup rounds, of
+// which the last, partial one costs most of a round, and every slab pays its launches and a pass over
+// the fp32 dH accumulators. When a slab has at most 1024 tiles of 384 ids x 256 tokens (4 rounds of 256
+// CUs), the vocabulary is cut into as few equal slabs as keep G within kFewTokenG: one, up to 4096
+// tokens of a 158208-id vocabulary. Measured, one slab against the rule's (us per step):
+//   2048 x 4096 x 128256 (7 slabs of 48 x 6 live tiles): G 1911 -> 1323, step 7130 -> 6650;
+//   1948 x 3584 x 152064 (8 slabs): G 1793 -> 1380, step 6700 -> 6280;
+//   4096 x 4096 x 128256 (7 slabs of 48 x 12): G 2950 -> 2490, step 10310 -> 9990;
+//   4096 x 2048 x 128256 (6 slabs of 64 x 12, whole rounds): G 1340 -> 1307, step 5370 -> 5300.
+// Above 1024 tiles a partial round is a small share (8192 x 2048 x 128256: 8 rounds) and the memory
+// stays with the rule.
+constexpr int64_t kFewTokenTiles = 1024;
+constexpr int64_t kFewTokenG = (int64_t)1280 << 20;
+int64_t few_token_slab(int64_t v, int64_t npad, int64_t vc) {
+  if (vc / 384 * (npad / TILE) > kFewTokenTiles) return vc;
+  int64_t cap = kFewTokenG / (2 * round_up(npad, 384)) / 768 * 768;
+  cap = std::min<int64_t>(cap, 0x7FFFFFFF / (2 * TILE) / 768 * 768);   // G offsets within a token tile
+  if (cap <= vc) return vc;
+  const int64_t slabs = (v + cap - 1) / cap;
+  return round_up((v + slabs - 1) / slabs, 768);
+}
+
 lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true) {
   if (!p) return LCE_ERR_NULL;
   if ((p->flags & ~(LCE_FLAG_ACCUMULATE_DW | LCE_FLAG_REUSE_FORWARD)) != 0) return LCE_ERR_ARG;
@@ -1978,7 +2000,8 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   // fp32 accumulator passes further (the distillation calls keep the narrow slab: their teacher
   // probabilities take 4 bytes per slab id and token). A multiple of 16 tiles of 384 ids, so that
   // the dW launch of a 4096-wide head is whole rounds of workgroups on 256 CUs; for other widths
-  // whole_round_slab picks the width whose dW launches leave the fewest idle CUs.
+  // whole_round_slab picks the width whose dW launches leave the fewest idle CUs. Calls of few
+  // tokens take wider slabs, up to the whole vocabulary (few_token_slab).
   int64_t vc = 4 * p->d;
   if (wide_slabs) vc = std::max<int64_t>(vc, std::min<int64_t>(24576, kGroupBytes / (2 * p->d) / 6144 * 6144));
   if (vc < 8192) vc = 8192;
@@ -1990,6 +2013,7 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   // leave the MALL)
   pl->gw = vc / 384;
   if (wide_slabs && vc < vround) vc = whole_round_slab(p->v, p->d, vc);
+  if (wide_slabs && vc < vround) vc = few_token_slab(p->v, pl->npad, vc);
   pl->vc = vc;
   pl->nslab = (p->v + vc - 1) / vc;
   if ((uint64_t)TILE * pl->npad * 2 > 0x7FFFFFFFull || (uint64_t)TILE * vc * 2 > 0x7FFFFFFFull) return LCE_ERR_SHAPE;

@@ -374,3 +374,24 @@ def test_forward_and_g_blocks_cover_every_tile_once_and_keep_w_tiles_on_one_xcd(
             assert tm % 8 == b % 8          # each XCD keeps its own W tiles of the aligned part
         else:
             assert tn % 8 == b % 8          # and its own token tiles of the last few vocabulary tiles
+
+
+@pytest.mark.parametrize("n,d,v,nslab", [(2048, 4096, 128256, 1), (1948, 3584, 152064, 1), (4096, 8192, 128256, 4),
+                                         (4096, 1024, 152064, 1), (4096, 1024, 170000, 2), (4000, 256, 1000001, 7),
+                                         (1, 64, 6000000, 4), (8192, 2048, 128256, 6), (16384, 4096, 128256, 7)])
+def test_few_token_calls_take_the_fewest_equal_slabs_within_the_budget(n, d, v, nslab):
+    info = B.lce_plan_info(B.problem(n, d, v))
+    vc = info["vc"]
+    assert info["nslab"] == nslab == cdiv(v, vc) and vc % 768 == 0
+    rule = rup(max(8192, 4 * d, min(24576, (160 << 20) // (2 * d) // 6144 * 6144)), 6144)
+    if rule // 384 * (info["npad"] // 256) > 1024:      # many tokens: the width of the rule (or near it: whole rounds)
+        assert vc <= max(rule, 24576)
+        return
+    assert 2 * info["rows_g"] * vc <= 1280 << 20
+    assert vc - cdiv(v, nslab) < 768                    # equal slabs
+    if nslab > 1:                                       # and one slab fewer would not fit G or a token tile's offsets
+        w = rup(cdiv(v, nslab - 1), 768)
+        assert 2 * info["rows_g"] * w > 1280 << 20 or 512 * w > 2 ** 31 - 1
+    for nv in (1, n):
+        e, sizes, _ = walk(n, d, v, nv)
+        e.check(sizes, f"n={n} d={d} v={v} nv={nv}")

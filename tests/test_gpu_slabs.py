@@ -1,0 +1,27 @@
+"""Vocabulary slabs on the GPU against the oracle, either side of the few-token rule: calls whose whole
+vocabulary is one slab although it is far wider than the rule's width for many tokens, and calls of
+more than 4096 tokens, whose vocabulary takes several slabs (the dH accumulators are added to slab by
+slab, the last slab is ragged)."""
+import numpy as np
+import pytest
+
+from oracle import lce_oracle as O
+from paper_2605_21442_amd import binding as B
+from paper_2605_21442_amd import workloads as WL
+from tests import lce_testutil as U
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,d,v,mask,reduction,nslab", [
+    (4400, 64, 50001, 0.3, "mean", 3), (4353, 192, 26000, 0.0, "sum", 2),
+    (700, 128, 50001, 0.2, "mean", 1), (257, 264, 33000, 0.1, "none", 1), (1, 64, 100000, 0.0, "mean", 1)])
+def test_slabs_match_the_oracle(n, d, v, mask, reduction, nslab):
+    assert B.lce_plan_info(B.problem(n, d, v))["nslab"] == nslab
+    inp = WL.custom(n, d, v, seed=n, mask_frac=mask, sigma_w=0.3, case_id=53)
+    grad = np.random.default_rng(n).standard_normal(n).astype(np.float32) if reduction == "none" else 1.0
+    print(f"case n={n} d={d} v={v} {reduction} slabs={nslab}", flush=True)
+    h, w, t = U.to_device(inp)
+    gpu = U.run_gpu(h, w, t, inp.ignore_index, reduction, grad)
+    U.assert_parity(gpu, O.lce(inp.h_bits, inp.w_bits, inp.targets, inp.ignore_index, reduction,
+                               grad.astype(np.float64) if reduction == "none" else 1.0))
