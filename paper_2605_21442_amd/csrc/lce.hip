@@ -1125,21 +1125,25 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict_
   }
 }
 
-// Tile scheduling of the dH launches whose K the host splits into parts (launches with fewer
-// tiles than CUs; one copy of this grid per part). Workgroups are dispatched round-robin over the
-// 8 XCDs (block b runs on XCD b % 8), each with its own L2. XCD x owns the band of row tiles
-// [x T / 8, (x + 1) T / 8) (T = live row tiles) and walks it column by column, so the workgroups
-// resident on one XCD share the band's A tiles and a few B tiles in its L2, and each A operand is
-// fetched by one XCD only. The grid is 8 * ceil(T_max / 8) * tn_count blocks; blocks past the live
-// tiles return false.
-__device__ __forceinline__ bool band_tile(int blk, int tm_live, int tn_count, int& tm, int& tn) {
-  const int x = blk & 7, k = blk >> 3;
-  const int r0 = (x * tm_live) >> 3, r1 = ((x + 1) * tm_live) >> 3;
-  const int rows = r1 - r0;
-  if (rows <= 0 || k >= rows * tn_count) return false;
-  tm = r0 + k % rows;
-  tn = k / rows;
-  return true;
+// dH launches with fewer output tiles than CUs: K is split so that every CU has a block. The host
+// reserves kz_max accumulators (2 to 8); the parts taken follow from the live tile count t = ceil(Nv
+// / 384) x ceil(D / 256): the number whose rounds of 256 units take the least K together (64 tiles: 4
+// parts, one round; 144 tiles: 3 parts, two rounds of a third of K each). The t * parts units
+// (part-major) are cut into 8 equal shares, one per XCD, so that all XCDs work whatever the number of row tiles, and an XCD's
+// blocks walk one or two K ranges of G and W in step, which its L2 then reads once. (With whole row
+// tiles dealt to the XCDs instead, 4 row tiles kept 4 of the 8 XCDs busy: dH of 2048 x 4096 x 128256
+// with 1536 valid tokens 2500 us, now 1154; of 1948 x 3584 x 152064 2220 -> 1257; of 4096 x 2048 x
+// 128256, whose 64 tiles took 3 parts by N and take 4 by Nv, 1365 -> 1133.)
+__device__ __forceinline__ int dh_split_parts(int t, int kz_max) {
+  int best = 1, rounds = (t + 255) / 256;
+  for (int kz = 2; kz <= kz_max; ++kz) {
+    const int r = (t * kz + 255) / 256;
+    if (r * best < rounds * kz) {
+      best = kz;
+      rounds = r;
+    }
+  }
+  return best;
 }
 
 // dH launches whose K the host did not split. With T = tm_live x dt live output tiles (tm_live =
@@ -1589,12 +1593,12 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_dw(const uint16_t* __re
 
 // K6: dH32[m][dd] (+)= sum_k G[m][k] Ws[k][dd] over the slab's k < vs; rows m < Nv. Ws = W + v0 ldw
 // is the slab's first row, read K-major (transposing LDS reads); ws_rows = V - v0 rows follow.
-// kz > 1 splits K in kz parts for launches with fewer output tiles than CUs: the blocks of part z
-// (the z-th kz-th of the grid) accumulate into accumulator z, at dH32 + z (dH32b - dH32) (the
-// parts follow each other), and the finalise adds the kz accumulators in a fixed order.
-// One dH tile (block blk of a dH grid of `grid` blocks, smem the workgroup's LDS).
+// kz > 1 splits K in up to kz parts (dh_split_parts) for launches with fewer output tiles than CUs:
+// part z accumulates into accumulator z, at dH32 + z (dH32b - dH32) (the parts follow each other),
+// and the finalise adds the accumulators in a fixed order.
+// One dH tile (block blk of the dH grid, smem the workgroup's LDS).
 template <int WM>
-__device__ __forceinline__ void dh_tile(char* smem, int blk, int grid, const uint16_t* __restrict__ G, int vc, int vs,
+__device__ __forceinline__ void dh_tile(char* smem, int blk, const uint16_t* __restrict__ G, int vc, int vs,
                                         const uint16_t* __restrict__ Ws, int64_t ldw, int64_t ws_rows, int d,
                                         const int* __restrict__ nv_ptr, float* __restrict__ dH32, int accumulate,
                                         int kz, float* __restrict__ dH32b, int acc_rows) {
@@ -1608,11 +1612,14 @@ __device__ __forceinline__ void dh_tile(char* smem, int blk, int grid, const uin
   float* acc_tile;
   int ldacc, cb;
   if (kz > 1) {
-    // the host split every tile's K into kz parts (launches with fewer tiles than CUs)
-    const int g1 = grid / kz;
-    z = blk / g1;
-    kzl = kz;
-    if (!band_tile(blk - z * g1, tm_live, dt, tm, tn)) return;
+    // every tile's K in kzl parts (launches with fewer tiles than CUs)
+    const int t = tm_live * dt;
+    if (t == 0) return;
+    kzl = dh_split_parts(t, kz);
+    const int u = t * kzl, x = blk & 7, l = dh_c0(x, u) + (blk >> 3);
+    if (l >= dh_c0(x + 1, u)) return;
+    z = l / t;
+    dh_band_tile(l - z * t, tm_live, dt, tm, tn);
     acc_tile = (z ? dH32 + (int64_t)z * (dH32b - dH32) : dH32) + (int64_t)tm * TM * d;
     ldacc = d;
     cb = tn * TILE;
@@ -1723,7 +1730,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_dh(const uint16_t* __re
                                                         float* __restrict__ dH32, int accumulate, int kz,
                                                         float* __restrict__ dH32b, int acc_rows) {
   __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
-  dh_tile<WM>(smem, (int)blockIdx.x, (int)gridDim.x, G, vc, vs, Ws, ldw, ws_rows, d, nv_ptr, dH32, accumulate, kz,
+  dh_tile<WM>(smem, (int)blockIdx.x, G, vc, vs, Ws, ldw, ws_rows, d, nv_ptr, dH32, accumulate, kz,
               dH32b, acc_rows);
 }
 
@@ -1732,7 +1739,7 @@ __global__ __launch_bounds__(256) void k_dh_finalize(const float* __restrict__ d
                                                      const int* __restrict__ pos, int64_t n, int d,
                                                      uint16_t* __restrict__ dH, float* __restrict__ dHf,
                                                      int has_slabs, const int* __restrict__ nv_ptr, int acc_rows) {
-  // kz accumulators (the K parts of split dH launches), `part` elements apart, added in order;
+  // kz > 1: the accumulators of the K parts the dH launches took, `part` elements apart, added in order;
   // with kz = 1, the slots of the tail tiles' K parts z = 1, 2, ... after part 0 (dh_tile)
   const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
   if (e >= n * d) return;
@@ -1749,10 +1756,12 @@ __global__ __launch_bounds__(256) void k_dh_finalize(const float* __restrict__ d
   if (p >= 0 && has_slabs) {
     a = *reinterpret_cast<const float4*>(dH32 + (int64_t)p * d + col);
     b = *reinterpret_cast<const float4*>(dH32 + (int64_t)p * d + col + 4);
-    for (int z = 1; z < kz; ++z) add(dH32 + z * part + (int64_t)p * d + col);
-    if (kz == 1) {
-      const int nv = *nv_ptr;
-      const int tm_live = (nv + 383) / 384, dt = (d + TILE - 1) / TILE, t = tm_live * dt;
+    const int nv = *nv_ptr;
+    const int tm_live = (nv + 383) / 384, dt = (d + TILE - 1) / TILE, t = tm_live * dt;
+    if (kz > 1) {
+      const int kzl = dh_split_parts(t, kz);
+      for (int z = 1; z < kzl; ++z) add(dH32 + z * part + (int64_t)p * d + col);
+    } else {
       if (dh_tail_fits(t, tm_live, d, acc_rows)) {
         const int tm = p / 384, tn = col / TILE;
         const int l = dh_band_index(tm, tn, tm_live, dt);
@@ -1879,7 +1888,7 @@ struct Plan {
   // workspace offsets; idx, pos, Nv and the gathered rows Hv form a prefix both passes share
   size_t o_idx, o_pos, o_nv, o_hv, o_pm, o_ps, o_terms, fwd_bytes;
   size_t o_g, o_dh32, o_dh32b, bwd_bytes;    // o_dh32b: accumulator of the second K part (or 0)
-  int dh_kz;                                 // K parts of the dH launches (1 to 8)
+  int dh_kz;                                 // most K parts a dH launch takes (1 to 8)
   int part_rows;                             // partial rows of the forward statistics
 };
 
@@ -2041,10 +2050,11 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   // the last token rows reach past Npad), so that no access leaves its region
   pl->rows_g = round_up(pl->npad, 384);
   pl->o_g = take(cur, 2 * (size_t)pl->rows_g * vc);
-  // dH launches with fewer 384 x 256 output tiles than the 256 CUs split K into kz parts (enough
-  // to give every CU a block, at most 8), each accumulated in an accumulator of its own
+  // dH launches with fewer 384 x 256 output tiles than the 256 CUs split K into parts (at most 8), each
+  // accumulated in an accumulator of its own; the kernel takes as many as the live tiles (of Nv, not N,
+  // tokens) leave CUs for, so twice as many are reserved as the tiles of all N tokens would take
   const int64_t dh_tiles = (pl->npad + 383) / 384 * ((p->d + TILE - 1) / TILE);
-  pl->dh_kz = (int)std::min<int64_t>(8, (256 + dh_tiles - 1) / dh_tiles);
+  pl->dh_kz = dh_tiles >= 256 ? 1 : (int)std::min<int64_t>(8, (512 + dh_tiles - 1) / dh_tiles);
   const size_t part = 4 * (size_t)pl->rows_g * p->d;     // a multiple of 256 bytes
   pl->o_dh32 = take(cur, part * pl->dh_kz);
   pl->o_dh32b = pl->dh_kz > 1 ? pl->o_dh32 + part : 0;
@@ -2365,9 +2375,9 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
           (int64_t)0, to.gw);
       }
     }
-    // split launches: kz copies of the banded grid; otherwise 8 XCDs x 32 CUs x (whole rounds of the
+    // split launches: a block for each part the tiles may take; otherwise 8 XCDs x 32 CUs x (whole rounds of the
     // largest per-XCD share + one round for the split tail)
-    const unsigned bdh = pl.dh_kz > 1 ? (unsigned)(pl.dh_kz * 8 * ((dh_tiles + 7) / 8) * dt)
+    const unsigned bdh = pl.dh_kz > 1 ? (unsigned)((pl.dh_kz * dh_tiles * dt + 7) / 8 * 8)
                                       : (unsigned)(256 * (((int64_t)dh_tiles * dt + 7) / 8 / 32 + 1));
     const int tmw = (vs + Geo<kDwWM>::TM - 1) / Geo<kDwWM>::TM;
     const unsigned bdw = (unsigned)(8 * (((int64_t)tmw * dt + 7) / 8));

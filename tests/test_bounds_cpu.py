@@ -395,3 +395,34 @@ def test_few_token_calls_take_the_fewest_equal_slabs_within_the_budget(n, d, v, 
     for nv in (1, n):
         e, sizes, _ = walk(n, d, v, nv)
         e.check(sizes, f"n={n} d={d} v={v} nv={nv}")
+
+
+def dh_split_blocks(n, nv, d, kz_max):
+    """(row tile, column tile, K part, parts) of every block of a split dH launch, as dh_tile maps them."""
+    tm_live, dtc = cdiv(nv, 384), cdiv(d, 256)
+    t = tm_live * dtc
+    kz = min(range(1, kz_max + 1), key=lambda k: (cdiv(t * k, 256) / k, k))
+    u = t * kz
+    for blk in range(rup(kz_max * cdiv(rup(n, 256), 384) * dtc, 8)):          # the host's dH grid
+        x, l = blk & 7, ((blk & 7) * u >> 3) + (blk >> 3)
+        if l >= ((x + 1) * u) >> 3:
+            continue
+        z, l = divmod(l, t)
+        band, k = divmod(l, 4 * dtc)
+        rows = min(4, tm_live - band * 4)
+        yield x, band * 4 + k % rows, k // rows, z, kz
+
+
+@pytest.mark.parametrize("n,d", [(256, 512), (1, 64), (700, 264), (2048, 4096), (1948, 3584), (4096, 2048), (4096, 4096),
+                                 (4352, 5120), (1536, 8192), (11008, 2048)])
+def test_split_dh_launches_cover_every_tile_and_part_once_on_all_xcds(n, d):
+    kz_max = B.lce_plan_info(B.problem(n, d, 9000))["dh_kz"]
+    assert kz_max > 1
+    for nv in sorted({1, max(n // 3, 1), max(3 * n // 4, 1), n}):
+        blocks = list(dh_split_blocks(n, nv, d, kz_max))
+        kz = blocks[0][4]
+        assert 1 <= kz <= kz_max
+        want = sorted((tm, tn, z) for tm in range(cdiv(nv, 384)) for tn in range(cdiv(d, 256)) for z in range(kz))
+        assert sorted(b[1:4] for b in blocks) == want
+        per_xcd = [sum(b[0] == x for b in blocks) for x in range(8)]
+        assert max(per_xcd) - min(per_xcd) <= 1

@@ -25,3 +25,24 @@ def test_slabs_match_the_oracle(n, d, v, mask, reduction, nslab):
     gpu = U.run_gpu(h, w, t, inp.ignore_index, reduction, grad)
     U.assert_parity(gpu, O.lce(inp.h_bits, inp.w_bits, inp.targets, inp.ignore_index, reduction,
                                grad.astype(np.float64) if reduction == "none" else 1.0))
+
+
+@pytest.mark.parametrize("n,d,nv,parts", [(256, 512, 230, 8), (700, 264, 1, 8), (2048, 1024, 1536, 8), (2048, 2048, 1537, 6),
+                                          (4096, 2048, 3072, 4), (4096, 2048, 4096, 5), (11008, 2048, 7000, 3)])
+def test_split_dh_parts_match_the_oracle_blockwise(n, d, nv, parts):
+    # the K parts a split dH launch takes follow from Nv; every 384 x 256 block of dH is compared
+    from tests.test_bounds_cpu import dh_split_blocks
+    from tests.test_gpu_dh_split import _inputs
+    kz_max = B.lce_plan_info(B.problem(n, d, 1000))["dh_kz"]
+    assert next(iter(dh_split_blocks(n, nv, d, kz_max)))[4] == parts
+    inp, valid = _inputs(n, d, nv, seed=7)
+    print(f"case n={n} d={d} nv={nv} parts={parts}", flush=True)
+    h, w, t = U.to_device(inp)
+    gpu = U.run_gpu(h, w, t, inp.ignore_index, "mean", 1.0)
+    ref = O.lce(inp.h_bits, inp.w_bits, inp.targets, inp.ignore_index, "mean", 1.0)
+    U.assert_parity(gpu, ref)
+    dh, dh_ref = gpu["dH"][valid], ref["dH"][valid]
+    for m0 in range(0, nv, 384):
+        for d0 in range(0, d, 256):
+            blk, rb = dh[m0:m0 + 384, d0:d0 + 256], dh_ref[m0:m0 + 384, d0:d0 + 256]
+            assert np.linalg.norm(blk - rb) <= U.GRAD_REL_TOL * np.linalg.norm(rb), (m0, d0)
