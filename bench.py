@@ -53,7 +53,7 @@ sys.path.insert(0, ROOT)
 PEAK_BF16_TFLOPS = 2500.0        # MI355X dense bf16 MFMA peak
 PEAK_HBM_GBS = 8000.0
 METRIC = "LCE fwd+bwd tokens/sec, % bf16 MFMA peak, peak HBM bytes (1 GPU)"
-GEMM_KERNELS = ("fwd_stats", "bwd_g", "bwd_dw", "bwd_dh")
+GEMM_KERNELS = {"fwd_stats": 1, "bwd_g": 1, "bwd_dw": 1, "bwd_dh": 1, "bwd_dhdw": 2}   # contractions a launch runs
 
 
 def _cpu_baseline(inp, seconds_target=10.0):
@@ -350,12 +350,12 @@ def main():
     flops_step = 8.0 * nvalid * d * v
     dom = max((k for k in kernels if k in GEMM_KERNELS), key=lambda k: kernels[k]["total_ms"])
     launches_per_step = kernels[dom]["launches"] / kpass
-    flops_launch = 2.0 * nvalid * d * v / launches_per_step
+    flops_launch = GEMM_KERNELS[dom] * 2.0 * nvalid * d * v / launches_per_step
     achieved = flops_launch / (kernels[dom]["avg_ms"] * 1e-3) / 1e12
     for k, r in sorted(kernels.items(), key=lambda kv: -kv[1]["total_ms"]):
         extra = ""
         if k in GEMM_KERNELS:
-            tf = 2.0 * nvalid * d * v / (r["launches"] / kpass) / (r["avg_ms"] * 1e-3) / 1e12
+            tf = GEMM_KERNELS[k] * 2.0 * nvalid * d * v / (r["launches"] / kpass) / (r["avg_ms"] * 1e-3) / 1e12
             extra = f" {tf:7.1f} TFLOP/s ({100 * tf / PEAK_BF16_TFLOPS:4.1f}% of peak)"
         print(f"[bench]   {k:12s} {r['total_ms'] / kpass:8.3f} ms/step  {r['launches']:5d} launches"
               f"  avg {r['avg_ms']:.4f} ms{extra}", file=sys.stderr)
@@ -493,10 +493,11 @@ def bench_kd(args, fused=False):
     nvalid = int(nv.item())
     # MFMA work per step and kernel (see the module docstring)
     work = {"fwd_stats": 2.0 * nvalid * v * (ds + dt), "kd_teacher_p": (2.0 if fused else 4.0) * nvalid * v * dt,
-            "bwd_g": 2.0 * nvalid * v * ds, "bwd_dw": 2.0 * nvalid * v * ds, "bwd_dh": 2.0 * nvalid * v * ds}
+            "bwd_g": 2.0 * nvalid * v * ds, "bwd_dw": 2.0 * nvalid * v * ds, "bwd_dh": 2.0 * nvalid * v * ds,
+            "bwd_dhdw": 4.0 * nvalid * v * ds}
     if not fused:
         work["kd_q"] = 2.0 * nvalid * v * ds
-    flops_step = sum(work.values())
+    flops_step = sum(work[k] for k in work if k in kernels)
     ms_step = elapsed * 1e3 / args.steps
     for kname, r in sorted(kernels.items(), key=lambda kv: -kv[1]["total_ms"]):
         extra = ""

@@ -15,7 +15,8 @@
 //   backward: compact -> gather Hv (both skipped when the forward's are reused) -> per
 //             vocabulary slab: G tile (recompute S^T, G = c (softmax - onehot)),
 //             dH32 (+)= G W_slab (K split into parts where a launch would leave CUs idle),
-//             dW slab = G^T Hv -> finalise dH (parts added in order)
+//             dW slab = G^T Hv (one launch with dH where few tiles would leave CUs idle) ->
+//             finalise dH (parts added in order)
 // Built on the same kernels: the backward with an AdamW step on each finished dW block
 // (paper Sec. 4.1), a vocabulary-shard (loss-parallel) forward / combine / backward, and a
 // fused linear knowledge-distillation loss whose G kernel takes the teacher's probabilities
@@ -1734,6 +1735,27 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_dh(const uint16_t* __re
               dH32b, acc_rows);
 }
 
+// K5 and K6 of one slab in one launch: the first dh_blocks blocks are the dH launch, the others the dW
+// launch (neither reads what the other writes). Blocks start in order, so the dH tiles, few and long (K =
+// the slab's ids), start first and the dW tiles, many and short (K = Nv), fill the CUs they leave idle
+// and the launches' two partial rounds become one.
+template <int kMode, int WM>
+__global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_dhdw(const uint16_t* __restrict__ G, int vc, int npad, int vs,
+                                                             const uint16_t* __restrict__ Ws, int64_t ldw,
+                                                             int64_t ws_rows, int d, const int* __restrict__ nv_ptr,
+                                                             float* __restrict__ dH32, int accumulate, int kz,
+                                                             float* __restrict__ dH32b, int acc_rows, int dh_blocks,
+                                                             const uint16_t* __restrict__ Hv, int tm_count,
+                                                             uint16_t* __restrict__ dW, int64_t v0) {
+  static_assert(kMode != DW_ADAMW, "the optimizer step of dW updates the W rows that dH reads");
+  __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
+  const int b = (int)blockIdx.x;
+  if (b < dh_blocks)
+    dh_tile<WM>(smem, b, G, vc, vs, Ws, ldw, ws_rows, d, nv_ptr, dH32, accumulate, kz, dH32b, acc_rows);
+  else
+    dw_tile<kMode, WM>(smem, b - dh_blocks, G, vc, npad, vs, Hv, d, nv_ptr, tm_count, dW, v0, AdamWState{}, AdamWConst{});
+}
+
 // K7: dH[row] = bf16(dH32[pos[row]]) for valid rows, +0.0 for the others. 8 elements per thread.
 __global__ __launch_bounds__(256) void k_dh_finalize(const float* __restrict__ dH32, int64_t part, int kz,
                                                      const int* __restrict__ pos, int64_t n, int d,
@@ -1863,10 +1885,10 @@ __global__ __launch_bounds__(256) void k_kd_terms(const float* __restrict__ qpar
 // Host side: validation, plan, workspace carve-up, launches, optional timing.
 // ---------------------------------------------------------------------------------------------
 enum KernelId { K_COMPACT = 0, K_FWD_STATS, K_COMBINE, K_LOSS, K_GATHER_H, K_BWD_G,
-                K_BWD_DW, K_BWD_DH, K_DH_FINAL, K_ADAMW, K_SHARD_COMBINE, K_KD_P, K_KD_Q, K_KD_TERMS, K_MISC,
+                K_BWD_DW, K_BWD_DH, K_BWD_DHDW, K_DH_FINAL, K_ADAMW, K_SHARD_COMBINE, K_KD_P, K_KD_Q, K_KD_TERMS, K_MISC,
                 K_COUNT };
 const char* const kKernelNames[K_COUNT] = {"compact", "fwd_stats", "combine", "loss", "gather_h",
-                                           "bwd_g", "bwd_dw", "bwd_dh", "dh_finalize", "adamw", "shard_combine",
+                                           "bwd_g", "bwd_dw", "bwd_dh", "bwd_dhdw", "dh_finalize", "adamw", "shard_combine",
                                            "kd_teacher_p", "kd_q", "kd_terms", "misc"};
 
 struct Timing {
@@ -2327,6 +2349,15 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
   void (*dw_kernel)(const uint16_t*, int, int, int, const uint16_t*, int, const int*, int, uint16_t*, int64_t,
                     AdamWState, AdamWConst) =
       adamw ? k_bwd_dw<DW_ADAMW, kDwWM> : accumulate ? k_bwd_dw<DW_ACCUMULATE, kDwWM> : k_bwd_dw<DW_STORE, kDwWM>;
+  // dH and dW of a slab as one launch (k_bwd_dhdw; not with the optimizer step, whose dW launch updates
+  // the W rows that dH reads) up to kMergeTiles dH tiles, 3 rounds of the CUs, of all N tokens. One launch
+  // against two, dH + dW: 4096 tokens of a 16032 x 8192 shard (352 tiles) 1706 -> 1283 us; 8192 x 8192 x
+  // 64000 (704) 11.5 -> 10.4 ms; 1948 x 3584 x 152064 (84) 2630 -> 2545 us; 256 x 512 x 4096 (2) 48 -> 25 us;
+  // 16384 x 4096 x 128256 (688) and 16384 x 2048 x 128256 (344) the same within 1 %; but 32768 x 3584 x
+  // 152064 (1204, several dH rounds anyway) 37.9 -> 38.3 ms.
+  static_assert(kDhWM == kDwWM, "one launch runs both");
+  constexpr int kMergeTiles = 768;
+  const bool merge = !adamw && (int64_t)dh_tiles * dt <= kMergeTiles;
   for (int64_t s = 0; s < pl.nslab; ++s) {
     const int64_t v0 = s * pl.vc;
     const int vs = (int)(pl.v - v0 < pl.vc ? pl.v - v0 : pl.vc);
@@ -2383,6 +2414,12 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
     const unsigned bdw = (unsigned)(8 * (((int64_t)tmw * dt + 7) / 8));
     // dH reads the slab's W rows before the dW launch, whose AdamW epilogue (in-backward step)
     // may update them; later slabs read only their own rows
+    if (merge) {
+      L(K_BWD_DHDW, accumulate ? k_bwd_dhdw<DW_ACCUMULATE, kDwWM> : k_bwd_dhdw<DW_STORE, kDwWM>, dim3(bdh + bdw),
+        dim3(Geo<kDwWM>::NT), (const uint16_t*)g, vc, npad, vs, w + v0 * pl.ldw, pl.ldw, pl.v - v0, d, (const int*)nv,
+        dh32, (int)(s > 0), pl.dh_kz, dh32b, (int)pl.rows_g, (int)bdh, (const uint16_t*)hv, tmw, dW, v0);
+      continue;
+    }
     L(K_BWD_DH, k_bwd_dh<kDhWM>, dim3(bdh), dim3(Geo<kDhWM>::NT), (const uint16_t*)g, vc, vs, w + v0 * pl.ldw, pl.ldw,
       pl.v - v0, d, (const int*)nv, dh32, (int)(s > 0), pl.dh_kz, dh32b, (int)pl.rows_g);
     L(K_BWD_DW, dw_kernel, dim3(bdw), dim3(Geo<kDwWM>::NT), (const uint16_t*)g, vc, npad, vs, (const uint16_t*)hv, d,

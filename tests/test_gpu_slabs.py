@@ -46,3 +46,28 @@ def test_split_dh_parts_match_the_oracle_blockwise(n, d, nv, parts):
         for d0 in range(0, d, 256):
             blk, rb = dh[m0:m0 + 384, d0:d0 + 256], dh_ref[m0:m0 + 384, d0:d0 + 256]
             assert np.linalg.norm(blk - rb) <= U.GRAD_REL_TOL * np.linalg.norm(rb), (m0, d0)
+
+
+@pytest.mark.parametrize("n,d,v,accumulate", [(8448, 4352, 700, False), (8600, 5888, 700, True), (8832, 8448, 400, False),
+                                              (300, 264, 1000, True), (500, 72, 26000, True)])
+def test_dh_and_dw_in_one_launch_or_two_match_the_oracle(n, d, v, accumulate):
+    # either side of the rule (768 dH tiles), with and without the accumulating dW epilogue; most rows
+    # ignored where the widths are large, so that the oracle stays quick
+    import torch
+    from paper_2605_21442_amd import autograd as A
+    rng = np.random.default_rng([n, d])
+    t = np.full(n, -100, dtype=np.int32)
+    valid = rng.choice(n, size=min(n, 420), replace=False)
+    t[valid] = rng.integers(0, v, size=len(valid), dtype=np.int32)
+    inp = WL.custom(n, d, v, seed=9, sigma_w=0.05, target_override=t)
+    print(f"case n={n} d={d} v={v} accumulate={accumulate}", flush=True)
+    h, w, tt = U.to_device(inp)
+    loss, lse, nv, _, ws = A.forward(h, w, tt, keep_workspace=True)
+    base = torch.randn((v, d), generator=torch.Generator("cuda").manual_seed(1), device="cuda").mul_(1e-3).bfloat16()
+    acc = base.clone() if accumulate else None
+    dh, dw = A.backward(h, w, tt, lse, nv, torch.ones(1, device="cuda"), accumulate_into=acc, workspace=ws)
+    ref = O.lce(inp.h_bits, inp.w_bits, inp.targets)
+    want = ref["dW"] + (base.float().cpu().numpy() if accumulate else 0.0)
+    assert abs(float(loss) - ref["loss"]) <= U.LOSS_ABS_TOL
+    assert U.rel_fro(dh.float().cpu().numpy(), ref["dH"]) <= U.GRAD_REL_TOL
+    assert U.rel_fro(dw.float().cpu().numpy(), want) <= U.GRAD_REL_TOL
