@@ -89,7 +89,7 @@ typedef struct lce_problem {
  * lce_backward_adamw rejects it (one update per backward pass). */
 #define LCE_FLAG_ACCUMULATE_DW 1
 
-/* For lce_backward, lce_backward_adamw and lce_backward_shard: the workspace still holds what the
+/* For lce_backward, lce_backward_select, lce_backward_adamw and lce_backward_shard: the workspace still holds what the
  * immediately preceding lce_forward (or lce_forward_shard, then lce_combine_shards) of the same
  * problem, H and targets left in it, on the same stream and with nothing else written to the
  * workspace in between. The backward then reuses that call's valid-row list (and, where the
@@ -194,6 +194,17 @@ lce_status_t lce_backward(const lce_problem_t* p,
                           const float* lse, const int32_t* n_valid, const float* grad_loss,
                           void* dH, void* dW,
                           void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * lce_backward of which only one gradient is wanted: dH or dW may be NULL (not both), and that
+ * gradient is not computed (a frozen head, as in LoRA fine-tuning, needs no dW; hidden states that
+ * need no gradient, no dH). The other is that of lce_backward, bit for bit.
+ */
+lce_status_t lce_backward_select(const lce_problem_t* p,
+                                 const void* H, const void* W, const void* targets,
+                                 const float* lse, const int32_t* n_valid, const float* grad_loss,
+                                 void* dH, void* dW,
+                                 void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * lce_forward for callers that cannot allocate device memory (code under HIP graph capture, tight

@@ -133,6 +133,20 @@ def backward(hidden: torch.Tensor, weight: torch.Tensor, targets: torch.Tensor, 
     return dh, dw
 
 
+def _backward_one(hidden, weight, targets, lse, n_valid, grad_loss, ignore_index, reduction, workspace, want_dh):
+    """The one gradient autograd asks for, by lce_backward_select: dH [N, D] (``want_dh``) or dW [V, D],
+    the bits of ``backward``."""
+    flags = B.LCE_FLAG_REUSE_FORWARD if workspace is not None else 0
+    p, h, w, t, g = _backward_args(hidden, weight, targets, lse, grad_loss, ignore_index, reduction, flags)
+    _, bwd_bytes = B.lce_workspace_size(p)
+    out = torch.empty((p.n, p.d) if want_dh else (p.v, p.d), dtype=torch.bfloat16, device=h.device)
+    ws = _workspace(workspace, bwd_bytes, h.device)
+    B.lce_backward_select(p, h.data_ptr(), w.data_ptr(), t.data_ptr(), lse.data_ptr(), n_valid.data_ptr(),
+                          g.data_ptr(), out.data_ptr() if want_dh else 0, 0 if want_dh else out.data_ptr(),
+                          ws.data_ptr(), bwd_bytes, _stream(h.device))
+    return out
+
+
 class AdamWState:
     """AdamW state of one bf16 weight [V, D] (paper Sec. 4.1): fp32 moments, an optional fp32
     master copy, the hyper-parameters and the step count. ``step_with(dW)`` is the two-phase
@@ -295,6 +309,11 @@ class LinearCrossEntropy(torch.autograd.Function):
         if g.dtype != torch.float32:
             g = g.float()
         ws, ctx.ws = ctx.ws, None     # used once: a second backward through the graph forms its own
+        want_h, want_w = ctx.needs_input_grad[:2]
+        # a tensor without elements has no address, which the library would take for an unwanted gradient
+        if want_h != want_w and hidden.numel() and weight.numel():
+            out = _backward_one(hidden, weight, targets, lse, nv, g, ctx.ignore_index, ctx.reduction, ws, want_h)
+            return (out.view(hidden.shape), None, None, None, None) if want_h else (None, out, None, None, None)
         dh, dw = backward(hidden, weight, targets, lse, nv, g, ctx.ignore_index, ctx.reduction, workspace=ws)
         return dh.view(hidden.shape), dw, None, None, None
 

@@ -44,7 +44,7 @@ EXPORTED = ("lce_workspace_size", "lce_forward", "lce_backward", "lce_status_str
             "lce_timing_read", "lce_adamw_step", "lce_backward_adamw", "lce_forward_shard",
             "lce_combine_shards", "lce_backward_shard", "lce_kd_workspace_size", "lce_kd_forward",
             "lce_kd_backward", "lce_kd_workspace_size_fused", "lce_kd_forward_backward", "lce_plan_info",
-            "lce_forward_noalloc")
+            "lce_forward_noalloc", "lce_backward_select")
 
 
 class LceError(RuntimeError):
@@ -123,6 +123,7 @@ def load() -> ctypes.CDLL:
         lib.lce_workspace_size.argtypes = [P, ctypes.POINTER(sz), ctypes.POINTER(sz)]
         lib.lce_forward.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         lib.lce_backward.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+        lib.lce_backward_select.argtypes = lib.lce_backward.argtypes
         A = ctypes.POINTER(LceAdamW)
         lib.lce_adamw_step.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, vp, vp, vp, vp, vp, A, vp]
         lib.lce_backward_adamw.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, A, vp, sz, vp]
@@ -150,7 +151,7 @@ def load() -> ctypes.CDLL:
                      "lce_timing_read", "lce_timing_kernel_count", "lce_adamw_step", "lce_backward_adamw",
                      "lce_forward_shard", "lce_combine_shards", "lce_backward_shard", "lce_kd_workspace_size",
                      "lce_kd_forward", "lce_kd_backward", "lce_kd_workspace_size_fused", "lce_kd_forward_backward",
-                     "lce_plan_info", "lce_forward_noalloc"):
+                     "lce_plan_info", "lce_forward_noalloc", "lce_backward_select"):
             getattr(lib, name).restype = ctypes.c_int
         _lib = lib
         return lib
@@ -198,6 +199,12 @@ def lce_backward(p: LceProblem, H: int, W: int, targets: int, lse: int, n_valid:
                  dH: int, dW: int, workspace: int, workspace_bytes: int, stream: int) -> None:
     _check(load().lce_backward(ctypes.byref(p), H, W, targets, lse, n_valid, grad_loss, dH, dW,
                                workspace, workspace_bytes, stream or None), "lce_backward")
+
+
+def lce_backward_select(p: LceProblem, H: int, W: int, targets: int, lse: int, n_valid: int, grad_loss: int,
+                        dH: int, dW: int, workspace: int, workspace_bytes: int, stream: int) -> None:
+    _check(load().lce_backward_select(ctypes.byref(p), H, W, targets, lse, n_valid, grad_loss, dH or None,
+                                      dW or None, workspace, workspace_bytes, stream or None), "lce_backward_select")
 
 
 def lce_adamw_step(v: int, d: int, ld_w: int, W: int, dW: int, exp_avg: int, exp_avg_sq: int,

@@ -311,3 +311,17 @@ def test_loading_the_library_first_keeps_one_hip_runtime_in_the_process():
     libs = eval(r.stdout.strip().splitlines()[-1])
     assert len(libs) == 1, libs
 
+
+
+def test_backward_select_rejects_what_it_cannot_run():
+    # host checks only: nothing is launched on these made-up addresses
+    p = B.problem(64, 64, 300)
+    _, bwd = B.lce_workspace_size(p)
+    ok = dict(H=0x100000, W=0x200000, targets=0x300000, lse=0x400000, n_valid=0x500000, grad_loss=0x600000, dH=0x700000,
+              dW=0x800000, workspace=0x900000, workspace_bytes=bwd, stream=0)
+    for change, code in [(dict(dH=0, dW=0), B.LCE_ERR_NULL), (dict(dH=0x700004), B.LCE_ERR_ALIGN),
+                         (dict(dW=0x800008, dH=0), B.LCE_ERR_ALIGN), (dict(dW=0, workspace_bytes=bwd - 1), B.LCE_ERR_WORKSPACE),
+                         (dict(dH=0, H=0), B.LCE_ERR_NULL), (dict(dW=0, lse=0), B.LCE_ERR_NULL)]:
+        with pytest.raises(B.LceError) as e:
+            B.lce_backward_select(p, **{**ok, **change})
+        assert e.value.code == code, change
