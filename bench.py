@@ -26,10 +26,9 @@ whole job's rate when G devices each run their share in parallel.
 ``kd`` times the fused linear knowledge-distillation loss (lce_kd_forward +
 lce_kd_backward, temperature 2) distilling the Llama-3.1-8B head (teacher,
 D = 4096) into the Llama-3.2-1B head (student, D = 2048) over 8 x 2048 tokens;
-its MFMA work per step is 6 Nv V Dt + 10 Nv V Ds (teacher statistics and two
-probability passes; student statistics, Q pass, G recompute, dW and dH).
-``kd_fused`` runs the same step as one lce_kd_forward_backward call: 4 Nv V Dt
-+ 8 Nv V Ds (one teacher probability pass, one student pass for G and Q).
+its MFMA work per step is 4 Nv V Dt + 8 Nv V Ds (teacher logits in the forward and
+its probabilities in the backward; student statistics, G recompute, dW and dH).
+``kd_fused`` runs the same step as one lce_kd_forward_backward call.
 
 Two diagnostics put the contractions' rate in context; neither is the benchmark:
 ``--data zeros`` runs the same launches on all-zero H and W (the workload's targets and mask),
@@ -492,11 +491,9 @@ def bench_kd(args, fused=False):
     kernels, kpass = _kernel_breakdown(B, step, args.steps)
     nvalid = int(nv.item())
     # MFMA work per step and kernel (see the module docstring)
-    work = {"fwd_stats": 2.0 * nvalid * v * (ds + dt), "kd_teacher_p": (2.0 if fused else 4.0) * nvalid * v * dt,
-            "bwd_g": 2.0 * nvalid * v * ds, "bwd_dw": 2.0 * nvalid * v * ds, "bwd_dh": 2.0 * nvalid * v * ds,
-            "bwd_dhdw": 4.0 * nvalid * v * ds}
-    if not fused:
-        work["kd_q"] = 2.0 * nvalid * v * ds
+    work = {"kd_teacher_z": 2.0 * nvalid * v * dt, "kd_student_stats": 2.0 * nvalid * v * ds,
+            "kd_teacher_p": 2.0 * nvalid * v * dt, "bwd_g": 2.0 * nvalid * v * ds, "bwd_dw": 2.0 * nvalid * v * ds,
+            "bwd_dh": 2.0 * nvalid * v * ds, "bwd_dhdw": 4.0 * nvalid * v * ds}
     flops_step = sum(work[k] for k in work if k in kernels)
     ms_step = elapsed * 1e3 / args.steps
     for kname, r in sorted(kernels.items(), key=lambda kv: -kv[1]["total_ms"]):

@@ -326,7 +326,9 @@ lce_status_t lce_backward_shard(const lce_problem_t* p, const lce_shard_t* shard
  *   G   = c (softmax(zs) - p_t) / T,  dHs = G Ws,  dWs = G^T Hs     (no teacher gradient)
  * Labels only define the valid set M (as for LCE: not ignore_index and in [0, V)). The loss
  * is not multiplied by T^2; neither logit matrix is ever held whole (the teacher's
- * probabilities exist one vocabulary slab at a time, in the workspace).
+ * logits or probabilities exist one vocabulary slab at a time, in the workspace; a call of few
+ * tokens, whose slab values fit 1.25 GiB, may take the whole vocabulary as one slab). The MFMA work
+ * is 2 Nv V (Dt + Ds) for the forward and 2 Nv V Dt + 6 Nv V Ds for the backward.
  */
 typedef struct lce_kd_problem {
   int64_t n;                /* tokens */
@@ -370,9 +372,7 @@ lce_status_t lce_kd_backward(const lce_kd_problem_t* p,
 /*
  * KD forward and backward in one call, for the usual case where the KD loss is the objective
  * being differentiated: grad_loss is read on the device when the gradient kernels run. The
- * teacher's probabilities are formed once per slab (not once in the forward and again in the
- * backward) and one student pass per slab yields both G and the loss's partial sums, so the MFMA
- * work is 4 Nv V Dt + 8 Nv V Ds instead of 6 Nv V Dt + 10 Nv V Ds. Outputs are those of
+ * valid-row list and the teacher's gathered rows are formed once. Outputs are those of
  * lce_kd_forward and lce_kd_backward, bit for bit. Workspace: lce_kd_workspace_size_fused.
  */
 lce_status_t lce_kd_workspace_size_fused(const lce_kd_problem_t* p, size_t* bytes);

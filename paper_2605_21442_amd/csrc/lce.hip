@@ -655,7 +655,7 @@ __device__ __forceinline__ Operand kmajor_operand(const uint16_t* base, int64_t 
 __global__ __launch_bounds__(1024) void k_compact(const void* targets, int tbytes, int64_t n, int64_t v,
                                                   int ignore, int* idx, int* pos, int* nv_ws,
                                                   int* nv_user, int* status, float* lse_zero,
-                                                  float* loss_zero) {
+                                                  float* loss_zero, float* zero3) {
   constexpr int kAhead = 16;
   __shared__ int wsum[2][16];
   __shared__ int bad_any;
@@ -697,6 +697,7 @@ __global__ __launch_bounds__(1024) void k_compact(const void* targets, int tbyte
           pos[i] = -1;
           if (lse_zero) lse_zero[i] = 0.0f;
           if (loss_zero) loss_zero[i] = 0.0f;
+          if (zero3) zero3[i] = 0.0f;
         }
       }
       base += total;
@@ -738,6 +739,16 @@ __device__ __forceinline__ void merge_pair(float& m, float& s, float m2, float s
   const float mn = fmaxf(m, m2);
   if (mn == -INFINITY) return;
   s = (m == -INFINITY ? 0.f : s * exp2f(m - mn)) + (m2 == -INFINITY ? 0.f : s2 * exp2f(m2 - mn));
+  m = mn;
+}
+
+// The same with a sum weighted by the same exponentials carried along (distillation).
+__device__ __forceinline__ void merge_weighted(float& m, float& s, float& q, float m2, float s2, float q2) {
+  const float mn = fmaxf(m, m2);
+  if (mn == -INFINITY) return;
+  const float a = m == -INFINITY ? 0.f : exp2f(m - mn), b = m2 == -INFINITY ? 0.f : exp2f(m2 - mn);
+  s = s * a + s2 * b;
+  q = q * a + q2 * b;
   m = mn;
 }
 
@@ -1206,14 +1217,21 @@ __device__ __forceinline__ float grad_scale(const float* grad, const int* n_norm
 // at or beyond Nv and of ids at or beyond the slab width are zeros, so the two contractions that
 // read G (dH with K = ids, dW with K = tokens, G read K-major) need no masking of G.
 // ---------------------------------------------------------------------------------------------
-// The same kernel serves the distillation loss (KD) with soft targets, in four modes:
-//   G_ONEHOT  LCE: G = c (softmax - onehot(t))
-//   G_SOFT    KD student: G = c (softmax(z/T) - P) / T, P the teacher's probabilities of this slab
-//   Q_SOFT    KD student forward: per token, sum over the tile's ids of P * z / T (partials qpart)
-//   P_WRITE   KD teacher: P = softmax(z/T) of this slab, fp32, P[v][token] (row stride ldt)
-//   G_SOFT_Q  KD student, forward and backward in one pass: G_SOFT and Q_SOFT together
+// The same kernel serves the distillation loss (KD) with soft targets, in four more modes:
+//   Z_WRITE   teacher, forward: the logits of this slab, fp32, P[v][token] (row stride ldt)
+//   KD_STATS  student, forward: per token, over the tile's ids, the (max, sum-exp) pairs of teacher and
+//             student logits / T and the teacher-weighted sum of the student's logits / T (qpart)
+//   P_WRITE   teacher, backward: P = softmax(z/T) of this slab, fp32, P[v][token]
+//   G_SOFT    student, backward: G = c (softmax(z/T) - P) / T
 // scale2 = log2(e) / T (log2(e) for LCE), inv_t = 1 / T; lse is that of the scaled logits.
-enum GMode { G_ONEHOT = 0, G_SOFT = 1, Q_SOFT = 2, P_WRITE = 3, G_SOFT_Q = 4 };
+//
+// The forward thus runs each head's contraction once: the weights exp(z_t/T - max) of the sum are taken
+// against the maximum of the tile's ids and the sums of all tiles are merged under their common maximum
+// (k_kd_combine), as the sum-exp itself. (Taken against the teacher's log-sum-exp, the sum needs both
+// heads' logits again after the statistics: 3072 valid tokens, 4096 -> 2048 wide, 128256 ids: forward
+// 9300 us, now 4760.)
+enum GMode { G_ONEHOT = 0, G_SOFT = 1, KD_STATS = 2, P_WRITE = 3, Z_WRITE = 4 };
+constexpr int kKdVals = 5;   // values per token and tile of KD_STATS: teacher max, sum, weighted sum; student max, sum
 
 template <int kMode, int WM>
 __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __restrict__ W, int64_t ldw, int64_t v0, int vs,
@@ -1227,7 +1245,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
                                                        float* __restrict__ qpart, int64_t qrow, int gsub) {
   // 12 waves (WM = 3, 384 ids per tile) serve the one-hot LCE gradient when D % 64 == 0; the
   // distillation modes and other widths keep 8 waves and the LDS-staged epilogue below
-  static_assert(WM == 2 || kMode == G_ONEHOT || kMode == P_WRITE, "");
+  static_assert(WM == 2 || kMode == G_ONEHOT || kMode == P_WRITE || kMode == Z_WRITE, "");
   constexpr int TM = Geo<WM>::TM;
   __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
   const int nv = *nv_ptr;
@@ -1259,9 +1277,10 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
       mma_mainloop<2, OP_GATHER, OP_GATHER, WM>(acc, masked_dense_operand<TM>(wt, vleft, ldw), opb, d, smem);
   }
 
-  // the gradient scale exists only for the modes that write G (the probability and Q passes get
-  // no upstream gradient: grad and n_norm may be null there)
-  constexpr bool kWritesG = kMode == G_ONEHOT || kMode == G_SOFT || kMode == G_SOFT_Q;
+  // the gradient scale exists only for the modes that write G (the other passes get no upstream
+  // gradient: grad and n_norm, and in the forward lse, may be null there)
+  constexpr bool kWritesG = kMode == G_ONEHOT || kMode == G_SOFT;
+  constexpr bool kUsesLse = kWritesG || kMode == P_WRITE;
   const float c_all = kWritesG ? grad_scale(grad, n_norm, reduction) : 0.f;
   int tok[2], tgt[2];
   float l2[2], cj[2];
@@ -1270,7 +1289,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
     tok[j] = n0 + wc * 64 + j * 32 + (lane & 31);
     if (tok[j] < nv) {
       const int row = idx[tok[j]];
-      l2[j] = lse[row] * kLog2e;
+      l2[j] = kUsesLse ? lse[row] * kLog2e : 0.f;
       tgt[j] = kMode == G_ONEHOT ? (int)(load_target(targets, tbytes, row) - id0 - v0) - vt0 : -1;
       cj[j] = kWritesG && reduction == LCE_REDUCE_NONE ? grad[row] : c_all;
     } else {
@@ -1334,41 +1353,98 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
     if (n0 + TILE <= nv && vleft >= TM) store_tile(std::true_type{});
     else store_tile(std::false_type{});
     return;
-  } else if constexpr (kMode == P_WRITE || kMode == Q_SOFT) {
+  } else if constexpr (kMode == P_WRITE || kMode == Z_WRITE) {
     // P[v][token] rows of this tile: lanes of a half-wave hold 32 consecutive tokens of one row
-    float q[2] = {0.f, 0.f};
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       if (tok[j] >= nv) continue;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if constexpr (kMode == P_WRITE) {
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int vr = vb + i * 32 + (r >> 2) * 8 + (r & 3);
-            if (vr < vleft)
-              P[(int64_t)(vt0 + vr) * ldt + tok[j]] = __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -l2[j]));
-          }
-        } else {
-          // the block's 16 probabilities are loaded together, then used
-          float pt[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int vr = vb + i * 32 + (r >> 2) * 8 + (r & 3);
-            pt[r] = vr < vleft ? P[(int64_t)(vt0 + vr) * ldt + tok[j]] : 0.f;
-          }
-#pragma unroll
-          for (int r = 0; r < 16; ++r) q[j] = fmaf(pt[r], acc[i][j][r] * inv_t, q[j]);
+        for (int r = 0; r < 16; ++r) {
+          const int vr = vb + i * 32 + (r >> 2) * 8 + (r & 3);
+          if (vr < vleft)
+            P[(int64_t)(vt0 + vr) * ldt + tok[j]] =
+                kMode == Z_WRITE ? acc[i][j][r] : __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -l2[j]));
         }
-      }
     }
-    if constexpr (kMode == Q_SOFT) {
-      // the two lane halves hold disjoint vocabulary rows of the same tokens
+    return;
+  } else if constexpr (kMode == KD_STATS) {
+    // the main loop ends with a barrier: its LDS is free for the two wave rows' values [2][kKdVals][256]
+    float* red = reinterpret_cast<float*>(smem);
+    // the teacher's logits through a buffer resource per block of 32 ids: a per-lane 32-bit offset and a
+    // uniform row offset; one block at a time folded into running values, so that 16 are held at once
+    const int wr_u = __builtin_amdgcn_readfirstlane(wr);
+    const uint32_t zoff = (uint32_t)(((lane >> 5) * 4 * ldt + wc * 64 + (lane & 31)) * 4);
+    auto zrow = [&](int r) { return (uint32_t)(((r >> 2) * 8 + (r & 3)) * ldt * 4); };
+    // (tiles of valid tokens and existing ids only test nothing per element)
+    auto stats = [&](auto kFull) {
+      constexpr bool kF = decltype(kFull)::value;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        q[j] += __shfl_xor(q[j], 32);
-        if (lane < 32 && tok[j] < nv) qpart[(qrow + 2 * tm + wr) * ldt + tok[j]] = q[j];
+        const bool tok_ok = kF || tok[j] < nv;
+        float mt = -INFINITY, st = 0.f, q = 0.f, ms = -INFINITY, ss = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row0 = wr_u * 128 + i * 32;
+          const __amdgpu_buffer_rsrc_t rz = make_rsrc(P + (int64_t)(vt0 + row0) * ldt + n0, (uint64_t)32 * ldt * 4);
+          float zt[16], mb = -INFINITY, sb = 0.f, qb = 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const bool ok = kF || (tok_ok && vb + i * 32 + (r >> 2) * 8 + (r & 3) < vleft);
+            zt[r] = ok ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rz, (int)(zoff + j * 128), (int)zrow(r), 0))
+                       : -INFINITY;
+            if (!kF && vb + i * 32 + (r >> 2) * 8 + (r & 3) >= vleft) acc[i][j][r] = -INFINITY;
+            ms = fmaxf(ms, acc[i][j][r]);
+            mb = fmaxf(mb, zt[r]);
+          }
+          mb *= scale2;
+          if (mb != -INFINITY) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const float e = __builtin_amdgcn_exp2f(fmaf(zt[r], scale2, -mb));
+              sb += e;
+              if (kF || vb + i * 32 + (r >> 2) * 8 + (r & 3) < vleft) qb = fmaf(e, acc[i][j][r] * inv_t, qb);
+            }
+          }
+          merge_weighted(mt, st, q, mb, sb, qb);
+        }
+        ms *= scale2;
+        if (ms != -INFINITY) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) ss += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -ms));
+        }
+        // merge the two lane halves (disjoint ids of the same tokens)
+        merge_weighted(mt, st, q, __shfl_xor(mt, 32), __shfl_xor(st, 32), __shfl_xor(q, 32));
+        merge_pair(ms, ss, __shfl_xor(ms, 32), __shfl_xor(ss, 32));
+        if (lane < 32) {
+          float* o = red + wr * kKdVals * TILE + wc * 64 + j * 32 + lane;
+          o[0] = mt;
+          o[TILE] = st;
+          o[2 * TILE] = q;
+          o[3 * TILE] = ms;
+          o[4 * TILE] = ss;
+        }
       }
+    };
+    if (n0 + TILE <= nv && vleft >= TM) stats(std::true_type{});
+    else stats(std::false_type{});
+    __syncthreads();
+    // merge the two wave rows; one thread per token of the tile
+    const int t = threadIdx.x;
+    if (t < TILE && n0 + t < nv) {
+      const float* b = red + kKdVals * TILE;
+      float mt = red[t], st = red[TILE + t], q = red[2 * TILE + t], ms = red[3 * TILE + t], ss = red[4 * TILE + t];
+      merge_weighted(mt, st, q, b[t], b[TILE + t], b[2 * TILE + t]);
+      merge_pair(ms, ss, b[3 * TILE + t], b[4 * TILE + t]);
+      float* o = qpart + (qrow + tm) * kKdVals * ldt + n0 + t;
+      o[0] = mt;
+      o[ldt] = st;
+      o[2 * (int64_t)ldt] = q;
+      o[3 * (int64_t)ldt] = ms;
+      o[4 * (int64_t)ldt] = ss;
     }
     return;
   }
@@ -1378,7 +1454,6 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
   // (ids 0-3, 4-7) trade places in token rows with bit 4 set: the 32 lanes of a half-wave, which
   // hold the same half of 32 consecutive token rows, then write 32 distinct 8-byte bank slots.
   char* T = smem;
-  float qs[2] = {0.f, 0.f};
   // a tile whose tokens are all valid and whose ids all lie in the slab tests nothing per element
   // (a runtime test would be kept, as masks and branches, on every tile)
   auto fill = [&](auto kFull) {
@@ -1390,7 +1465,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         float pt[16];
-        if constexpr (kMode == G_SOFT || kMode == G_SOFT_Q) {
+        if constexpr (kMode == G_SOFT) {
           // the block's 16 teacher probabilities are loaded together, then used
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
@@ -1408,9 +1483,8 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
             float g = 0.f;
             if (kF || (tok_ok && vr < vleft)) {
               const float e2 = __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -l2[j]));
-              if constexpr (kMode == G_SOFT || kMode == G_SOFT_Q) {
+              if constexpr (kMode == G_SOFT) {
                 g = cj[j] * inv_t * (e2 - pt[r]);
-                if constexpr (kMode == G_SOFT_Q) qs[j] = fmaf(pt[r], acc[i][j][r] * inv_t, qs[j]);
               } else {
                 g = cj[j] * e2;
                 if (vr == tgt[j]) g -= cj[j];
@@ -1431,13 +1505,6 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
   };
   if (n0 + TILE <= nv && vleft >= TM) fill(std::true_type{});
   else fill(std::false_type{});
-  if constexpr (kMode == G_SOFT_Q) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      qs[j] += __shfl_xor(qs[j], 32);
-      if (lane < 32 && tok[j] < nv) qpart[(qrow + 2 * tm + wr) * ldt + tok[j]] = qs[j];
-    }
-  }
   __syncthreads();
   // G rows, the whole tile (rows of tokens >= Nv are zeros): 16-byte chunks, one 512-byte row
   // per 32 threads
@@ -1860,36 +1927,62 @@ __global__ __launch_bounds__(256) void k_adamw(int64_t v, int d, const uint16_t*
   }
 }
 
-// KD per-token loss: l = lse_s - sum of the token's Q partials (fixed order), for valid rows; terms
-// (compact order) feed the mean / sum, per_token (row order, 0 on rows outside M) is the "none"
-// output.
-__global__ __launch_bounds__(256) void k_kd_terms(const float* __restrict__ qpart, int nq, int64_t ldq,
-                                                  const int* __restrict__ pos, int64_t n,
-                                                  const float* __restrict__ lse_s, float* __restrict__ terms,
-                                                  float* __restrict__ per_token) {
-  const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (row >= n) return;
-  const int i = pos[row];
-  if (i < 0) {
-    if (per_token) per_token[row] = 0.f;
-    return;
+// KD: per valid token, the tiles' values (KD_STATS) merged into both log-sum-exps and the loss l = lse_s -
+// sum_v p_t(v) zs(v); terms (compact order) feed the mean / sum, per_token (row order) is the "none"
+// output. A workgroup of 16 waves serves 16 tokens: a wave's four groups of 16 lanes fold every 64th tile
+// (64-byte reads along the tokens), then the groups and the waves are merged in a fixed order. (One
+// thread per token and a serial fold left most CUs idle: 4096 tokens, 501 tiles: 417 us, now 31.)
+constexpr int kKdTok = 16;
+
+__global__ __launch_bounds__(1024) void k_kd_combine(const float* __restrict__ part, int tiles, int64_t ldp,
+                                                     const int* __restrict__ idx, const int* __restrict__ nv_ptr,
+                                                     float* __restrict__ lse_s, float* __restrict__ lse_t,
+                                                     float* __restrict__ terms, float* __restrict__ per_token) {
+  __shared__ float red[kKdVals][16][kKdTok];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = lane & 15;
+  const int i = blockIdx.x * kKdTok + t, nv = *nv_ptr;
+  if ((int)blockIdx.x * kKdTok >= nv) return;
+  float mt = -INFINITY, st = 0.f, q = 0.f, ms = -INFINITY, ss = 0.f;
+  if (i < nv)
+    for (int k = 4 * wave + (lane >> 4); k < tiles; k += 64) {
+      const float* p = part + (int64_t)k * kKdVals * ldp + i;
+      merge_weighted(mt, st, q, p[0], p[ldp], p[2 * ldp]);
+      merge_pair(ms, ss, p[3 * ldp], p[4 * ldp]);
+    }
+  for (int o = 16; o <= 32; o <<= 1) {
+    merge_weighted(mt, st, q, __shfl_xor(mt, o), __shfl_xor(st, o), __shfl_xor(q, o));
+    merge_pair(ms, ss, __shfl_xor(ms, o), __shfl_xor(ss, o));
   }
-  float q = 0.f;
-  for (int k = 0; k < nq; ++k) q += qpart[k * ldq + i];
-  const float l = lse_s[row] - q;
-  terms[i] = l;
-  if (per_token) per_token[row] = l;
+  if (lane < kKdTok) {
+    red[0][wave][t] = mt;
+    red[1][wave][t] = st;
+    red[2][wave][t] = q;
+    red[3][wave][t] = ms;
+    red[4][wave][t] = ss;
+  }
+  __syncthreads();
+  if (threadIdx.x >= kKdTok || i >= nv) return;
+  for (int w = 1; w < 16; ++w) {
+    merge_weighted(mt, st, q, red[0][w][t], red[1][w][t], red[2][w][t]);
+    merge_pair(ms, ss, red[3][w][t], red[4][w][t]);
+  }
+  const int row = idx[i];
+  const float ls = (ms + log2f(ss)) * kLn2;
+  lse_s[row] = ls;
+  lse_t[row] = (mt + log2f(st)) * kLn2;
+  terms[i] = ls - q / st;
+  if (per_token) per_token[row] = ls - q / st;
 }
 
 // ---------------------------------------------------------------------------------------------
 // Host side: validation, plan, workspace carve-up, launches, optional timing.
 // ---------------------------------------------------------------------------------------------
 enum KernelId { K_COMPACT = 0, K_FWD_STATS, K_COMBINE, K_LOSS, K_GATHER_H, K_BWD_G,
-                K_BWD_DW, K_BWD_DH, K_BWD_DHDW, K_DH_FINAL, K_ADAMW, K_SHARD_COMBINE, K_KD_P, K_KD_Q, K_KD_TERMS, K_MISC,
+                K_BWD_DW, K_BWD_DH, K_BWD_DHDW, K_DH_FINAL, K_ADAMW, K_SHARD_COMBINE, K_KD_Z, K_KD_STATS, K_KD_COMBINE, K_KD_P, K_MISC,
                 K_COUNT };
 const char* const kKernelNames[K_COUNT] = {"compact", "fwd_stats", "combine", "loss", "gather_h",
                                            "bwd_g", "bwd_dw", "bwd_dh", "bwd_dhdw", "dh_finalize", "adamw", "shard_combine",
-                                           "kd_teacher_p", "kd_q", "kd_terms", "misc"};
+                                           "kd_teacher_z", "kd_student_stats", "kd_combine", "kd_teacher_p", "misc"};
 
 struct Timing {
   std::mutex mu;
@@ -1992,11 +2085,13 @@ int64_t whole_round_slab(int64_t v, int64_t d, int64_t vc) {
 //   4096 x 2048 x 128256 (6 slabs of 64 x 12, whole rounds): G 1340 -> 1307, step 5370 -> 5300.
 // Above 1024 tiles a partial round is a small share (8192 x 2048 x 128256: 8 rounds) and the memory
 // stays with the rule.
+// The distillation calls, whose teacher values take 4 bytes per slab id and token, keep those within
+// the same bytes.
 constexpr int64_t kFewTokenTiles = 1024;
 constexpr int64_t kFewTokenG = (int64_t)1280 << 20;
-int64_t few_token_slab(int64_t v, int64_t npad, int64_t vc) {
+int64_t few_token_slab(int64_t v, int64_t npad, int64_t vc, int64_t elem_bytes) {
   if (vc / 384 * (npad / TILE) > kFewTokenTiles) return vc;
-  int64_t cap = kFewTokenG / (2 * round_up(npad, 384)) / 768 * 768;
+  int64_t cap = kFewTokenG / (elem_bytes * round_up(npad, 384)) / 768 * 768;
   cap = std::min<int64_t>(cap, 0x7FFFFFFF / (2 * TILE) / 768 * 768);   // G offsets within a token tile
   if (cap <= vc) return vc;
   const int64_t slabs = (v + cap - 1) / cap;
@@ -2044,7 +2139,7 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   // leave the MALL)
   pl->gw = vc / 384;
   if (wide_slabs && vc < vround) vc = whole_round_slab(p->v, p->d, vc);
-  if (wide_slabs && vc < vround) vc = few_token_slab(p->v, pl->npad, vc);
+  if (vc < vround) vc = few_token_slab(p->v, pl->npad, vc, wide_slabs ? 2 : 4);
   pl->vc = vc;
   pl->nslab = (p->v + vc - 1) / vc;
   if ((uint64_t)TILE * pl->npad * 2 > 0x7FFFFFFFull || (uint64_t)TILE * vc * 2 > 0x7FFFFFFFull) return LCE_ERR_SHAPE;
@@ -2245,7 +2340,7 @@ lce_status_t forward_impl(const lce_problem_t* p, const ShardInfo* shard, const 
 
   // rows that are not valid get lse 0 and a zero per-token loss (or shard target logit)
   L(K_COMPACT, k_compact, dim3(1), dim3(1024), targets, p->target_bytes, pl.n, si.v_total, p->ignore_index,
-    idx, pos, nv, n_valid, dev_status, lse, none ? loss : tgt_part);
+    idx, pos, nv, n_valid, dev_status, lse, none ? loss : tgt_part, (float*)nullptr);
   const PartRows pr = launch_fwd_stats(L, pl, w, pl.ldw, h, pl.ldh, (int)pl.d, (const int*)idx, (const int*)nv,
                                        (uint16_t*)(ws + pl.o_hv), pm, ps, kLog2e);
   L(K_COMBINE, k_combine, dim3((unsigned)((pl.n + kCombTok - 1) / kCombTok)), dim3(1024), h, pl.ldh, w, pl.ldw,
@@ -2266,8 +2361,21 @@ struct KdArgs {
   int dt;
   const float* lse_t;
   float scale2, inv_t;
-  float* qpart;   // non-null: the student pass also writes the loss's Q partials (fused KD call)
+  bool formed;   // the valid-row list and the teacher's gathered rows are in place (fused KD call)
 };
+
+// The teacher's pass over one slab: its logits (Z_WRITE) or probabilities (P_WRITE, from lse_t) into P
+// [Vc][Npad], on 12-wave tiles over the gathered rows hvt, or (null) 8-wave tiles that gather.
+template <int kMode>
+void launch_teacher(Launcher& L, int kind, const KdArgs& kd, const uint16_t* hvt, const Plan& pl, int64_t v0, int vs,
+                    const int* idx, const int* nv, float* P) {
+  const int wm = hvt ? 3 : 2, rows = 128 * wm, tm = (vs + rows - 1) / rows;
+  const TileOrder to = tile_order(tm, pl.nt_max, hvt ? group_tiles(tm, rows, kd.dt) : tm);
+  L(kind, hvt ? k_bwd_g<kMode, 3> : k_bwd_g<kMode, 2>, dim3(to.grid), dim3(256 * wm), kd.wt, kd.ldwt, v0, vs,
+    hvt ? hvt : kd.ht, hvt ? (int64_t)kd.dt : kd.ldht, pl.n, (const void*)nullptr, 4, (int64_t)0, idx, nv, kd.lse_t,
+    (const float*)nullptr, (const int*)nullptr, (int)LCE_REDUCE_MEAN, kd.dt, tm, (uint16_t*)nullptr, (int)pl.vc,
+    (int)pl.npad, kd.scale2, kd.inv_t, P, (float*)nullptr, (int64_t)0, to.gw);
+}
 
 inline size_t kd_p_bytes(const Plan& pl) { return (size_t)4 * pl.vc * pl.npad; }
 
@@ -2275,14 +2383,6 @@ inline size_t kd_p_bytes(const Plan& pl) { return (size_t)4 * pl.vc * pl.npad; }
 // Dt % 64 == 0; placed after P.
 inline size_t kd_hvt_bytes(const Plan& pl, int64_t dt) {
   return dt % KSLICE == 0 ? ((size_t)2 * dt * pl.npad + 255) / 256 * 256 : 0;
-}
-
-// Gather buffer for the 12-wave statistics of both distillation heads (Npad x max(Ds, Dt) bf16),
-// placed in the teacher-probability buffer P (free before the slab loop), or null when P is
-// too small (the 8-wave statistics then need none).
-inline uint16_t* kd_stats_gather(const Plan& s, const Plan& t, char* p_buf) {
-  const int64_t dmax = s.d > t.d ? s.d : t.d;
-  return (size_t)2 * dmax * s.npad <= kd_p_bytes(s) ? (uint16_t*)p_buf : nullptr;
 }
 
 // The backward pass behind lce_backward (dW != null), lce_backward_adamw (adamw != null),
@@ -2335,17 +2435,17 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
 
   // with LCE_FLAG_REUSE_FORWARD the workspace holds the forward's valid-row list (and, when the
   // forward gathered them, the rows Hv); otherwise both are formed again
-  const bool reuse = !kd && (p->flags & LCE_FLAG_REUSE_FORWARD) != 0;
+  const bool reuse = kd ? kd->formed : (p->flags & LCE_FLAG_REUSE_FORWARD) != 0;
   if (!reuse)
     L(K_COMPACT, k_compact, dim3(1), dim3(1024), targets, p->target_bytes, pl.n, si.v_total, p->ignore_index,
-      idx, pos, nv, (int*)nullptr, (int*)nullptr, (float*)nullptr, (float*)nullptr);
+      idx, pos, nv, (int*)nullptr, (int*)nullptr, (float*)nullptr, (float*)nullptr, (float*)nullptr);
   // Hv[i] = H[idx[i]] for i < Nv, zero rows up to round_up(Nv, 64)
-  if (!(reuse && fwd_gathers(pl)))
+  if (kd || !(reuse && fwd_gathers(pl)))
     L(K_GATHER_H, k_gather_rows, dim3((unsigned)std::min<int64_t>((npad * (d / 8) + 255) / 256, 16384)), dim3(256),
       h, pl.ldh, (const int*)idx, (const int*)nv, d, hv);
   // KD: the teacher's valid rows for its 12-wave probability pass
   uint16_t* hvt = (kd && kd_hvt_bytes(pl, kd->dt) > 0) ? (uint16_t*)(ws + pl.bwd_bytes + kd_p_bytes(pl)) : nullptr;
-  if (hvt)
+  if (hvt && !kd->formed)
     L(K_GATHER_H, k_gather_rows, dim3((unsigned)std::min<int64_t>(((int64_t)npad * (kd->dt / 8) + 255) / 256, 16384)),
       dim3(256), kd->ht, kd->ldht, (const int*)idx, (const int*)nv, kd->dt, hvt);
   const int dt = (d + TILE - 1) / TILE;
@@ -2369,31 +2469,12 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
     if (kd) {
       // teacher probabilities of this slab, then G = c (softmax(zs / T) - P) / T
       float* P = (float*)(ws + pl.bwd_bytes);
-      if (hvt) {
-        const int tmg = (vs + Geo<3>::TM - 1) / Geo<3>::TM;
-        const TileOrder to = tile_order(tmg, pl.nt_max, group_tiles(tmg, Geo<3>::TM, kd->dt));
-        L(K_KD_P, k_bwd_g<P_WRITE, 3>, dim3(to.grid), dim3(Geo<3>::NT), kd->wt, kd->ldwt, v0, vs,
-          (const uint16_t*)hvt, (int64_t)kd->dt, pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx,
-          (const int*)nv, kd->lse_t, grad_loss, (const int*)n_valid, p->reduction, kd->dt, tmg, (uint16_t*)nullptr, vc,
-          npad, kd->scale2, kd->inv_t, P, (float*)nullptr, (int64_t)0, to.gw);
-      } else {
-        const TileOrder to = tile_order(tm, pl.nt_max, tm);
-        L(K_KD_P, k_bwd_g<P_WRITE, 2>, dim3(to.grid), dim3(NTHREADS), kd->wt, kd->ldwt, v0, vs,
-          kd->ht, kd->ldht, pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, kd->lse_t,
-          grad_loss, (const int*)n_valid, p->reduction, kd->dt, tm, (uint16_t*)nullptr, vc, npad,
-          kd->scale2, kd->inv_t, P, (float*)nullptr, (int64_t)0, to.gw);
-      }
+      launch_teacher<P_WRITE>(L, K_KD_P, *kd, hvt, pl, v0, vs, idx, nv, P);
       const TileOrder to = tile_order(tm, pl.nt_max, tm);
-      if (kd->qpart)
-        L(K_BWD_G, k_bwd_g<G_SOFT_Q, 2>, dim3(to.grid), dim3(NTHREADS), w, pl.ldw, v0, vs, h,
-          pl.ldh, pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, lse, grad_loss,
-          (const int*)n_valid, p->reduction, d, tm, g, vc, npad, kd->scale2, kd->inv_t, P, kd->qpart,
-          (int64_t)(2 * (v0 / TILE)), to.gw);
-      else
-        L(K_BWD_G, k_bwd_g<G_SOFT, 2>, dim3(to.grid), dim3(NTHREADS), w, pl.ldw, v0, vs, h,
-          pl.ldh, pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, lse, grad_loss,
-          (const int*)n_valid, p->reduction, d, tm, g, vc, npad, kd->scale2, kd->inv_t, P, (float*)nullptr,
-          (int64_t)0, to.gw);
+      L(K_BWD_G, k_bwd_g<G_SOFT, 2>, dim3(to.grid), dim3(NTHREADS), w, pl.ldw, v0, vs, h,
+        pl.ldh, pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, lse, grad_loss,
+        (const int*)n_valid, p->reduction, d, tm, g, vc, npad, kd->scale2, kd->inv_t, P, (float*)nullptr,
+        (int64_t)0, to.gw);
     } else {
       if (d % KSLICE == 0) {
         const int tmg = (vs + Geo<kGWM>::TM - 1) / Geo<kGWM>::TM;
@@ -2443,8 +2524,10 @@ struct KdPlan {
   lce_problem_t ps, pt;   // student and teacher heads as LCE problems
   Plan s, t;
   float scale2, inv_t;
-  size_t o_tgt, o_q, o_p, o_hvt, fwd_bytes, bwd_bytes;
-  size_t f_q, f_tgt, fused_bytes;   // fused call: backward regions, P, then Q partials and scratch
+  // the forward's regions: the student's valid-row list, then the tiles' values and the teacher's logits
+  // and gathered rows (where the backward keeps its probabilities and gathered rows in the fused call)
+  size_t o_q, o_terms, o_p, o_hvt, fwd_bytes, bwd_bytes;
+  size_t f_q, f_terms, fused_bytes;
 };
 
 lce_status_t make_kd_plan(const lce_kd_problem_t* p, KdPlan* k) {
@@ -2460,32 +2543,62 @@ lce_status_t make_kd_plan(const lce_kd_problem_t* p, KdPlan* k) {
   if (st != LCE_OK) return st;
   k->scale2 = (float)(1.4426950408889634 / (double)p->temperature);
   k->inv_t = (float)(1.0 / (double)p->temperature);
-  // forward: the student plan's forward regions (index arrays, partials, terms; the teacher's
-  // partials have the same shape), then target-logit scratch, Q partials and P
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  size_t cur = up(k->s.fwd_bytes);
-  k->o_tgt = cur;
-  cur += up(4 * (size_t)k->s.npad);
+  const size_t q_bytes = up((size_t)4 * kKdVals * k->s.vt_count * k->s.npad), t_bytes = up(4 * (size_t)k->s.npad);
+  const size_t p_bytes = up(kd_p_bytes(k->s)), hvt_bytes = kd_hvt_bytes(k->s, k->t.d);
+  size_t cur = up(k->s.o_hv);   // after idx, pos and Nv
   k->o_q = cur;
-  cur += up((size_t)4 * 2 * k->s.vt_count * k->s.npad);
-  k->o_p = cur;
-  cur += up(kd_p_bytes(k->s));
-  k->o_hvt = cur;
-  cur += kd_hvt_bytes(k->s, k->t.d);
-  k->fwd_bytes = cur;
-  k->bwd_bytes = k->s.bwd_bytes + kd_p_bytes(k->s) + kd_hvt_bytes(k->s, k->t.d);
-  cur = up(k->bwd_bytes);
-  k->f_q = cur;
-  cur += up((size_t)4 * 2 * k->s.vt_count * k->s.npad);
-  k->f_tgt = cur;
-  cur += up(4 * (size_t)k->s.npad);
-  k->fused_bytes = cur;
+  k->o_terms = k->o_q + q_bytes;
+  k->o_p = k->o_terms + t_bytes;
+  k->o_hvt = k->o_p + p_bytes;
+  k->fwd_bytes = k->o_hvt + hvt_bytes;
+  k->bwd_bytes = k->s.bwd_bytes + kd_p_bytes(k->s) + hvt_bytes;
+  k->f_q = up(k->bwd_bytes);
+  k->f_terms = k->f_q + q_bytes;
+  k->fused_bytes = k->f_terms + t_bytes;
   return LCE_OK;
 }
 
+// The KD forward: both heads' log-sum-exps and the loss. Per slab, one teacher pass (its logits into P)
+// and one student pass (KD_STATS), then one merge of all tiles' values.
+lce_status_t kd_forward_launches(Launcher& L, const lce_kd_problem_t* p, const KdPlan& k, const KdArgs& kd,
+                                 const uint16_t* hs, const uint16_t* wsm, const void* targets, float* loss,
+                                 float* lse_s, float* lse_t, int32_t* n_valid, int32_t* dev_status, char* ws,
+                                 size_t o_q, size_t o_terms, size_t o_p, size_t o_hvt) {
+  const Plan& pl = k.s;
+  const bool none = p->reduction == LCE_REDUCE_NONE;
+  int* idx = (int*)(ws + pl.o_idx);
+  int* nv = (int*)(ws + pl.o_nv);
+  float* terms = (float*)(ws + o_terms);
+  float* qpart = (float*)(ws + o_q);
+  float* P = (float*)(ws + o_p);
+  const int npad = (int)pl.npad;
+  L(K_COMPACT, k_compact, dim3(1), dim3(1024), targets, p->target_bytes, pl.n, pl.v, p->ignore_index,
+    idx, (int*)(ws + pl.o_pos), nv, n_valid, dev_status, lse_s, lse_t, none ? loss : (float*)nullptr);
+  uint16_t* hvt = kd_hvt_bytes(pl, kd.dt) > 0 ? (uint16_t*)(ws + o_hvt) : nullptr;
+  if (hvt)
+    L(K_GATHER_H, k_gather_rows, dim3((unsigned)std::min<int64_t>(((int64_t)npad * (kd.dt / 8) + 255) / 256, 16384)),
+      dim3(256), kd.ht, kd.ldht, (const int*)idx, (const int*)nv, kd.dt, hvt);
+  for (int64_t s = 0; s < pl.nslab; ++s) {
+    const int64_t v0 = s * pl.vc;
+    const int vs = (int)(pl.v - v0 < pl.vc ? pl.v - v0 : pl.vc);
+    launch_teacher<Z_WRITE>(L, K_KD_Z, kd, hvt, pl, v0, vs, idx, nv, P);
+    const int tm = (vs + TILE - 1) / TILE;
+    const TileOrder to = tile_order(tm, pl.nt_max, tm);
+    L(K_KD_STATS, k_bwd_g<KD_STATS, 2>, dim3(to.grid), dim3(NTHREADS), wsm, pl.ldw, v0, vs, hs, pl.ldh,
+      pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, (const float*)nullptr,
+      (const float*)nullptr, (const int*)nullptr, p->reduction, (int)pl.d, tm, (uint16_t*)nullptr, (int)pl.vc,
+      npad, k.scale2, k.inv_t, P, qpart, v0 / TILE, to.gw);
+  }
+  L(K_KD_COMBINE, k_kd_combine, dim3((unsigned)((pl.n + kKdTok - 1) / kKdTok)), dim3(1024), (const float*)qpart,
+    pl.vt_count, (int64_t)npad, (const int*)idx, (const int*)nv, lse_s, lse_t, terms, none ? loss : (float*)nullptr);
+  if (!none) L(K_LOSS, k_loss, dim3(1), dim3(1024), (const float*)terms, (const int*)nv, p->reduction, loss);
+  return L.st;
+}
+
 // Forward and backward of the KD loss in one call (the upstream gradient is read on the device
-// when the gradient kernels run): both heads' statistics, then per slab one teacher pass and one
-// student pass that writes G and the loss's Q partials together.
+// when the gradient kernels run): the two calls' kernels, with the valid-row list and the teacher's
+// gathered rows formed once.
 lce_status_t kd_fused_impl(const lce_kd_problem_t* p, const void* Hs, const void* Ws, const void* Ht,
                            const void* Wt, const void* targets, const float* grad_loss, float* loss, float* lse_s,
                            float* lse_t, int32_t* n_valid, int32_t* dev_status, void* dHs, void* dWs,
@@ -2510,50 +2623,13 @@ lce_status_t kd_fused_impl(const lce_kd_problem_t* p, const void* Hs, const void
     return backward_impl(&k.ps, nullptr, Hs, Ws, targets, lse_s, n_valid, grad_loss, dHs, nullptr,
                          (uint16_t*)dWs, nullptr, nullptr, workspace, workspace_bytes, stream);
   }
-  char* ws = (char*)workspace;
-  int* idx = (int*)(ws + pl.o_idx);
-  int* pos = (int*)(ws + pl.o_pos);
-  int* nv = (int*)(ws + pl.o_nv);
-  float* pm = (float*)(ws + pl.o_pm);
-  float* ps = (float*)(ws + pl.o_ps);
-  float* tgt = (float*)(ws + k.f_tgt);
-  float* qpart = (float*)(ws + k.f_q);
-  const uint16_t* hs = (const uint16_t*)Hs;
-  const uint16_t* wsm = (const uint16_t*)Ws;
-  const uint16_t* ht = (const uint16_t*)Ht;
-  const uint16_t* wt = (const uint16_t*)Wt;
-  const Plan& tp = k.t;
-  const int npad = (int)pl.npad;
-  {
-    Launcher L{(hipStream_t)stream};
-    L(K_COMPACT, k_compact, dim3(1), dim3(1024), targets, p->target_bytes, pl.n, pl.v, p->ignore_index,
-      idx, pos, nv, n_valid, dev_status, lse_s, lse_t);
-    // the statistics' row gathers use the P buffer, free until the slab loop
-    uint16_t* hvk = kd_stats_gather(pl, tp, ws + pl.bwd_bytes);
-    const PartRows pt = launch_fwd_stats(L, pl, wt, tp.ldw, ht, tp.ldh, (int)tp.d, (const int*)idx, (const int*)nv, hvk,
-                                         pm, ps, k.scale2);
-    L(K_COMBINE, k_combine, dim3((unsigned)((pl.n + kCombTok - 1) / kCombTok)), dim3(1024), ht, tp.ldh, wt, tp.ldw, targets,
-      p->target_bytes, (int64_t)0, (int64_t)0, (const int*)idx, (const int*)nv, (int)tp.d, pt.count, pt.m, pt.s, npad,
-      pt.run_m, pt.run_s, lse_t, (float*)nullptr, (float*)nullptr, tgt);
-    const PartRows pq = launch_fwd_stats(L, pl, wsm, pl.ldw, hs, pl.ldh, (int)pl.d, (const int*)idx, (const int*)nv, hvk,
-                                         pm, ps, k.scale2);
-    L(K_COMBINE, k_combine, dim3((unsigned)((pl.n + kCombTok - 1) / kCombTok)), dim3(1024), hs, pl.ldh, wsm, pl.ldw, targets,
-      p->target_bytes, (int64_t)0, (int64_t)0, (const int*)idx, (const int*)nv, (int)pl.d, pq.count, pq.m, pq.s, npad,
-      pq.run_m, pq.run_s, lse_s, (float*)nullptr, (float*)nullptr, tgt);
-    if (L.st != LCE_OK) return L.st;
-  }
-  const KdArgs kd{ht, tp.ldh, wt, tp.ldw, (int)tp.d, lse_t, k.scale2, k.inv_t, qpart};
-  st = backward_impl(&k.ps, nullptr, Hs, Ws, targets, lse_s, n_valid, grad_loss, dHs, nullptr, (uint16_t*)dWs,
-                     nullptr, nullptr, workspace, workspace_bytes, stream, &kd);
-  if (st != LCE_OK) return st;
-  // the backward's workspace (idx, pos, Nv) is still valid; the per-token terms reuse the
-  // student-statistics region, free again
   Launcher L{(hipStream_t)stream};
-  float* terms = (float*)(ws + pl.o_terms);
-  L(K_KD_TERMS, k_kd_terms, dim3((unsigned)((pl.n + 255) / 256)), dim3(256), (const float*)qpart,
-    2 * pl.vt_count, (int64_t)npad, (const int*)pos, pl.n, (const float*)lse_s, terms, none ? loss : (float*)nullptr);
-  if (!none) L(K_LOSS, k_loss, dim3(1), dim3(1024), (const float*)terms, (const int*)nv, p->reduction, loss);
-  return L.st;
+  const KdArgs kd{(const uint16_t*)Ht, k.t.ldh, (const uint16_t*)Wt, k.t.ldw, (int)k.t.d, lse_t, k.scale2, k.inv_t, true};
+  st = kd_forward_launches(L, p, k, kd, (const uint16_t*)Hs, (const uint16_t*)Ws, targets, loss, lse_s, lse_t, n_valid,
+                           dev_status, (char*)workspace, k.f_q, k.f_terms, pl.bwd_bytes, pl.bwd_bytes + kd_p_bytes(pl));
+  if (st != LCE_OK) return st;
+  return backward_impl(&k.ps, nullptr, Hs, Ws, targets, lse_s, n_valid, grad_loss, dHs, nullptr, (uint16_t*)dWs,
+                       nullptr, nullptr, workspace, workspace_bytes, stream, &kd);
 }
 
 lce_status_t kd_forward_impl(const lce_kd_problem_t* p, const void* Hs, const void* Ws, const void* Ht,
@@ -2576,71 +2652,9 @@ lce_status_t kd_forward_impl(const lce_kd_problem_t* p, const void* Hs, const vo
     L(K_MISC, k_fwd_empty, dim3(1), dim3(64), none ? (float*)nullptr : loss, n_valid, dev_status);
     return L.st;
   }
-  char* ws = (char*)workspace;
-  int* idx = (int*)(ws + pl.o_idx);
-  int* pos = (int*)(ws + pl.o_pos);
-  int* nv = (int*)(ws + pl.o_nv);
-  float* pm = (float*)(ws + pl.o_pm);
-  float* ps = (float*)(ws + pl.o_ps);
-  float* terms = (float*)(ws + pl.o_terms);
-  float* tgt = (float*)(ws + k.o_tgt);
-  float* qpart = (float*)(ws + k.o_q);
-  float* P = (float*)(ws + k.o_p);
-  const uint16_t* hs = (const uint16_t*)Hs;
-  const uint16_t* wsm = (const uint16_t*)Ws;
-  const uint16_t* ht = (const uint16_t*)Ht;
-  const uint16_t* wt = (const uint16_t*)Wt;
-  const int npad = (int)pl.npad, vc = (int)pl.vc;
-
-  L(K_COMPACT, k_compact, dim3(1), dim3(1024), targets, p->target_bytes, pl.n, pl.v, p->ignore_index,
-    idx, pos, nv, n_valid, dev_status, lse_s, lse_t);
-  // log-sum-exp of both heads' logits / T (no target logit: an empty id range)
-  const Plan& tp = k.t;
-  // the statistics' row gathers use the P buffer, free until the slab loop
-  uint16_t* hvk = kd_stats_gather(pl, tp, (char*)P);
-  const PartRows pt = launch_fwd_stats(L, pl, wt, tp.ldw, ht, tp.ldh, (int)tp.d, (const int*)idx, (const int*)nv, hvk,
-                                       pm, ps, k.scale2);
-  L(K_COMBINE, k_combine, dim3((unsigned)((pl.n + kCombTok - 1) / kCombTok)), dim3(1024), ht, tp.ldh, wt, tp.ldw, targets,
-    p->target_bytes, (int64_t)0, (int64_t)0, (const int*)idx, (const int*)nv, (int)tp.d, pt.count, pt.m, pt.s, npad,
-    pt.run_m, pt.run_s, lse_t, terms, (float*)nullptr, tgt);
-  const PartRows pq = launch_fwd_stats(L, pl, wsm, pl.ldw, hs, pl.ldh, (int)pl.d, (const int*)idx, (const int*)nv, hvk,
-                                       pm, ps, k.scale2);
-  L(K_COMBINE, k_combine, dim3((unsigned)((pl.n + kCombTok - 1) / kCombTok)), dim3(1024), hs, pl.ldh, wsm, pl.ldw, targets,
-    p->target_bytes, (int64_t)0, (int64_t)0, (const int*)idx, (const int*)nv, (int)pl.d, pq.count, pq.m, pq.s, npad,
-    pq.run_m, pq.run_s, lse_s, terms, (float*)nullptr, tgt);
-  // per slab: teacher probabilities P, then the student's sum_v P zs / T per token and tile
-  uint16_t* hvt = kd_hvt_bytes(pl, tp.d) > 0 ? (uint16_t*)(ws + k.o_hvt) : nullptr;
-  if (hvt)
-    L(K_GATHER_H, k_gather_rows, dim3((unsigned)std::min<int64_t>(((int64_t)npad * (tp.d / 8) + 255) / 256, 16384)),
-      dim3(256), ht, tp.ldh, (const int*)idx, (const int*)nv, (int)tp.d, hvt);
-  for (int64_t s = 0; s < pl.nslab; ++s) {
-    const int64_t v0 = s * pl.vc;
-    const int vs = (int)(pl.v - v0 < pl.vc ? pl.v - v0 : pl.vc);
-    const int tm = (vs + TILE - 1) / TILE;
-    if (hvt) {
-      const int tmg = (vs + Geo<3>::TM - 1) / Geo<3>::TM;
-      const TileOrder to = tile_order(tmg, pl.nt_max, group_tiles(tmg, Geo<3>::TM, tp.d));
-      L(K_KD_P, k_bwd_g<P_WRITE, 3>, dim3(to.grid), dim3(Geo<3>::NT), wt, tp.ldw, v0, vs,
-        (const uint16_t*)hvt, tp.d, pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv,
-        (const float*)lse_t, (const float*)nullptr, (const int*)nullptr, p->reduction, (int)tp.d, tmg,
-        (uint16_t*)nullptr, vc, npad, k.scale2, k.inv_t, P, (float*)nullptr, (int64_t)0, to.gw);
-    } else {
-      const TileOrder to = tile_order(tm, pl.nt_max, tm);
-      L(K_KD_P, k_bwd_g<P_WRITE, 2>, dim3(to.grid), dim3(NTHREADS), wt, tp.ldw, v0, vs, ht, tp.ldh,
-        pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, (const float*)lse_t,
-        (const float*)nullptr, (const int*)nullptr, p->reduction, (int)tp.d, tm, (uint16_t*)nullptr, vc,
-        npad, k.scale2, k.inv_t, P, (float*)nullptr, (int64_t)0, to.gw);
-    }
-    const TileOrder to = tile_order(tm, pl.nt_max, tm);
-    L(K_KD_Q, k_bwd_g<Q_SOFT, 2>, dim3(to.grid), dim3(NTHREADS), wsm, pl.ldw, v0, vs, hs, pl.ldh,
-      pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, (const float*)lse_s,
-      (const float*)nullptr, (const int*)nullptr, p->reduction, (int)pl.d, tm, (uint16_t*)nullptr, vc,
-      npad, k.scale2, k.inv_t, P, qpart, (int64_t)(2 * (v0 / TILE)), to.gw);
-  }
-  L(K_KD_TERMS, k_kd_terms, dim3((unsigned)((pl.n + 255) / 256)), dim3(256), (const float*)qpart,
-    2 * pl.vt_count, (int64_t)npad, (const int*)pos, pl.n, (const float*)lse_s, terms, none ? loss : (float*)nullptr);
-  if (!none) L(K_LOSS, k_loss, dim3(1), dim3(1024), (const float*)terms, (const int*)nv, p->reduction, loss);
-  return L.st;
+  const KdArgs kd{(const uint16_t*)Ht, k.t.ldh, (const uint16_t*)Wt, k.t.ldw, (int)k.t.d, nullptr, k.scale2, k.inv_t, false};
+  return kd_forward_launches(L, p, k, kd, (const uint16_t*)Hs, (const uint16_t*)Ws, targets, loss, lse_s, lse_t, n_valid,
+                             dev_status, (char*)workspace, k.o_q, k.o_terms, k.o_p, k.o_hvt);
 }
 
 }  // namespace
@@ -2780,7 +2794,7 @@ lce_status_t lce_combine_shards(const lce_problem_t* p, int32_t n_shards, const 
   int* nv = (int*)(ws + pl.o_nv);
   float* terms = (float*)(ws + pl.o_terms);
   L(K_COMPACT, k_compact, dim3(1), dim3(1024), targets, p->target_bytes, pl.n, pl.v, p->ignore_index,
-    idx, pos, nv, n_valid, dev_status, lse, none ? loss : (float*)nullptr);
+    idx, pos, nv, n_valid, dev_status, lse, none ? loss : (float*)nullptr, (float*)nullptr);
   L(K_SHARD_COMBINE, k_shard_combine, dim3((unsigned)((pl.n + 255) / 256)), dim3(256), (int)n_shards, lse_parts,
     tgt_parts, pl.n, (const int*)idx, (const int*)nv, lse, terms, none ? loss : (float*)nullptr);
   if (!none) L(K_LOSS, k_loss, dim3(1), dim3(1024), (const float*)terms, (const int*)nv, p->reduction, loss);
@@ -2899,7 +2913,7 @@ lce_status_t lce_kd_backward(const lce_kd_problem_t* p, const void* Hs, const vo
   if (p->n > 0 && (!Ht || !Wt || !lse_t)) return LCE_ERR_NULL;
   if (p->n > 0 && (!aligned16(Ht) || !aligned16(Wt))) return LCE_ERR_ALIGN;
   const KdArgs kd{(const uint16_t*)Ht, k.t.ldh, (const uint16_t*)Wt, k.t.ldw, (int)k.t.d, lse_t, k.scale2, k.inv_t,
-                  nullptr};
+                  false};
   return backward_impl(&k.ps, nullptr, Hs, Ws, targets, lse_s, n_valid, grad_loss, dHs, nullptr, (uint16_t*)dWs,
                        nullptr, nullptr, workspace, workspace_bytes, stream, &kd);
 }

@@ -154,3 +154,28 @@ def test_fused_without_tokens():
     f = AG.kd_forward_backward(hs, ws, ht, wt, t, torch.ones(1, device="cuda:0"))
     torch.cuda.synchronize()
     assert float(f[0].item()) == 0.0 and int(f[3].item()) == 0 and not f[6].float().abs().sum().item()
+
+
+@pytest.mark.parametrize("n,ds,dt,v,mask", [(255, 64, 64, 257, 0.0), (256, 64, 128, 768, 0.0), (16, 72, 64, 256, 0.0),
+                                            (33, 64, 200, 12345, 0.5), (17, 8, 8, 1, 0.0)])
+@pytest.mark.parametrize("sigma", [0.02, 3.0])
+def test_kd_statistics_at_tile_edges(n, ds, dt, v, mask, sigma):
+    # the tiles' values (maxima, sum-exps, weighted sum) and their merge: one tile, an id past a tile, whole
+    # and ragged token tiles, flat logits and logits so peaked that most tiles vanish under the maximum. The
+    # per-token loss is lse_s - sum p_t z_s, each fp32 sum within 1e-5 of its largest term (|z| up to ~100)
+    inp = WL.kd_custom(n, ds, dt, v, seed=v, sigma_s=sigma, sigma_t=sigma, mask_frac=mask)
+    print(f"kd edges n={n} ds={ds} dt={dt} v={v} sigma={sigma}", flush=True)
+    gpu = _run(inp, 1.0, "none", np.ones(n, np.float32))
+    ref = K.kd_bits(inp.hs_bits, inp.ws_bits, inp.ht_bits, inp.wt_bits, inp.targets, reduction="none",
+                    grad=np.ones(n))
+    scale = max(1.0, np.max(np.abs(ref["lse_s"])), np.max(np.abs(ref["lse_t"])))
+    for k in ("lse_s", "lse_t", "loss"):
+        assert np.max(np.abs(gpu[k] - ref[k])) <= 2e-5 * scale, k
+
+
+@pytest.mark.parametrize("n,ds,dt,v,mask", [(6000, 64, 128, 60001, 0.9), (8300, 72, 64, 26000, 0.93)])
+def test_kd_over_several_slabs(n, ds, dt, v, mask):
+    # enough tokens for several slabs (the teacher's values of one slab are replaced by the next's), most ignored
+    inp = WL.kd_custom(n, ds, dt, v, seed=n, mask_frac=mask)
+    print(f"kd slabs n={n} ds={ds} dt={dt} v={v}", flush=True)
+    _check(_run(inp, 2.0), K.kd_bits(inp.hs_bits, inp.ws_bits, inp.ht_bits, inp.wt_bits, inp.targets, temperature=2.0))
