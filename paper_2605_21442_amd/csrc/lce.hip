@@ -745,9 +745,9 @@ __device__ __forceinline__ void merge_pair(float& m, float& s, float m2, float s
 // The same with a sum weighted by the same exponentials carried along (distillation).
 __device__ __forceinline__ void merge_weighted(float& m, float& s, float& q, float m2, float s2, float q2) {
   const float mn = fmaxf(m, m2);
-  if (mn == -INFINITY) return;
-  const float a = m == -INFINITY ? 0.f : exp2f(m - mn), b = m2 == -INFINITY ? 0.f : exp2f(m2 - mn);
-  s = s * a + s2 * b;
+  const float a = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - mn);
+  const float b = m2 == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m2 - mn);
+  s = s * a + s2 * b;   // (both sums are 0 where both maxima are -infinity)
   q = q * a + q2 * b;
   m = mn;
 }
@@ -1218,10 +1218,10 @@ __device__ __forceinline__ float grad_scale(const float* grad, const int* n_norm
 // read G (dH with K = ids, dW with K = tokens, G read K-major) need no masking of G.
 // ---------------------------------------------------------------------------------------------
 // The same kernel serves the distillation loss (KD) with soft targets, in four more modes:
-//   Z_WRITE   teacher, forward: the logits of this slab, fp32, P[v][token] (row stride ldt)
+//   Z_WRITE   teacher, forward: the logits of this slab, fp32, into P
 //   KD_STATS  student, forward: per token, over the tile's ids, the (max, sum-exp) pairs of teacher and
 //             student logits / T and the teacher-weighted sum of the student's logits / T (qpart)
-//   P_WRITE   teacher, backward: P = softmax(z/T) of this slab, fp32, P[v][token]
+//   P_WRITE   teacher, backward: P = softmax(z/T) of this slab, fp32
 //   G_SOFT    student, backward: G = c (softmax(z/T) - P) / T
 // scale2 = log2(e) / T (log2(e) for LCE), inv_t = 1 / T; lse is that of the scaled logits.
 //
@@ -1299,6 +1299,33 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
     }
   }
   const int vb = wr * 128 + (lane >> 5) * 4;  // tile-relative vocabulary row base of this lane
+  // The teacher's values P of one slab lie in units of 128 ids x 64 tokens, the part of a tile that one
+  // wave holds (in 12- and 8-wave tiles alike), each in the order of its accumulators: register group q of
+  // block (i, j) is 1 KB, 16 bytes a lane. Producer and consumer move 16 bytes per lane and whole lines
+  // (id-major rows of P took 4 bytes per lane and two 128-byte pieces per instruction).
+  const int wr_u = __builtin_amdgcn_readfirstlane(wr), wc_u = __builtin_amdgcn_readfirstlane(wc);
+  float* punit = nullptr;
+  if constexpr (kMode == P_WRITE || kMode == Z_WRITE || kMode == G_SOFT || kMode == KD_STATS)
+    punit = P + ((int64_t)(vt0 / 128 + wr_u) * (ldt / 64) + (n0 / 64 + wc_u)) * (128 * 64);
+  // The student's epilogues take block b + 1's loads in flight while they use block b = 4 j + i (kF: no test
+  // per element; else `absent` stands for ids past the slab and tokens past Nv).
+  auto load_teacher = [&](float (&x)[16], int b, auto kFull, float absent) {
+    constexpr bool kF = decltype(kFull)::value;
+    const int i = b & 3, j = b >> 2;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 v = *reinterpret_cast<const float4*>(punit + ((i * 2 + j) * 4 + q) * 256 + lane * 4);
+      x[4 * q] = v.x;
+      x[4 * q + 1] = v.y;
+      x[4 * q + 2] = v.z;
+      x[4 * q + 3] = v.w;
+    }
+    if constexpr (!kF) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        x[r] = (tok[j] < nv && vb + i * 32 + (r >> 2) * 8 + (r & 3) < vleft) ? x[r] : absent;
+    }
+  };
   if constexpr (WM == 3 && kMode == G_ONEHOT) {
     // G straight from registers. A lane holds 4 consecutive ids of a token row per (block, group
     // of 8 ids), the other 4 sit in lane L ^ 32; one lane swap across the wave halves
@@ -1354,68 +1381,65 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
     else store_tile(std::false_type{});
     return;
   } else if constexpr (kMode == P_WRITE || kMode == Z_WRITE) {
-    // P[v][token] rows of this tile: lanes of a half-wave hold 32 consecutive tokens of one row
+    // the whole tile is written (the consumer masks the ids and tokens that do not exist)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (tok[j] >= nv) continue;
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int vr = vb + i * 32 + (r >> 2) * 8 + (r & 3);
-          if (vr < vleft)
-            P[(int64_t)(vt0 + vr) * ldt + tok[j]] =
-                kMode == Z_WRITE ? acc[i][j][r] : __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -l2[j]));
+        for (int q = 0; q < 4; ++q) {
+          float x[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float z = acc[i][j][4 * q + e];
+            // a copy made here, store by store: the compiler forms all stores' operands at once and spills
+            if constexpr (kMode == Z_WRITE) asm volatile("" : "+v"(z));
+            x[e] = kMode == Z_WRITE ? z : __builtin_amdgcn_exp2f(fmaf(z, scale2, -l2[j]));
+          }
+          store16_padded(punit + ((i * 2 + j) * 4 + q) * 256 + lane * 4,
+                         __builtin_bit_cast(i32x4_t, make_float4(x[0], x[1], x[2], x[3])));
         }
-    }
     return;
   } else if constexpr (kMode == KD_STATS) {
     // the main loop ends with a barrier: its LDS is free for the two wave rows' values [2][kKdVals][256]
     float* red = reinterpret_cast<float*>(smem);
-    // the teacher's logits through a buffer resource per block of 32 ids: a per-lane 32-bit offset and a
-    // uniform row offset; one block at a time folded into running values, so that 16 are held at once
-    const int wr_u = __builtin_amdgcn_readfirstlane(wr);
-    const uint32_t zoff = (uint32_t)(((lane >> 5) * 4 * ldt + wc * 64 + (lane & 31)) * 4);
-    auto zrow = [&](int r) { return (uint32_t)(((r >> 2) * 8 + (r & 3)) * ldt * 4); };
     // (tiles of valid tokens and existing ids only test nothing per element)
     auto stats = [&](auto kFull) {
       constexpr bool kF = decltype(kFull)::value;
+      float zt[2][16];
+      load_teacher(zt[0], 0, kFull, -INFINITY);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const bool tok_ok = kF || tok[j] < nv;
         float mt = -INFINITY, st = 0.f, q = 0.f, ms = -INFINITY, ss = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int row0 = wr_u * 128 + i * 32;
-          const __amdgpu_buffer_rsrc_t rz = make_rsrc(P + (int64_t)(vt0 + row0) * ldt + n0, (uint64_t)32 * ldt * 4);
-          float zt[16], mb = -INFINITY, sb = 0.f, qb = 0.f;
+          const int b = 4 * j + i;
+          if (b < 7) load_teacher(zt[(b + 1) & 1], b + 1, kFull, -INFINITY);
+          float mb = -INFINITY, sb = 0.f, qb = 0.f;
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const bool ok = kF || (tok_ok && vb + i * 32 + (r >> 2) * 8 + (r & 3) < vleft);
-            zt[r] = ok ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rz, (int)(zoff + j * 128), (int)zrow(r), 0))
-                       : -INFINITY;
             if (!kF && vb + i * 32 + (r >> 2) * 8 + (r & 3) >= vleft) acc[i][j][r] = -INFINITY;
             ms = fmaxf(ms, acc[i][j][r]);
-            mb = fmaxf(mb, zt[r]);
+            mb = fmaxf(mb, zt[b & 1][r]);
           }
           mb *= scale2;
-          if (mb != -INFINITY) {
+          // no value in the block: every exponential is 0 under any finite reference (no branch here, so
+          // that the next block's loads stay in flight)
+          const float ref = mb == -INFINITY ? 0.f : mb;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const float e = __builtin_amdgcn_exp2f(fmaf(zt[r], scale2, -mb));
-              sb += e;
-              if (kF || vb + i * 32 + (r >> 2) * 8 + (r & 3) < vleft) qb = fmaf(e, acc[i][j][r] * inv_t, qb);
-            }
+          for (int r = 0; r < 16; ++r) {
+            const float e = __builtin_amdgcn_exp2f(fmaf(zt[b & 1][r], scale2, -ref));
+            sb += e;
+            if (kF || vb + i * 32 + (r >> 2) * 8 + (r & 3) < vleft) qb = fmaf(e, acc[i][j][r] * inv_t, qb);
           }
           merge_weighted(mt, st, q, mb, sb, qb);
         }
         ms *= scale2;
-        if (ms != -INFINITY) {
+        const float ref = ms == -INFINITY ? 0.f : ms;
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) ss += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -ms));
-        }
+          for (int r = 0; r < 16; ++r) ss += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -ref));
         // merge the two lane halves (disjoint ids of the same tokens)
         merge_weighted(mt, st, q, __shfl_xor(mt, 32), __shfl_xor(st, 32), __shfl_xor(q, 32));
         merge_pair(ms, ss, __shfl_xor(ms, 32), __shfl_xor(ss, 32));
@@ -1458,20 +1482,17 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
   // (a runtime test would be kept, as masks and branches, on every tile)
   auto fill = [&](auto kFull) {
     constexpr bool kF = decltype(kFull)::value;
+    float pt[2][16];
+    if constexpr (kMode == G_SOFT) load_teacher(pt[0], 0, kFull, 0.f);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const bool tok_ok = kF || tok[j] < nv;
       const int nl = wc * 64 + j * 32 + (lane & 31);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float pt[16];
+        const int blk = 4 * j + i;
         if constexpr (kMode == G_SOFT) {
-          // the block's 16 teacher probabilities are loaded together, then used
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int vr = vb + i * 32 + (r >> 2) * 8 + (r & 3);
-            pt[r] = (kF || (tok_ok && vr < vleft)) ? P[(int64_t)(vt0 + vr) * ldt + tok[j]] : 0.f;
-          }
+          if (blk < 7) load_teacher(pt[(blk + 1) & 1], blk + 1, kFull, 0.f);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -1484,7 +1505,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
             if (kF || (tok_ok && vr < vleft)) {
               const float e2 = __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -l2[j]));
               if constexpr (kMode == G_SOFT) {
-                g = cj[j] * inv_t * (e2 - pt[r]);
+                g = cj[j] * inv_t * (e2 - pt[blk & 1][r]);
               } else {
                 g = cj[j] * e2;
                 if (vr == tgt[j]) g -= cj[j];
