@@ -126,7 +126,7 @@ typedef struct lce_adamw {
  * Calls of few tokens (a slab of that width times the tokens is at most 1024 tiles of
  * 384 x 256) take the fewest equal slabs that keep the [N, V_slab] bf16 block within 1.25 GiB.
  * The backward's size does not depend on V; the forward's vocabulary partials
- * take at most 2*D bytes per token. Either output pointer may be NULL.
+ * take at most max(2*D, 4096) bytes per token. Either output pointer may be NULL.
  */
 lce_status_t lce_workspace_size(const lce_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes);
 
@@ -150,7 +150,7 @@ typedef struct lce_plan_info {
   int64_t vc, nslab;        /* backward slab width (ids) and slab count */
   int64_t dh_kz;            /* most K parts of a dH launch: 1, or up to 8 for launches with few tiles */
   int64_t part_rows;        /* partial rows of the forward statistics */
-  int64_t fwd_gathers;      /* 1 if the forward leaves the gathered rows of H in the prefix */
+  int64_t fwd_gathers;      /* 1 if d % 64 == 0: the gathered rows the forward leaves in the prefix are whole K slices */
   int64_t fwd_one_launch;   /* 1 if the forward statistics run as one launch */
   int64_t o_idx, o_pos, o_nv, o_hv;
   int64_t o_pm, o_ps, o_terms, fwd_bytes;

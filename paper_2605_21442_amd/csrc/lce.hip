@@ -25,8 +25,8 @@
 // Every contraction C = A B^T (C [M, N], sum over K) runs one MFMA main loop: bf16
 // v_mfma_f32_32x32x16 with fp32 accumulation, waves of 128x64 outputs, K streamed through
 // two 64-wide LDS slices filled by direct-to-LDS buffer loads (XOR-swizzled 16-byte
-// chunks). Tiles are 384x256 with 12 waves (three per SIMD) for the LCE contractions when
-// D % 64 == 0, else 256x256 with 8 waves. Each operand is either K-contiguous (W and Hv in
+// chunks). Tiles are 384x256 with 12 waves (three per SIMD) for the LCE contractions, and
+// 256x256 with 8 waves for the distillation student and teachers with Dt % 64 != 0. Each operand is either K-contiguous (W and Hv in
 // the forward and G kernels; G in dH) or K-major (G and Hv in dW, the W slab in dH: the
 // MFMA fragments then come from transposing LDS reads), so G is written once, token-major,
 // and W is never copied.
@@ -69,7 +69,6 @@ typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 constexpr int TILE = 256;         // output tile edge (rows of A and of B per workgroup)
 constexpr int KPAD = 64;          // K padding granularity of the backward's staged operands
 constexpr int NTHREADS = 512;     // 8 waves, two per SIMD
-constexpr int MAX_PARTS = 32;     // vocabulary partitions of the forward (x2 wave rows <= 64 lanes)
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr uint32_t kRsrcWord3 = 0x00020000u;  // gfx9 raw buffer: 32-bit data format
@@ -249,7 +248,6 @@ struct Geo {
   static constexpr int SLICE = AREG + 32768;
   static constexpr int LDS = 2 * SLICE;
 };
-constexpr int LDS_BYTES = Geo<2>::LDS;
 constexpr int kDhWM = 3;   // wave rows of the dH contraction
 constexpr int kDwWM = 3;   // wave rows of the dW contraction
 constexpr int kGWM = 3;    // wave rows of the (one-hot) G kernel
@@ -418,6 +416,19 @@ __device__ __forceinline__ void load_operand(const Operand& op, const char* dstp
   }
 }
 
+// Point the chunks of slice k0 at or past K outside the buffer resource (row-major operands). The
+// offsets are changed in place, which takes no registers beside them in the loop, so this is for the
+// last slice that is loaded. (An odd-q offset of a dense operand is the neighbouring lane's even one,
+// which that lane masks by the same chunk index.)
+template <int kKind>
+__device__ __forceinline__ void mask_tail(Operand& op, int k0, int K) {
+  static_assert(kKind != OP_KMAJOR, "");
+  const int ce = lane_chunk_even();
+#pragma unroll
+  for (int q = 0; q < (kKind == OP_DENSE ? 1 : 4); ++q)
+    if (k0 + (ce ^ (q & 1)) * 8 >= K) op.off[q] = kOobOffset;
+}
+
 // w: this wave's index in the workgroup, a wave-uniform (scalar) value
 template <bool kAsm, int kAKind, int kBKind, int WM, bool kMasked>
 __device__ __forceinline__ void load_slice(const Operand& A, const Operand& B, const char* buf, int bufoff, int k0,
@@ -435,8 +446,10 @@ __device__ __forceinline__ void load_slice(const Operand& A, const Operand& B, c
 // buffered (read one substep ahead). WM = 3: 12 waves (three per SIMD), 384 A rows, fragments
 // single-buffered (the 168 registers a wave may hold at three waves per SIMD leave no room for a
 // second set; the other two waves of the SIMD cover the read latency).
-template <int kLateGroups, int kAKind = OP_DENSE, int kBKind = OP_GATHER, int WM = 2, bool kRagged = true>
-__device__ __forceinline__ void mma_mainloop(f32x16_t (&acc)[4][2], const Operand& A, const Operand& B, int K,
+// kTail (row-major operands): K is not a multiple of 64; the last slice's chunks past K read zeros.
+template <int kLateGroups, int kAKind = OP_DENSE, int kBKind = OP_GATHER, int WM = 2, bool kRagged = true,
+          bool kTail = false>
+__device__ __forceinline__ void mma_mainloop(f32x16_t (&acc)[4][2], Operand A, Operand B, int K,
                                              char* smem) {
   using G = Geo<WM>;
   constexpr bool kAKM = kAKind == OP_KMAJOR, kBKM = kBKind == OP_KMAJOR;
@@ -471,6 +484,12 @@ __device__ __forceinline__ void mma_mainloop(f32x16_t (&acc)[4][2], const Operan
   auto load = [&](int s) {
     char* buf = smem + (s & 1) * G::SLICE;
     const int bufoff = lds0 + (s & 1) * G::SLICE;
+    if constexpr (kTail) {
+      if (s == S - 1) {   // (the last slice is the last one loaded)
+        mask_tail<kAKind>(A, s * KSLICE, K);
+        mask_tail<kBKind>(B, s * KSLICE, K);
+      }
+    }
     if (ragged && s == S - 1) load_slice<kAsm, kAKind, kBKind, WM, true>(A, B, buf, bufoff, s * KSLICE, K, wsc);
     else load_slice<kAsm, kAKind, kBKind, WM, false>(A, B, buf, bufoff, s * KSLICE, K, wsc);
   };
@@ -715,23 +734,20 @@ __global__ __launch_bounds__(1024) void k_compact(const void* targets, int tbyte
 // ---------------------------------------------------------------------------------------------
 // K2: forward statistics. The objective (Sec. 4.2) needs each valid row's log-sum-exp over the
 // whole vocabulary; here it is accumulated tile by tile from logits that are never stored (this
-// library's design: the paper states the objective, not an algorithm for it). Two forms, both
-// writing per-token partial pairs (max, sum of exp) in log2 units, part[row * npad + token],
-// merged by K3:
-//  - k_fwd_tile (12 waves, D % 64 == 0): one 384-id x 256-token tile per workgroup, H given as the
-//    gathered valid rows Hv; one partial row per vocabulary tile.
-//  - k_fwd_stats (8 waves, any D): workgroup (token tile nt, vocabulary partition p) walks the
-//    partition's 256-wide tiles with a running pair per token and lane, H's valid rows gathered
-//    through idx by the main loop; two partial rows (one per wave row) per partition.
-// In both, a tile's S^T = W_tile H^T runs a token's logits down a lane's registers.
+// library's design: the paper states the objective, not an algorithm for it). One 384-id x 256-token tile
+// per workgroup of 12 waves, H given as the gathered valid rows Hv: a tile's S^T = W_tile H^T runs a
+// token's logits down a lane's registers, and each tile writes one partial pair (max, sum of exp) per
+// token in log2 units, part[row * npad + token], merged by K3. Widths that are not a multiple of 64
+// (kTail) take the same tiles with both operands masked in the last slice: 2999 x
+// 1000 x 32003 (2549 valid) forward 237 -> 172 us against 256 x 256 tiles of 8 waves that gathered rows
+// in the loop.
 // ---------------------------------------------------------------------------------------------
 // Tiles are taken in the order of xcd_tile (below), in groups of gw vocabulary tiles (the slab
 // rule's width, within the MALL cap, a multiple of 8) by all token tiles, ids fastest: the group's
 // W rows stay in the MALL while the token tiles pass, and the workgroups resident on one XCD share
 // their W and H tiles through its L2 as in the backward's G launches. One launch covers vt_launch tiles from tm0
-// on and writes one partial row per tile (row tm - tm0). When the rows of all tiles would take
-// more than 2 D bytes per token (one bf16 row of H), the host launches one group at a time
-// instead: group g writes to one of two row sets (by the parity of g), and in launch g >= 1 the
+// on and writes one partial row per tile (row tm - tm0). When the rows of all tiles would take too
+// much space (fwd_one_launch), the host launches one group at a time instead: group g writes to one of two row sets (by the parity of g), and in launch g >= 1 the
 // workgroup of the group's first tile of each token tile first folds the other set (group g - 1,
 // complete since launches on a stream run in order) into a running pair per token. The workspace
 // thus stays independent of V.
@@ -777,6 +793,7 @@ __device__ __forceinline__ bool xcd_tile(int b, int tiles, int gw, int nt, int& 
   return tn < nt;
 }
 
+template <bool kTail>
 __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __restrict__ W, int64_t ldw, int v,
                                                             const uint16_t* __restrict__ Hv, int64_t ldh,
                                                             const int* __restrict__ nv_ptr, int d, int tm0,
@@ -813,13 +830,13 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
 
   const Operand opb = dense_operand(Hv + (int64_t)n0 * ldh, nv - n0, ldh);
   f32x16_t acc[4][2];
-  // d % 64 == 0 (host); the last vocabulary tile may hold fewer than TM rows of W
+  // (kTail: d % 64 != 0); the last vocabulary tile may hold fewer than TM rows of W
   if (vleft >= TM)
-    mma_mainloop<1, OP_DENSE, OP_DENSE, WM, false>(acc, dense_operand(W + (int64_t)v0 * ldw, vleft, ldw), opb, d,
-                                                   smem);
+    mma_mainloop<1, OP_DENSE, OP_DENSE, WM, false, kTail>(acc, dense_operand(W + (int64_t)v0 * ldw, vleft, ldw), opb,
+                                                          d, smem);
   else
-    mma_mainloop<1, OP_GATHER, OP_DENSE, WM, false>(acc, masked_dense_operand<TM>(W + (int64_t)v0 * ldw, vleft, ldw),
-                                                    opb, d, smem);
+    mma_mainloop<1, OP_GATHER, OP_DENSE, WM, false, kTail>(
+        acc, masked_dense_operand<TM>(W + (int64_t)v0 * ldw, vleft, ldw), opb, d, smem);
   // the main loop ends with a barrier: its LDS is free for the wave rows' pairs [3][256] (m, s)
   float* red_m = reinterpret_cast<float*>(smem);
   float* red_s = red_m + WM * TILE;
@@ -886,100 +903,6 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
     if (tok < nv) {
       part_m[(int64_t)tl * npad + tok] = m;
       part_s[(int64_t)tl * npad + tok] = s;
-    }
-  }
-}
-
-template <int WM>
-__global__ __launch_bounds__(Geo<WM>::NT, WM) void k_fwd_stats(const uint16_t* __restrict__ W, int64_t ldw, int v,
-                                                           const uint16_t* __restrict__ H, int64_t ldh, int64_t n,
-                                                           const int* __restrict__ idx, const int* __restrict__ nv_ptr,
-                                                           int d, int nparts, int nt_max, int vt_count,
-                                                           float* __restrict__ part_m, float* __restrict__ part_s,
-                                                           int npad, float scale2) {
-  // scale2 = log2(e) / T: partials are kept in base-2 units of the logits divided by T.
-  static_assert(WM == 2, "");
-  constexpr int TM = Geo<WM>::TM;
-  __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
-  // Workgroups are dispatched round-robin over the 8 XCDs (block b runs on XCD b % 8). Each XCD
-  // owns whole vocabulary partitions (p = xcd + 8 k, k < ppx) and runs its workgroups in rounds of
-  // about 32 (one per CU): every round covers all ppx partitions for a group of 32 / ppx token
-  // tiles, so the resident workgroups share ppx W tiles and 32 / ppx H tiles through the XCD's L2
-  // (12 distinct tiles per 32 workgroups at ppx = 4, where one partition over 32 token tiles
-  // would stream 32 distinct H tiles). The last round takes the token tiles that are left.
-  int nt, p;
-  if (nparts % 8 == 0) {
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int ppx = nparts >> 3;
-    const int gn = ppx >= 32 ? 1 : 32 / ppx;
-    const int r = slot / (ppx * gn), rem = slot % (ppx * gn);
-    p = xcd + 8 * (rem % ppx);
-    nt = r * gn + rem / ppx;
-  } else {
-    nt = blockIdx.x % nt_max;
-    p = blockIdx.x / nt_max;
-  }
-  const int nv = *nv_ptr;
-  const int n0 = nt * TILE;
-  if (n0 >= nv) return;
-  const int vt0 = (int)((int64_t)p * vt_count / nparts), vt1 = (int)((int64_t)(p + 1) * vt_count / nparts);
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wr = wave >> 2, wc = wave & 3;
-  const Operand opb = gather_operand(H, n, ldh, idx, n0, nv);
-
-  f32x16_t acc[4][2];
-  float m2[2], ss[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) { m2[j] = -INFINITY; ss[j] = 0.f; }
-
-  for (int vt = vt0; vt < vt1; ++vt) {
-    const int v0 = vt * TM;
-    const int vleft = v - v0;
-    if (vleft >= TM)
-      mma_mainloop<2, OP_DENSE, OP_GATHER, WM>(acc, dense_operand(W + (int64_t)v0 * ldw, vleft, ldw), opb, d, smem);
-    else
-      mma_mainloop<2, OP_GATHER, OP_GATHER, WM>(acc, masked_dense_operand<TM>(W + (int64_t)v0 * ldw, vleft, ldw), opb,
-                                                d, smem);
-
-    // rows (vocabulary ids) of this lane: v0 + wr*128 + 32 bi + 8 (r/4) + 4 (lane/32) + r%4
-    const int vb = wr * 128 + (lane >> 5) * 4;
-    const bool ragged = vleft < TM;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      float mx = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          if (ragged && (vb + i * 32 + (r >> 2) * 8 + (r & 3)) >= vleft) acc[i][j][r] = -INFINITY;
-          mx = fmaxf(mx, acc[i][j][r]);
-        }
-      const float nm = fmaxf(m2[j], mx * scale2);
-      if (nm == -INFINITY) continue;
-      float s = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -nm));
-      ss[j] = (m2[j] == -INFINITY ? 0.f : ss[j] * __builtin_amdgcn_exp2f(m2[j] - nm)) + s;
-      m2[j] = nm;
-    }
-  }
-  // merge the two lane halves (disjoint vocabulary rows), then write this wave row's partial
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const float om = __shfl_xor(m2[j], 32), os = __shfl_xor(ss[j], 32);
-    const float nm = fmaxf(m2[j], om);
-    float s = 0.f;
-    if (nm != -INFINITY) {
-      s = (m2[j] == -INFINITY ? 0.f : ss[j] * __builtin_amdgcn_exp2f(m2[j] - nm)) +
-          (om == -INFINITY ? 0.f : os * __builtin_amdgcn_exp2f(om - nm));
-    }
-    const int tok = n0 + wc * 64 + j * 32 + (lane & 31);
-    if (lane < 32 && tok < nv) {
-      const int64_t o = (int64_t)(WM * p + wr) * npad + tok;
-      part_m[o] = nm;
-      part_s[o] = s;
     }
   }
 }
@@ -1233,7 +1156,7 @@ __device__ __forceinline__ float grad_scale(const float* grad, const int* n_norm
 enum GMode { G_ONEHOT = 0, G_SOFT = 1, KD_STATS = 2, P_WRITE = 3, Z_WRITE = 4 };
 constexpr int kKdVals = 5;   // values per token and tile of KD_STATS: teacher max, sum, weighted sum; student max, sum
 
-template <int kMode, int WM>
+template <int kMode, int WM, bool kTail = false>
 __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __restrict__ W, int64_t ldw, int64_t v0, int vs,
                                                        const uint16_t* __restrict__ H, int64_t ldh, int64_t n,
                                                        const void* targets, int tbytes, int64_t id0,
@@ -1243,9 +1166,9 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
                                                        uint16_t* __restrict__ G, int vc, int ldt,
                                                        float scale2, float inv_t, float* __restrict__ P,
                                                        float* __restrict__ qpart, int64_t qrow, int gsub) {
-  // 12 waves (WM = 3, 384 ids per tile) serve the one-hot LCE gradient when D % 64 == 0; the
-  // distillation modes and other widths keep 8 waves and the LDS-staged epilogue below
-  static_assert(WM == 2 || kMode == G_ONEHOT || kMode == P_WRITE || kMode == Z_WRITE, "");
+  // 12 waves (WM = 3, 384 ids per tile) serve the one-hot LCE gradient and the teacher when Dt % 64 == 0;
+  // the student and other teachers keep 8 waves (and the student's G the LDS-staged epilogue below)
+  static_assert(WM == 2 ? kMode != G_ONEHOT : (kMode == G_ONEHOT || kMode == P_WRITE || kMode == Z_WRITE), "");
   constexpr int TM = Geo<WM>::TM;
   __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
   const int nv = *nv_ptr;
@@ -1263,12 +1186,12 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
   f32x16_t acc[4][2];
   // the last tile of the vocabulary may hold fewer than TM rows of W
   if constexpr (WM == 3) {
-    // H is the gathered valid rows Hv (row stride ldh = d): a dense operand; d % 64 == 0 (host)
+    // H is the gathered valid rows Hv (row stride ldh = d): a dense operand (kTail: d % 64 != 0)
     const Operand opb = dense_operand(H + (int64_t)n0 * ldh, nv - n0, ldh);
     if (vleft >= TM)
-      mma_mainloop<1, OP_DENSE, OP_DENSE, WM, false>(acc, dense_operand(wt, vleft, ldw), opb, d, smem);
+      mma_mainloop<1, OP_DENSE, OP_DENSE, WM, false, kTail>(acc, dense_operand(wt, vleft, ldw), opb, d, smem);
     else
-      mma_mainloop<1, OP_GATHER, OP_DENSE, WM, false>(acc, masked_dense_operand<TM>(wt, vleft, ldw), opb, d, smem);
+      mma_mainloop<1, OP_GATHER, OP_DENSE, WM, false, kTail>(acc, masked_dense_operand<TM>(wt, vleft, ldw), opb, d, smem);
   } else {
     const Operand opb = gather_operand(H, n, ldh, idx, n0, nv);
     if (vleft >= TM)
@@ -1504,12 +1427,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
             float g = 0.f;
             if (kF || (tok_ok && vr < vleft)) {
               const float e2 = __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -l2[j]));
-              if constexpr (kMode == G_SOFT) {
-                g = cj[j] * inv_t * (e2 - pt[blk & 1][r]);
-              } else {
-                g = cj[j] * e2;
-                if (vr == tgt[j]) g -= cj[j];
-              }
+              g = cj[j] * inv_t * (e2 - pt[blk & 1][r]);
             }
             gq[e] = g;
           }
@@ -2017,7 +1935,7 @@ Timing g_timing;
 
 struct Plan {
   int64_t n, d, v, ldh, ldw, npad;
-  int nt_max, vt_count, nparts, vt_count3;   // vt_count3: 384-id tiles
+  int nt_max, vt_count, vt_count3;           // vt_count3: 384-id tiles
   int64_t vc, nslab;
   int64_t gw;                                // 384-id tiles of the forward's vocabulary groups
   int64_t rows_g;                            // rows of G and dH32: Npad rounded up to a 384-row tile
@@ -2026,17 +1944,16 @@ struct Plan {
   size_t o_g, o_dh32, o_dh32b, bwd_bytes;    // o_dh32b: accumulator of the second K part (or 0)
   int dh_kz;                                 // most K parts a dH launch takes (1 to 8)
   int part_rows;                             // partial rows of the forward statistics
+  int fgw;                                   // 384-id tiles of a group of the forward (more than one launch)
+  bool few_rows;                             // the forward's partials in the least space (few_partial_rows)
 };
 
-// the 12-wave forward in one launch: its partial rows (8 bytes per 384-id tile and token) take at
-// most 2 D bytes per token
+// the forward in one launch: its partial rows (8 bytes per 384-id tile and token) take at most 2 D bytes
+// per token or, for narrow heads, 4 KiB (512 tiles, 196608 ids: 16384 x 72 x 100000 in five launches of 64
+// tiles, each waiting for the fold of the one before, 1314 us, in one 563)
 inline bool fwd_one_launch(const Plan& pl) {
-  return pl.vt_count3 <= pl.d / 4 && (int64_t)pl.vt_count3 * pl.nt_max <= INT32_MAX;
-}
-
-// the forward statistics run on 12-wave tiles over the gathered rows Hv (left in the workspace)
-inline bool fwd_gathers(const Plan& pl) {
-  return pl.d % KSLICE == 0 && (int64_t)pl.vt_count3 * pl.nt_max <= INT32_MAX;
+  return !pl.few_rows && pl.vt_count3 <= std::max<int64_t>(pl.d / 4, 512) &&
+         (int64_t)pl.vt_count3 * pl.nt_max <= INT32_MAX;
 }
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
@@ -2119,6 +2036,31 @@ int64_t few_token_slab(int64_t v, int64_t npad, int64_t vc, int64_t elem_bytes) 
   return round_up((v + slabs - 1) / slabs, 768);
 }
 
+// The forward's regions after the prefix: rows partial pairs per token and the per-row terms.
+void place_partials(Plan* pl, int64_t rows) {
+  const size_t arr = (4 * (size_t)rows * pl->npad + 255) / 256 * 256;
+  pl->part_rows = (int)rows;
+  pl->o_pm = pl->o_hv + (2 * (size_t)pl->d * pl->npad + 255) / 256 * 256;
+  pl->o_ps = pl->o_pm + arr;
+  pl->o_terms = pl->o_ps + arr;
+  pl->fwd_bytes = pl->o_terms + 4 * (size_t)pl->npad;
+}
+
+// For a workspace smaller than the plan's forward, which callers may hold from before these took the rows
+// they take now, or which the library's fixed array is: widths that are not a multiple of 64 once took at
+// most kFewRows partial rows (two per 256 ids), and narrow heads (more than D / 4 tiles) groups of at least
+// 24 tiles. Groups of 24 tiles, a launch each, need 2 x 24 + 1 rows (a vocabulary of at most 24 tiles its
+// tiles'), never more than either.
+constexpr int kFewRows = 64;
+bool few_partial_rows(Plan* pl, size_t workspace_bytes) {
+  if ((pl->d % KSLICE != 0 || pl->vt_count3 > pl->d / 4) && pl->fwd_bytes > workspace_bytes) {
+    pl->few_rows = true;
+    pl->fgw = 24;
+    place_partials(pl, pl->vt_count3 <= 24 ? pl->vt_count3 : 2 * 24 + 1);
+  }
+  return pl->fwd_bytes <= workspace_bytes;
+}
+
 lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true) {
   if (!p) return LCE_ERR_NULL;
   if ((p->flags & ~(LCE_FLAG_ACCUMULATE_DW | LCE_FLAG_REUSE_FORWARD)) != 0) return LCE_ERR_ARG;
@@ -2139,7 +2081,6 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   pl->npad = round_up(p->n > 0 ? p->n : 1, TILE);
   pl->nt_max = (int)(pl->npad / TILE);
   pl->vt_count = (int)((p->v + TILE - 1) / TILE);
-  pl->nparts = pl->vt_count < MAX_PARTS ? pl->vt_count : MAX_PARTS;
   pl->vt_count3 = (int)((p->v + 383) / 384);
   // backward vocabulary slab: about 4 D columns (at least 8192) keeps G at O(N D) while halving
   // the dH accumulator passes of a 2 D slab. Narrower heads take up to 24576 ids while the slab's
@@ -2170,20 +2111,14 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   pl->o_idx = take(cur, 4 * (size_t)pl->npad);
   pl->o_pos = take(cur, 4 * (size_t)pl->npad);
   pl->o_nv = take(cur, 256);
-  // valid rows of H, gathered by the forward (12-wave statistics) and by the backward; a backward
-  // with LCE_FLAG_REUSE_FORWARD finds the forward's here
+  // valid rows of H, gathered by the forward and by the backward; a backward with
+  // LCE_FLAG_REUSE_FORWARD finds the forward's here
   pl->o_hv = take(cur, 2 * (size_t)p->d * pl->npad);
-  const size_t common = cur;
-  // partial rows: 2 per partition (8-wave forward); one per 384-id tile while that is at most
-  // 2 D bytes per token, else two sets of vc / 384 rows and a running pair (12-wave forward)
+  // partial rows: one per 384-id tile in one launch, else two sets of vc / 384 rows and a running pair
+  pl->few_rows = false;
+  pl->fgw = (int)(vc / 384);
   const int64_t rows3 = fwd_one_launch(*pl) ? pl->vt_count3 : 2 * (vc / 384) + 1;
-  const int64_t part_rows = 2 * pl->nparts > rows3 ? 2 * pl->nparts : rows3;
-  pl->part_rows = (int)part_rows;
-  pl->o_pm = take(cur, 4 * (size_t)part_rows * pl->npad);
-  pl->o_ps = take(cur, 4 * (size_t)part_rows * pl->npad);
-  pl->o_terms = take(cur, 4 * (size_t)pl->npad);
-  pl->fwd_bytes = cur;
-  cur = common;
+  place_partials(pl, std::max<int64_t>(2 * std::min(pl->vt_count, kFewRows / 2), rows3));
   // G and the fp32 dH accumulators hold every row a 384-row dH tile can address (the tiles of
   // the last token rows reach past Npad), so that no access leaves its region
   pl->rows_g = round_up(pl->npad, 384);
@@ -2285,31 +2220,29 @@ struct PartRows {
   const float* run_s;
 };
 
-// Vocabulary statistics of one head, in log2 units of the logits times scale2 / log2(e). With
-// D % 64 == 0 and a gather buffer hv (Npad x D bf16), the valid rows of H are gathered and the
-// 12-wave tiles run, in one launch or one per group of tiles as `layout` (the plan that sized the
-// partial rows pm / ps) decides; otherwise the 8-wave partitions gather rows in their loop.
+// The valid rows of H (row stride ldh, d wide) made contiguous in hv.
+void launch_gather(Launcher& L, const uint16_t* H, int64_t ldh, int d, int64_t npad, const int* idx, const int* nv,
+                   uint16_t* hv) {
+  L(K_GATHER_H, k_gather_rows, dim3((unsigned)std::min<int64_t>((npad * (d / 8) + 255) / 256, 16384)), dim3(256), H,
+    ldh, idx, nv, d, hv);
+}
+
+// Vocabulary statistics, in log2 units of the logits: the valid rows of H are gathered into hv and the
+// tiles run, in one launch or one per group of tiles (as the plan that sized the partial rows decides).
 PartRows launch_fwd_stats(Launcher& L, const Plan& layout, const uint16_t* W, int64_t ldw, const uint16_t* H,
-                          int64_t ldh, int d, const int* idx, const int* nv, uint16_t* hv, float* pm, float* ps,
-                          float scale2) {
-  const int v = (int)layout.v, npad = (int)layout.npad, nt_max = layout.nt_max;
-  // (the same condition as fwd_gathers(layout) when d is the plan's own width)
-  if (!(hv && d % KSLICE == 0 && (int64_t)layout.vt_count3 * nt_max <= INT32_MAX)) {
-    L(K_FWD_STATS, k_fwd_stats<2>, dim3(nt_max * layout.nparts), dim3(NTHREADS), W, ldw, v, H, ldh, layout.n, idx,
-      nv, d, layout.nparts, nt_max, layout.vt_count, pm, ps, npad, scale2);
-    return PartRows{pm, ps, 2 * layout.nparts, nullptr, nullptr};
-  }
-  L(K_GATHER_H, k_gather_rows, dim3((unsigned)std::min<int64_t>(((int64_t)npad * (d / 8) + 255) / 256, 16384)),
-    dim3(256), H, ldh, idx, nv, d, hv);
-  const int gw = (int)(layout.vc / Geo<3>::TM);
+                          int64_t ldh, const int* idx, const int* nv, uint16_t* hv, float* pm, float* ps) {
+  const int v = (int)layout.v, npad = (int)layout.npad, nt_max = layout.nt_max, d = (int)layout.d;
+  const auto kernel = d % KSLICE == 0 ? k_fwd_tile<false> : k_fwd_tile<true>;
+  launch_gather(L, H, ldh, d, npad, idx, nv, hv);
+  const int gw = layout.fgw;
   const int ntl = layout.vt_count3;
   if (fwd_one_launch(layout)) {
     // one launch: the groups only order the tiles (as wide as the slab rule's width, or narrower
     // where its W rows would not stay in the MALL)
     const TileOrder to = tile_order(ntl, nt_max, group_tiles(layout.gw, Geo<3>::TM, d));
-    L(K_FWD_STATS, k_fwd_tile, dim3(to.grid), dim3(Geo<3>::NT), W, ldw, v, (const uint16_t*)hv,
+    L(K_FWD_STATS, kernel, dim3(to.grid), dim3(Geo<3>::NT), W, ldw, v, (const uint16_t*)hv,
       (int64_t)d, nv, d, 0, ntl, to.gw, nt_max, pm, ps, (const float*)nullptr, (const float*)nullptr, 0,
-      (float*)nullptr, (float*)nullptr, 0, npad, scale2);
+      (float*)nullptr, (float*)nullptr, 0, npad, kLog2e);
     return PartRows{pm, ps, ntl, nullptr, nullptr};
   }
   // one group per launch; row sets: parity 0 at rows [0, gw), parity 1 at [gw, 2 gw), the
@@ -2322,10 +2255,10 @@ PartRows launch_fwd_stats(Launcher& L, const Plan& layout, const uint16_t* W, in
     const int tm0 = g * gw, wl = std::min(gw, ntl - tm0);
     const int64_t cur = (g & 1) * rs, prev = ((g + 1) & 1) * rs;
     const TileOrder to = tile_order(wl, nt_max, wl);
-    L(K_FWD_STATS, k_fwd_tile, dim3(to.grid), dim3(Geo<3>::NT), W, ldw, v, (const uint16_t*)hv,
+    L(K_FWD_STATS, kernel, dim3(to.grid), dim3(Geo<3>::NT), W, ldw, v, (const uint16_t*)hv,
       (int64_t)d, nv, d, tm0, wl, to.gw, nt_max, pm + cur, ps + cur,
       g > 0 ? (const float*)(pm + prev) : (const float*)nullptr, (const float*)(ps + prev), gw, run_m, run_s,
-      g == 1 ? 1 : 0, npad, scale2);
+      g == 1 ? 1 : 0, npad, kLog2e);
   }
   const int64_t last = ((ng - 1) & 1) * rs;
   return PartRows{pm + last, ps + last, ntl - (ng - 1) * gw, ng > 1 ? run_m : nullptr, run_s};
@@ -2342,7 +2275,7 @@ lce_status_t forward_impl(const lce_problem_t* p, const ShardInfo* shard, const 
   if ((!shard && !loss) || (shard && !tgt_part) || !n_valid) return LCE_ERR_NULL;
   if (pl.n > 0 && (!H || !W || !targets || !lse || !workspace)) return LCE_ERR_NULL;
   if (pl.n > 0 && (!aligned16(H) || !aligned16(W) || ((uintptr_t)workspace & 255) != 0)) return LCE_ERR_ALIGN;
-  if (pl.n > 0 && workspace_bytes < pl.fwd_bytes) return LCE_ERR_WORKSPACE;
+  if (pl.n > 0 && !few_partial_rows(&pl, workspace_bytes)) return LCE_ERR_WORKSPACE;
   Launcher L{(hipStream_t)stream};
   const bool none = !shard && p->reduction == LCE_REDUCE_NONE;
   if (pl.n == 0) {
@@ -2362,8 +2295,8 @@ lce_status_t forward_impl(const lce_problem_t* p, const ShardInfo* shard, const 
   // rows that are not valid get lse 0 and a zero per-token loss (or shard target logit)
   L(K_COMPACT, k_compact, dim3(1), dim3(1024), targets, p->target_bytes, pl.n, si.v_total, p->ignore_index,
     idx, pos, nv, n_valid, dev_status, lse, none ? loss : tgt_part, (float*)nullptr);
-  const PartRows pr = launch_fwd_stats(L, pl, w, pl.ldw, h, pl.ldh, (int)pl.d, (const int*)idx, (const int*)nv,
-                                       (uint16_t*)(ws + pl.o_hv), pm, ps, kLog2e);
+  const PartRows pr = launch_fwd_stats(L, pl, w, pl.ldw, h, pl.ldh, (const int*)idx, (const int*)nv,
+                                       (uint16_t*)(ws + pl.o_hv), pm, ps);
   L(K_COMBINE, k_combine, dim3((unsigned)((pl.n + kCombTok - 1) / kCombTok)), dim3(1024), h, pl.ldh, w, pl.ldw,
     targets, p->target_bytes, si.v_begin, pl.v, (const int*)idx, (const int*)nv, (int)pl.d, pr.count, pr.m, pr.s,
     (int)pl.npad, pr.run_m, pr.run_s, lse, terms, none ? loss : (float*)nullptr, tgt_part);
@@ -2454,21 +2387,17 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
   const uint16_t* w = (const uint16_t*)W;
   const int d = (int)pl.d, npad = (int)pl.npad, vc = (int)pl.vc;
 
-  // with LCE_FLAG_REUSE_FORWARD the workspace holds the forward's valid-row list (and, when the
-  // forward gathered them, the rows Hv); otherwise both are formed again
+  // with LCE_FLAG_REUSE_FORWARD the workspace holds the forward's valid-row list and the rows Hv;
+  // otherwise both are formed again
   const bool reuse = kd ? kd->formed : (p->flags & LCE_FLAG_REUSE_FORWARD) != 0;
   if (!reuse)
     L(K_COMPACT, k_compact, dim3(1), dim3(1024), targets, p->target_bytes, pl.n, si.v_total, p->ignore_index,
       idx, pos, nv, (int*)nullptr, (int*)nullptr, (float*)nullptr, (float*)nullptr, (float*)nullptr);
   // Hv[i] = H[idx[i]] for i < Nv, zero rows up to round_up(Nv, 64)
-  if (kd || !(reuse && fwd_gathers(pl)))
-    L(K_GATHER_H, k_gather_rows, dim3((unsigned)std::min<int64_t>((npad * (d / 8) + 255) / 256, 16384)), dim3(256),
-      h, pl.ldh, (const int*)idx, (const int*)nv, d, hv);
+  if (kd || !reuse) launch_gather(L, h, pl.ldh, d, npad, idx, nv, hv);
   // KD: the teacher's valid rows for its 12-wave probability pass
   uint16_t* hvt = (kd && kd_hvt_bytes(pl, kd->dt) > 0) ? (uint16_t*)(ws + pl.bwd_bytes + kd_p_bytes(pl)) : nullptr;
-  if (hvt && !kd->formed)
-    L(K_GATHER_H, k_gather_rows, dim3((unsigned)std::min<int64_t>(((int64_t)npad * (kd->dt / 8) + 255) / 256, 16384)),
-      dim3(256), kd->ht, kd->ldht, (const int*)idx, (const int*)nv, kd->dt, hvt);
+  if (hvt && !kd->formed) launch_gather(L, kd->ht, kd->ldht, kd->dt, npad, idx, nv, hvt);
   const int dt = (d + TILE - 1) / TILE;
   const int dh_tiles = (int)((pl.npad + Geo<kDhWM>::TM - 1) / Geo<kDhWM>::TM);
   void (*dw_kernel)(const uint16_t*, int, int, int, const uint16_t*, int, const int*, int, uint16_t*, int64_t,
@@ -2497,20 +2426,12 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
         (const int*)n_valid, p->reduction, d, tm, g, vc, npad, kd->scale2, kd->inv_t, P, (float*)nullptr,
         (int64_t)0, to.gw);
     } else {
-      if (d % KSLICE == 0) {
-        const int tmg = (vs + Geo<kGWM>::TM - 1) / Geo<kGWM>::TM;
-        const TileOrder to = tile_order(tmg, pl.nt_max, group_tiles(tmg, Geo<3>::TM, d));
-        L(K_BWD_G, k_bwd_g<G_ONEHOT, kGWM>, dim3(to.grid), dim3(Geo<kGWM>::NT), w, pl.ldw, v0, vs,
-          (const uint16_t*)hv, (int64_t)d, pl.n, targets, p->target_bytes, si.v_begin, (const int*)idx, (const int*)nv,
-          lse, grad_loss, (const int*)n_valid, p->reduction, d, tmg, g, vc, npad, kLog2e, 1.f, (float*)nullptr,
-          (float*)nullptr, (int64_t)0, to.gw);
-      } else {
-        const TileOrder to = tile_order(tm, pl.nt_max, tm);
-        L(K_BWD_G, k_bwd_g<G_ONEHOT, 2>, dim3(to.grid), dim3(NTHREADS), w, pl.ldw, v0, vs, h,
-          pl.ldh, pl.n, targets, p->target_bytes, si.v_begin, (const int*)idx, (const int*)nv, lse, grad_loss,
-          (const int*)n_valid, p->reduction, d, tm, g, vc, npad, kLog2e, 1.f, (float*)nullptr, (float*)nullptr,
-          (int64_t)0, to.gw);
-      }
+      const int tmg = (vs + Geo<kGWM>::TM - 1) / Geo<kGWM>::TM;
+      const TileOrder to = tile_order(tmg, pl.nt_max, group_tiles(tmg, Geo<3>::TM, d));
+      L(K_BWD_G, d % KSLICE == 0 ? k_bwd_g<G_ONEHOT, kGWM> : k_bwd_g<G_ONEHOT, kGWM, true>, dim3(to.grid),
+        dim3(Geo<kGWM>::NT), w, pl.ldw, v0, vs, (const uint16_t*)hv, (int64_t)d, pl.n, targets, p->target_bytes, si.v_begin,
+        (const int*)idx, (const int*)nv, lse, grad_loss, (const int*)n_valid, p->reduction, d, tmg, g, vc, npad, kLog2e,
+        1.f, (float*)nullptr, (float*)nullptr, (int64_t)0, to.gw);
     }
     // split launches: a block for each part the tiles may take; otherwise 8 XCDs x 32 CUs x (whole rounds of the
     // largest per-XCD share + one round for the split tail)
@@ -2597,9 +2518,7 @@ lce_status_t kd_forward_launches(Launcher& L, const lce_kd_problem_t* p, const K
   L(K_COMPACT, k_compact, dim3(1), dim3(1024), targets, p->target_bytes, pl.n, pl.v, p->ignore_index,
     idx, (int*)(ws + pl.o_pos), nv, n_valid, dev_status, lse_s, lse_t, none ? loss : (float*)nullptr);
   uint16_t* hvt = kd_hvt_bytes(pl, kd.dt) > 0 ? (uint16_t*)(ws + o_hvt) : nullptr;
-  if (hvt)
-    L(K_GATHER_H, k_gather_rows, dim3((unsigned)std::min<int64_t>(((int64_t)npad * (kd.dt / 8) + 255) / 256, 16384)),
-      dim3(256), kd.ht, kd.ldht, (const int*)idx, (const int*)nv, kd.dt, hvt);
+  if (hvt) launch_gather(L, kd.ht, kd.ldht, kd.dt, npad, idx, nv, hvt);
   for (int64_t s = 0; s < pl.nslab; ++s) {
     const int64_t v0 = s * pl.vc;
     const int vs = (int)(pl.v - v0 < pl.vc ? pl.v - v0 : pl.vc);
@@ -2707,7 +2626,7 @@ lce_status_t lce_plan_info(const lce_problem_t* p, lce_plan_info_t* out) {
   out->nslab = pl.nslab;
   out->dh_kz = pl.dh_kz;
   out->part_rows = pl.part_rows;
-  out->fwd_gathers = fwd_gathers(pl) ? 1 : 0;
+  out->fwd_gathers = pl.d % KSLICE == 0 ? 1 : 0;
   out->fwd_one_launch = fwd_one_launch(pl) ? 1 : 0;
   out->o_idx = (int64_t)pl.o_idx;
   out->o_pos = (int64_t)pl.o_pos;
@@ -2772,7 +2691,7 @@ lce_status_t lce_forward_noalloc(const lce_problem_t* p, const void* H, const vo
   Plan pl;
   lce_status_t st = make_plan(p, &pl);
   if (st != LCE_OK) return st;
-  if (pl.fwd_bytes > (size_t)LCE_NOALLOC_SCRATCH_BYTES) return LCE_ERR_WORKSPACE;
+  if (!few_partial_rows(&pl, (size_t)LCE_NOALLOC_SCRATCH_BYTES)) return LCE_ERR_WORKSPACE;
   void* ws = nullptr;
   st = noalloc_scratch(stream, &ws);
   if (st != LCE_OK) return st;

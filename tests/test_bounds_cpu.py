@@ -426,3 +426,48 @@ def test_split_dh_launches_cover_every_tile_and_part_once_on_all_xcds(n, d):
         assert sorted(b[1:4] for b in blocks) == want
         per_xcd = [sum(b[0] == x for b in blocks) for x in range(8)]
         assert max(per_xcd) - min(per_xcd) <= 1
+
+
+@pytest.mark.parametrize("d", [8, 56, 64, 72, 264, 1000, 1016])
+def test_the_tail_mask_keeps_row_major_loads_inside_their_rows(d):
+    # the last K slice of a width that is not a multiple of 64, as mask_tail and load_operand form it: lane j of
+    # a wave loads row j // 8 of each of 4 groups of 8 rows, chunk ce for even groups and ce ^ 1 for odd ones (a
+    # dense operand takes the odd one's offset, mask included, from lane j ^ 1); every chunk below d is loaded
+    # once per row and none at or past d
+    k0 = (cdiv(d, 64) - 1) * 64
+
+    def ce(j):
+        return (j & 7) ^ ((j >> 3) & 7)
+
+    for dense in (True, False):
+        for q in range(4):
+            got = {}
+            for j in range(64):
+                src = j ^ (q & 1) if dense else j           # whose offset register is used
+                chunk = ce(src) if dense else ce(j) ^ (q & 1)
+                masked = k0 + chunk * 8 >= d
+                assert chunk == ce(j) ^ (q & 1) and src // 8 == j // 8
+                if not masked:
+                    got.setdefault(j // 8, []).append(chunk)
+            for row in range(8):
+                assert sorted(got.get(row, [])) == list(range(cdiv(d - k0, 8)))
+
+
+@pytest.mark.parametrize("n,d,v", [(60000, 1400, 128256), (3000000, 8, 256), (70000, 1000, 128256), (9000, 72, 9216),
+                                   (9000, 72, 9217), (5, 8, 1), (100000, 200, 1000000)])
+def test_a_workspace_of_the_former_ragged_width_size_still_serves_the_forward(n, d, v):
+    # widths that are not a multiple of 64 once took two partial rows per 256 ids, at most 64: callers may hold
+    # workspaces of that size, and the fixed array of lce_forward_noalloc served the problems that fit so. The
+    # forward then takes groups of 24 tiles: 2 x 24 + 1 rows, or the tiles themselves where they are at most 24
+    info = B.lce_plan_info(B.problem(n, d, v))
+    npad = info["npad"]
+    former = info["o_pm"] + 2 * rup(4 * 2 * min(cdiv(v, 256), 32) * npad, 256) + 4 * npad
+    vt3 = cdiv(v, 384)
+    rows = vt3 if vt3 <= 24 else 49
+    assert info["o_pm"] + 2 * rup(4 * rows * npad, 256) + 4 * npad <= former <= info["fwd_bytes"]
+    ok = dict(H=0x100000, W=0x200000, targets=0x300000, loss=0x400000, lse=0x500000, n_valid=0x600000, dev_status=0,
+              workspace=0x700000, stream=0)
+    with pytest.raises(B.LceError) as e:                      # (one byte less than the least: refused, nothing launched)
+        B.lce_forward(B.problem(n, d, v), **ok,
+                      workspace_bytes=info["o_pm"] + 2 * rup(4 * rows * npad, 256) + 4 * npad - 1)
+    assert e.value.code == B.LCE_ERR_WORKSPACE

@@ -91,3 +91,35 @@ def test_a_gradient_that_is_not_wanted_leaves_the_other_as_it_was(n, d, v, froze
     k = 0 if frozen == "weight" else 1
     assert grads[False][1 - k] is None
     assert torch.equal(grads[True][k].view(torch.int16), grads[False][k].view(torch.int16))
+
+
+@pytest.mark.parametrize("n,d,v", [(700, 264, 20000), (300, 72, 9216), (520, 1000, 9217), (64, 8, 40000), (257, 56, 384), (300, 64, 40000),
+                                   (64, 8, 200000)])
+def test_ragged_widths_and_the_least_forward_workspace(n, d, v):
+    # widths that are not a multiple of 64 on the 384 x 256 tiles (their last K slice masked), and the forward
+    # of those and of narrow heads in the least workspace (groups of 24 tiles, a launch each, folded into running pairs): the losses agree
+    # to fp32 rounding of the merge order
+    import torch
+    inp = WL.custom(n, d, v, seed=3, mask_frac=0.2, sigma_w=0.3, case_id=55)
+    print(f"case n={n} d={d} v={v}", flush=True)
+    h, w, t = U.to_device(inp)
+    p = B.problem(n, d, v, reduction="none")
+    info = B.lce_plan_info(p)
+    rows = (v + 383) // 384
+    rows = rows if rows <= 24 else 49
+    least = info["o_pm"] + 2 * ((4 * rows * info["npad"] + 255) // 256 * 256) + 4 * info["npad"]
+    ref = O.lce(inp.h_bits, inp.w_bits, inp.targets, reduction="none", grad=np.ones(n))
+    out = []
+    for nbytes in (info["fwd_bytes"], least):
+        loss = torch.empty(n, dtype=torch.float32, device="cuda")
+        lse = torch.empty(n, dtype=torch.float32, device="cuda")
+        nv = torch.empty(1, dtype=torch.int32, device="cuda")
+        ws = torch.full((nbytes + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+        B.lce_forward(p, h.data_ptr(), w.data_ptr(), t.data_ptr(), loss.data_ptr(), lse.data_ptr(), nv.data_ptr(), 0,
+                      ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+        assert torch.all(ws[nbytes:] == 0xFF)
+        assert np.max(np.abs(loss.cpu().numpy() - ref["loss"])) <= 2e-5 * max(1.0, np.max(np.abs(ref["lse"])))
+        out.append(lse.cpu().numpy())
+    assert np.max(np.abs(out[0] - out[1])) <= 1e-5 * max(1.0, np.max(np.abs(out[0])))
+    gpu = U.run_gpu(h, w, t, inp.ignore_index, "none", np.ones(n, np.float32))
+    U.assert_parity(gpu, ref)
