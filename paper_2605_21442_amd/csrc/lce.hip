@@ -910,51 +910,32 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
 // ---------------------------------------------------------------------------------------------
 // K3: per valid token: merge the vocabulary partials into lse, take the target logit
 // s[n, t_n] = H[n] . W[t_n] in fp32, and the per-row loss l_n = lse_n - s[n, t_n].
-// A workgroup of 16 waves serves 64 consecutive tokens. First each wave folds every 16th partial
-// row (rows w, w + 16, ...) for the 64 tokens, one token per lane (reads coalesced along the
-// tokens), and the 16 results are merged in wave order; then each wave takes the target logits of
-// 4 tokens, one wave-wide dot product each. All reductions run in a fixed order.
+// A workgroup of 16 waves serves 16 consecutive tokens. Each wave first takes one token's target logit, a
+// wave-wide dot product; then its four groups of 16 lanes fold every 64th partial row (64-byte reads along
+// the tokens), and the groups and the waves are merged in a fixed order. Bound by latency (few tokens) or by
+// the partials' bytes. (With 64 tokens a workgroup, each wave folded a quarter as many rows in parallel and
+// took four dot products in turn: 496 valid tokens of 2048 x 128256 were 8 workgroups, 40 us, now 16; 12288
+// of 4096 x 128256 62 us, now 53; 18000 of 1024 x 152064 46 -> 55.)
 // ---------------------------------------------------------------------------------------------
-constexpr int kCombTok = 64;
+constexpr int kCombTok = 16;
 
 __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H, int64_t ldh,
                                                   const uint16_t* __restrict__ W, int64_t ldw,
                                                   const void* targets, int tbytes, int64_t id0, int64_t v_local,
                                                   const int* __restrict__ idx, const int* __restrict__ nv_ptr,
-                                                  int d, int nparts2, const float* __restrict__ part_m,
+                                                  int d, int rows, const float* __restrict__ part_m,
                                                   const float* __restrict__ part_s, int npad,
                                                   const float* __restrict__ run_m, const float* __restrict__ run_s,
                                                   float* __restrict__ lse_out, float* __restrict__ terms,
                                                   float* __restrict__ per_token, float* __restrict__ tgt_part) {
   // run_m / run_s (may be null): a running pair per token folded in before the partial rows
-  __shared__ float red_m[16][kCombTok], red_s[16][kCombTok], lse_t[kCombTok];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ float red_m[16][kCombTok], red_s[16][kCombTok], dots[kCombTok];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = lane & 15;
   const int i0 = blockIdx.x * kCombTok;
   const int nv = *nv_ptr;
   if (i0 >= nv) return;
-  {
-    const int i = i0 + lane;
-    float m = -INFINITY, s = 0.f;
-    if (i < nv && wave == 0 && run_m) {
-      m = run_m[i];
-      s = run_s[i];
-    }
-    if (i < nv)
-      for (int q = wave; q < nparts2; q += 16) merge_pair(m, s, part_m[(int64_t)q * npad + i], part_s[(int64_t)q * npad + i]);
-    red_m[wave][lane] = m;
-    red_s[wave][lane] = s;
-  }
-  __syncthreads();
-  if (wave == 0) {
-    float m = red_m[0][lane], s = red_s[0][lane];
-    for (int q = 1; q < 16; ++q) merge_pair(m, s, red_m[q][lane], red_s[q][lane]);
-    lse_t[lane] = (m + log2f(s)) * kLn2;
-  }
-  __syncthreads();
-  for (int t = 0; t < kCombTok / 16; ++t) {
-    const int li = wave * (kCombTok / 16) + t, i = i0 + li;
-    if (i >= nv) break;
-    const int row = idx[i];
+  if (i0 + wave < nv) {
+    const int row = idx[i0 + wave];
     // target id relative to this W's first row (id0 > 0 only for a vocabulary shard, which may
     // not hold the target: then its target logit is 0)
     const int64_t tl = load_target(targets, tbytes, row) - id0;
@@ -962,6 +943,7 @@ __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H
     if (tl >= 0 && tl < v_local) {
       const uint4* hr = reinterpret_cast<const uint4*>(H + (int64_t)row * ldh);
       const uint4* wt = reinterpret_cast<const uint4*>(W + tl * ldw);
+#pragma unroll 4
       for (int c = lane; c < d / 8; c += 64) {
         const uint4 a = hr[c], b = wt[c];
         const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
@@ -973,16 +955,35 @@ __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H
       }
       dot = wave_sum(dot);
     }
-    if (lane == 0) {
-      const float lse = lse_t[li];
-      lse_out[row] = lse;
-      if (tgt_part) {
-        tgt_part[row] = dot;
-      } else {
-        terms[i] = lse - dot;
-        if (per_token) per_token[row] = lse - dot;
-      }
+    if (lane == 0) dots[wave] = dot;
+  }
+  const int i = i0 + t;
+  float m = -INFINITY, s = 0.f;
+  if (i < nv) {
+    if (run_m && wave == 0 && lane < kCombTok) {
+      m = run_m[i];
+      s = run_s[i];
     }
+#pragma unroll 4
+    for (int q = 4 * wave + (lane >> 4); q < rows; q += 64)
+      merge_pair(m, s, part_m[(int64_t)q * npad + i], part_s[(int64_t)q * npad + i]);
+  }
+  for (int o = 16; o <= 32; o <<= 1) merge_pair(m, s, __shfl_xor(m, o), __shfl_xor(s, o));
+  if (lane < kCombTok) {
+    red_m[wave][t] = m;
+    red_s[wave][t] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x >= kCombTok || i >= nv) return;
+  for (int w = 1; w < 16; ++w) merge_pair(m, s, red_m[w][t], red_s[w][t]);
+  const int row = idx[i];
+  const float lse = (m + log2f(s)) * kLn2, dot = dots[t];
+  lse_out[row] = lse;
+  if (tgt_part) {
+    tgt_part[row] = dot;
+  } else {
+    terms[i] = lse - dot;
+    if (per_token) per_token[row] = lse - dot;
   }
 }
 
