@@ -2334,6 +2334,12 @@ void launch_teacher(Launcher& L, int kind, const KdArgs& kd, const uint16_t* hvt
 
 inline size_t kd_p_bytes(const Plan& pl) { return (size_t)4 * pl.vc * pl.npad; }
 
+// Id tiles per vocabulary group of the student's launches: half the W rows of an LCE group, since the
+// teacher's values of every tile stream through the MALL beside them. (A wide slab as one group lost its W
+// rows between token tiles: 3072 valid tokens, 2048 wide, 64512 ids: statistics 1790 us and G 1980, in groups
+// of 160 MiB 1625 and 1700, of 80 MiB 1567 and 1675, of 40 MiB 1582 and 1684.)
+inline int student_group(int tiles, int64_t d) { return group_tiles(tiles, TILE, 2 * d); }
+
 // The teacher's valid rows gathered for its 12-wave probability pass (Npad x Dt bf16), when
 // Dt % 64 == 0; placed after P.
 inline size_t kd_hvt_bytes(const Plan& pl, int64_t dt) {
@@ -2421,7 +2427,7 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
       // teacher probabilities of this slab, then G = c (softmax(zs / T) - P) / T
       float* P = (float*)(ws + pl.bwd_bytes);
       launch_teacher<P_WRITE>(L, K_KD_P, *kd, hvt, pl, v0, vs, idx, nv, P);
-      const TileOrder to = tile_order(tm, pl.nt_max, tm);
+      const TileOrder to = tile_order(tm, pl.nt_max, student_group(tm, pl.d));
       L(K_BWD_G, k_bwd_g<G_SOFT, 2>, dim3(to.grid), dim3(NTHREADS), w, pl.ldw, v0, vs, h,
         pl.ldh, pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, lse, grad_loss,
         (const int*)n_valid, p->reduction, d, tm, g, vc, npad, kd->scale2, kd->inv_t, P, (float*)nullptr,
@@ -2525,7 +2531,7 @@ lce_status_t kd_forward_launches(Launcher& L, const lce_kd_problem_t* p, const K
     const int vs = (int)(pl.v - v0 < pl.vc ? pl.v - v0 : pl.vc);
     launch_teacher<Z_WRITE>(L, K_KD_Z, kd, hvt, pl, v0, vs, idx, nv, P);
     const int tm = (vs + TILE - 1) / TILE;
-    const TileOrder to = tile_order(tm, pl.nt_max, tm);
+    const TileOrder to = tile_order(tm, pl.nt_max, student_group(tm, pl.d));
     L(K_KD_STATS, k_bwd_g<KD_STATS, 2>, dim3(to.grid), dim3(NTHREADS), wsm, pl.ldw, v0, vs, hs, pl.ldh,
       pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, (const float*)nullptr,
       (const float*)nullptr, (const int*)nullptr, p->reduction, (int)pl.d, tm, (uint16_t*)nullptr, (int)pl.vc,
