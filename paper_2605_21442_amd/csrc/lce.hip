@@ -237,20 +237,23 @@ __device__ __forceinline__ float wave_sum(float x) {
 constexpr int KSLICE = 64;
 constexpr uint32_t kOobOffset = 0x80000000u;
 
-// Tile geometry of the main loop with WM wave rows: the A tile has 128 WM rows (256 or 384), the
-// B tile 256; 4 WM waves (2 or 3 per SIMD). A slice buffer holds the A region (128 WM rows x 128
-// bytes) followed by the B region (32 KB); two buffers.
-template <int WM>
+// Tile geometry of the main loop with WM wave rows of 4 waves, each wave BI x BJ blocks of 32 x 32 (4 x 2
+// except in the partial tiles of the forward and G launches): TM rows of A by TN of B. A slice buffer
+// holds the A region (TM rows x 128 bytes) followed by the B region; two buffers. 32 rows of an operand
+// are one wave's share of its loads; B's are taken by the last waves where A's leave some without any.
+template <int WM, int BI = 4, int BJ = 2>
 struct Geo {
-  static constexpr int TM = 128 * WM;
+  static constexpr int TM = 32 * BI * WM;
+  static constexpr int TN = 128 * BJ;
   static constexpr int NT = 256 * WM;
   static constexpr int AREG = TM * 128;
-  static constexpr int SLICE = AREG + 32768;
+  static constexpr int SLICE = AREG + TN * 128;
   static constexpr int LDS = 2 * SLICE;
+  static constexpr int A_WAVES = TM / 32, B_WAVES = TN / 32;
+  static constexpr int B_FIRST = A_WAVES == 4 * WM ? 0 : 4 * WM - B_WAVES;
 };
 constexpr int kDhWM = 3;   // wave rows of the dH contraction
 constexpr int kDwWM = 3;   // wave rows of the dW contraction
-constexpr int kGWM = 3;    // wave rows of the (one-hot) G kernel
 
 // One operand of the main loop, kW (256 or 384) tile rows (row-major) or tile columns (K-major)
 // wide. Waves w < kW / 32 load it, 4 KB of the operand's region per wave and slice; the load of
@@ -280,8 +283,9 @@ struct Operand {
 // row list, or K-major.
 enum OpKind { OP_DENSE = 0, OP_GATHER = 1, OP_KMAJOR = 2 };
 
+template <int BI, int BJ>
 struct FragSet {
-  bf16x8_t a[4], b[2];
+  bf16x8_t a[BI], b[BJ];
 };
 
 // chunk this lane loads for its even-numbered rows (odd rows: ^ 1), row-major operands
@@ -376,11 +380,12 @@ __device__ __forceinline__ void read_operand(bf16x8_t (&f)[kBlocks], const char*
   }
 }
 
-__device__ __forceinline__ void mma_substep(f32x16_t (&acc)[4][2], const FragSet& f) {
+template <int BI, int BJ>
+__device__ __forceinline__ void mma_substep(f32x16_t (&acc)[BI][BJ], const FragSet<BI, BJ>& f) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < BI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+    for (int j = 0; j < BJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
 }
 
 // This wave's 4 load instructions of one kW-wide operand's slice k0 (dstp = the operand's region
@@ -430,13 +435,15 @@ __device__ __forceinline__ void mask_tail(Operand& op, int k0, int K) {
 }
 
 // w: this wave's index in the workgroup, a wave-uniform (scalar) value
-template <bool kAsm, int kAKind, int kBKind, int WM, bool kMasked>
+template <bool kAsm, int kAKind, int kBKind, class G, bool kMasked>
 __device__ __forceinline__ void load_slice(const Operand& A, const Operand& B, const char* buf, int bufoff, int k0,
                                            int K, int w) {
   const char* dstp = buf + w * 4096;
   const int dst = bufoff + w * 4096;   // LDS byte address (asm loads)
-  load_operand<kAsm, kAKind, Geo<WM>::TM, kMasked>(A, dstp, dst, k0, K);
-  if (WM == 2 || w < 8) load_operand<kAsm, kBKind, 256, kMasked>(B, dstp + Geo<WM>::AREG, dst + Geo<WM>::AREG, k0, K);
+  constexpr int breg = G::AREG - G::B_FIRST * 4096;
+  if (G::A_WAVES == G::NT / 64 || w < G::A_WAVES) load_operand<kAsm, kAKind, G::TM, kMasked>(A, dstp, dst, k0, K);
+  if (G::B_FIRST ? w >= G::B_FIRST : (G::B_WAVES == G::NT / 64 || w < G::B_WAVES))
+    load_operand<kAsm, kBKind, G::TN, kMasked>(B, dstp + breg, dst + breg, k0, K);
 }
 
 // s_waitcnt with only the vector-memory counter constrained (expcnt / lgkmcnt left at max)
@@ -448,26 +455,27 @@ __device__ __forceinline__ void load_slice(const Operand& A, const Operand& B, c
 // second set; the other two waves of the SIMD cover the read latency).
 // kTail (row-major operands): K is not a multiple of 64; the last slice's chunks past K read zeros.
 template <int kLateGroups, int kAKind = OP_DENSE, int kBKind = OP_GATHER, int WM = 2, bool kRagged = true,
-          bool kTail = false>
-__device__ __forceinline__ void mma_mainloop(f32x16_t (&acc)[4][2], Operand A, Operand B, int K,
+          bool kTail = false, int BI = 4, int BJ = 2>
+__device__ __forceinline__ void mma_mainloop(f32x16_t (&acc)[BI][BJ], Operand A, Operand B, int K,
                                              char* smem) {
-  using G = Geo<WM>;
+  using G = Geo<WM, BI, BJ>;
   constexpr bool kAKM = kAKind == OP_KMAJOR, kBKM = kBKind == OP_KMAJOR;
   const int wave = threadIdx.x >> 6;
   const int wr = wave >> 2, wc = wave & 3;
-  FragAddr<4> fa;
-  FragAddr<2> fb;
-  frag_addr<kAKM, G::TM>(fa, wr * 128);
-  frag_addr<kBKM, 256>(fb, wc * 64);
-  auto read_frags = [&](FragSet& f, const char* buf, int ks) {
+  static_assert((BI == 4 && BJ == 2) || (WM == 3 && !kAKM && !kBKM), "partial tiles: row-major operands");
+  FragAddr<BI> fa;
+  FragAddr<BJ> fb;
+  frag_addr<kAKM, G::TM>(fa, wr * 32 * BI);
+  frag_addr<kBKM, G::TN>(fb, wc * 32 * BJ);
+  auto read_frags = [&](FragSet<BI, BJ>& f, const char* buf, int ks) {
     read_operand<kAKM, G::TM>(f.a, buf, fa, ks);
-    read_operand<kBKM, 256>(f.b, buf + G::AREG, fb, ks);
+    read_operand<kBKM, G::TN>(f.b, buf + G::AREG, fb, ks);
   };
 
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < BI; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (f32x16_t){};
+    for (int j = 0; j < BJ; ++j) acc[i][j] = (f32x16_t){};
 
   const int S = (K + KSLICE - 1) / KSLICE;
   if (S <= 0) return;
@@ -490,17 +498,19 @@ __device__ __forceinline__ void mma_mainloop(f32x16_t (&acc)[4][2], Operand A, O
         mask_tail<kBKind>(B, s * KSLICE, K);
       }
     }
-    if (ragged && s == S - 1) load_slice<kAsm, kAKind, kBKind, WM, true>(A, B, buf, bufoff, s * KSLICE, K, wsc);
-    else load_slice<kAsm, kAKind, kBKind, WM, false>(A, B, buf, bufoff, s * KSLICE, K, wsc);
+    if (ragged && s == S - 1) load_slice<kAsm, kAKind, kBKind, G, true>(A, B, buf, bufoff, s * KSLICE, K, wsc);
+    else load_slice<kAsm, kAKind, kBKind, G, false>(A, B, buf, bufoff, s * KSLICE, K, wsc);
   };
 
-  // waves of a 12-wave workgroup past the eighth load only A: 4 loads per slice instead of 8
-  const bool a_only = WM == 3 && wsc >= 8;
+  // a wave that takes a share of one operand only issues 4 loads per slice instead of 8
+  const bool loads_a = G::A_WAVES == G::NT / 64 || wsc < G::A_WAVES;
+  const bool loads_b = G::B_FIRST ? wsc >= G::B_FIRST : (G::B_WAVES == G::NT / 64 || wsc < G::B_WAVES);
   load(0);
   if (S > 1) {
     load(1);
-    if (a_only) LCE_WAIT_VM(4);
-    else LCE_WAIT_VM(8);
+    if (loads_a && loads_b) LCE_WAIT_VM(8);
+    else if (loads_a || loads_b) LCE_WAIT_VM(4);
+    else LCE_WAIT_VM(0);
   } else {
     LCE_WAIT_VM(0);
   }
@@ -518,7 +528,7 @@ __device__ __forceinline__ void mma_mainloop(f32x16_t (&acc)[4][2], Operand A, O
   const bool late = slot != 0;
   int pend = -1;
   if constexpr (WM == 2) {
-    FragSet f0, f1;
+    FragSet<BI, BJ> f0, f1;
     read_frags(f0, smem, 0);
     for (int j = 0; j < S; ++j) {
       const char* cur = smem + (j & 1) * G::SLICE;
@@ -550,7 +560,7 @@ __device__ __forceinline__ void mma_mainloop(f32x16_t (&acc)[4][2], Operand A, O
       }
     }
   } else {
-    FragSet f;
+    FragSet<BI, BJ> f;
     for (int j = 0; j < S; ++j) {
       const char* cur = smem + (j & 1) * G::SLICE;
       read_frags(f, cur, 0);
@@ -586,13 +596,14 @@ __device__ __forceinline__ void mma_mainloop(f32x16_t (&acc)[4][2], Operand A, O
 
 // A row-major operand of rows [row0, row0 + kW) (tile = row0's start) of a dense buffer with
 // rows_left rows from row0 on.
-__device__ __forceinline__ Operand dense_operand(const uint16_t* tile, int rows_left, int64_t ld) {
+// (wave `first` loads the first 32 rows)
+__device__ __forceinline__ Operand dense_operand(const uint16_t* tile, int rows_left, int64_t ld, int first = 0) {
   Operand op;
   op.rsrc = make_rsrc(tile, (uint64_t)rows_left * ld * 2);
   op.rwords = make_rsrc_words(tile, (uint64_t)rows_left * ld * 2);
   const int j = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int ce = lane_chunk_even();
-  const uint32_t row = (uint32_t)((int64_t)(w * 32 + (j >> 3)) * ld * 2);
+  const uint32_t row = (uint32_t)((int64_t)((w - first) * 32 + (j >> 3)) * ld * 2);   // (used by the waves from first on)
   op.off[0] = row + ce * 16;
   op.qstride = (uint32_t)(16 * ld);   // 8 rows
   return op;
@@ -793,26 +804,152 @@ __device__ __forceinline__ bool xcd_tile(int b, int tiles, int gw, int nt, int& 
   return tn < nt;
 }
 
+// The tiles a forward or G launch leaves for its last, partial round of the 256 CUs (all of them in a small
+// launch) are cut into parts of 192 ids x 256 tokens (2 per tile, up to 128 tiles) or 192 x 128 (4 per tile,
+// up to 64), so that the round has two or four times the workgroups. A half tile takes about 0.73 and a
+// quarter 0.57 of a tile's time (less work per byte loaded), so that more tiles than that are left whole,
+// as is everything in launches of more than kSplitTiles tiles, where the last round is a small share.
+// Forward, before and after: 3276 x 8192 x 16032 (546 tiles) 784 -> 673 us; 900 x 2048 x 32000 (336) 140 ->
+// 122; 2549 x 1000 x 32003 (840) 174 -> 162; 230 x 512 x 4096 (11) 22 -> 12, its G 28 -> 14. `t` is the index
+// space of xcd_tile (a multiple of 8, so that all parts of a tile run on one XCD).
+constexpr int kSplitTiles = 2048;
+__host__ __device__ inline int tile_space(int tiles, int nt) {
+  const int a = tiles & ~7;
+  return a * nt + (tiles - a) * ((nt + 7) / 8 * 8);
+}
+__device__ __forceinline__ int tail_parts(int t, bool split) {   // parts of the tail tiles (1: no tail is cut)
+  const int rem = t & 255;
+  return !split || t > kSplitTiles || rem == 0 || rem > 128 ? 1 : rem > 64 ? 2 : 4;
+}
+struct TilePart {
+  int tm, tn;        // vocabulary tile, token tile
+  int parts, part;   // parts of the tile, this block's (bit 0: its ids, bit 1: its tokens)
+};
+__device__ __forceinline__ bool tile_part(int b, int tiles, int gw, int nt, bool split, TilePart& p) {
+  const int t = tile_space(tiles, nt), parts = tail_parts(t, split), whole = parts > 1 ? t & ~255 : t;
+  int l = b;
+  p.parts = 1;
+  p.part = 0;
+  if (b >= whole) {
+    if (parts == 1) return false;
+    const int j = b - whole;
+    l = whole + j / (8 * parts) * 8 + (j & 7);
+    p.parts = parts;
+    p.part = (j >> 3) % parts;
+  }
+  return l < t && xcd_tile(l, tiles, gw, nt, p.tm, p.tn);
+}
+
+// The forward statistics of one tile or part: ids of the vleft rows of W from wt on, the tleft tokens of Hv
+// from ht on; one partial pair per token to out_m / out_s.
+template <bool kTail, int BI, int BJ>
+__device__ __forceinline__ void fwd_part(char* smem, const uint16_t* wt, int64_t ldw, int vleft, const uint16_t* ht,
+                                         int64_t ldh, int tleft, int d, float* __restrict__ out_m,
+                                         float* __restrict__ out_s, float scale2) {
+  constexpr int WM = 3;
+  using G = Geo<WM, BI, BJ>;
+  constexpr int TM = G::TM, TN = G::TN;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wr = wave >> 2, wc = wave & 3;
+  const Operand opb = dense_operand(ht, tleft, ldh, G::B_FIRST);
+  f32x16_t acc[BI][BJ];
+  // (kTail: d % 64 != 0); the last vocabulary tile may hold fewer than TM rows of W
+  if (vleft >= TM)
+    mma_mainloop<1, OP_DENSE, OP_DENSE, WM, false, kTail, BI, BJ>(acc, dense_operand(wt, vleft, ldw), opb, d, smem);
+  else
+    mma_mainloop<1, OP_GATHER, OP_DENSE, WM, false, kTail, BI, BJ>(acc, masked_dense_operand<TM>(wt, vleft, ldw), opb, d,
+                                                                   smem);
+  // the main loop ends with a barrier: its LDS is free for the wave rows' pairs [3][TN] (m, s)
+  float* red_m = reinterpret_cast<float*>(smem);
+  float* red_s = red_m + WM * TN;
+
+  // rows (vocabulary ids) of this lane: 32 (BI wr + bi) + 8 (r/4) + 4 (lane/32) + r%4
+  const int vb = wr * 32 * BI + (lane >> 5) * 4;
+  // the rows past V of the last vocabulary tile drop out of the max and the sum; every other tile
+  // takes a path with no per-element test (a runtime test would be kept, as masks, on every tile)
+  auto mask_rows = [&](auto kRagged) {
+    if constexpr (decltype(kRagged)::value) {
+#pragma unroll
+      for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int j = 0; j < BJ; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (vb + i * 32 + (r >> 2) * 8 + (r & 3) >= vleft) acc[i][j][r] = -INFINITY;
+    }
+  };
+  if (vleft < TM) mask_rows(std::true_type{});
+#pragma unroll
+  for (int j = 0; j < BJ; ++j) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < BI; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[i][j][r]);
+    const float nm = mx * scale2;
+    float st = 0.f;
+    if (nm != -INFINITY) {
+#pragma unroll
+      for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) st += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -nm));
+    }
+    // merge the two lane halves (disjoint ids of the same tokens)
+    const float om = __shfl_xor(nm, 32), os = __shfl_xor(st, 32);
+    const float mm = fmaxf(nm, om);
+    float sm = 0.f;
+    if (mm != -INFINITY) {
+      sm = (nm == -INFINITY ? 0.f : st * __builtin_amdgcn_exp2f(nm - mm)) +
+           (om == -INFINITY ? 0.f : os * __builtin_amdgcn_exp2f(om - mm));
+    }
+    if (lane < 32) {
+      const int t = wr * TN + wc * 32 * BJ + j * 32 + lane;
+      red_m[t] = mm;
+      red_s[t] = sm;
+    }
+  }
+  __syncthreads();
+  // merge the three wave rows in order; one thread per token of the tile
+  if (threadIdx.x < TN) {
+    const int t = threadIdx.x;
+    float m = red_m[t], s = red_s[t];
+#pragma unroll
+    for (int q = 1; q < WM; ++q) {
+      const float m2 = red_m[q * TN + t], s2 = red_s[q * TN + t];
+      const float mn = fmaxf(m, m2);
+      if (mn != -INFINITY)
+        s = (m == -INFINITY ? 0.f : s * __builtin_amdgcn_exp2f(m - mn)) +
+            (m2 == -INFINITY ? 0.f : s2 * __builtin_amdgcn_exp2f(m2 - mn));
+      m = mn;
+    }
+    if (t < tleft) {
+      out_m[t] = m;
+      out_s[t] = s;
+    }
+  }
+}
+
+// split: the last round's tiles may be cut; the partial rows are then two sets of vt_launch, tile tl writing row
+// tl (the first half of its ids, or all) and row vt_launch + tl (the second half, or an empty pair).
 template <bool kTail>
 __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __restrict__ W, int64_t ldw, int v,
                                                             const uint16_t* __restrict__ Hv, int64_t ldh,
                                                             const int* __restrict__ nv_ptr, int d, int tm0,
-                                                            int vt_launch, int gw, int nt_max,
+                                                            int vt_launch, int gw, int split,
                                                             float* __restrict__ part_m, float* __restrict__ part_s,
                                                             const float* __restrict__ prev_m,
                                                             const float* __restrict__ prev_s, int wprev,
                                                             float* __restrict__ run_m, float* __restrict__ run_s,
                                                             int run_init, int npad, float scale2) {
-  constexpr int WM = 3, TM = Geo<WM>::TM;
-  __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
-  int tl, tn;   // launch-relative vocabulary tile, token tile
-  if (!xcd_tile((int)blockIdx.x, vt_launch, gw, nt_max, tl, tn)) return;
-  const int tm = tm0 + tl;
+  constexpr int TM = Geo<3>::TM;
+  __shared__ __attribute__((aligned(16))) char smem[Geo<3>::LDS];
   const int nv = *nv_ptr;
-  const int n0 = tn * TILE;
-  if (n0 >= nv) return;
-  const int v0 = tm * TM, vleft = v - v0;
-  if (prev_m && tl == 0 && threadIdx.x < TILE) {
+  if (nv == 0) return;
+  const int nt = (nv + TILE - 1) / TILE;
+  TilePart p;   // p.tm: launch-relative vocabulary tile
+  if (!tile_part((int)blockIdx.x, vt_launch, gw, nt, split, p)) return;
+  const int tl = p.tm, n0 = p.tn * TILE;
+  const int v0 = (tm0 + tl) * TM, vleft = v - v0;
+  if (prev_m && tl == 0 && threadIdx.x < TILE) {   // (launches with a previous group are not split)
     const int tok = n0 + threadIdx.x;
     if (tok < nv) {
       float m = -INFINITY, s = 0.f;
@@ -826,84 +963,28 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
       run_s[tok] = s;
     }
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wr = wave >> 2, wc = wave & 3;
-
-  const Operand opb = dense_operand(Hv + (int64_t)n0 * ldh, nv - n0, ldh);
-  f32x16_t acc[4][2];
-  // (kTail: d % 64 != 0); the last vocabulary tile may hold fewer than TM rows of W
-  if (vleft >= TM)
-    mma_mainloop<1, OP_DENSE, OP_DENSE, WM, false, kTail>(acc, dense_operand(W + (int64_t)v0 * ldw, vleft, ldw), opb,
-                                                          d, smem);
-  else
-    mma_mainloop<1, OP_GATHER, OP_DENSE, WM, false, kTail>(
-        acc, masked_dense_operand<TM>(W + (int64_t)v0 * ldw, vleft, ldw), opb, d, smem);
-  // the main loop ends with a barrier: its LDS is free for the wave rows' pairs [3][256] (m, s)
-  float* red_m = reinterpret_cast<float*>(smem);
-  float* red_s = red_m + WM * TILE;
-
-  // rows (vocabulary ids) of this lane: v0 + wr*128 + 32 bi + 8 (r/4) + 4 (lane/32) + r%4
-  const int vb = wr * 128 + (lane >> 5) * 4;
-  // the rows past V of the last vocabulary tile drop out of the max and the sum; every other tile
-  // takes a path with no per-element test (a runtime test would be kept, as masks, on every tile)
-  auto mask_rows = [&](auto kRagged) {
-    if constexpr (decltype(kRagged)::value) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (vb + i * 32 + (r >> 2) * 8 + (r & 3) >= vleft) acc[i][j][r] = -INFINITY;
+  float* om = part_m + (int64_t)tl * npad + n0;
+  float* os = part_s + (int64_t)tl * npad + n0;
+  if (p.parts == 1) {
+    fwd_part<kTail, 4, 2>(smem, W + (int64_t)v0 * ldw, ldw, vleft, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os, scale2);
+    if (tail_parts(tile_space(vt_launch, nt), split) > 1 && threadIdx.x < TILE && n0 + (int)threadIdx.x < nv) {
+      om[(int64_t)vt_launch * npad + threadIdx.x] = -INFINITY;
+      os[(int64_t)vt_launch * npad + threadIdx.x] = 0.f;
     }
-  };
-  if (vleft < TM) mask_rows(std::true_type{});
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    float mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[i][j][r]);
-    const float nm = mx * scale2;
-    float st = 0.f;
-    if (nm != -INFINITY) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) st += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], scale2, -nm));
-    }
-    // merge the two lane halves (disjoint ids of the same tokens)
-    const float om = __shfl_xor(nm, 32), os = __shfl_xor(st, 32);
-    const float mm = fmaxf(nm, om);
-    float sm = 0.f;
-    if (mm != -INFINITY) {
-      sm = (nm == -INFINITY ? 0.f : st * __builtin_amdgcn_exp2f(nm - mm)) +
-           (om == -INFINITY ? 0.f : os * __builtin_amdgcn_exp2f(om - mm));
-    }
-    if (lane < 32) {
-      const int t = wr * TILE + wc * 64 + j * 32 + lane;
-      red_m[t] = mm;
-      red_s[t] = sm;
-    }
+    return;
   }
-  __syncthreads();
-  // merge the three wave rows in order; one thread per token of the tile
-  if (threadIdx.x < TILE) {
-    const int t = threadIdx.x, tok = n0 + t;
-    float m = red_m[t], s = red_s[t];
-#pragma unroll
-    for (int q = 1; q < WM; ++q) {
-      const float m2 = red_m[q * TILE + t], s2 = red_s[q * TILE + t];
-      const float mn = fmaxf(m, m2);
-      if (mn != -INFINITY)
-        s = (m == -INFINITY ? 0.f : s * __builtin_amdgcn_exp2f(m - mn)) +
-            (m2 == -INFINITY ? 0.f : s2 * __builtin_amdgcn_exp2f(m2 - mn));
-      m = mn;
-    }
-    if (tok < nv) {
-      part_m[(int64_t)tl * npad + tok] = m;
-      part_s[(int64_t)tl * npad + tok] = s;
-    }
+  // a part: half of the tile's ids (none of them may exist), all or half of its tokens
+  const int ih = p.part & 1, th = p.part >> 1;
+  const int vl = vleft - ih * (TM / 2) > 0 ? vleft - ih * (TM / 2) : 0;
+  const uint16_t* wt = W + (int64_t)(v0 + (vl > 0 ? ih * (TM / 2) : 0)) * ldw;
+  om += (int64_t)ih * vt_launch * npad;
+  os += (int64_t)ih * vt_launch * npad;
+  if (p.parts == 2) {
+    fwd_part<kTail, 2, 2>(smem, wt, ldw, vl, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os, scale2);
+  } else {
+    const int t0 = th * (TILE / 2);
+    if (n0 + t0 >= nv) return;
+    fwd_part<kTail, 2, 1>(smem, wt, ldw, vl, Hv + (int64_t)(n0 + t0) * ldh, ldh, nv - n0 - t0, d, om + t0, os + t0, scale2);
   }
 }
 
@@ -923,12 +1004,13 @@ __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H
                                                   const uint16_t* __restrict__ W, int64_t ldw,
                                                   const void* targets, int tbytes, int64_t id0, int64_t v_local,
                                                   const int* __restrict__ idx, const int* __restrict__ nv_ptr,
-                                                  int d, int rows, const float* __restrict__ part_m,
+                                                  int d, int tiles, int split, const float* __restrict__ part_m,
                                                   const float* __restrict__ part_s, int npad,
                                                   const float* __restrict__ run_m, const float* __restrict__ run_s,
                                                   float* __restrict__ lse_out, float* __restrict__ terms,
                                                   float* __restrict__ per_token, float* __restrict__ tgt_part) {
-  // run_m / run_s (may be null): a running pair per token folded in before the partial rows
+  // run_m / run_s (may be null): a running pair per token folded in before the partial rows (two sets where
+  // the forward cut its last tiles)
   __shared__ float red_m[16][kCombTok], red_s[16][kCombTok], dots[kCombTok];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = lane & 15;
   const int i0 = blockIdx.x * kCombTok;
@@ -958,6 +1040,7 @@ __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H
     if (lane == 0) dots[wave] = dot;
   }
   const int i = i0 + t;
+  const int rows = tail_parts(tile_space(tiles, (nv + TILE - 1) / TILE), split) > 1 ? 2 * tiles : tiles;
   float m = -INFINITY, s = 0.f;
   if (i < nv) {
     if (run_m && wave == 0 && lane < kCombTok) {
@@ -1141,7 +1224,130 @@ __device__ __forceinline__ float grad_scale(const float* grad, const int* n_norm
 // at or beyond Nv and of ids at or beyond the slab width are zeros, so the two contractions that
 // read G (dH with K = ids, dW with K = tokens, G read K-major) need no masking of G.
 // ---------------------------------------------------------------------------------------------
-// The same kernel serves the distillation loss (KD) with soft targets, in four more modes:
+// One tile or part of the LCE gradient: the vleft ids from W row wt on (target of a token: id tbase), the tleft
+// tokens of Hv / idx from ht / idx0 on, G from element (first token, first id) on (row stride vc).
+template <bool kTail, int BI, int BJ>
+__device__ __forceinline__ void g_part(char* smem, const uint16_t* wt, int64_t ldw, int vleft, const uint16_t* ht,
+                                       int64_t ldh, int tleft, const void* targets, int tbytes, int64_t tbase,
+                                       const int* __restrict__ idx0, const float* __restrict__ lse,
+                                       const float* __restrict__ grad, const int* __restrict__ n_norm, int reduction,
+                                       int d, uint16_t* __restrict__ G0, int vc) {
+  using G = Geo<3, BI, BJ>;
+  constexpr int TM = G::TM, TN = G::TN;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wr = wave >> 2, wc = wave & 3;
+  const Operand opb = dense_operand(ht, tleft, ldh, G::B_FIRST);
+  f32x16_t acc[BI][BJ];
+  // (kTail: d % 64 != 0); the last tile of the vocabulary may hold fewer than TM rows of W
+  if (vleft >= TM)
+    mma_mainloop<1, OP_DENSE, OP_DENSE, 3, false, kTail, BI, BJ>(acc, dense_operand(wt, vleft, ldw), opb, d, smem);
+  else
+    mma_mainloop<1, OP_GATHER, OP_DENSE, 3, false, kTail, BI, BJ>(acc, masked_dense_operand<TM>(wt, vleft, ldw), opb, d,
+                                                                  smem);
+  const float c_all = grad_scale(grad, n_norm, reduction);
+  int tgt[BJ];
+  float l2[BJ], cj[BJ];
+#pragma unroll
+  for (int j = 0; j < BJ; ++j) {
+    const int t = wc * 32 * BJ + j * 32 + (lane & 31);
+    if (t < tleft) {
+      const int row = idx0[t];
+      l2[j] = lse[row] * kLog2e;
+      tgt[j] = (int)(load_target(targets, tbytes, row) - tbase);
+      cj[j] = reduction == LCE_REDUCE_NONE ? grad[row] : c_all;
+    } else {
+      l2[j] = 0.f;
+      tgt[j] = -1;
+      cj[j] = 0.f;
+    }
+  }
+  const int vb = wr * 32 * BI + (lane >> 5) * 4;  // tile-relative vocabulary row base of this lane
+  // G straight from registers. A lane holds 4 consecutive ids of a token row per (block, group
+  // of 8 ids), the other 4 sit in lane L ^ 32; one lane swap across the wave halves
+  // (permlane32 swap) per pair of groups gives each lane 8 consecutive ids (lanes < 32 the even
+  // group, the others the odd one), stored as 16 bytes. Rows of tokens >= Nv and ids >= the
+  // slab width get zeros, so the whole tile is written (the slab width vc is a multiple of 384).
+  const i32x4_t rg = make_rsrc_words(G0, (uint64_t)TN * vc * 2);
+  const uint32_t voff = (uint32_t)(((wc * 32 * BJ + (lane & 31)) * vc + wr * 32 * BI + (lane >> 5) * 8) * 2);
+  // A tile whose tokens are all valid and whose ids all lie in the slab needs no test per
+  // element; on the other tiles the values out of range are replaced by zeros (a select, not a
+  // branch per element: the exponential of a row past Nv may be anything, even NaN).
+  auto store_tile = [&](auto kFull) {
+#pragma unroll
+    for (int j = 0; j < BJ; ++j) {
+      const bool tok_ok = wc * 32 * BJ + j * 32 + (lane & 31) < tleft;
+      // the lane's element (i, q, e) is the target's when dt == 32 i + 8 q + e: one compare
+      // with a constant per element, and the one-hot term folded into the scaling fma
+      const int dt = tgt[j] - vb;
+      const float nc = -cj[j];
+#pragma unroll
+      for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          u32x2_t pk[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int q = 2 * p + h;
+            float gq[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int k = i * 32 + q * 8 + e;
+              const float ex = __builtin_amdgcn_exp2f(fmaf(acc[i][j][q * 4 + e], kLog2e, -l2[j]));
+              float g = fmaf(cj[j], ex, dt == k ? nc : 0.f);
+              if constexpr (!decltype(kFull)::value) g = (tok_ok && vb + k < vleft) ? g : 0.f;
+              gq[e] = g;
+            }
+            pk[h].x = pack_bf16x2(gq[0], gq[1]);
+            pk[h].y = pack_bf16x2(gq[2], gq[3]);
+          }
+          // lane L < 32: (its group 2p ids 0-3, lane L + 32's ids 4-7); lane L + 32: (lane L's
+          // group 2p + 1 ids 0-3, its own ids 4-7)
+          const auto sx = __builtin_amdgcn_permlane32_swap(pk[0].x, pk[1].x, false, false);
+          const auto sy = __builtin_amdgcn_permlane32_swap(pk[0].y, pk[1].y, false, false);
+          const i32x4_t v16 = {(int)sx[0], (int)sy[0], (int)sx[1], (int)sy[1]};
+          const uint32_t so = (uint32_t)((j * 32 * vc + i * 32 + p * 16) * 2);
+          // (the compiled code may rewrite v16's registers right after the store: padded)
+          buffer_store16_padded(v16, rg, voff, so);
+        }
+    }
+  };
+  if (tleft >= TN && vleft >= TM) store_tile(std::true_type{});
+  else store_tile(std::false_type{});
+}
+
+template <bool kTail>
+__global__ __launch_bounds__(Geo<3>::NT, 3) void k_bwd_g(const uint16_t* __restrict__ W, int64_t ldw, int64_t v0, int vs,
+                                                       const uint16_t* __restrict__ Hv, int64_t ldh,
+                                                       const void* targets, int tbytes, int64_t id0,
+                                                       const int* __restrict__ idx, const int* __restrict__ nv_ptr,
+                                                       const float* __restrict__ lse, const float* __restrict__ grad,
+                                                       const int* __restrict__ n_norm, int reduction, int d, int tm_count,
+                                                       int gw, int split, uint16_t* __restrict__ G, int vc) {
+  constexpr int TM = Geo<3>::TM;
+  __shared__ __attribute__((aligned(16))) char smem[Geo<3>::LDS];
+  const int nv = *nv_ptr;
+  if (nv == 0) return;
+  TilePart p;
+  if (!tile_part((int)blockIdx.x, tm_count, gw, (nv + TILE - 1) / TILE, split, p)) return;
+  const int ih = p.parts > 1 ? p.part & 1 : 0, th = p.part >> 1;
+  const int n0 = p.tn * TILE + th * (TILE / 2), vt0 = p.tm * TM + ih * (TM / 2);   // slab-relative
+  // (a part without ids of the slab or without valid tokens: no column or row of G that is read)
+  if (n0 >= nv || vt0 >= vs) return;
+  const uint16_t* wt = W + (v0 + vt0) * ldw;
+  const uint16_t* ht = Hv + (int64_t)n0 * ldh;
+  uint16_t* g0 = G + (int64_t)n0 * vc + vt0;
+  const int64_t tbase = id0 + v0 + vt0;
+  if (p.parts == 1)
+    g_part<kTail, 4, 2>(smem, wt, ldw, vs - vt0, ht, ldh, nv - n0, targets, tbytes, tbase, idx + n0, lse, grad, n_norm,
+                        reduction, d, g0, vc);
+  else if (p.parts == 2)
+    g_part<kTail, 2, 2>(smem, wt, ldw, vs - vt0, ht, ldh, nv - n0, targets, tbytes, tbase, idx + n0, lse, grad, n_norm,
+                        reduction, d, g0, vc);
+  else
+    g_part<kTail, 2, 1>(smem, wt, ldw, vs - vt0, ht, ldh, nv - n0, targets, tbytes, tbase, idx + n0, lse, grad, n_norm,
+                        reduction, d, g0, vc);
+}
+
+// The tiles of the distillation loss (KD, soft targets), in four modes:
 //   Z_WRITE   teacher, forward: the logits of this slab, fp32, into P
 //   KD_STATS  student, forward: per token, over the tile's ids, the (max, sum-exp) pairs of teacher and
 //             student logits / T and the teacher-weighted sum of the student's logits / T (qpart)
@@ -1154,22 +1360,21 @@ __device__ __forceinline__ float grad_scale(const float* grad, const int* n_norm
 // (k_kd_combine), as the sum-exp itself. (Taken against the teacher's log-sum-exp, the sum needs both
 // heads' logits again after the statistics: 3072 valid tokens, 4096 -> 2048 wide, 128256 ids: forward
 // 9300 us, now 4760.)
-enum GMode { G_ONEHOT = 0, G_SOFT = 1, KD_STATS = 2, P_WRITE = 3, Z_WRITE = 4 };
+enum KdMode { G_SOFT, KD_STATS, P_WRITE, Z_WRITE };
 constexpr int kKdVals = 5;   // values per token and tile of KD_STATS: teacher max, sum, weighted sum; student max, sum
 
-template <int kMode, int WM, bool kTail = false>
-__global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __restrict__ W, int64_t ldw, int64_t v0, int vs,
+template <int kMode, int WM>
+__global__ __launch_bounds__(Geo<WM>::NT, WM) void k_kd_tile(const uint16_t* __restrict__ W, int64_t ldw, int64_t v0, int vs,
                                                        const uint16_t* __restrict__ H, int64_t ldh, int64_t n,
-                                                       const void* targets, int tbytes, int64_t id0,
                                                        const int* __restrict__ idx, const int* __restrict__ nv_ptr,
                                                        const float* __restrict__ lse, const float* __restrict__ grad,
                                                        const int* __restrict__ n_norm, int reduction, int d, int tm_count,
                                                        uint16_t* __restrict__ G, int vc, int ldt,
                                                        float scale2, float inv_t, float* __restrict__ P,
                                                        float* __restrict__ qpart, int64_t qrow, int gsub) {
-  // 12 waves (WM = 3, 384 ids per tile) serve the one-hot LCE gradient and the teacher when Dt % 64 == 0;
-  // the student and other teachers keep 8 waves (and the student's G the LDS-staged epilogue below)
-  static_assert(WM == 2 ? kMode != G_ONEHOT : (kMode == G_ONEHOT || kMode == P_WRITE || kMode == Z_WRITE), "");
+  // 12 waves (WM = 3, 384 ids per tile) serve the teacher when Dt % 64 == 0; the student and other
+  // teachers keep 8 waves (and the student's G the LDS-staged epilogue below)
+  static_assert(WM == 2 || kMode == P_WRITE || kMode == Z_WRITE, "");
   constexpr int TM = Geo<WM>::TM;
   __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
   const int nv = *nv_ptr;
@@ -1187,12 +1392,12 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
   f32x16_t acc[4][2];
   // the last tile of the vocabulary may hold fewer than TM rows of W
   if constexpr (WM == 3) {
-    // H is the gathered valid rows Hv (row stride ldh = d): a dense operand (kTail: d % 64 != 0)
+    // H is the gathered valid rows Hv (row stride ldh = d): a dense operand; d % 64 == 0 (host)
     const Operand opb = dense_operand(H + (int64_t)n0 * ldh, nv - n0, ldh);
     if (vleft >= TM)
-      mma_mainloop<1, OP_DENSE, OP_DENSE, WM, false, kTail>(acc, dense_operand(wt, vleft, ldw), opb, d, smem);
+      mma_mainloop<1, OP_DENSE, OP_DENSE, WM, false>(acc, dense_operand(wt, vleft, ldw), opb, d, smem);
     else
-      mma_mainloop<1, OP_GATHER, OP_DENSE, WM, false, kTail>(acc, masked_dense_operand<TM>(wt, vleft, ldw), opb, d, smem);
+      mma_mainloop<1, OP_GATHER, OP_DENSE, WM, false>(acc, masked_dense_operand<TM>(wt, vleft, ldw), opb, d, smem);
   } else {
     const Operand opb = gather_operand(H, n, ldh, idx, n0, nv);
     if (vleft >= TM)
@@ -1203,10 +1408,10 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
 
   // the gradient scale exists only for the modes that write G (the other passes get no upstream
   // gradient: grad and n_norm, and in the forward lse, may be null there)
-  constexpr bool kWritesG = kMode == G_ONEHOT || kMode == G_SOFT;
+  constexpr bool kWritesG = kMode == G_SOFT;
   constexpr bool kUsesLse = kWritesG || kMode == P_WRITE;
   const float c_all = kWritesG ? grad_scale(grad, n_norm, reduction) : 0.f;
-  int tok[2], tgt[2];
+  int tok[2];
   float l2[2], cj[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -1214,11 +1419,9 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
     if (tok[j] < nv) {
       const int row = idx[tok[j]];
       l2[j] = kUsesLse ? lse[row] * kLog2e : 0.f;
-      tgt[j] = kMode == G_ONEHOT ? (int)(load_target(targets, tbytes, row) - id0 - v0) - vt0 : -1;
       cj[j] = kWritesG && reduction == LCE_REDUCE_NONE ? grad[row] : c_all;
     } else {
       l2[j] = 0.f;
-      tgt[j] = -1;
       cj[j] = 0.f;
     }
   }
@@ -1250,61 +1453,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_g(const uint16_t* __res
         x[r] = (tok[j] < nv && vb + i * 32 + (r >> 2) * 8 + (r & 3) < vleft) ? x[r] : absent;
     }
   };
-  if constexpr (WM == 3 && kMode == G_ONEHOT) {
-    // G straight from registers. A lane holds 4 consecutive ids of a token row per (block, group
-    // of 8 ids), the other 4 sit in lane L ^ 32; one lane swap across the wave halves
-    // (permlane32 swap) per pair of groups gives each lane 8 consecutive ids (lanes < 32 the even
-    // group, the others the odd one), stored as 16 bytes. Rows of tokens >= Nv and ids >= the
-    // slab width get zeros, so the whole 256 x 384 tile is written (the slab width vc is a
-    // multiple of 384).
-    const i32x4_t rg = make_rsrc_words(G + (int64_t)n0 * vc, (uint64_t)TILE * vc * 2);
-    const uint32_t voff = (uint32_t)(((wc * 64 + (lane & 31)) * vc + vt0 + wr * 128 + (lane >> 5) * 8) * 2);
-    // A tile whose tokens are all valid and whose ids all lie in the slab needs no test per
-    // element; on the other tiles the values out of range are replaced by zeros (a select, not a
-    // branch per element: the exponential of a row past Nv may be anything, even NaN).
-    auto store_tile = [&](auto kFull) {
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const bool tok_ok = tok[j] < nv;
-        // the lane's element (i, q, e) is the target's when dt == 32 i + 8 q + e: one compare
-        // with a constant per element, and the one-hot term folded into the scaling fma
-        const int dt = tgt[j] - vb;
-        const float nc = -cj[j];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int p = 0; p < 2; ++p) {
-            u32x2_t pk[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const int q = 2 * p + h;
-              float gq[4];
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const int k = i * 32 + q * 8 + e;
-                const float ex = __builtin_amdgcn_exp2f(fmaf(acc[i][j][q * 4 + e], scale2, -l2[j]));
-                float g = fmaf(cj[j], ex, dt == k ? nc : 0.f);
-                if constexpr (!decltype(kFull)::value) g = (tok_ok && vb + k < vleft) ? g : 0.f;
-                gq[e] = g;
-              }
-              pk[h].x = pack_bf16x2(gq[0], gq[1]);
-              pk[h].y = pack_bf16x2(gq[2], gq[3]);
-            }
-            // lane L < 32: (its group 2p ids 0-3, lane L + 32's ids 4-7); lane L + 32: (lane L's
-            // group 2p + 1 ids 0-3, its own ids 4-7)
-            const auto sx = __builtin_amdgcn_permlane32_swap(pk[0].x, pk[1].x, false, false);
-            const auto sy = __builtin_amdgcn_permlane32_swap(pk[0].y, pk[1].y, false, false);
-            const i32x4_t v16 = {(int)sx[0], (int)sy[0], (int)sx[1], (int)sy[1]};
-            const uint32_t so = (uint32_t)((j * 32 * vc + i * 32 + p * 16) * 2);
-            // (the compiled code may rewrite v16's registers right after the store: padded)
-            buffer_store16_padded(v16, rg, voff, so);
-          }
-      }
-    };
-    if (n0 + TILE <= nv && vleft >= TM) store_tile(std::true_type{});
-    else store_tile(std::false_type{});
-    return;
-  } else if constexpr (kMode == P_WRITE || kMode == Z_WRITE) {
+  if constexpr (kMode == P_WRITE || kMode == Z_WRITE) {
     // the whole tile is written (the consumer masks the ids and tokens that do not exist)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -1947,6 +2096,7 @@ struct Plan {
   int part_rows;                             // partial rows of the forward statistics
   int fgw;                                   // 384-id tiles of a group of the forward (more than one launch)
   bool few_rows;                             // the forward's partials in the least space (few_partial_rows)
+  bool split;                                // the forward may cut its last tiles (two partial rows each)
 };
 
 // the forward in one launch: its partial rows (8 bytes per 384-id tile and token) take at most 2 D bytes
@@ -1970,14 +2120,15 @@ inline int group_tiles(int64_t tiles, int64_t tile_rows, int64_t d) {
 }
 
 // Grid and group width of a launch in the order of xcd_tile: `tiles` vocabulary tiles by nt token
-// tiles, in groups at most `width` tiles wide (rounded down to a multiple of 8).
+// tiles, in groups at most `width` tiles wide (rounded down to a multiple of 8). A split launch's parts
+// take at most a round of 256 blocks beside the whole tiles.
 struct TileOrder {
   unsigned grid;
   int gw;
 };
-inline TileOrder tile_order(int64_t tiles, int64_t nt, int64_t width) {
+inline TileOrder tile_order(int64_t tiles, int64_t nt, int64_t width, bool split = false) {
   const int64_t a = tiles & ~(int64_t)7, rem = tiles - a;
-  return TileOrder{(unsigned)(a * nt + (rem ? 8 * rem * ((nt + 7) / 8) : 0)),
+  return TileOrder{(unsigned)(a * nt + (rem ? 8 * rem * ((nt + 7) / 8) : 0) + (split ? 256 : 0)),
                    (int)std::max<int64_t>(8, std::min(width, a) & ~(int64_t)7)};
 }
 
@@ -2047,13 +2198,18 @@ void place_partials(Plan* pl, int64_t rows) {
   pl->fwd_bytes = pl->o_terms + 4 * (size_t)pl->npad;
 }
 
-// For a workspace smaller than the plan's forward, which callers may hold from before these took the rows
-// they take now, or which the library's fixed array is: widths that are not a multiple of 64 once took at
+// For a workspace smaller than the plan's forward: its launch is first left unsplit (one partial row a
+// tile). Then those whose rows have grown, callers may hold a workspace from before
+// that, or fit the library's fixed array with it: widths that are not a multiple of 64 once took at
 // most kFewRows partial rows (two per 256 ids), and narrow heads (more than D / 4 tiles) groups of at least
 // 24 tiles. Groups of 24 tiles, a launch each, need 2 x 24 + 1 rows (a vocabulary of at most 24 tiles its
 // tiles'), never more than either.
 constexpr int kFewRows = 64;
 bool few_partial_rows(Plan* pl, size_t workspace_bytes) {
+  if (pl->split && pl->fwd_bytes > workspace_bytes) {
+    pl->split = false;
+    place_partials(pl, std::max<int64_t>(2 * std::min(pl->vt_count, kFewRows / 2), pl->vt_count3));
+  }
   if ((pl->d % KSLICE != 0 || pl->vt_count3 > pl->d / 4) && pl->fwd_bytes > workspace_bytes) {
     pl->few_rows = true;
     pl->fgw = 24;
@@ -2119,7 +2275,11 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   pl->few_rows = false;
   pl->fgw = (int)(vc / 384);
   const int64_t rows3 = fwd_one_launch(*pl) ? pl->vt_count3 : 2 * (vc / 384) + 1;
-  place_partials(pl, std::max<int64_t>(2 * std::min(pl->vt_count, kFewRows / 2), rows3));
+  const int64_t rows = std::max<int64_t>(2 * std::min(pl->vt_count, kFewRows / 2), rows3);
+  place_partials(pl, rows);
+  // (up to twice kSplitTiles tiles of all N tokens, of which fewer may be valid)
+  pl->split = fwd_one_launch(*pl) && (int64_t)pl->vt_count3 * pl->nt_max <= 2 * kSplitTiles;
+  if (pl->split) place_partials(pl, std::max<int64_t>(rows, 2 * pl->vt_count3));
   // G and the fp32 dH accumulators hold every row a 384-row dH tile can address (the tiles of
   // the last token rows reach past Npad), so that no access leaves its region
   pl->rows_g = round_up(pl->npad, 384);
@@ -2216,7 +2376,8 @@ lce_status_t shard_info(const lce_problem_t* p, const lce_shard_t* sh, ShardInfo
 struct PartRows {
   const float* m;
   const float* s;
-  int count;
+  int count;          // tiles; two rows each where the launch was split (k_fwd_tile)
+  int split;
   const float* run_m;
   const float* run_s;
 };
@@ -2240,11 +2401,11 @@ PartRows launch_fwd_stats(Launcher& L, const Plan& layout, const uint16_t* W, in
   if (fwd_one_launch(layout)) {
     // one launch: the groups only order the tiles (as wide as the slab rule's width, or narrower
     // where its W rows would not stay in the MALL)
-    const TileOrder to = tile_order(ntl, nt_max, group_tiles(layout.gw, Geo<3>::TM, d));
+    const TileOrder to = tile_order(ntl, nt_max, group_tiles(layout.gw, Geo<3>::TM, d), layout.split);
     L(K_FWD_STATS, kernel, dim3(to.grid), dim3(Geo<3>::NT), W, ldw, v, (const uint16_t*)hv,
-      (int64_t)d, nv, d, 0, ntl, to.gw, nt_max, pm, ps, (const float*)nullptr, (const float*)nullptr, 0,
+      (int64_t)d, nv, d, 0, ntl, to.gw, (int)layout.split, pm, ps, (const float*)nullptr, (const float*)nullptr, 0,
       (float*)nullptr, (float*)nullptr, 0, npad, kLog2e);
-    return PartRows{pm, ps, ntl, nullptr, nullptr};
+    return PartRows{pm, ps, ntl, layout.split, nullptr, nullptr};
   }
   // one group per launch; row sets: parity 0 at rows [0, gw), parity 1 at [gw, 2 gw), the
   // running pair at row 2 gw
@@ -2257,12 +2418,12 @@ PartRows launch_fwd_stats(Launcher& L, const Plan& layout, const uint16_t* W, in
     const int64_t cur = (g & 1) * rs, prev = ((g + 1) & 1) * rs;
     const TileOrder to = tile_order(wl, nt_max, wl);
     L(K_FWD_STATS, kernel, dim3(to.grid), dim3(Geo<3>::NT), W, ldw, v, (const uint16_t*)hv,
-      (int64_t)d, nv, d, tm0, wl, to.gw, nt_max, pm + cur, ps + cur,
+      (int64_t)d, nv, d, tm0, wl, to.gw, 0, pm + cur, ps + cur,
       g > 0 ? (const float*)(pm + prev) : (const float*)nullptr, (const float*)(ps + prev), gw, run_m, run_s,
       g == 1 ? 1 : 0, npad, kLog2e);
   }
   const int64_t last = ((ng - 1) & 1) * rs;
-  return PartRows{pm + last, ps + last, ntl - (ng - 1) * gw, ng > 1 ? run_m : nullptr, run_s};
+  return PartRows{pm + last, ps + last, ntl - (ng - 1) * gw, 0, ng > 1 ? run_m : nullptr, run_s};
 }
 
 // The forward pass behind lce_forward and (tgt_part != null) lce_forward_shard.
@@ -2299,7 +2460,7 @@ lce_status_t forward_impl(const lce_problem_t* p, const ShardInfo* shard, const 
   const PartRows pr = launch_fwd_stats(L, pl, w, pl.ldw, h, pl.ldh, (const int*)idx, (const int*)nv,
                                        (uint16_t*)(ws + pl.o_hv), pm, ps);
   L(K_COMBINE, k_combine, dim3((unsigned)((pl.n + kCombTok - 1) / kCombTok)), dim3(1024), h, pl.ldh, w, pl.ldw,
-    targets, p->target_bytes, si.v_begin, pl.v, (const int*)idx, (const int*)nv, (int)pl.d, pr.count, pr.m, pr.s,
+    targets, p->target_bytes, si.v_begin, pl.v, (const int*)idx, (const int*)nv, (int)pl.d, pr.count, pr.split, pr.m, pr.s,
     (int)pl.npad, pr.run_m, pr.run_s, lse, terms, none ? loss : (float*)nullptr, tgt_part);
   if (!none && !shard) L(K_LOSS, k_loss, dim3(1), dim3(1024), (const float*)terms, (const int*)nv, p->reduction, loss);
   return L.st;
@@ -2326,8 +2487,8 @@ void launch_teacher(Launcher& L, int kind, const KdArgs& kd, const uint16_t* hvt
                     const int* idx, const int* nv, float* P) {
   const int wm = hvt ? 3 : 2, rows = 128 * wm, tm = (vs + rows - 1) / rows;
   const TileOrder to = tile_order(tm, pl.nt_max, hvt ? group_tiles(tm, rows, kd.dt) : tm);
-  L(kind, hvt ? k_bwd_g<kMode, 3> : k_bwd_g<kMode, 2>, dim3(to.grid), dim3(256 * wm), kd.wt, kd.ldwt, v0, vs,
-    hvt ? hvt : kd.ht, hvt ? (int64_t)kd.dt : kd.ldht, pl.n, (const void*)nullptr, 4, (int64_t)0, idx, nv, kd.lse_t,
+  L(kind, hvt ? k_kd_tile<kMode, 3> : k_kd_tile<kMode, 2>, dim3(to.grid), dim3(256 * wm), kd.wt, kd.ldwt, v0, vs,
+    hvt ? hvt : kd.ht, hvt ? (int64_t)kd.dt : kd.ldht, pl.n, idx, nv, kd.lse_t,
     (const float*)nullptr, (const int*)nullptr, (int)LCE_REDUCE_MEAN, kd.dt, tm, (uint16_t*)nullptr, (int)pl.vc,
     (int)pl.npad, kd.scale2, kd.inv_t, P, (float*)nullptr, (int64_t)0, to.gw);
 }
@@ -2428,17 +2589,16 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
       float* P = (float*)(ws + pl.bwd_bytes);
       launch_teacher<P_WRITE>(L, K_KD_P, *kd, hvt, pl, v0, vs, idx, nv, P);
       const TileOrder to = tile_order(tm, pl.nt_max, student_group(tm, pl.d));
-      L(K_BWD_G, k_bwd_g<G_SOFT, 2>, dim3(to.grid), dim3(NTHREADS), w, pl.ldw, v0, vs, h,
-        pl.ldh, pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, lse, grad_loss,
+      L(K_BWD_G, k_kd_tile<G_SOFT, 2>, dim3(to.grid), dim3(NTHREADS), w, pl.ldw, v0, vs, h,
+        pl.ldh, pl.n, (const int*)idx, (const int*)nv, lse, grad_loss,
         (const int*)n_valid, p->reduction, d, tm, g, vc, npad, kd->scale2, kd->inv_t, P, (float*)nullptr,
         (int64_t)0, to.gw);
     } else {
-      const int tmg = (vs + Geo<kGWM>::TM - 1) / Geo<kGWM>::TM;
-      const TileOrder to = tile_order(tmg, pl.nt_max, group_tiles(tmg, Geo<3>::TM, d));
-      L(K_BWD_G, d % KSLICE == 0 ? k_bwd_g<G_ONEHOT, kGWM> : k_bwd_g<G_ONEHOT, kGWM, true>, dim3(to.grid),
-        dim3(Geo<kGWM>::NT), w, pl.ldw, v0, vs, (const uint16_t*)hv, (int64_t)d, pl.n, targets, p->target_bytes, si.v_begin,
-        (const int*)idx, (const int*)nv, lse, grad_loss, (const int*)n_valid, p->reduction, d, tmg, g, vc, npad, kLog2e,
-        1.f, (float*)nullptr, (float*)nullptr, (int64_t)0, to.gw);
+      const int tmg = (vs + Geo<3>::TM - 1) / Geo<3>::TM;
+      const TileOrder to = tile_order(tmg, pl.nt_max, group_tiles(tmg, Geo<3>::TM, d), true);
+      L(K_BWD_G, d % KSLICE == 0 ? k_bwd_g<false> : k_bwd_g<true>, dim3(to.grid), dim3(Geo<3>::NT), w, pl.ldw, v0, vs,
+        (const uint16_t*)hv, (int64_t)d, targets, p->target_bytes, si.v_begin, (const int*)idx, (const int*)nv, lse,
+        grad_loss, (const int*)n_valid, p->reduction, d, tmg, to.gw, 1, g, vc);
     }
     // split launches: a block for each part the tiles may take; otherwise 8 XCDs x 32 CUs x (whole rounds of the
     // largest per-XCD share + one round for the split tail)
@@ -2532,8 +2692,8 @@ lce_status_t kd_forward_launches(Launcher& L, const lce_kd_problem_t* p, const K
     launch_teacher<Z_WRITE>(L, K_KD_Z, kd, hvt, pl, v0, vs, idx, nv, P);
     const int tm = (vs + TILE - 1) / TILE;
     const TileOrder to = tile_order(tm, pl.nt_max, student_group(tm, pl.d));
-    L(K_KD_STATS, k_bwd_g<KD_STATS, 2>, dim3(to.grid), dim3(NTHREADS), wsm, pl.ldw, v0, vs, hs, pl.ldh,
-      pl.n, targets, p->target_bytes, (int64_t)0, (const int*)idx, (const int*)nv, (const float*)nullptr,
+    L(K_KD_STATS, k_kd_tile<KD_STATS, 2>, dim3(to.grid), dim3(NTHREADS), wsm, pl.ldw, v0, vs, hs, pl.ldh,
+      pl.n, (const int*)idx, (const int*)nv, (const float*)nullptr,
       (const float*)nullptr, (const int*)nullptr, p->reduction, (int)pl.d, tm, (uint16_t*)nullptr, (int)pl.vc,
       npad, k.scale2, k.inv_t, P, qpart, v0 / TILE, to.gw);
   }

@@ -471,3 +471,43 @@ def test_a_workspace_of_the_former_ragged_width_size_still_serves_the_forward(n,
         B.lce_forward(B.problem(n, d, v), **ok,
                       workspace_bytes=info["o_pm"] + 2 * rup(4 * rows * npad, 256) + 4 * npad - 1)
     assert e.value.code == B.LCE_ERR_WORKSPACE
+
+
+def tile_part(b, tiles, gw, nt, split=True):
+    """The (vocabulary tile, token tile, parts, part) of block b of a split forward or G launch, as tile_part maps
+    it: the last, partial round of 256 tiles in 2 parts per tile (up to 128 tiles) or 4 (up to 64)."""
+    a = tiles & ~7
+    t = a * nt + (tiles - a) * rup(nt, 8)
+    rem = t & 255
+    parts = 1 if not split or t > 2048 or rem == 0 or rem > 128 else (2 if rem > 64 else 4)
+    whole = t & ~255 if parts > 1 else t
+    part, n = 0, 1
+    l = b
+    if b >= whole:
+        if parts == 1:
+            return None
+        j = b - whole
+        l, n, part = whole + j // (8 * parts) * 8 + (j & 7), parts, (j >> 3) % parts
+    if l >= t:
+        return None
+    got = xcd_tile(l, tiles, gw, nt)
+    return None if got is None else (*got, n, part)
+
+
+@pytest.mark.parametrize("tiles,nt", [(1, 1), (3, 1), (7, 9), (8, 1), (11, 1), (42, 13), (64, 1), (65, 2), (84, 10), (128, 2),
+                                      (129, 2), (167, 1), (334, 2), (334, 6), (17, 16), (256, 8), (333, 7)])
+def test_split_launches_cover_every_part_once_and_keep_a_tile_on_one_xcd(tiles, nt):
+    grid, gw = tile_order(tiles, nt, tiles)
+    seen, xcd = {}, {}
+    for b in range(grid + 256):
+        p = tile_part(b, tiles, gw, nt)
+        if p is None:
+            continue
+        tm, tn, parts, part = p
+        assert 0 <= part < parts
+        seen.setdefault((tm, tn, parts), []).append(part)
+        xcd.setdefault((tm, tn), set()).add(b % 8)
+    assert sorted(k[:2] for k in seen) == sorted((tm, tn) for tm in range(tiles) for tn in range(nt))
+    for (tm, tn, parts), got in seen.items():
+        assert sorted(got) == list(range(parts))
+        assert len(xcd[(tm, tn)]) == 1

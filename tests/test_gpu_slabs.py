@@ -123,3 +123,22 @@ def test_ragged_widths_and_the_least_forward_workspace(n, d, v):
     assert np.max(np.abs(out[0] - out[1])) <= 1e-5 * max(1.0, np.max(np.abs(out[0])))
     gpu = U.run_gpu(h, w, t, inp.ignore_index, "none", np.ones(n, np.float32))
     U.assert_parity(gpu, ref)
+
+
+@pytest.mark.parametrize("n,d,v", [(256, 64, 384 * 64), (255, 72, 384 * 64 + 1), (257, 64, 384 * 65 - 191), (1, 128, 384 * 33),
+                                   (129, 64, 384 * 128), (128, 200, 192), (384, 64, 193), (300, 64, 384 * 129),
+                                   (513, 64, 384 * 105), (640, 64, 384 * 110 + 200), (64, 1024, 5000)])
+@pytest.mark.parametrize("sigma", [0.05, 1.0])
+def test_launches_whose_last_round_is_cut_match_the_oracle(n, d, v, sigma):
+    # forward and G launches of 64, 65, 128 and 129 tiles (4, 2, 2 and 1 parts per tile), tails after whole rounds,
+    # ids and tokens that end inside, at and before a part; every token's loss and lse to fp32 rounding
+    inp = WL.custom(n, d, v, seed=v % 1000 + n, mask_frac=0.0, sigma_w=sigma, case_id=56)
+    g = np.random.default_rng(n).standard_normal(n).astype(np.float32)
+    print(f"case n={n} d={d} v={v} sigma={sigma}", flush=True)
+    h, w, t = U.to_device(inp)
+    gpu = U.run_gpu(h, w, t, inp.ignore_index, "none", g)
+    ref = O.lce(inp.h_bits, inp.w_bits, inp.targets, inp.ignore_index, "none", g.astype(np.float64))
+    U.assert_parity(gpu, ref)
+    scale = max(1.0, np.max(np.abs(ref["lse"])))
+    assert np.max(np.abs(gpu["lse"] - ref["lse"])) <= 1e-5 * scale
+    assert np.max(np.abs(gpu["loss"] - ref["loss"])) <= 2e-5 * scale
