@@ -965,8 +965,14 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
   }
   float* om = part_m + (int64_t)tl * npad + n0;
   float* os = part_s + (int64_t)tl * npad + n0;
+  // (a token tile of at most 128 valid tokens takes a tile half as wide: 1364 tokens of 3584 x 152064, whose
+  // last of six token tiles holds 84, forward 1290 -> 1255 us and G 1330 -> 1240; 285 of 2048 x 128256 205 ->
+  // 190 and 238 -> 213)
   if (p.parts == 1) {
-    fwd_part<kTail, 4, 2>(smem, W + (int64_t)v0 * ldw, ldw, vleft, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os, scale2);
+    if (nv - n0 > TILE / 2)
+      fwd_part<kTail, 4, 2>(smem, W + (int64_t)v0 * ldw, ldw, vleft, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os, scale2);
+    else
+      fwd_part<kTail, 4, 1>(smem, W + (int64_t)v0 * ldw, ldw, vleft, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os, scale2);
     if (tail_parts(tile_space(vt_launch, nt), split) > 1 && threadIdx.x < TILE && n0 + (int)threadIdx.x < nv) {
       om[(int64_t)vt_launch * npad + threadIdx.x] = -INFINITY;
       os[(int64_t)vt_launch * npad + threadIdx.x] = 0.f;
@@ -979,7 +985,7 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
   const uint16_t* wt = W + (int64_t)(v0 + (vl > 0 ? ih * (TM / 2) : 0)) * ldw;
   om += (int64_t)ih * vt_launch * npad;
   os += (int64_t)ih * vt_launch * npad;
-  if (p.parts == 2) {
+  if (p.parts == 2 && nv - n0 > TILE / 2) {
     fwd_part<kTail, 2, 2>(smem, wt, ldw, vl, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os, scale2);
   } else {
     const int t0 = th * (TILE / 2);
@@ -1336,10 +1342,14 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_bwd_g(const uint16_t* __restr
   const uint16_t* ht = Hv + (int64_t)n0 * ldh;
   uint16_t* g0 = G + (int64_t)n0 * vc + vt0;
   const int64_t tbase = id0 + v0 + vt0;
-  if (p.parts == 1)
+  const bool wide = nv - n0 > TILE / 2;   // (else the tile's tokens fit one half as wide, and no other row is read)
+  if (p.parts == 1 && wide)
     g_part<kTail, 4, 2>(smem, wt, ldw, vs - vt0, ht, ldh, nv - n0, targets, tbytes, tbase, idx + n0, lse, grad, n_norm,
                         reduction, d, g0, vc);
-  else if (p.parts == 2)
+  else if (p.parts == 1)
+    g_part<kTail, 4, 1>(smem, wt, ldw, vs - vt0, ht, ldh, nv - n0, targets, tbytes, tbase, idx + n0, lse, grad, n_norm,
+                        reduction, d, g0, vc);
+  else if (p.parts == 2 && wide)
     g_part<kTail, 2, 2>(smem, wt, ldw, vs - vt0, ht, ldh, nv - n0, targets, tbytes, tbase, idx + n0, lse, grad, n_norm,
                         reduction, d, g0, vc);
   else

@@ -127,11 +127,13 @@ def test_ragged_widths_and_the_least_forward_workspace(n, d, v):
 
 @pytest.mark.parametrize("n,d,v", [(256, 64, 384 * 64), (255, 72, 384 * 64 + 1), (257, 64, 384 * 65 - 191), (1, 128, 384 * 33),
                                    (129, 64, 384 * 128), (128, 200, 192), (384, 64, 193), (300, 64, 384 * 129),
-                                   (513, 64, 384 * 105), (640, 64, 384 * 110 + 200), (64, 1024, 5000)])
+                                   (513, 64, 384 * 105), (640, 64, 384 * 110 + 200), (64, 1024, 5000),
+                                   (100, 136, 384 * 150 + 7), (384, 64, 384 * 90), (385, 64, 384 * 90)])
 @pytest.mark.parametrize("sigma", [0.05, 1.0])
 def test_launches_whose_last_round_is_cut_match_the_oracle(n, d, v, sigma):
     # forward and G launches of 64, 65, 128 and 129 tiles (4, 2, 2 and 1 parts per tile), tails after whole rounds,
-    # ids and tokens that end inside, at and before a part; every token's loss and lse to fp32 rounding
+    # ids and tokens that end inside, at and before a part, last token tiles of 1, 100, 128 and 129 tokens (half as
+    # wide up to 128); every token's loss and lse to fp32 rounding
     inp = WL.custom(n, d, v, seed=v % 1000 + n, mask_frac=0.0, sigma_w=sigma, case_id=56)
     g = np.random.default_rng(n).standard_normal(n).astype(np.float32)
     print(f"case n={n} d={d} v={v} sigma={sigma}", flush=True)
