@@ -92,8 +92,8 @@ typedef struct lce_problem {
 /* For lce_backward, lce_backward_select, lce_backward_adamw and lce_backward_shard: the workspace still holds what the
  * immediately preceding lce_forward (or lce_forward_shard, then lce_combine_shards) of the same
  * problem, H and targets left in it, on the same stream and with nothing else written to the
- * workspace in between. The backward then reuses that call's valid-row list (and, where the
- * forward gathered them, the valid rows of H) instead of forming them again: two fewer kernels
+ * workspace in between. The backward then reuses that call's valid-row list and gathered valid
+ * rows of H instead of forming them again: two fewer kernels
  * per step. Without the flag the backward depends on no earlier call. The forward and the
  * combine ignore the flag; the KD calls reject it (LCE_ERR_ARG). The workspace must be at
  * least max(fwd_bytes, bwd_bytes). */

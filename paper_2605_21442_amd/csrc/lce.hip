@@ -2898,7 +2898,7 @@ lce_status_t lce_combine_shards(const lce_problem_t* p, int32_t n_shards, const 
   if (!loss || !n_valid) return LCE_ERR_NULL;
   if (pl.n > 0 && (!lse_parts || !tgt_parts || !targets || !lse || !workspace)) return LCE_ERR_NULL;
   if (pl.n > 0 && ((uintptr_t)workspace & 255) != 0) return LCE_ERR_ALIGN;
-  if (pl.n > 0 && workspace_bytes < pl.fwd_bytes) return LCE_ERR_WORKSPACE;
+  if (pl.n > 0 && !few_partial_rows(&pl, workspace_bytes)) return LCE_ERR_WORKSPACE;
   Launcher L{(hipStream_t)stream};
   const bool none = p->reduction == LCE_REDUCE_NONE;
   if (pl.n == 0) {
