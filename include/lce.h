@@ -126,7 +126,8 @@ typedef struct lce_adamw {
  * Calls of few tokens (a slab of that width times the tokens is at most 1024 tiles of
  * 384 x 256) take the fewest equal slabs that keep the [N, V_slab] bf16 block within 1.25 GiB.
  * The backward's size does not depend on V; the forward's vocabulary partials
- * take at most max(2*D, 4096) bytes per token. Either output pointer may be NULL.
+ * take at most max(2*D, 4096) bytes per token, and up to 8 MiB more. Either output
+ * pointer may be NULL.
  */
 lce_status_t lce_workspace_size(const lce_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes);
 

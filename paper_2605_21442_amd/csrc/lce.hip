@@ -2098,6 +2098,7 @@ struct Plan {
   int nt_max, vt_count, vt_count3;           // vt_count3: 384-id tiles
   int64_t vc, nslab;
   int64_t gw;                                // 384-id tiles of the forward's vocabulary groups
+  int rule_gw;                               // 384-id tiles of the slab rule's width (many tokens)
   int64_t rows_g;                            // rows of G and dH32: Npad rounded up to a 384-row tile
   // workspace offsets; idx, pos, Nv and the gathered rows Hv form a prefix both passes share
   size_t o_idx, o_pos, o_nv, o_hv, o_pm, o_ps, o_terms, fwd_bytes;
@@ -2268,6 +2269,7 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   // leave the MALL)
   pl->gw = vc / 384;
   if (wide_slabs && vc < vround) vc = whole_round_slab(p->v, p->d, vc);
+  pl->rule_gw = (int)(vc / 384);
   if (vc < vround) vc = few_token_slab(p->v, pl->npad, vc, wide_slabs ? 2 : 4);
   pl->vc = vc;
   pl->nslab = (p->v + vc - 1) / vc;
@@ -2281,10 +2283,12 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   // valid rows of H, gathered by the forward and by the backward; a backward with
   // LCE_FLAG_REUSE_FORWARD finds the forward's here
   pl->o_hv = take(cur, 2 * (size_t)p->d * pl->npad);
-  // partial rows: one per 384-id tile in one launch, else two sets of vc / 384 rows and a running pair
+  // partial rows: one per 384-id tile in one launch, else two sets of a group's rows and a running pair. A
+  // group has the rule's width whatever the tokens: as wide as a call of few tokens' slab, its rows would
+  // grow with V and its W rows leave the MALL (4096 x 2048 x 400000: forward 5450 us, so 4920)
   pl->few_rows = false;
-  pl->fgw = (int)(vc / 384);
-  const int64_t rows3 = fwd_one_launch(*pl) ? pl->vt_count3 : 2 * (vc / 384) + 1;
+  pl->fgw = pl->rule_gw;
+  const int64_t rows3 = fwd_one_launch(*pl) ? pl->vt_count3 : 2 * (int64_t)pl->fgw + 1;
   const int64_t rows = std::max<int64_t>(2 * std::min(pl->vt_count, kFewRows / 2), rows3);
   place_partials(pl, rows);
   // (up to twice kSplitTiles tiles of all N tokens, of which fewer may be valid)

@@ -119,7 +119,7 @@ def walk(n, d, v, nv, ld_h=None, ld_w=None):
             if info["fwd_one_launch"]:
                 e.touch("pm", 4 * ((vt3 - 1) * npad + nv))
             else:
-                gw = vc // 384
+                gw = (info["part_rows"] - 1) // 2
                 e.touch("pm", 4 * (2 * gw * npad + nv))             # running pair after the two row sets
         else:
             e.touch("H", 2 * ((n - 1) * ld_h + d))                  # rows gathered through idx (< n)
@@ -511,3 +511,13 @@ def test_split_launches_cover_every_part_once_and_keep_a_tile_on_one_xcd(tiles, 
     for (tm, tn, parts), got in seen.items():
         assert sorted(got) == list(range(parts))
         assert len(xcd[(tm, tn)]) == 1
+
+
+@pytest.mark.parametrize("v", [1, 385, 4096, 32003, 152064, 196609, 600000, 6000000])
+def test_forward_partials_take_at_most_the_stated_bytes_per_token(v):
+    # max(2 D, 4096) bytes per token (with a floor of 64 rows) whatever V, and up to 8 MiB more for the second
+    # rows of cut tiles
+    for d in (8, 64, 72, 1000, 1024, 2048, 4096, 8192):
+        for n in (1, 64, 256, 1024, 2048, 4096, 5000, 16384):
+            info = B.lce_plan_info(B.problem(n, d, v))
+            assert 8 * info["part_rows"] * info["npad"] <= max(2 * d, 4096) * info["npad"] + (8 << 20), (n, d, v)
