@@ -38,7 +38,8 @@
  *    returns LCE_ERR_HIP. Bad target values are data, seen only on the device:
  *    such rows are treated as ignored and bit 0 of *dev_status is set.
  *  - Results are deterministic: the same inputs give the same bits on every run
- *    (no atomics in any reduction; fixed summation orders).
+ *    (no atomics in any reduction; fixed summation orders), whatever the size of a
+ *    workspace that holds the reported bytes.
  */
 #ifndef LCE_H_
 #define LCE_H_
@@ -56,7 +57,7 @@ typedef enum lce_status {
   LCE_ERR_SHAPE = 2,        /* n < 0, d < 1, v < 1, ld < d, or sizes beyond 32-bit offsets */
   LCE_ERR_ALIGN = 3,        /* pointer, stride or workspace misaligned */
   LCE_ERR_UNSUPPORTED = 4,  /* d % 8 != 0, unknown reduction or target width */
-  LCE_ERR_WORKSPACE = 5,    /* workspace smaller than lce_workspace_size() */
+  LCE_ERR_WORKSPACE = 5,    /* workspace too small (lce_workspace_size()) */
   LCE_ERR_HIP = 6,          /* a HIP runtime call or kernel launch failed */
   LCE_ERR_ARG = 7           /* other invalid argument */
 } lce_status_t;
@@ -128,6 +129,12 @@ typedef struct lce_adamw {
  * The backward's size does not depend on V; the forward's vocabulary partials
  * take at most max(2*D, 4096) bytes per token, and up to 8 MiB more. Either output
  * pointer may be NULL.
+ *
+ * A smaller forward workspace, as callers may hold from an earlier version of this library,
+ * is served as long as the least form of the forward fits it (groups of 24 vocabulary tiles,
+ * a launch each, or the one launch without the 8 MiB); a still smaller one is
+ * LCE_ERR_WORKSPACE. That form adds the same terms in another order: its lse and loss may
+ * differ in their last bits from those of a workspace of the reported size.
  */
 lce_status_t lce_workspace_size(const lce_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes);
 
@@ -214,7 +221,8 @@ lce_status_t lce_backward_select(const lce_problem_t* p,
  * instead of from the caller. The array holds LCE_NOALLOC_SCRATCH_BYTES (256 MiB) on every GPU
  * the library runs on, from the first call on that GPU until the process ends; problems whose
  * forward workspace (lce_workspace_size's fwd_bytes) is larger are rejected with
- * LCE_ERR_WORKSPACE before anything is launched. The call itself allocates nothing. All calls on
+ * LCE_ERR_WORKSPACE before anything is launched. (A problem that fits the array in the least
+ * form of the forward only takes that form in lce_forward too, and reports its bytes.) The call itself allocates nothing. All calls on
  * one GPU share its array: calls that may overlap on one GPU (on different streams, or from
  * several threads onto different streams) race and must be ordered by the caller; calls on one
  * stream are ordered by it. `stream` must belong to the current device (else LCE_ERR_ARG). The

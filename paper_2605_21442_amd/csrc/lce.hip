@@ -758,10 +758,10 @@ __global__ __launch_bounds__(1024) void k_compact(const void* targets, int tbyte
 // W rows stay in the MALL while the token tiles pass, and the workgroups resident on one XCD share
 // their W and H tiles through its L2 as in the backward's G launches. One launch covers vt_launch tiles from tm0
 // on and writes one partial row per tile (row tm - tm0). When the rows of all tiles would take too
-// much space (fwd_one_launch), the host launches one group at a time instead: group g writes to one of two row sets (by the parity of g), and in launch g >= 1 the
-// workgroup of the group's first tile of each token tile first folds the other set (group g - 1,
-// complete since launches on a stream run in order) into a running pair per token. The workspace
-// thus stays independent of V.
+// much space (plan_forward), the host launches one group at a time instead: group g writes to one of two
+// row sets (by the parity of g), and in launch g >= 1 the workgroup of the group's first tile of each token
+// tile first folds the other set (group g - 1, complete since launches on a stream run in order) into a
+// running pair per token. The workspace thus stays independent of V.
 __device__ __forceinline__ void merge_pair(float& m, float& s, float m2, float s2) {
   const float mn = fmaxf(m, m2);
   if (mn == -INFINITY) return;
@@ -2105,18 +2105,10 @@ struct Plan {
   size_t o_g, o_dh32, o_dh32b, bwd_bytes;    // o_dh32b: accumulator of the second K part (or 0)
   int dh_kz;                                 // most K parts a dH launch takes (1 to 8)
   int part_rows;                             // partial rows of the forward statistics
+  bool one_launch;                           // the forward statistics run as one launch
   int fgw;                                   // 384-id tiles of a group of the forward (more than one launch)
-  bool few_rows;                             // the forward's partials in the least space (few_partial_rows)
   bool split;                                // the forward may cut its last tiles (two partial rows each)
 };
-
-// the forward in one launch: its partial rows (8 bytes per 384-id tile and token) take at most 2 D bytes
-// per token or, for narrow heads, 4 KiB (512 tiles, 196608 ids: 16384 x 72 x 100000 in five launches of 64
-// tiles, each waiting for the fold of the one before, 1314 us, in one 563)
-inline bool fwd_one_launch(const Plan& pl) {
-  return !pl.few_rows && pl.vt_count3 <= std::max<int64_t>(pl.d / 4, 512) &&
-         (int64_t)pl.vt_count3 * pl.nt_max <= INT32_MAX;
-}
 
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
@@ -2199,33 +2191,39 @@ int64_t few_token_slab(int64_t v, int64_t npad, int64_t vc, int64_t elem_bytes) 
   return round_up((v + slabs - 1) / slabs, 768);
 }
 
-// The forward's regions after the prefix: rows partial pairs per token and the per-row terms.
-void place_partials(Plan* pl, int64_t rows) {
-  const size_t arr = (4 * (size_t)rows * pl->npad + 255) / 256 * 256;
-  pl->part_rows = (int)rows;
+// The forward's launches and its regions after the prefix: the partial rows (pairs per 384-id tile and
+// token) and the per-row terms. One launch where a row per tile takes at most 2 D bytes per token or, for
+// narrow heads, 4 KiB (512 tiles, 196608 ids: 16384 x 72 x 100000 in five launches of 64 tiles, each waiting
+// for the fold of the one before, 1314 us, in one 563); otherwise groups of the slab rule's width, a launch
+// each, in two sets of rows and a running pair (as wide as a call of few tokens' slab, the rows would grow
+// with V and a group's W rows leave the MALL: 4096 x 2048 x 400000 forward 5450 us, so 4920). A launch of up
+// to twice kSplitTiles tiles of all N tokens (fewer may be valid) may cut its last tiles: a second set of
+// rows, at most 8 MiB.
+//
+// least: the form in the least space, which needs no more than any version of this library has asked for: no
+// cut tiles, and where there may be more rows than before (narrow heads, and widths that are not a multiple
+// of 64, which once took at most 64) groups of 24 tiles, 2 x 24 + 1 rows.
+void plan_forward(Plan* pl, bool least) {
+  const int64_t vt = pl->vt_count3, tiles = vt * pl->nt_max;
+  const bool few = least && (pl->d % KSLICE != 0 || vt > pl->d / 4);
+  pl->one_launch = (few ? vt <= 24 : vt <= std::max<int64_t>(pl->d / 4, 512)) && tiles <= INT32_MAX;
+  pl->split = !least && pl->one_launch && tiles <= 2 * kSplitTiles;
+  pl->fgw = few ? 24 : pl->rule_gw;
+  const int64_t rows = pl->one_launch || vt <= pl->fgw ? vt : 2 * (int64_t)pl->fgw + 1;
+  // (not below two rows per 256 ids, up to 64: small heads then ask for the same bytes in either form)
+  pl->part_rows = (int)std::max<int64_t>(pl->split ? 2 * rows : rows, few ? 0 : 2 * std::min(pl->vt_count, 32));
+  const size_t arr = (4 * (size_t)pl->part_rows * pl->npad + 255) / 256 * 256;
   pl->o_pm = pl->o_hv + (2 * (size_t)pl->d * pl->npad + 255) / 256 * 256;
   pl->o_ps = pl->o_pm + arr;
   pl->o_terms = pl->o_ps + arr;
   pl->fwd_bytes = pl->o_terms + 4 * (size_t)pl->npad;
 }
 
-// For a workspace smaller than the plan's forward: its launch is first left unsplit (one partial row a
-// tile). Then those whose rows have grown, callers may hold a workspace from before
-// that, or fit the library's fixed array with it: widths that are not a multiple of 64 once took at
-// most kFewRows partial rows (two per 256 ids), and narrow heads (more than D / 4 tiles) groups of at least
-// 24 tiles. Groups of 24 tiles, a launch each, need 2 x 24 + 1 rows (a vocabulary of at most 24 tiles its
-// tiles'), never more than either.
-constexpr int kFewRows = 64;
-bool few_partial_rows(Plan* pl, size_t workspace_bytes) {
-  if (pl->split && pl->fwd_bytes > workspace_bytes) {
-    pl->split = false;
-    place_partials(pl, std::max<int64_t>(2 * std::min(pl->vt_count, kFewRows / 2), pl->vt_count3));
-  }
-  if ((pl->d % KSLICE != 0 || pl->vt_count3 > pl->d / 4) && pl->fwd_bytes > workspace_bytes) {
-    pl->few_rows = true;
-    pl->fgw = 24;
-    place_partials(pl, pl->vt_count3 <= 24 ? pl->vt_count3 : 2 * 24 + 1);
-  }
+// The plan of a forward in workspace_bytes. The form follows from the problem alone wherever the workspace
+// holds the size that is reported for it, so that its size never shows in the results; a smaller one, which
+// callers may hold from before the present forms, is served in the least form as long as that fits.
+bool forward_fits(Plan* pl, size_t workspace_bytes) {
+  if (pl->fwd_bytes > workspace_bytes) plan_forward(pl, true);
   return pl->fwd_bytes <= workspace_bytes;
 }
 
@@ -2283,17 +2281,13 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   // valid rows of H, gathered by the forward and by the backward; a backward with
   // LCE_FLAG_REUSE_FORWARD finds the forward's here
   pl->o_hv = take(cur, 2 * (size_t)p->d * pl->npad);
-  // partial rows: one per 384-id tile in one launch, else two sets of a group's rows and a running pair. A
-  // group has the rule's width whatever the tokens: as wide as a call of few tokens' slab, its rows would
-  // grow with V and its W rows leave the MALL (4096 x 2048 x 400000: forward 5450 us, so 4920)
-  pl->few_rows = false;
-  pl->fgw = pl->rule_gw;
-  const int64_t rows3 = fwd_one_launch(*pl) ? pl->vt_count3 : 2 * (int64_t)pl->fgw + 1;
-  const int64_t rows = std::max<int64_t>(2 * std::min(pl->vt_count, kFewRows / 2), rows3);
-  place_partials(pl, rows);
-  // (up to twice kSplitTiles tiles of all N tokens, of which fewer may be valid)
-  pl->split = fwd_one_launch(*pl) && (int64_t)pl->vt_count3 * pl->nt_max <= 2 * kSplitTiles;
-  if (pl->split) place_partials(pl, std::max<int64_t>(rows, 2 * pl->vt_count3));
+  // a forward beyond the library's fixed array takes the least form if that fits it, so that
+  // lce_forward_noalloc and lce_forward run the same launches for every problem the former serves
+  plan_forward(pl, false);
+  if (pl->fwd_bytes > (size_t)LCE_NOALLOC_SCRATCH_BYTES) {
+    plan_forward(pl, true);
+    if (pl->fwd_bytes > (size_t)LCE_NOALLOC_SCRATCH_BYTES) plan_forward(pl, false);
+  }
   // G and the fp32 dH accumulators hold every row a 384-row dH tile can address (the tiles of
   // the last token rows reach past Npad), so that no access leaves its region
   pl->rows_g = round_up(pl->npad, 384);
@@ -2412,7 +2406,7 @@ PartRows launch_fwd_stats(Launcher& L, const Plan& layout, const uint16_t* W, in
   launch_gather(L, H, ldh, d, npad, idx, nv, hv);
   const int gw = layout.fgw;
   const int ntl = layout.vt_count3;
-  if (fwd_one_launch(layout)) {
+  if (layout.one_launch) {
     // one launch: the groups only order the tiles (as wide as the slab rule's width, or narrower
     // where its W rows would not stay in the MALL)
     const TileOrder to = tile_order(ntl, nt_max, group_tiles(layout.gw, Geo<3>::TM, d), layout.split);
@@ -2451,7 +2445,7 @@ lce_status_t forward_impl(const lce_problem_t* p, const ShardInfo* shard, const 
   if ((!shard && !loss) || (shard && !tgt_part) || !n_valid) return LCE_ERR_NULL;
   if (pl.n > 0 && (!H || !W || !targets || !lse || !workspace)) return LCE_ERR_NULL;
   if (pl.n > 0 && (!aligned16(H) || !aligned16(W) || ((uintptr_t)workspace & 255) != 0)) return LCE_ERR_ALIGN;
-  if (pl.n > 0 && !few_partial_rows(&pl, workspace_bytes)) return LCE_ERR_WORKSPACE;
+  if (pl.n > 0 && !forward_fits(&pl, workspace_bytes)) return LCE_ERR_WORKSPACE;
   Launcher L{(hipStream_t)stream};
   const bool none = !shard && p->reduction == LCE_REDUCE_NONE;
   if (pl.n == 0) {
@@ -2808,7 +2802,7 @@ lce_status_t lce_plan_info(const lce_problem_t* p, lce_plan_info_t* out) {
   out->dh_kz = pl.dh_kz;
   out->part_rows = pl.part_rows;
   out->fwd_gathers = pl.d % KSLICE == 0 ? 1 : 0;
-  out->fwd_one_launch = fwd_one_launch(pl) ? 1 : 0;
+  out->fwd_one_launch = pl.one_launch ? 1 : 0;
   out->o_idx = (int64_t)pl.o_idx;
   out->o_pos = (int64_t)pl.o_pos;
   out->o_nv = (int64_t)pl.o_nv;
@@ -2872,7 +2866,7 @@ lce_status_t lce_forward_noalloc(const lce_problem_t* p, const void* H, const vo
   Plan pl;
   lce_status_t st = make_plan(p, &pl);
   if (st != LCE_OK) return st;
-  if (!few_partial_rows(&pl, (size_t)LCE_NOALLOC_SCRATCH_BYTES)) return LCE_ERR_WORKSPACE;
+  if (pl.fwd_bytes > (size_t)LCE_NOALLOC_SCRATCH_BYTES) return LCE_ERR_WORKSPACE;
   void* ws = nullptr;
   st = noalloc_scratch(stream, &ws);
   if (st != LCE_OK) return st;
@@ -2902,7 +2896,7 @@ lce_status_t lce_combine_shards(const lce_problem_t* p, int32_t n_shards, const 
   if (!loss || !n_valid) return LCE_ERR_NULL;
   if (pl.n > 0 && (!lse_parts || !tgt_parts || !targets || !lse || !workspace)) return LCE_ERR_NULL;
   if (pl.n > 0 && ((uintptr_t)workspace & 255) != 0) return LCE_ERR_ALIGN;
-  if (pl.n > 0 && !few_partial_rows(&pl, workspace_bytes)) return LCE_ERR_WORKSPACE;
+  if (pl.n > 0 && !forward_fits(&pl, workspace_bytes)) return LCE_ERR_WORKSPACE;
   Launcher L{(hipStream_t)stream};
   const bool none = p->reduction == LCE_REDUCE_NONE;
   if (pl.n == 0) {

@@ -457,19 +457,21 @@ def test_the_tail_mask_keeps_row_major_loads_inside_their_rows(d):
                                    (9000, 72, 9217), (5, 8, 1), (100000, 200, 1000000)])
 def test_a_workspace_of_the_former_ragged_width_size_still_serves_the_forward(n, d, v):
     # widths that are not a multiple of 64 once took two partial rows per 256 ids, at most 64: callers may hold
-    # workspaces of that size, and the fixed array of lce_forward_noalloc served the problems that fit so. The
-    # forward then takes groups of 24 tiles: 2 x 24 + 1 rows, or the tiles themselves where they are at most 24
+    # workspaces of that size. The forward then takes groups of 24 tiles: 2 x 24 + 1 rows, or the tiles
+    # themselves where they are at most 24; where the fixed array of lce_forward_noalloc holds only that form, it
+    # is the one reported
     info = B.lce_plan_info(B.problem(n, d, v))
     npad = info["npad"]
     former = info["o_pm"] + 2 * rup(4 * 2 * min(cdiv(v, 256), 32) * npad, 256) + 4 * npad
     vt3 = cdiv(v, 384)
     rows = vt3 if vt3 <= 24 else 49
-    assert info["o_pm"] + 2 * rup(4 * rows * npad, 256) + 4 * npad <= former <= info["fwd_bytes"]
+    least = info["o_pm"] + 2 * rup(4 * rows * npad, 256) + 4 * npad
+    assert least <= former
+    assert least == info["fwd_bytes"] if info["part_rows"] == rows else least < info["fwd_bytes"]
     ok = dict(H=0x100000, W=0x200000, targets=0x300000, loss=0x400000, lse=0x500000, n_valid=0x600000, dev_status=0,
               workspace=0x700000, stream=0)
     with pytest.raises(B.LceError) as e:                      # (one byte less than the least: refused, nothing launched)
-        B.lce_forward(B.problem(n, d, v), **ok,
-                      workspace_bytes=info["o_pm"] + 2 * rup(4 * rows * npad, 256) + 4 * npad - 1)
+        B.lce_forward(B.problem(n, d, v), **ok, workspace_bytes=least - 1)
     assert e.value.code == B.LCE_ERR_WORKSPACE
 
 
@@ -521,3 +523,26 @@ def test_forward_partials_take_at_most_the_stated_bytes_per_token(v):
         for n in (1, 64, 256, 1024, 2048, 4096, 5000, 16384):
             info = B.lce_plan_info(B.problem(n, d, v))
             assert 8 * info["part_rows"] * info["npad"] <= max(2 * d, 4096) * info["npad"] + (8 << 20), (n, d, v)
+
+
+@pytest.mark.parametrize("n,d,v", [(70000, 1000, 128256), (15616, 8192, 24960), (140000, 72, 100000), (65536, 1024, 152064),
+                                   (16384, 4096, 128256), (32768, 3584, 152064), (100000, 1400, 128256), (2048, 2048, 128256),
+                                   (300, 264, 1000)])
+def test_the_fixed_array_serves_exactly_the_problems_whose_reported_forward_bytes_it_holds(n, d, v):
+    # one launch form per problem: what lce_forward_noalloc accepts is what lce_forward's reported size fits, and
+    # nothing is launched either way here (no stream, no GPU)
+    if __import__("torch").cuda.is_available():
+        pytest.skip("host checks on made-up addresses")
+    p = B.problem(n, d, v)
+    with pytest.raises(B.LceError) as e:
+        B.lce_forward_noalloc(p, 0, 0, 0, 0, 0, 0, 0, 0)
+    assert (e.value.code == B.LCE_ERR_WORKSPACE) == (B.lce_workspace_size(p)[0] > B.LCE_NOALLOC_SCRATCH_BYTES)
+
+
+@pytest.mark.parametrize("n,d,v", [(70000, 1000, 128256), (15616, 8192, 24960), (140000, 72, 100000), (65536, 1024, 152064)])
+def test_a_forward_that_fits_the_fixed_array_in_the_least_form_reports_that_form(n, d, v):
+    info = B.lce_plan_info(B.problem(n, d, v))
+    vt3 = cdiv(v, 384)
+    assert info["part_rows"] == (49 if d % 64 or vt3 > d // 4 else vt3)
+    assert info["fwd_bytes"] <= B.LCE_NOALLOC_SCRATCH_BYTES
+    assert info["o_pm"] + 2 * 4 * 2 * vt3 * info["npad"] > B.LCE_NOALLOC_SCRATCH_BYTES or not info["fwd_one_launch"]

@@ -84,3 +84,37 @@ def test_the_largest_workspace_the_array_holds():
     for x, y in zip(a, b):
         assert torch.equal(x.view(torch.int32), y.view(torch.int32))
     assert int(a[2].item()) == n - n // 4
+
+
+@pytest.mark.parametrize("n,d,v,nv", [(15616, 8192, 24960, 1200), (140000, 72, 100000, 1400)])
+def test_problems_the_array_holds_in_the_least_form_only(n, d, v, nv):
+    # a launch that would cut its last tiles (328 live tiles) and one of 261 rows, were there more space: both
+    # calls take the same form, so the same bits, and the double-precision values to fp32 rounding
+    import torch
+    from paper_2605_21442_amd import binding as B
+    print(f"case noalloc least {n}x{d}x{v} nv={nv}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(6)
+    h = torch.randn(n, d, device="cuda:0", generator=g).to(torch.bfloat16)
+    w = (0.1 * torch.randn(v, d, device="cuda:0", generator=g)).to(torch.bfloat16)
+    t = torch.full((n,), -100, device="cuda:0", dtype=torch.int32)
+    rows = torch.randperm(n, device="cuda:0", generator=g)[:nv].sort().values
+    t[rows] = torch.randint(0, v, (nv,), device="cuda:0", generator=g, dtype=torch.int32)
+    p = B.problem(n, d, v)
+    fb, _ = B.lce_workspace_size(p)
+    assert fb <= B.LCE_NOALLOC_SCRATCH_BYTES
+    s = torch.cuda.current_stream().cuda_stream
+    a, b = _outs(n, h.device), _outs(n, h.device)
+    B.lce_forward_noalloc(p, h.data_ptr(), w.data_ptr(), t.data_ptr(), *[x.data_ptr() for x in a], s)
+    size = fb + (64 << 20)                 # more than is asked for changes nothing
+    ws = torch.empty(size, dtype=torch.uint8, device=h.device)
+    B.lce_forward(p, h.data_ptr(), w.data_ptr(), t.data_ptr(), *[x.data_ptr() for x in b], ws.data_ptr(), size, s)
+    torch.cuda.synchronize()
+    for x, y in zip(a, b):
+        assert torch.equal(x.view(torch.int32), y.view(torch.int32))
+    x = h[rows].double()
+    lse = torch.full((nv,), -float("inf"), device="cuda:0", dtype=torch.float64)
+    for v0 in range(0, v, 8192):
+        lse = torch.logaddexp(lse, torch.logsumexp(x @ w[v0:v0 + 8192].double().T, 1))
+    loss = (lse - (x * w[t[rows].long()].double()).sum(1)).mean()
+    assert torch.max(torch.abs(a[1][rows].double() - lse)) <= 1e-5 * torch.max(torch.abs(lse))
+    assert abs(float(a[0]) - float(loss)) <= 2e-5 * float(torch.max(torch.abs(lse)))
