@@ -125,10 +125,10 @@ typedef struct lce_adamw {
  * workgroup rounds, another multiple of 768 between max(8192, 4*D) and
  * min(24576, 160 MiB / (2*D)) (lce_plan_info reports the width): never O(N*V).
  * Calls of few tokens (a slab of that width times the tokens is at most 1024 tiles of
- * 384 x 256) take the fewest equal slabs that keep the [N, V_slab] bf16 block within 1.25 GiB.
- * The backward's size does not depend on V; the forward's vocabulary partials
- * take at most max(2*D, 4096) bytes per token, and up to 8 MiB more. Either output
- * pointer may be NULL.
+ * 384 x 256) take the fewest equal slabs that keep the [N, V_slab] bf16 block within 512 MiB:
+ * it may then hold all V ids, where 2 N V is no more than that. The backward's size thus
+ * has a bound that does not depend on V; the forward's vocabulary partials take at most
+ * max(2*D, 4096) bytes per token, and up to 8 MiB more. Either output pointer may be NULL.
  *
  * A smaller forward workspace, as callers may hold from an earlier version of this library,
  * is served as long as the least form of the forward fits it (groups of 24 vocabulary tiles,
@@ -334,9 +334,9 @@ lce_status_t lce_backward_shard(const lce_problem_t* p, const lce_shard_t* shard
  *   L   = mean / sum over M, or the per-token l_n (0 outside M), as for lce_forward
  *   G   = c (softmax(zs) - p_t) / T,  dHs = G Ws,  dWs = G^T Hs     (no teacher gradient)
  * Labels only define the valid set M (as for LCE: not ignore_index and in [0, V)). The loss
- * is not multiplied by T^2; neither logit matrix is ever held whole (the teacher's
- * logits or probabilities exist one vocabulary slab at a time, in the workspace; a call of few
- * tokens, whose slab values fit 1.25 GiB, may take the whole vocabulary as one slab). The MFMA work
+ * is not multiplied by T^2. The student's logits are never held, and the teacher's logits or
+ * probabilities one vocabulary slab at a time, in the workspace (of a call of few tokens, up to
+ * 512 MiB of them: all V ids where 4 N V is no more than that). The MFMA work
  * is 2 Nv V (Dt + Ds) for the forward and 2 Nv V Dt + 6 Nv V Ds for the backward.
  */
 typedef struct lce_kd_problem {

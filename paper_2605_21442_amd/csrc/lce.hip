@@ -2170,18 +2170,21 @@ int64_t whole_round_slab(int64_t v, int64_t d, int64_t vc) {
 // Few tokens: at the width vc chosen above a slab's G launch is then only a few workgroup rounds, of
 // which the last, partial one costs most of a round, and every slab pays its launches and a pass over
 // the fp32 dH accumulators. When a slab has at most 1024 tiles of 384 ids x 256 tokens (4 rounds of 256
-// CUs), the vocabulary is cut into as few equal slabs as keep G within kFewTokenG: one, up to 4096
-// tokens of a 158208-id vocabulary. Measured, one slab against the rule's (us per step):
-//   2048 x 4096 x 128256 (7 slabs of 48 x 6 live tiles): G 1911 -> 1323, step 7130 -> 6650;
-//   1948 x 3584 x 152064 (8 slabs): G 1793 -> 1380, step 6700 -> 6280;
-//   4096 x 4096 x 128256 (7 slabs of 48 x 12): G 2950 -> 2490, step 10310 -> 9990;
-//   4096 x 2048 x 128256 (6 slabs of 64 x 12, whole rounds): G 1340 -> 1307, step 5370 -> 5300.
+// CUs), the vocabulary is cut into as few equal slabs as keep G within kFewTokenG, whatever V: one
+// where [N, V] itself is that small, 1984 tokens of a 131072-id vocabulary. Measured, the rule's slabs, these,
+// and as few as 1280 MiB allow (a matrix as large as the bf16 logits; us per step and backward workspace):
+//   2048 x 4096 x 128256:        5490 us  313 MiB, 5200 us  516 MiB, 5180 us  796 MiB;
+//   1948 x 3584 x 152064:        5515 us  326 MiB, 5225 us  569 MiB, 5150 us  903 MiB;
+//   4096 x 4096 x 128256:       10060 us  379 MiB, 9900 us  577 MiB, 9800 us 1263 MiB;
+//   4096 x 2048 x 128256:        5270 us  412 MiB, 5295 us  561 MiB, 5185 us 1247 MiB;
+//   2048 x (4096 -> 2048) x 128256: 7000 us  318 MiB, 6290 us  693 MiB, 5810 us 1734 MiB;
+//   4096 x (4096 -> 2048) x 128256: 12600 us  537 MiB, 11900 us  864 MiB, 11140 us 1774 MiB.
 // Above 1024 tiles a partial round is a small share (8192 x 2048 x 128256: 8 rounds) and the memory
 // stays with the rule.
 // The distillation calls, whose teacher values take 4 bytes per slab id and token, keep those within
 // the same bytes.
 constexpr int64_t kFewTokenTiles = 1024;
-constexpr int64_t kFewTokenG = (int64_t)1280 << 20;
+constexpr int64_t kFewTokenG = (int64_t)512 << 20;
 int64_t few_token_slab(int64_t v, int64_t npad, int64_t vc, int64_t elem_bytes) {
   if (vc / 384 * (npad / TILE) > kFewTokenTiles) return vc;
   int64_t cap = kFewTokenG / (elem_bytes * round_up(npad, 384)) / 768 * 768;
@@ -2255,7 +2258,7 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   // probabilities take 4 bytes per slab id and token). A multiple of 16 tiles of 384 ids, so that
   // the dW launch of a 4096-wide head is whole rounds of workgroups on 256 CUs; for other widths
   // whole_round_slab picks the width whose dW launches leave the fewest idle CUs. Calls of few
-  // tokens take wider slabs, up to the whole vocabulary (few_token_slab).
+  // tokens take wider slabs, within a fixed number of bytes (few_token_slab).
   int64_t vc = 4 * p->d;
   if (wide_slabs) vc = std::max<int64_t>(vc, std::min<int64_t>(24576, kGroupBytes / (2 * p->d) / 6144 * 6144));
   if (vc < 8192) vc = 8192;

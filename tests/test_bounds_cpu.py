@@ -319,9 +319,11 @@ def dw_rounds(v, d, r):
 @pytest.mark.parametrize("d,v", [(512, 4096), (2048, 128256), (4096, 128256), (3584, 152064), (8192, 128256),
                                  (2560, 151936), (1536, 151936), (5120, 152064), (3584, 1000)])
 def test_the_slab_width_gives_the_dw_launches_the_fewest_rounds_in_its_range(d, v):
-    info = B.lce_plan_info(B.problem(4096, d, v))
+    # (more tokens than the few-token rule takes, so that the rule on rounds is the one that acts)
+    info = B.lce_plan_info(B.problem(32768, d, v))
     vc = info["vc"]
     assert vc % 768 == 0 and info["nslab"] == cdiv(v, vc)
+    assert (info["nslab"] > 1) == (v > 8192)
     lo = max(8192, 4 * d)
     hi = min(rup(v, 768), max(vc, min(24576, (160 << 20) // (2 * d))))
     if vc >= rup(v, 768):
@@ -376,9 +378,9 @@ def test_forward_and_g_blocks_cover_every_tile_once_and_keep_w_tiles_on_one_xcd(
             assert tn % 8 == b % 8          # and its own token tiles of the last few vocabulary tiles
 
 
-@pytest.mark.parametrize("n,d,v,nslab", [(2048, 4096, 128256, 1), (1948, 3584, 152064, 1), (4096, 8192, 128256, 4),
-                                         (4096, 1024, 152064, 1), (4096, 1024, 170000, 2), (4000, 256, 1000001, 7),
-                                         (1, 64, 6000000, 4), (8192, 2048, 128256, 6), (16384, 4096, 128256, 7)])
+@pytest.mark.parametrize("n,d,v,nslab", [(2048, 4096, 128256, 2), (1948, 3584, 152064, 2), (4096, 8192, 128256, 4),
+                                         (4096, 1024, 152064, 3), (1024, 1024, 170000, 1), (4000, 256, 1000001, 16),
+                                         (1, 64, 6000000, 9), (8192, 2048, 128256, 6), (16384, 4096, 128256, 7)])
 def test_few_token_calls_take_the_fewest_equal_slabs_within_the_budget(n, d, v, nslab):
     info = B.lce_plan_info(B.problem(n, d, v))
     vc = info["vc"]
@@ -387,11 +389,11 @@ def test_few_token_calls_take_the_fewest_equal_slabs_within_the_budget(n, d, v, 
     if rule // 384 * (info["npad"] // 256) > 1024:      # many tokens: the width of the rule (or near it: whole rounds)
         assert vc <= max(rule, 24576)
         return
-    assert 2 * info["rows_g"] * vc <= 1280 << 20
+    assert 2 * info["rows_g"] * vc <= 512 << 20
     assert vc - cdiv(v, nslab) < 768                    # equal slabs
     if nslab > 1:                                       # and one slab fewer would not fit G or a token tile's offsets
         w = rup(cdiv(v, nslab - 1), 768)
-        assert 2 * info["rows_g"] * w > 1280 << 20 or 512 * w > 2 ** 31 - 1
+        assert 2 * info["rows_g"] * w > 512 << 20 or 512 * w > 2 ** 31 - 1
     for nv in (1, n):
         e, sizes, _ = walk(n, d, v, nv)
         e.check(sizes, f"n={n} d={d} v={v} nv={nv}")
@@ -546,3 +548,17 @@ def test_a_forward_that_fits_the_fixed_array_in_the_least_form_reports_that_form
     assert info["part_rows"] == (49 if d % 64 or vt3 > d // 4 else vt3)
     assert info["fwd_bytes"] <= B.LCE_NOALLOC_SCRATCH_BYTES
     assert info["o_pm"] + 2 * 4 * 2 * vt3 * info["npad"] > B.LCE_NOALLOC_SCRATCH_BYTES or not info["fwd_one_launch"]
+
+
+@pytest.mark.parametrize("d", [8, 72, 1024, 2048, 4096, 8192])
+def test_the_gradient_block_and_the_teacher_block_have_a_bound_that_v_does_not_move(d):
+    # the rule's slab (max(8192, 4 D), or up to 24576 ids) of every token, or 512 MiB where that is more: never
+    # a share of N V that grows with V. The distillation's block is 4 bytes per id and token
+    for n in (1, 700, 2048, 4096, 5000, 16384):
+        info = B.lce_plan_info(B.problem(n, d, 152064))
+        for v in (152064, 400000, 6000000):
+            g = 2 * info["rows_g"] * B.lce_plan_info(B.problem(n, d, v))["vc"]
+            assert g <= max(2 * info["rows_g"] * max(30720, rup(4 * d, 6144)), 512 << 20), (n, d, v)
+            kd = B.lce_kd_workspace_size(B.kd_problem(n, d, 64, v))[1]
+            rest = info["o_hv"] + 2 * info["npad"] * (d + 64) + 4 * info["rows_g"] * d * 8 + 4096
+            assert kd <= rest + max(6 * info["rows_g"] * rup(max(8192, 4 * d), 6144), 768 << 20), (n, d, v)
