@@ -1381,7 +1381,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_kd_tile(const uint16_t* __r
                                                        const int* __restrict__ n_norm, int reduction, int d, int tm_count,
                                                        uint16_t* __restrict__ G, int vc, int ldt,
                                                        float scale2, float inv_t, float* __restrict__ P,
-                                                       float* __restrict__ qpart, int64_t qrow, int gsub) {
+                                                       float* __restrict__ qpart, int gsub) {
   // 12 waves (WM = 3, 384 ids per tile) serve the teacher when Dt % 64 == 0; the student and other
   // teachers keep 8 waves (and the student's G the LDS-staged epilogue below)
   static_assert(WM == 2 || kMode == P_WRITE || kMode == Z_WRITE, "");
@@ -1546,7 +1546,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_kd_tile(const uint16_t* __r
       float mt = red[t], st = red[TILE + t], q = red[2 * TILE + t], ms = red[3 * TILE + t], ss = red[4 * TILE + t];
       merge_weighted(mt, st, q, b[t], b[TILE + t], b[2 * TILE + t]);
       merge_pair(ms, ss, b[3 * TILE + t], b[4 * TILE + t]);
-      float* o = qpart + (qrow + tm) * kKdVals * ldt + n0 + t;
+      float* o = qpart + (int64_t)tm * kKdVals * ldt + n0 + t;
       o[0] = mt;
       o[ldt] = st;
       o[2 * (int64_t)ldt] = q;
@@ -2026,14 +2026,17 @@ __global__ __launch_bounds__(256) void k_adamw(int64_t v, int d, const uint16_t*
   }
 }
 
-// KD: per valid token, the tiles' values (KD_STATS) merged into both log-sum-exps and the loss l = lse_s -
-// sum_v p_t(v) zs(v); terms (compact order) feed the mean / sum, per_token (row order) is the "none"
-// output. A workgroup of 16 waves serves 16 tokens: a wave's four groups of 16 lanes fold every 64th tile
+// KD: per valid token, the values of a slab's tiles (KD_STATS) merged, after those of the slabs before (run:
+// one row of values per token, written unless this is the last slab), and behind the last slab turned into
+// both log-sum-exps and the loss l = lse_s - sum_v p_t(v) zs(v); terms (compact order) feed the mean / sum,
+// per_token (row order) is the "none" output. So the values of one slab's tiles are held at a time, 20 bytes
+// per 256 ids and token. A workgroup of 16 waves serves 16 tokens: a wave's four groups of 16 lanes fold every 64th tile
 // (64-byte reads along the tokens), then the groups and the waves are merged in a fixed order. (One
 // thread per token and a serial fold left most CUs idle: 4096 tokens, 501 tiles: 417 us, now 31.)
 constexpr int kKdTok = 16;
 
 __global__ __launch_bounds__(1024) void k_kd_combine(const float* __restrict__ part, int tiles, int64_t ldp,
+                                                     float* __restrict__ run, int first, int last,
                                                      const int* __restrict__ idx, const int* __restrict__ nv_ptr,
                                                      float* __restrict__ lse_s, float* __restrict__ lse_t,
                                                      float* __restrict__ terms, float* __restrict__ per_token) {
@@ -2042,6 +2045,13 @@ __global__ __launch_bounds__(1024) void k_kd_combine(const float* __restrict__ p
   const int i = blockIdx.x * kKdTok + t, nv = *nv_ptr;
   if ((int)blockIdx.x * kKdTok >= nv) return;
   float mt = -INFINITY, st = 0.f, q = 0.f, ms = -INFINITY, ss = 0.f;
+  if (!first && wave == 0 && lane < kKdTok && i < nv) {
+    mt = run[i];
+    st = run[ldp + i];
+    q = run[2 * ldp + i];
+    ms = run[3 * ldp + i];
+    ss = run[4 * ldp + i];
+  }
   if (i < nv)
     for (int k = 4 * wave + (lane >> 4); k < tiles; k += 64) {
       const float* p = part + (int64_t)k * kKdVals * ldp + i;
@@ -2064,6 +2074,14 @@ __global__ __launch_bounds__(1024) void k_kd_combine(const float* __restrict__ p
   for (int w = 1; w < 16; ++w) {
     merge_weighted(mt, st, q, red[0][w][t], red[1][w][t], red[2][w][t]);
     merge_pair(ms, ss, red[3][w][t], red[4][w][t]);
+  }
+  if (!last) {   // (the thread that reads a token's running values is the one that writes them)
+    run[i] = mt;
+    run[ldp + i] = st;
+    run[2 * ldp + i] = q;
+    run[3 * ldp + i] = ms;
+    run[4 * ldp + i] = ss;
+    return;
   }
   const int row = idx[i];
   const float ls = (ms + log2f(ss)) * kLn2;
@@ -2501,7 +2519,7 @@ void launch_teacher(Launcher& L, int kind, const KdArgs& kd, const uint16_t* hvt
   L(kind, hvt ? k_kd_tile<kMode, 3> : k_kd_tile<kMode, 2>, dim3(to.grid), dim3(256 * wm), kd.wt, kd.ldwt, v0, vs,
     hvt ? hvt : kd.ht, hvt ? (int64_t)kd.dt : kd.ldht, pl.n, idx, nv, kd.lse_t,
     (const float*)nullptr, (const int*)nullptr, (int)LCE_REDUCE_MEAN, kd.dt, tm, (uint16_t*)nullptr, (int)pl.vc,
-    (int)pl.npad, kd.scale2, kd.inv_t, P, (float*)nullptr, (int64_t)0, to.gw);
+    (int)pl.npad, kd.scale2, kd.inv_t, P, (float*)nullptr, to.gw);
 }
 
 inline size_t kd_p_bytes(const Plan& pl) { return (size_t)4 * pl.vc * pl.npad; }
@@ -2602,8 +2620,7 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
       const TileOrder to = tile_order(tm, pl.nt_max, student_group(tm, pl.d));
       L(K_BWD_G, k_kd_tile<G_SOFT, 2>, dim3(to.grid), dim3(NTHREADS), w, pl.ldw, v0, vs, h,
         pl.ldh, pl.n, (const int*)idx, (const int*)nv, lse, grad_loss,
-        (const int*)n_valid, p->reduction, d, tm, g, vc, npad, kd->scale2, kd->inv_t, P, (float*)nullptr,
-        (int64_t)0, to.gw);
+        (const int*)n_valid, p->reduction, d, tm, g, vc, npad, kd->scale2, kd->inv_t, P, (float*)nullptr, to.gw);
     } else {
       const int tmg = (vs + Geo<3>::TM - 1) / Geo<3>::TM;
       const TileOrder to = tile_order(tmg, pl.nt_max, group_tiles(tmg, Geo<3>::TM, d), true);
@@ -2644,10 +2661,11 @@ struct KdPlan {
   lce_problem_t ps, pt;   // student and teacher heads as LCE problems
   Plan s, t;
   float scale2, inv_t;
-  // the forward's regions: the student's valid-row list, then the tiles' values and the teacher's logits
-  // and gathered rows (where the backward keeps its probabilities and gathered rows in the fused call)
+  // the forward's regions: the student's valid-row list, then the values of a slab's tiles and the running
+  // ones, the per-row terms and the teacher's logits and gathered rows. (In the fused call these two lie where
+  // the backward keeps its probabilities and gathered rows, the values in G and the terms in the dH
+  // accumulators, which the backward writes after the forward has read them.)
   size_t o_q, o_terms, o_p, o_hvt, fwd_bytes, bwd_bytes;
-  size_t f_q, f_terms, fused_bytes;
 };
 
 lce_status_t make_kd_plan(const lce_kd_problem_t* p, KdPlan* k) {
@@ -2664,7 +2682,8 @@ lce_status_t make_kd_plan(const lce_kd_problem_t* p, KdPlan* k) {
   k->scale2 = (float)(1.4426950408889634 / (double)p->temperature);
   k->inv_t = (float)(1.0 / (double)p->temperature);
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-  const size_t q_bytes = up((size_t)4 * kKdVals * k->s.vt_count * k->s.npad), t_bytes = up(4 * (size_t)k->s.npad);
+  const size_t q_rows = (std::min(k->s.vc, k->s.v) + TILE - 1) / TILE + (k->s.nslab > 1 ? 1 : 0);
+  const size_t q_bytes = up(4 * kKdVals * q_rows * k->s.npad), t_bytes = up(4 * (size_t)k->s.npad);
   const size_t p_bytes = up(kd_p_bytes(k->s)), hvt_bytes = kd_hvt_bytes(k->s, k->t.d);
   size_t cur = up(k->s.o_hv);   // after idx, pos and Nv
   k->o_q = cur;
@@ -2673,14 +2692,11 @@ lce_status_t make_kd_plan(const lce_kd_problem_t* p, KdPlan* k) {
   k->o_hvt = k->o_p + p_bytes;
   k->fwd_bytes = k->o_hvt + hvt_bytes;
   k->bwd_bytes = k->s.bwd_bytes + kd_p_bytes(k->s) + hvt_bytes;
-  k->f_q = up(k->bwd_bytes);
-  k->f_terms = k->f_q + q_bytes;
-  k->fused_bytes = k->f_terms + t_bytes;
   return LCE_OK;
 }
 
 // The KD forward: both heads' log-sum-exps and the loss. Per slab, one teacher pass (its logits into P)
-// and one student pass (KD_STATS), then one merge of all tiles' values.
+// and one student pass (KD_STATS), then a merge of its tiles' values.
 lce_status_t kd_forward_launches(Launcher& L, const lce_kd_problem_t* p, const KdPlan& k, const KdArgs& kd,
                                  const uint16_t* hs, const uint16_t* wsm, const void* targets, float* loss,
                                  float* lse_s, float* lse_t, int32_t* n_valid, int32_t* dev_status, char* ws,
@@ -2706,10 +2722,11 @@ lce_status_t kd_forward_launches(Launcher& L, const lce_kd_problem_t* p, const K
     L(K_KD_STATS, k_kd_tile<KD_STATS, 2>, dim3(to.grid), dim3(NTHREADS), wsm, pl.ldw, v0, vs, hs, pl.ldh,
       pl.n, (const int*)idx, (const int*)nv, (const float*)nullptr,
       (const float*)nullptr, (const int*)nullptr, p->reduction, (int)pl.d, tm, (uint16_t*)nullptr, (int)pl.vc,
-      npad, k.scale2, k.inv_t, P, qpart, v0 / TILE, to.gw);
+      npad, k.scale2, k.inv_t, P, qpart, to.gw);
+    L(K_KD_COMBINE, k_kd_combine, dim3((unsigned)((pl.n + kKdTok - 1) / kKdTok)), dim3(1024), (const float*)qpart,
+      tm, (int64_t)npad, qpart + (int64_t)(pl.vc / TILE) * kKdVals * npad, (int)(s == 0), (int)(s + 1 == pl.nslab),
+      (const int*)idx, (const int*)nv, lse_s, lse_t, terms, none ? loss : (float*)nullptr);
   }
-  L(K_KD_COMBINE, k_kd_combine, dim3((unsigned)((pl.n + kKdTok - 1) / kKdTok)), dim3(1024), (const float*)qpart,
-    pl.vt_count, (int64_t)npad, (const int*)idx, (const int*)nv, lse_s, lse_t, terms, none ? loss : (float*)nullptr);
   if (!none) L(K_LOSS, k_loss, dim3(1), dim3(1024), (const float*)terms, (const int*)nv, p->reduction, loss);
   return L.st;
 }
@@ -2732,7 +2749,7 @@ lce_status_t kd_fused_impl(const lce_kd_problem_t* p, const void* Hs, const void
   if (pl.n > 0 && (!aligned16(Hs) || !aligned16(Ws) || !aligned16(Ht) || !aligned16(Wt) || !aligned16(dHs) ||
                    ((uintptr_t)workspace & 255) != 0))
     return LCE_ERR_ALIGN;
-  if (pl.n > 0 && workspace_bytes < k.fused_bytes) return LCE_ERR_WORKSPACE;
+  if (pl.n > 0 && workspace_bytes < k.bwd_bytes) return LCE_ERR_WORKSPACE;
   const bool none = p->reduction == LCE_REDUCE_NONE;
   if (pl.n == 0) {
     Launcher L{(hipStream_t)stream};
@@ -2744,7 +2761,7 @@ lce_status_t kd_fused_impl(const lce_kd_problem_t* p, const void* Hs, const void
   Launcher L{(hipStream_t)stream};
   const KdArgs kd{(const uint16_t*)Ht, k.t.ldh, (const uint16_t*)Wt, k.t.ldw, (int)k.t.d, lse_t, k.scale2, k.inv_t, true};
   st = kd_forward_launches(L, p, k, kd, (const uint16_t*)Hs, (const uint16_t*)Ws, targets, loss, lse_s, lse_t, n_valid,
-                           dev_status, (char*)workspace, k.f_q, k.f_terms, pl.bwd_bytes, pl.bwd_bytes + kd_p_bytes(pl));
+                           dev_status, (char*)workspace, pl.o_g, pl.o_dh32, pl.bwd_bytes, pl.bwd_bytes + kd_p_bytes(pl));
   if (st != LCE_OK) return st;
   return backward_impl(&k.ps, nullptr, Hs, Ws, targets, lse_s, n_valid, grad_loss, dHs, nullptr, (uint16_t*)dWs,
                        nullptr, nullptr, workspace, workspace_bytes, stream, &kd);
@@ -3015,7 +3032,7 @@ lce_status_t lce_kd_workspace_size_fused(const lce_kd_problem_t* p, size_t* byte
   KdPlan k;
   lce_status_t st = make_kd_plan(p, &k);
   if (st != LCE_OK) return st;
-  if (bytes) *bytes = k.fused_bytes;
+  if (bytes) *bytes = k.bwd_bytes;
   return LCE_OK;
 }
 

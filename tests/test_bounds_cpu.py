@@ -561,4 +561,9 @@ def test_the_gradient_block_and_the_teacher_block_have_a_bound_that_v_does_not_m
             assert g <= max(2 * info["rows_g"] * max(30720, rup(4 * d, 6144)), 512 << 20), (n, d, v)
             kd = B.lce_kd_workspace_size(B.kd_problem(n, d, 64, v))[1]
             rest = info["o_hv"] + 2 * info["npad"] * (d + 64) + 4 * info["rows_g"] * d * 8 + 4096
-            assert kd <= rest + max(6 * info["rows_g"] * rup(max(8192, 4 * d), 6144), 768 << 20), (n, d, v)
+            block = max(6 * info["rows_g"] * rup(max(8192, 4 * d), 6144), 768 << 20)
+            assert kd <= rest + block, (n, d, v)
+            # the forward: the teacher's block and 20 bytes per 256 of its ids and token, plus a running row
+            kf = B.lce_kd_workspace_size(B.kd_problem(n, d, 64, v))[0]
+            assert kf <= info["o_hv"] + info["npad"] * (128 + 44) + 4096 + block * 2 // 3 * 65 // 64, (n, d, v)
+            assert B.lce_kd_workspace_size_fused(B.kd_problem(n, d, 64, v)) <= rest + block, (n, d, v)
