@@ -57,7 +57,7 @@ typedef enum lce_status {
   LCE_ERR_SHAPE = 2,        /* n < 0, d < 1, v < 1, ld < d, or sizes beyond 32-bit offsets */
   LCE_ERR_ALIGN = 3,        /* pointer, stride or workspace misaligned */
   LCE_ERR_UNSUPPORTED = 4,  /* d % 8 != 0, unknown reduction or target width */
-  LCE_ERR_WORKSPACE = 5,    /* workspace too small (lce_workspace_size()) */
+  LCE_ERR_WORKSPACE = 5,    /* workspace smaller than lce_workspace_size_least() */
   LCE_ERR_HIP = 6,          /* a HIP runtime call or kernel launch failed */
   LCE_ERR_ARG = 7           /* other invalid argument */
 } lce_status_t;
@@ -96,8 +96,8 @@ typedef struct lce_problem {
  * workspace in between. The backward then reuses that call's valid-row list and gathered valid
  * rows of H instead of forming them again: two fewer kernels
  * per step. Without the flag the backward depends on no earlier call. The forward and the
- * combine ignore the flag; the KD calls reject it (LCE_ERR_ARG). The workspace must be at
- * least max(fwd_bytes, bwd_bytes). */
+ * combine ignore the flag; the KD calls reject it (LCE_ERR_ARG). The workspace must hold
+ * both calls' bytes (it is one buffer). */
 #define LCE_FLAG_REUSE_FORWARD 2
 
 /*
@@ -130,13 +130,16 @@ typedef struct lce_adamw {
  * has a bound that does not depend on V; the forward's vocabulary partials take at most
  * max(2*D, 4096) bytes per token, and up to 8 MiB more. Either output pointer may be NULL.
  *
- * A smaller forward workspace, as callers may hold from an earlier version of this library,
- * is served as long as the least form of the forward fits it (groups of 24 vocabulary tiles,
- * a launch each, or the one launch without the 8 MiB); a still smaller one is
- * LCE_ERR_WORKSPACE. That form adds the same terms in another order: its lse and loss may
- * differ in their last bits from those of a workspace of the reported size.
+ * lce_workspace_size_least gives the least bytes a call runs in, for callers short of
+ * memory: a workspace that is smaller than the sizes above but holds these is served in the
+ * least form, which is slower. Its forward takes vocabulary tiles in groups of 24, a launch
+ * each, or one launch without the 8 MiB; its backward keeps slabs of the width V_slab for
+ * few tokens too, and at most half as many dH accumulators. The least bytes never exceed what an
+ * earlier version of this library asked for. The least form adds the same terms in another
+ * order: lse, loss and gradients may differ in their last bits from those of the larger sizes.
  */
 lce_status_t lce_workspace_size(const lce_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes);
+lce_status_t lce_workspace_size_least(const lce_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes);
 
 /*
  * Layout of the workspace that lce_forward and lce_backward carve for problem p, for tests and
@@ -353,8 +356,11 @@ typedef struct lce_kd_problem {
 } lce_kd_problem_t;
 
 /* Workspace bytes of lce_kd_forward / lce_kd_backward: O(N (Ds + Dt) + N V_slab) with the
- * student's slab width, never O(N V). */
+ * student's slab width, or 512 MiB of teacher values where few tokens make that more; never O(N V).
+ * lce_kd_workspace_size_least is what the calls run in with the slabs of many tokens, as
+ * lce_workspace_size_least (its backward bytes serve lce_kd_forward_backward too). */
 lce_status_t lce_kd_workspace_size(const lce_kd_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes);
+lce_status_t lce_kd_workspace_size_least(const lce_kd_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes);
 
 /*
  * KD forward. Outputs (device): loss ([1], or [N] per token for LCE_REDUCE_NONE), lse_s and

@@ -51,6 +51,18 @@ def _stream(dev: torch.device) -> int:
     return torch.cuda.current_stream(dev).cuda_stream
 
 
+def _alloc_workspace(nbytes: int, least, dev: torch.device) -> torch.Tensor:
+    """A workspace of nbytes or, on a device that has no room for it, of the least bytes the calls run in
+    (``least()``): slower, and sums in another order, but nothing that fitted before fails for speed's sake."""
+    try:
+        return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=dev)
+    except torch.OutOfMemoryError:
+        small = max(least(), 1)
+        if small >= nbytes:
+            raise
+        return torch.empty(small, dtype=torch.uint8, device=dev)
+
+
 def forward(hidden: torch.Tensor, weight: torch.Tensor, targets: torch.Tensor,
             ignore_index: int = -100, reduction: str = "mean", keep_workspace: bool = False):
     """(loss, lse fp32 [N], n_valid int32 [1], status int32 [1]) computed by lce_forward; loss is
@@ -73,9 +85,10 @@ def forward(hidden: torch.Tensor, weight: torch.Tensor, targets: torch.Tensor,
     lse = torch.empty(n, dtype=torch.float32, device=dev)
     nv = torch.empty(1, dtype=torch.int32, device=dev)
     status = torch.empty(1, dtype=torch.int32, device=dev)
-    ws = torch.empty(max(fwd_bytes, bwd_bytes if keep_workspace else 0, 1), dtype=torch.uint8, device=dev)
+    ws = _alloc_workspace(max(fwd_bytes, bwd_bytes) if keep_workspace else fwd_bytes,
+                          lambda: max(B.lce_workspace_size_least(p)[:2 if keep_workspace else 1]), dev)
     B.lce_forward(p, h.data_ptr(), w.data_ptr(), t.data_ptr(), loss.data_ptr(), lse.data_ptr(),
-                  nv.data_ptr(), status.data_ptr(), ws.data_ptr(), fwd_bytes, _stream(dev))
+                  nv.data_ptr(), status.data_ptr(), ws.data_ptr(), ws.numel(), _stream(dev))
     if keep_workspace:
         return loss, lse, nv, status, ws
     return loss, lse, nv, status
@@ -97,11 +110,13 @@ def _backward_args(hidden, weight, targets, lse, grad_loss, ignore_index, reduct
     return p, h, w, t, grad_loss.contiguous()
 
 
-def _workspace(workspace, nbytes, dev):
-    """The caller's workspace (from ``forward(..., keep_workspace=True)``) or a new one."""
+def _workspace(workspace, p, dev):
+    """The caller's workspace (from ``forward(..., keep_workspace=True)``) or a new one for p's backward."""
+    nbytes = B.lce_workspace_size(p)[1]
     if workspace is None:
-        return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=dev)
-    if workspace.dtype != torch.uint8 or workspace.numel() < nbytes or not workspace.is_contiguous():
+        return _alloc_workspace(nbytes, lambda: B.lce_workspace_size_least(p)[1], dev)
+    if (workspace.dtype != torch.uint8 or not workspace.is_contiguous()
+            or (workspace.numel() < nbytes and workspace.numel() < B.lce_workspace_size_least(p)[1])):
         raise ValueError("workspace is not the one forward(..., keep_workspace=True) returned for this problem")
     return workspace
 
@@ -118,7 +133,6 @@ def backward(hidden: torch.Tensor, weight: torch.Tensor, targets: torch.Tensor, 
     if workspace is not None:
         flags |= B.LCE_FLAG_REUSE_FORWARD
     p, h, w, t, g = _backward_args(hidden, weight, targets, lse, grad_loss, ignore_index, reduction, flags)
-    _, bwd_bytes = B.lce_workspace_size(p)
     dev = h.device
     dh = torch.empty((p.n, p.d), dtype=torch.bfloat16, device=dev)
     if accumulate_into is None:
@@ -127,9 +141,9 @@ def backward(hidden: torch.Tensor, weight: torch.Tensor, targets: torch.Tensor, 
         dw = accumulate_into
         if dw.dtype != torch.bfloat16 or tuple(dw.shape) != (p.v, p.d) or not dw.is_contiguous():
             raise ValueError("accumulate_into must be a contiguous bf16 [V, D] tensor")
-    ws = _workspace(workspace, bwd_bytes, dev)
+    ws = _workspace(workspace, p, dev)
     B.lce_backward(p, h.data_ptr(), w.data_ptr(), t.data_ptr(), lse.data_ptr(), n_valid.data_ptr(),
-                   g.data_ptr(), dh.data_ptr(), dw.data_ptr(), ws.data_ptr(), bwd_bytes, _stream(dev))
+                   g.data_ptr(), dh.data_ptr(), dw.data_ptr(), ws.data_ptr(), ws.numel(), _stream(dev))
     return dh, dw
 
 
@@ -138,12 +152,11 @@ def _backward_one(hidden, weight, targets, lse, n_valid, grad_loss, ignore_index
     the bits of ``backward``."""
     flags = B.LCE_FLAG_REUSE_FORWARD if workspace is not None else 0
     p, h, w, t, g = _backward_args(hidden, weight, targets, lse, grad_loss, ignore_index, reduction, flags)
-    _, bwd_bytes = B.lce_workspace_size(p)
     out = torch.empty((p.n, p.d) if want_dh else (p.v, p.d), dtype=torch.bfloat16, device=h.device)
-    ws = _workspace(workspace, bwd_bytes, h.device)
+    ws = _workspace(workspace, p, h.device)
     B.lce_backward_select(p, h.data_ptr(), w.data_ptr(), t.data_ptr(), lse.data_ptr(), n_valid.data_ptr(),
                           g.data_ptr(), out.data_ptr() if want_dh else 0, 0 if want_dh else out.data_ptr(),
-                          ws.data_ptr(), bwd_bytes, _stream(h.device))
+                          ws.data_ptr(), ws.numel(), _stream(h.device))
     return out
 
 
@@ -214,13 +227,12 @@ def backward_adamw(hidden: torch.Tensor, targets: torch.Tensor, lse: torch.Tenso
     p, h, w, t, g = _backward_args(hidden, state.weight, targets, lse, grad_loss, ignore_index, reduction, flags)
     if w.data_ptr() != state.weight.data_ptr():
         raise ValueError("the weight must be usable in place")
-    _, bwd_bytes = B.lce_workspace_size(p)
     dev = h.device
     dh = torch.empty((p.n, p.d), dtype=torch.bfloat16, device=dev)
-    ws = _workspace(workspace, bwd_bytes, dev)
+    ws = _workspace(workspace, p, dev)
     B.lce_backward_adamw(p, h.data_ptr(), w.data_ptr(), t.data_ptr(), lse.data_ptr(), n_valid.data_ptr(),
                          g.data_ptr(), dh.data_ptr(), *state._ptrs(), state.next_opt(), ws.data_ptr(),
-                         bwd_bytes, _stream(dev))
+                         ws.numel(), _stream(dev))
     state.step += 1
     return dh
 
@@ -243,10 +255,10 @@ def forward_shard(hidden, weight_shard, targets, v_begin: int, v_total: int, ign
     tgt_part = torch.empty(n, dtype=torch.float32, device=dev)
     nv = torch.empty(1, dtype=torch.int32, device=dev)
     status = torch.empty(1, dtype=torch.int32, device=dev)
-    ws = torch.empty(max(fwd_bytes, 1), dtype=torch.uint8, device=dev)
+    ws = _alloc_workspace(fwd_bytes, lambda: B.lce_workspace_size_least(p)[0], dev)
     B.lce_forward_shard(p, B.LceShard(v_total, v_begin), h.data_ptr(), w.data_ptr(), t.data_ptr(),
                         lse_part.data_ptr(), tgt_part.data_ptr(), nv.data_ptr(), status.data_ptr(),
-                        ws.data_ptr(), fwd_bytes, _stream(dev))
+                        ws.data_ptr(), ws.numel(), _stream(dev))
     return lse_part, tgt_part, nv, status
 
 
@@ -265,9 +277,9 @@ def combine_shards(lse_parts: torch.Tensor, tgt_parts: torch.Tensor, targets: to
     lse = torch.empty(n, dtype=torch.float32, device=dev)
     nv = torch.empty(1, dtype=torch.int32, device=dev)
     status = torch.empty(1, dtype=torch.int32, device=dev)
-    ws = torch.empty(max(fwd_bytes, 1), dtype=torch.uint8, device=dev)
+    ws = _alloc_workspace(fwd_bytes, lambda: B.lce_workspace_size_least(p)[0], dev)
     B.lce_combine_shards(p, g, lse_parts.data_ptr(), tgt_parts.data_ptr(), t.data_ptr(), loss.data_ptr(),
-                         lse.data_ptr(), nv.data_ptr(), status.data_ptr(), ws.data_ptr(), fwd_bytes, _stream(dev))
+                         lse.data_ptr(), nv.data_ptr(), status.data_ptr(), ws.data_ptr(), ws.numel(), _stream(dev))
     return loss, lse, nv, status
 
 
@@ -276,14 +288,13 @@ def backward_shard(hidden, weight_shard, targets, lse, n_valid, grad_loss, v_beg
     """(dH term fp32 [N, D], dW rows bf16 [V_shard, D]) of one shard, given the global lse
     (lce_backward_shard); the dH terms of all shards sum to dH."""
     p, h, w, t, g = _backward_args(hidden, weight_shard, targets, lse, grad_loss, ignore_index, reduction)
-    _, bwd_bytes = B.lce_workspace_size(p)
     dev = h.device
     dh = torch.empty((p.n, p.d), dtype=torch.float32, device=dev)
     dw = torch.empty((p.v, p.d), dtype=torch.bfloat16, device=dev)
-    ws = torch.empty(max(bwd_bytes, 1), dtype=torch.uint8, device=dev)
+    ws = _workspace(None, p, dev)
     B.lce_backward_shard(p, B.LceShard(v_total, v_begin), h.data_ptr(), w.data_ptr(), t.data_ptr(),
                          lse.data_ptr(), n_valid.data_ptr(), g.data_ptr(), dh.data_ptr(), dw.data_ptr(),
-                         ws.data_ptr(), bwd_bytes, _stream(dev))
+                         ws.data_ptr(), ws.numel(), _stream(dev))
     return dh, dw
 
 
@@ -387,10 +398,10 @@ def kd_forward(hs, ws, ht, wt, targets, temperature: float = 1.0, ignore_index: 
     lse_t = torch.empty(n, dtype=torch.float32, device=dev)
     nv = torch.empty(1, dtype=torch.int32, device=dev)
     status = torch.empty(1, dtype=torch.int32, device=dev)
-    ws_ = torch.empty(max(fwd_bytes, 1), dtype=torch.uint8, device=dev)
+    ws_ = _alloc_workspace(fwd_bytes, lambda: B.lce_kd_workspace_size_least(p)[0], dev)
     B.lce_kd_forward(p, h_s.data_ptr(), w_s.data_ptr(), h_t.data_ptr(), w_t.data_ptr(), t.data_ptr(),
                      loss.data_ptr(), lse_s.data_ptr(), lse_t.data_ptr(), nv.data_ptr(), status.data_ptr(),
-                     ws_.data_ptr(), fwd_bytes, _stream(dev))
+                     ws_.data_ptr(), ws_.numel(), _stream(dev))
     return loss, lse_s, lse_t, nv, status
 
 
@@ -416,10 +427,10 @@ def kd_backward(hs, ws, ht, wt, targets, lse_s, lse_t, n_valid, grad_loss, tempe
         if dw.dtype != torch.bfloat16 or tuple(dw.shape) != (v, ds) or not dw.is_contiguous():
             raise ValueError("accumulate_into must be a contiguous bf16 [V, Ds] tensor")
     g = grad_loss.contiguous()
-    ws_ = torch.empty(max(bwd_bytes, 1), dtype=torch.uint8, device=dev)
+    ws_ = _alloc_workspace(bwd_bytes, lambda: B.lce_kd_workspace_size_least(p)[1], dev)
     B.lce_kd_backward(p, h_s.data_ptr(), w_s.data_ptr(), h_t.data_ptr(), w_t.data_ptr(), t.data_ptr(),
                       lse_s.data_ptr(), lse_t.data_ptr(), n_valid.data_ptr(), g.data_ptr(), dh.data_ptr(),
-                      dw.data_ptr(), ws_.data_ptr(), bwd_bytes, _stream(dev))
+                      dw.data_ptr(), ws_.data_ptr(), ws_.numel(), _stream(dev))
     return dh, dw
 
 
@@ -442,10 +453,10 @@ def kd_forward_backward(hs, ws, ht, wt, targets, grad_loss, temperature: float =
     status = torch.empty(1, dtype=torch.int32, device=dev)
     dh = torch.empty((n, ds), dtype=torch.bfloat16, device=dev)
     dw = torch.empty((v, ds), dtype=torch.bfloat16, device=dev)
-    ws_ = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=dev)
+    ws_ = _alloc_workspace(nbytes, lambda: B.lce_kd_workspace_size_least(p)[1], dev)
     B.lce_kd_forward_backward(p, h_s.data_ptr(), w_s.data_ptr(), h_t.data_ptr(), w_t.data_ptr(), t.data_ptr(),
                               g.data_ptr(), loss.data_ptr(), lse_s.data_ptr(), lse_t.data_ptr(), nv.data_ptr(),
-                              status.data_ptr(), dh.data_ptr(), dw.data_ptr(), ws_.data_ptr(), nbytes, _stream(dev))
+                              status.data_ptr(), dh.data_ptr(), dw.data_ptr(), ws_.data_ptr(), ws_.numel(), _stream(dev))
     return loss, lse_s, lse_t, nv, status, dh, dw
 
 

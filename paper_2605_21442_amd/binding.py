@@ -44,7 +44,8 @@ EXPORTED = ("lce_workspace_size", "lce_forward", "lce_backward", "lce_status_str
             "lce_timing_read", "lce_adamw_step", "lce_backward_adamw", "lce_forward_shard",
             "lce_combine_shards", "lce_backward_shard", "lce_kd_workspace_size", "lce_kd_forward",
             "lce_kd_backward", "lce_kd_workspace_size_fused", "lce_kd_forward_backward", "lce_plan_info",
-            "lce_forward_noalloc", "lce_backward_select")
+            "lce_forward_noalloc", "lce_backward_select", "lce_workspace_size_least",
+            "lce_kd_workspace_size_least")
 
 
 class LceError(RuntimeError):
@@ -121,6 +122,7 @@ def load() -> ctypes.CDLL:
         P = ctypes.POINTER(LceProblem)
         vp, sz = ctypes.c_void_p, ctypes.c_size_t
         lib.lce_workspace_size.argtypes = [P, ctypes.POINTER(sz), ctypes.POINTER(sz)]
+        lib.lce_workspace_size_least.argtypes = lib.lce_workspace_size.argtypes
         lib.lce_forward.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         lib.lce_backward.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         lib.lce_backward_select.argtypes = lib.lce_backward.argtypes
@@ -133,6 +135,7 @@ def load() -> ctypes.CDLL:
         lib.lce_backward_shard.argtypes = [P, S, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         KP = ctypes.POINTER(LceKdProblem)
         lib.lce_kd_workspace_size.argtypes = [KP, ctypes.POINTER(sz), ctypes.POINTER(sz)]
+        lib.lce_kd_workspace_size_least.argtypes = lib.lce_kd_workspace_size.argtypes
         lib.lce_kd_forward.argtypes = [KP, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         lib.lce_kd_backward.argtypes = [KP, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         lib.lce_kd_workspace_size_fused.argtypes = [KP, ctypes.POINTER(sz)]
@@ -151,7 +154,8 @@ def load() -> ctypes.CDLL:
                      "lce_timing_read", "lce_timing_kernel_count", "lce_adamw_step", "lce_backward_adamw",
                      "lce_forward_shard", "lce_combine_shards", "lce_backward_shard", "lce_kd_workspace_size",
                      "lce_kd_forward", "lce_kd_backward", "lce_kd_workspace_size_fused", "lce_kd_forward_backward",
-                     "lce_plan_info", "lce_forward_noalloc", "lce_backward_select"):
+                     "lce_plan_info", "lce_forward_noalloc", "lce_backward_select", "lce_workspace_size_least",
+                     "lce_kd_workspace_size_least"):
             getattr(lib, name).restype = ctypes.c_int
         _lib = lib
         return lib
@@ -170,6 +174,13 @@ def lce_workspace_size(p: LceProblem) -> tuple[int, int]:
     f, b = ctypes.c_size_t(0), ctypes.c_size_t(0)
     _check(load().lce_workspace_size(ctypes.byref(p), ctypes.byref(f), ctypes.byref(b)),
            "lce_workspace_size")
+    return f.value, b.value
+
+
+def lce_workspace_size_least(p: LceProblem) -> tuple[int, int]:
+    f, b = ctypes.c_size_t(0), ctypes.c_size_t(0)
+    _check(load().lce_workspace_size_least(ctypes.byref(p), ctypes.byref(f), ctypes.byref(b)),
+           "lce_workspace_size_least")
     return f.value, b.value
 
 
@@ -248,6 +259,13 @@ def lce_backward_shard(p: LceProblem, shard: LceShard, H: int, W: int, targets: 
 def lce_kd_workspace_size(p: LceKdProblem) -> tuple[int, int]:
     f, b = ctypes.c_size_t(0), ctypes.c_size_t(0)
     _check(load().lce_kd_workspace_size(ctypes.byref(p), ctypes.byref(f), ctypes.byref(b)), "lce_kd_workspace_size")
+    return f.value, b.value
+
+
+def lce_kd_workspace_size_least(p: LceKdProblem) -> tuple[int, int]:
+    f, b = ctypes.c_size_t(0), ctypes.c_size_t(0)
+    _check(load().lce_kd_workspace_size_least(ctypes.byref(p), ctypes.byref(f), ctypes.byref(b)),
+           "lce_kd_workspace_size_least")
     return f.value, b.value
 
 

@@ -2116,7 +2116,8 @@ struct Plan {
   int nt_max, vt_count, vt_count3;           // vt_count3: 384-id tiles
   int64_t vc, nslab;
   int64_t gw;                                // 384-id tiles of the forward's vocabulary groups
-  int rule_gw;                               // 384-id tiles of the slab rule's width (many tokens)
+  int64_t rule_vc;                           // the slab rule's width (many tokens)
+  int slab_elem;                             // bytes per id and token that few_token_slab keeps within its budget
   int64_t rows_g;                            // rows of G and dH32: Npad rounded up to a 384-row tile
   // workspace offsets; idx, pos, Nv and the gathered rows Hv form a prefix both passes share
   size_t o_idx, o_pos, o_nv, o_hv, o_pm, o_ps, o_terms, fwd_bytes;
@@ -2229,7 +2230,7 @@ void plan_forward(Plan* pl, bool least) {
   const bool few = least && (pl->d % KSLICE != 0 || vt > pl->d / 4);
   pl->one_launch = (few ? vt <= 24 : vt <= std::max<int64_t>(pl->d / 4, 512)) && tiles <= INT32_MAX;
   pl->split = !least && pl->one_launch && tiles <= 2 * kSplitTiles;
-  pl->fgw = few ? 24 : pl->rule_gw;
+  pl->fgw = few ? 24 : (int)(pl->rule_vc / 384);
   const int64_t rows = pl->one_launch || vt <= pl->fgw ? vt : 2 * (int64_t)pl->fgw + 1;
   // (not below two rows per 256 ids, up to 64: small heads then ask for the same bytes in either form)
   pl->part_rows = (int)std::max<int64_t>(pl->split ? 2 * rows : rows, few ? 0 : 2 * std::min(pl->vt_count, 32));
@@ -2247,6 +2248,35 @@ bool forward_fits(Plan* pl, size_t workspace_bytes) {
   if (pl->fwd_bytes > workspace_bytes) plan_forward(pl, true);
   return pl->fwd_bytes <= workspace_bytes;
 }
+
+// The backward's slabs, its dH launches and its regions after the prefix.
+//
+// least: the form in the least space, which needs no more than any version of this library has asked for: the
+// rule's slabs, and as many K parts as fill the CUs once with the tiles of all N tokens.
+void plan_backward(Plan* pl, bool least) {
+  const int64_t vround = round_up(pl->v, 768);
+  pl->vc = pl->rule_vc;
+  if (pl->vc < vround) pl->vc = few_token_slab(pl->v, pl->npad, pl->vc, pl->slab_elem);
+  if (least) pl->vc = std::min(pl->vc, pl->rule_vc);   // (as many equal slabs as the rule's may be narrower)
+  pl->nslab = (pl->v + pl->vc - 1) / pl->vc;
+  auto take = [](size_t& cur, size_t bytes) { size_t o = cur; cur += (bytes + 255) / 256 * 256; return o; };
+  size_t cur = pl->o_hv;
+  take(cur, 2 * (size_t)pl->d * pl->npad);
+  // G and the fp32 dH accumulators hold every row a 384-row dH tile can address (the tiles of
+  // the last token rows reach past Npad), so that no access leaves its region
+  pl->rows_g = round_up(pl->npad, 384);
+  pl->o_g = take(cur, 2 * (size_t)pl->rows_g * pl->vc);
+  // dH launches with fewer 384 x 256 output tiles than the 256 CUs split K into parts (at most 8), each
+  // accumulated in an accumulator of its own; the kernel takes as many as the live tiles (of Nv, not N,
+  // tokens) leave CUs for, so twice as many are reserved as the tiles of all N tokens would take
+  const int64_t dh_tiles = (pl->npad + 383) / 384 * ((pl->d + TILE - 1) / TILE), units = least ? 256 : 512;
+  pl->dh_kz = dh_tiles >= 256 ? 1 : (int)std::min<int64_t>(8, (units + dh_tiles - 1) / dh_tiles);
+  const size_t part = 4 * (size_t)pl->rows_g * pl->d;     // a multiple of 256 bytes
+  pl->o_dh32 = take(cur, part * pl->dh_kz);
+  pl->o_dh32b = pl->dh_kz > 1 ? pl->o_dh32 + part : 0;
+  pl->bwd_bytes = cur;
+}
+
 
 lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true) {
   if (!p) return LCE_ERR_NULL;
@@ -2288,10 +2318,8 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
   // leave the MALL)
   pl->gw = vc / 384;
   if (wide_slabs && vc < vround) vc = whole_round_slab(p->v, p->d, vc);
-  pl->rule_gw = (int)(vc / 384);
-  if (vc < vround) vc = few_token_slab(p->v, pl->npad, vc, wide_slabs ? 2 : 4);
-  pl->vc = vc;
-  pl->nslab = (p->v + vc - 1) / vc;
+  pl->rule_vc = vc;
+  pl->slab_elem = wide_slabs ? 2 : 4;
   if ((uint64_t)TILE * pl->npad * 2 > 0x7FFFFFFFull || (uint64_t)TILE * vc * 2 > 0x7FFFFFFFull) return LCE_ERR_SHAPE;
 
   auto take = [](size_t& cur, size_t bytes) { size_t o = cur; cur += (bytes + 255) / 256 * 256; return o; };
@@ -2309,19 +2337,7 @@ lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true)
     plan_forward(pl, true);
     if (pl->fwd_bytes > (size_t)LCE_NOALLOC_SCRATCH_BYTES) plan_forward(pl, false);
   }
-  // G and the fp32 dH accumulators hold every row a 384-row dH tile can address (the tiles of
-  // the last token rows reach past Npad), so that no access leaves its region
-  pl->rows_g = round_up(pl->npad, 384);
-  pl->o_g = take(cur, 2 * (size_t)pl->rows_g * vc);
-  // dH launches with fewer 384 x 256 output tiles than the 256 CUs split K into parts (at most 8), each
-  // accumulated in an accumulator of its own; the kernel takes as many as the live tiles (of Nv, not N,
-  // tokens) leave CUs for, so twice as many are reserved as the tiles of all N tokens would take
-  const int64_t dh_tiles = (pl->npad + 383) / 384 * ((p->d + TILE - 1) / TILE);
-  pl->dh_kz = dh_tiles >= 256 ? 1 : (int)std::min<int64_t>(8, (512 + dh_tiles - 1) / dh_tiles);
-  const size_t part = 4 * (size_t)pl->rows_g * p->d;     // a multiple of 256 bytes
-  pl->o_dh32 = take(cur, part * pl->dh_kz);
-  pl->o_dh32b = pl->dh_kz > 1 ? pl->o_dh32 + part : 0;
-  pl->bwd_bytes = cur;
+  plan_backward(pl, false);
   return LCE_OK;
 }
 
@@ -2556,8 +2572,13 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
   if (pl.n > 0 && (!H || !targets || !lse || (!dH_any && (want & WANT_DH)) || !workspace)) return LCE_ERR_NULL;
   if (!aligned16(W)) return LCE_ERR_ALIGN;
   if (pl.n > 0 && (!aligned16(H) || !aligned16(dH_any) || ((uintptr_t)workspace & 255) != 0)) return LCE_ERR_ALIGN;
-  const size_t need = pl.bwd_bytes + (kd ? kd_p_bytes(pl) + kd_hvt_bytes(pl, kd->dt) : 0);
-  if (pl.n > 0 && workspace_bytes < need) return LCE_ERR_WORKSPACE;
+  // (a workspace smaller than what is reported, as callers may hold from before the present slabs, is served in
+  // the least form)
+  auto need = [&] { return pl.bwd_bytes + (kd ? kd_p_bytes(pl) + kd_hvt_bytes(pl, kd->dt) : 0); };
+  if (pl.n > 0 && workspace_bytes < need()) {
+    plan_backward(&pl, true);
+    if (workspace_bytes < need()) return LCE_ERR_WORKSPACE;
+  }
   const bool accumulate = (p->flags & LCE_FLAG_ACCUMULATE_DW) != 0;
   const AdamWState as = adamw ? *adamw : AdamWState{nullptr, 0, nullptr, nullptr, nullptr};
   const AdamWConst c = oc ? *oc : AdamWConst{};
@@ -2668,7 +2689,7 @@ struct KdPlan {
   size_t o_q, o_terms, o_p, o_hvt, fwd_bytes, bwd_bytes;
 };
 
-lce_status_t make_kd_plan(const lce_kd_problem_t* p, KdPlan* k) {
+lce_status_t make_kd_plan(const lce_kd_problem_t* p, KdPlan* k, bool least = false) {
   if (!p) return LCE_ERR_NULL;
   if (p->reserved != 0) return LCE_ERR_ARG;
   if (!(p->temperature > 0.f && p->temperature < INFINITY)) return LCE_ERR_ARG;
@@ -2679,6 +2700,7 @@ lce_status_t make_kd_plan(const lce_kd_problem_t* p, KdPlan* k) {
   if (st != LCE_OK) return st;
   st = make_plan(&k->pt, &k->t, false);
   if (st != LCE_OK) return st;
+  if (least) plan_backward(&k->s, true);
   k->scale2 = (float)(1.4426950408889634 / (double)p->temperature);
   k->inv_t = (float)(1.0 / (double)p->temperature);
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
@@ -2740,6 +2762,7 @@ lce_status_t kd_fused_impl(const lce_kd_problem_t* p, const void* Hs, const void
                            void* workspace, size_t workspace_bytes, void* stream) {
   KdPlan k;
   lce_status_t st = make_kd_plan(p, &k);
+  if (st == LCE_OK && workspace_bytes < k.bwd_bytes) st = make_kd_plan(p, &k, true);   // (as backward_impl will)
   if (st != LCE_OK) return st;
   const Plan& pl = k.s;
   if (!loss || !n_valid || !grad_loss || !dWs) return LCE_ERR_NULL;
@@ -2773,6 +2796,7 @@ lce_status_t kd_forward_impl(const lce_kd_problem_t* p, const void* Hs, const vo
                              void* stream) {
   KdPlan k;
   lce_status_t st = make_kd_plan(p, &k);
+  if (st == LCE_OK && workspace_bytes < k.fwd_bytes) st = make_kd_plan(p, &k, true);
   if (st != LCE_OK) return st;
   const Plan& pl = k.s;
   if (!loss || !n_valid) return LCE_ERR_NULL;
@@ -2871,6 +2895,22 @@ lce_status_t lce_workspace_size(const lce_problem_t* p, size_t* fwd_bytes, size_
   if (st != LCE_OK) return st;
   if (fwd_bytes) *fwd_bytes = pl.fwd_bytes;
   if (bwd_bytes) *bwd_bytes = pl.bwd_bytes;
+  return LCE_OK;
+}
+
+lce_status_t lce_workspace_size_least(const lce_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes) {
+  Plan pl;
+  lce_status_t st = make_plan(p, &pl);
+  if (st != LCE_OK) return st;
+  if (fwd_bytes) {
+    const size_t full = pl.fwd_bytes;
+    plan_forward(&pl, true);
+    *fwd_bytes = std::min(full, pl.fwd_bytes);
+  }
+  if (bwd_bytes) {
+    plan_backward(&pl, true);
+    *bwd_bytes = pl.bwd_bytes;
+  }
   return LCE_OK;
 }
 
@@ -3006,6 +3046,15 @@ lce_status_t lce_backward_adamw(const lce_problem_t* p, const void* H, void* W, 
 lce_status_t lce_kd_workspace_size(const lce_kd_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes) {
   KdPlan k;
   lce_status_t st = make_kd_plan(p, &k);
+  if (st != LCE_OK) return st;
+  if (fwd_bytes) *fwd_bytes = k.fwd_bytes;
+  if (bwd_bytes) *bwd_bytes = k.bwd_bytes;
+  return LCE_OK;
+}
+
+lce_status_t lce_kd_workspace_size_least(const lce_kd_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes) {
+  KdPlan k;
+  lce_status_t st = make_kd_plan(p, &k, true);
   if (st != LCE_OK) return st;
   if (fwd_bytes) *fwd_bytes = k.fwd_bytes;
   if (bwd_bytes) *bwd_bytes = k.bwd_bytes;

@@ -567,3 +567,63 @@ def test_the_gradient_block_and_the_teacher_block_have_a_bound_that_v_does_not_m
             kf = B.lce_kd_workspace_size(B.kd_problem(n, d, 64, v))[0]
             assert kf <= info["o_hv"] + info["npad"] * (128 + 44) + 4096 + block * 2 // 3 * 65 // 64, (n, d, v)
             assert B.lce_kd_workspace_size_fused(B.kd_problem(n, d, 64, v)) <= rest + block, (n, d, v)
+
+
+def former_sizes(n, d, v, wide=True):
+    """Forward and backward bytes that the library asked for before few-token slabs, cut tiles and one-launch
+    forwards of narrow heads (``wide``: the plain calls' slabs, else the distillation's), and its slab width."""
+    npad = rup(max(n, 1), 256)
+    vt2, vt3, vround = cdiv(v, 256), cdiv(v, 384), rup(v, 768)
+    vc = max(4 * d, 8192, min(24576, (160 << 20) // (2 * d) // 6144 * 6144) if wide else 0)
+    vc = min(rup(vc, 6144), vround)
+    if wide and vc < vround:                    # the multiple of 768 whose dW launches take the fewest rounds
+        lo, hi = max(8192, 4 * d), min(vround, max(vc, min(24576, (160 << 20) // (2 * d))))
+        cost = c0 = dw_rounds(v, d, vc // 384)
+        best = vc // 384
+        for r in range(cdiv(lo, 768) * 2, hi // 384 + 1, 2):
+            c = dw_rounds(v, d, r)
+            if c < cost or (c == cost and c < c0):
+                best, cost = r, c
+        vc = best * 384
+    rows = max(2 * min(vt2, 32), vt3 if vt3 <= d // 4 else 2 * (vc // 384) + 1)
+    prefix = 2 * rup(4 * npad, 256) + 256 + rup(2 * d * npad, 256)
+    fwd = prefix + 2 * rup(4 * rows * npad, 256) + rup(4 * npad, 256)
+    rows_g, dh_tiles = rup(npad, 384), cdiv(npad, 384) * cdiv(d, 256)
+    bwd = prefix + rup(2 * rows_g * vc, 256) + 4 * rows_g * d * min(8, cdiv(256, dh_tiles))
+    return fwd, bwd, vc
+
+
+FORMER = [(n, d, v) for n in (1, 256, 700, 2048, 4096, 5000, 16384, 32768) for d in (8, 72, 512, 1000, 2048, 3584, 4096, 8192)
+          for v in (5, 4096, 32003, 128256, 600000) if n * d < 1 << 30]
+
+
+def test_workspaces_of_the_former_sizes_still_hold_every_call():
+    # the least form needs no more than what callers were told before; one byte less is refused on the host
+    ok = dict(H=0x100000, W=0x200000, targets=0x300000, lse=0x400000, n_valid=0x500000, grad_loss=0x600000, dH=0x700000,
+              dW=0x800000, workspace=0x900000, stream=0)
+    for n, d, v in FORMER:
+        p = B.problem(n, d, v)
+        fwd, bwd, _ = former_sizes(n, d, v)
+        f, b = B.lce_workspace_size_least(p)
+        f1, b1 = B.lce_workspace_size(p)
+        assert f <= fwd and b <= bwd and f <= f1 and b <= b1, (n, d, v)
+        with pytest.raises(B.LceError) as e:
+            B.lce_backward(p, **ok, workspace_bytes=b - 1)
+        assert e.value.code == B.LCE_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("dt", [1000, 4096])
+def test_distillation_workspaces_of_the_former_sizes_still_hold_every_call(dt):
+    # (students at least 32 wide: narrower ones have no rows of H to spare for the tiles' values of one slab)
+    for n, d, v in FORMER:
+        if d < 32:
+            continue
+        npad, vt2 = rup(max(n, 1), 256), cdiv(v, 256)
+        fwd, bwd, vc = former_sizes(n, d, v, wide=False)
+        p_bytes, hvt = 4 * vc * npad, rup(2 * dt * npad, 256) if dt % 64 == 0 else 0
+        q = rup(8 * vt2 * npad, 256)
+        f, b = B.lce_kd_workspace_size_least(B.kd_problem(n, d, dt, v))
+        assert f <= fwd + rup(4 * npad, 256) + q + rup(p_bytes, 256) + hvt, (n, d, v)
+        assert b <= bwd + p_bytes + hvt, (n, d, v)
+        full = B.lce_kd_workspace_size(B.kd_problem(n, d, dt, v))
+        assert f <= full[0] and b <= full[1] == B.lce_kd_workspace_size_fused(B.kd_problem(n, d, dt, v))

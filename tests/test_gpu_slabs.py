@@ -144,3 +144,115 @@ def test_launches_whose_last_round_is_cut_match_the_oracle(n, d, v, sigma):
     scale = max(1.0, np.max(np.abs(ref["lse"])))
     assert np.max(np.abs(gpu["lse"] - ref["lse"])) <= 1e-5 * scale
     assert np.max(np.abs(gpu["loss"] - ref["loss"])) <= 2e-5 * scale
+
+
+def _guarded(nbytes):
+    """A workspace of nbytes between two runs of 0xFF that a call must leave as they are."""
+    import torch
+    buf = torch.full((nbytes + 8192,), 0xFF, dtype=torch.uint8, device="cuda")
+    start = 256 * ((buf.data_ptr() + 4096 + 255) // 256) - buf.data_ptr()
+    return buf, buf[start:start + nbytes], lambda: bool((buf[:start] == 0xFF).all() and (buf[start + nbytes:] == 0xFF).all())
+
+
+@pytest.mark.parametrize("n,d,v,mask", [(700, 128, 50001, 0.2), (300, 264, 33000, 0.0), (2048, 1024, 30000, 0.25), (64, 64, 800, 0.0)])
+def test_the_least_workspace_serves_forward_backward_and_optimizer_step(n, d, v, mask):
+    # the rule's slabs and fewer K parts of dH in place of the few-token form, both passes in one buffer (reuse)
+    import torch
+    inp = WL.custom(n, d, v, seed=12, mask_frac=mask, sigma_w=0.3, case_id=57)
+    print(f"case least n={n} d={d} v={v}", flush=True)
+    h, w, t = U.to_device(inp)
+    p, pb = B.problem(n, d, v), B.problem(n, d, v, flags=B.LCE_FLAG_REUSE_FORWARD)
+    size = max(B.lce_workspace_size_least(p))
+    buf, ws, whole = _guarded(size)
+    s = torch.cuda.current_stream().cuda_stream
+    f32 = lambda k: torch.empty(k, dtype=torch.float32, device="cuda")
+    loss, lse, nv, g = f32(1), f32(n), torch.empty(1, dtype=torch.int32, device="cuda"), torch.ones(1, device="cuda")
+    dh, dw, dh2 = torch.empty_like(h), torch.empty_like(w), torch.empty_like(h)
+    B.lce_forward(p, h.data_ptr(), w.data_ptr(), t.data_ptr(), loss.data_ptr(), lse.data_ptr(), nv.data_ptr(), 0,
+                  ws.data_ptr(), size, s)
+    for q in (pb, p):
+        B.lce_backward(q, h.data_ptr(), w.data_ptr(), t.data_ptr(), lse.data_ptr(), nv.data_ptr(), g.data_ptr(),
+                       dh.data_ptr(), dw.data_ptr(), ws.data_ptr(), size, s)
+        torch.cuda.synchronize()
+        gpu = dict(loss=float(loss), lse=lse.cpu().numpy().astype(np.float64), n_valid=int(nv), status=0,
+                   dH=dh.float().cpu().numpy().astype(np.float64), dW=dw.float().cpu().numpy().astype(np.float64))
+        U.assert_parity(gpu, O.lce(inp.h_bits, inp.w_bits, inp.targets))
+    w2, m, v2 = w.clone(), torch.zeros_like(w, dtype=torch.float32), torch.zeros_like(w, dtype=torch.float32)
+    B.lce_backward_adamw(p, h.data_ptr(), w2.data_ptr(), t.data_ptr(), lse.data_ptr(), nv.data_ptr(), g.data_ptr(),
+                         dh2.data_ptr(), m.data_ptr(), v2.data_ptr(), 0, B.adamw(1e-3, 0.9, 0.999, 1e-8, 0.01, 1),
+                         ws.data_ptr(), size, s)
+    torch.cuda.synchronize()
+    assert torch.equal(dh.view(torch.int16), dh2.view(torch.int16))
+    assert torch.equal(m, dw.float() * np.float32(1 - np.float64(np.float32(0.9))))
+    assert whole()
+
+
+@pytest.mark.parametrize("n,ds,dt,v,mask", [(300, 64, 128, 30000, 0.2), (513, 128, 200, 26001, 0.0), (40, 64, 64, 700, 0.0)])
+def test_the_least_workspace_serves_the_distillation_calls(n, ds, dt, v, mask):
+    import torch
+    from oracle import kd_oracle as K
+    inp = WL.kd_custom(n, ds, dt, v, seed=13, mask_frac=mask)
+    print(f"case kd least n={n} ds={ds} dt={dt} v={v}", flush=True)
+    bf = lambda b: torch.from_numpy(b.view(np.int16)).view(torch.bfloat16).cuda()
+    hs, ws, ht, wt, t = bf(inp.hs_bits), bf(inp.ws_bits), bf(inp.ht_bits), bf(inp.wt_bits), torch.from_numpy(inp.targets).cuda()
+    p = B.kd_problem(n, ds, dt, v, temperature=2.0, target_bytes=t.element_size())
+    ref = K.kd_bits(inp.hs_bits, inp.ws_bits, inp.ht_bits, inp.wt_bits, inp.targets, temperature=2.0)
+    fb, bb = B.lce_kd_workspace_size_least(p)
+    s = torch.cuda.current_stream().cuda_stream
+    ptrs = [x.data_ptr() for x in (hs, ws, ht, wt, t)]
+    g = torch.ones(1, device="cuda")
+    got = []
+    for fused in (False, True):
+        loss, lse_s, lse_t = (torch.empty(k, dtype=torch.float32, device="cuda") for k in (1, n, n))
+        nv, st = (torch.empty(1, dtype=torch.int32, device="cuda") for _ in range(2))
+        dh, dw = torch.empty_like(hs), torch.empty_like(ws)
+        fbuf, fws, fwhole = _guarded(fb)
+        bbuf, bws, bwhole = _guarded(bb)
+        if fused:
+            B.lce_kd_forward_backward(p, *ptrs, g.data_ptr(), loss.data_ptr(), lse_s.data_ptr(), lse_t.data_ptr(),
+                                      nv.data_ptr(), st.data_ptr(), dh.data_ptr(), dw.data_ptr(), bws.data_ptr(), bb, s)
+        else:
+            B.lce_kd_forward(p, *ptrs, loss.data_ptr(), lse_s.data_ptr(), lse_t.data_ptr(), nv.data_ptr(), st.data_ptr(),
+                             fws.data_ptr(), fb, s)
+            B.lce_kd_backward(p, *ptrs, lse_s.data_ptr(), lse_t.data_ptr(), nv.data_ptr(), g.data_ptr(), dh.data_ptr(),
+                              dw.data_ptr(), bws.data_ptr(), bb, s)
+        torch.cuda.synchronize()
+        assert fwhole() and bwhole()
+        assert abs(float(loss) - ref["loss"]) <= U.LOSS_ABS_TOL
+        for x, k in ((dh, "dHs"), (dw, "dWs")):
+            assert U.rel_fro(x.float().cpu().numpy(), ref[k]) <= U.GRAD_REL_TOL, k
+        got.append((loss, lse_s, lse_t, dh.view(torch.int16), dw.view(torch.int16)))
+    assert all(torch.equal(a, b) for a, b in zip(*got))       # one call or two, the same bits
+
+
+def test_a_device_without_room_for_the_wide_slabs_takes_the_least_workspace(monkeypatch):
+    # a cap on the process's memory between the two sizes: forward and backward run in the smaller one
+    import torch
+    from paper_2605_21442_amd import autograd as A, linear_cross_entropy, linear_kd_loss
+    n, d, v = 2048, 512, 100000
+    p = B.problem(n, d, v, target_bytes=8)
+    big, least = max(B.lce_workspace_size(p)), max(B.lce_workspace_size_least(p))
+    assert big > 3 * least // 2
+    real, asked = torch.empty, []
+
+    def empty(*size, **kw):
+        if kw.get("dtype") is torch.uint8:
+            asked.append(size[0])
+            if size[0] > (big + least) // 2:
+                raise torch.OutOfMemoryError("no room")
+        return real(*size, **kw)
+
+    inp = WL.custom(n, d, v, seed=14, mask_frac=0.25, sigma_w=0.1, case_id=58)
+    h, w, t = U.to_device(inp, target_dtype=torch.int64)
+    grads = []
+    for tight in (False, True):
+        if tight:
+            monkeypatch.setattr(A.torch, "empty", empty)
+        x, y = h.clone().requires_grad_(True), w.clone().requires_grad_(True)
+        linear_cross_entropy(x, y, t).backward()
+        kd = linear_kd_loss(x, y, h[:, :64], w[:, :64], t)
+        grads.append([x.grad.float(), y.grad.float(), *(g.float() for g in torch.autograd.grad(kd, (x, y)))])
+    monkeypatch.undo()
+    assert asked[0] == big and asked[1] == least
+    for a, b in zip(*grads):
+        assert float((a - b).norm() / a.norm()) <= 1e-3 and bool(torch.isfinite(b).all())
