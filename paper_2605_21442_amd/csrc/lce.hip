@@ -1901,10 +1901,13 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_dh(const uint16_t* __re
               dH32b, acc_rows);
 }
 
-// K5 and K6 of one slab in one launch: the first dh_blocks blocks are the dH launch, the others the dW
-// launch (neither reads what the other writes). Blocks start in order, so the dH tiles, few and long (K =
-// the slab's ids), start first and the dW tiles, many and short (K = Nv), fill the CUs they leave idle
-// and the launches' two partial rounds become one.
+// K5 and K6 of one slab in one launch: dh_blocks blocks are the dH launch, the others the dW launch (neither
+// reads what the other writes). Blocks start in order, so the units with the longer K start first and the
+// shorter ones fill the CUs they leave idle: the launches' two partial rounds become one. With few tokens
+// that is dH, whose tiles are few and run over the slab's ids, or a part of them; narrow heads with many
+// tokens have few dW tiles, which run over all valid tokens and, started last, end alone (dH + dW, dH first,
+// then by this rule: 16384 x 256 x 8192 394 -> 358 us; 16384 x 512 x 128256 3690 -> 2920; 32768 x 512 x 8192
+// 861 -> 733; 32768 x 768 x 32768 2647 -> 2446; 8192 x 512 x 32768 560 -> 438).
 template <int kMode, int WM>
 __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_dhdw(const uint16_t* __restrict__ G, int vc, int npad, int vs,
                                                              const uint16_t* __restrict__ Ws, int64_t ldw,
@@ -1915,7 +1918,11 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_dhdw(const uint16_t* __
                                                              uint16_t* __restrict__ dW, int64_t v0) {
   static_assert(kMode != DW_ADAMW, "the optimizer step of dW updates the W rows that dH reads");
   __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
-  const int b = (int)blockIdx.x;
+  const int nv = *nv_ptr, t = (nv + Geo<WM>::TM - 1) / Geo<WM>::TM * ((d + TILE - 1) / TILE);
+  const bool dw_first = (int64_t)nv * (kz > 1 ? dh_split_parts(t, kz) : 1) > vs;
+  // (both counts are multiples of 8, so that either part's blocks keep their XCDs)
+  int b = (int)blockIdx.x;
+  if (dw_first) b = b < (int)gridDim.x - dh_blocks ? b + dh_blocks : b - ((int)gridDim.x - dh_blocks);
   if (b < dh_blocks)
     dh_tile<WM>(smem, b, G, vc, vs, Ws, ldw, ws_rows, d, nv_ptr, dH32, accumulate, kz, dH32b, acc_rows);
   else
@@ -2625,8 +2632,9 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
   // the W rows that dH reads) up to kMergeTiles dH tiles, 3 rounds of the CUs, of all N tokens. One launch
   // against two, dH + dW: 4096 tokens of a 16032 x 8192 shard (352 tiles) 1706 -> 1283 us; 8192 x 8192 x
   // 64000 (704) 11.5 -> 10.4 ms; 1948 x 3584 x 152064 (84) 2630 -> 2545 us; 256 x 512 x 4096 (2) 48 -> 25 us;
-  // 16384 x 4096 x 128256 (688) and 16384 x 2048 x 128256 (344) the same within 1 %; but 32768 x 3584 x
-  // 152064 (1204, several dH rounds anyway) 37.9 -> 38.3 ms.
+  // 16384 x 4096 x 128256 (688) the same within 1 %; narrow heads with many tokens (256 to 1024 wide, 8192
+  // to 32768 tokens, 43 to 344 tiles) 1 to 25 % less; but 32768 x 3584 x 152064 (1204, several dH rounds
+  // anyway) 37.9 -> 38.3 ms.
   static_assert(kDhWM == kDwWM, "one launch runs both");
   constexpr int kMergeTiles = 768;
   const bool merge = !adamw && want == (WANT_DH | WANT_DW) && (int64_t)dh_tiles * dt <= kMergeTiles;

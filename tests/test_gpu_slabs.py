@@ -49,7 +49,10 @@ def test_split_dh_parts_match_the_oracle_blockwise(n, d, nv, parts):
 
 
 @pytest.mark.parametrize("n,d,v,accumulate", [(8448, 4352, 700, False), (8600, 5888, 700, True), (8832, 8448, 400, False),
-                                              (300, 264, 1000, True), (500, 72, 26000, True)])
+                                              (300, 264, 1000, True), (500, 72, 26000, True),
+                                              # dW's blocks first (420 valid tokens against a part of 376 ids), and
+                                              # dH's (against 2500)
+                                              (9000, 512, 3001, False), (9000, 512, 20000, False)])
 def test_dh_and_dw_in_one_launch_or_two_match_the_oracle(n, d, v, accumulate):
     # either side of the rule (768 dH tiles), with and without the accumulating dW epilogue; most rows
     # ignored where the widths are large, so that the oracle stays quick
