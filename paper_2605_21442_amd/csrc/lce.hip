@@ -997,15 +997,14 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
 // ---------------------------------------------------------------------------------------------
 // K3: per valid token: merge the vocabulary partials into lse, take the target logit
 // s[n, t_n] = H[n] . W[t_n] in fp32, and the per-row loss l_n = lse_n - s[n, t_n].
-// A workgroup of 16 waves serves 16 consecutive tokens. Each wave first takes one token's target logit, a
-// wave-wide dot product; then its four groups of 16 lanes fold every 64th partial row (64-byte reads along
-// the tokens), and the groups and the waves are merged in a fixed order. Bound by latency (few tokens) or by
-// the partials' bytes. (With 64 tokens a workgroup, each wave folded a quarter as many rows in parallel and
-// took four dot products in turn: 496 valid tokens of 2048 x 128256 were 8 workgroups, 40 us, now 16; 12288
-// of 4096 x 128256 62 us, now 53; 18000 of 1024 x 152064 46 -> 55.)
+// A workgroup of 16 waves serves kTok consecutive tokens, 16 or 64. Its waves first take the target logits, a
+// wave-wide dot product each; then a wave's 64 / kTok groups of lanes fold a partial row each (reads along the
+// tokens), and the groups and the waves are merged in a fixed order. Bound by latency (few tokens) or by
+// the partials' bytes. With 64 tokens a workgroup, a wave folds a quarter as many rows in parallel and takes
+// four dot products in turn: 496 valid tokens of 2048 x 128256 are 8 workgroups, 40 us against 16; 12288
+// of 4096 x 128256 62 against 53. Many tokens of a narrow head with few rows to fold prefer it (wide_combine).
 // ---------------------------------------------------------------------------------------------
-constexpr int kCombTok = 16;
-
+template <int kTok>
 __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H, int64_t ldh,
                                                   const uint16_t* __restrict__ W, int64_t ldw,
                                                   const void* targets, int tbytes, int64_t id0, int64_t v_local,
@@ -1017,13 +1016,14 @@ __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H
                                                   float* __restrict__ per_token, float* __restrict__ tgt_part) {
   // run_m / run_s (may be null): a running pair per token folded in before the partial rows (two sets where
   // the forward cut its last tiles)
-  __shared__ float red_m[16][kCombTok], red_s[16][kCombTok], dots[kCombTok];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = lane & 15;
-  const int i0 = blockIdx.x * kCombTok;
+  constexpr int kGroups = 64 / kTok;   // of lanes, a partial row each
+  __shared__ float red_m[16][kTok], red_s[16][kTok], dots[kTok];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = lane % kTok;
+  const int i0 = blockIdx.x * kTok;
   const int nv = *nv_ptr;
   if (i0 >= nv) return;
-  if (i0 + wave < nv) {
-    const int row = idx[i0 + wave];
+  for (int w = wave; w < kTok && i0 + w < nv; w += 16) {
+    const int row = idx[i0 + w];
     // target id relative to this W's first row (id0 > 0 only for a vocabulary shard, which may
     // not hold the target: then its target logit is 0)
     const int64_t tl = load_target(targets, tbytes, row) - id0;
@@ -1043,27 +1043,27 @@ __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H
       }
       dot = wave_sum(dot);
     }
-    if (lane == 0) dots[wave] = dot;
+    if (lane == 0) dots[w] = dot;
   }
   const int i = i0 + t;
   const int rows = tail_parts(tile_space(tiles, (nv + TILE - 1) / TILE), split) > 1 ? 2 * tiles : tiles;
   float m = -INFINITY, s = 0.f;
   if (i < nv) {
-    if (run_m && wave == 0 && lane < kCombTok) {
+    if (run_m && wave == 0 && lane < kTok) {
       m = run_m[i];
       s = run_s[i];
     }
 #pragma unroll 4
-    for (int q = 4 * wave + (lane >> 4); q < rows; q += 64)
+    for (int q = kGroups * wave + lane / kTok; q < rows; q += 16 * kGroups)
       merge_pair(m, s, part_m[(int64_t)q * npad + i], part_s[(int64_t)q * npad + i]);
   }
-  for (int o = 16; o <= 32; o <<= 1) merge_pair(m, s, __shfl_xor(m, o), __shfl_xor(s, o));
-  if (lane < kCombTok) {
+  for (int o = kTok; o <= 32; o <<= 1) merge_pair(m, s, __shfl_xor(m, o), __shfl_xor(s, o));
+  if (lane < kTok) {
     red_m[wave][t] = m;
     red_s[wave][t] = s;
   }
   __syncthreads();
-  if (threadIdx.x >= kCombTok || i >= nv) return;
+  if (threadIdx.x >= kTok || i >= nv) return;
   for (int w = 1; w < 16; ++w) merge_pair(m, s, red_m[w][t], red_s[w][t]);
   const int row = idx[i];
   const float lse = (m + log2f(s)) * kLn2, dot = dots[t];
@@ -2375,6 +2375,13 @@ unsigned adamw_grid(int64_t v, int64_t d) {
   return (unsigned)(blocks < 16384 ? blocks : 16384);
 }
 
+// k_combine with 64 tokens a workgroup: short dot products, few partial rows, and enough workgroups all the
+// same. 64 tokens against 16: 16384 tokens of 256 / 512 / 768 / 1024 x 8192 14 / 14 / 16 / 17 us against
+// 15 / 16 / 20 / 19, 32768 tokens 20 / 20 / 24 / 26 against 25 / 24 / 28 / 32, and x 32768 25 / 26 / 30 / 31
+// against 30 / 29 / 36 / 35; but 16384 tokens x 128256 30 / 29 / 36 / 38 against 28 / 27 / 33 / 41, 8192
+// tokens x 128256 29 to 35 against 20 to 24, and 24576 x 2048 x 32768 48 against 41.
+inline bool wide_combine(const Plan& pl) { return pl.n > 12288 && pl.d <= 1536 && pl.vt_count3 <= 128; }
+
 struct Launcher {
   hipStream_t s;
   lce_status_t st = LCE_OK;
@@ -2511,9 +2518,10 @@ lce_status_t forward_impl(const lce_problem_t* p, const ShardInfo* shard, const 
     idx, pos, nv, n_valid, dev_status, lse, none ? loss : tgt_part, (float*)nullptr);
   const PartRows pr = launch_fwd_stats(L, pl, w, pl.ldw, h, pl.ldh, (const int*)idx, (const int*)nv,
                                        (uint16_t*)(ws + pl.o_hv), pm, ps);
-  L(K_COMBINE, k_combine, dim3((unsigned)((pl.n + kCombTok - 1) / kCombTok)), dim3(1024), h, pl.ldh, w, pl.ldw,
-    targets, p->target_bytes, si.v_begin, pl.v, (const int*)idx, (const int*)nv, (int)pl.d, pr.count, pr.split, pr.m, pr.s,
-    (int)pl.npad, pr.run_m, pr.run_s, lse, terms, none ? loss : (float*)nullptr, tgt_part);
+  const int ctok = wide_combine(pl) ? 64 : 16;
+  L(K_COMBINE, ctok == 64 ? k_combine<64> : k_combine<16>, dim3((unsigned)((pl.n + ctok - 1) / ctok)), dim3(1024), h,
+    pl.ldh, w, pl.ldw, targets, p->target_bytes, si.v_begin, pl.v, (const int*)idx, (const int*)nv, (int)pl.d,
+    pr.count, pr.split, pr.m, pr.s, (int)pl.npad, pr.run_m, pr.run_s, lse, terms, none ? loss : (float*)nullptr, tgt_part);
   if (!none && !shard) L(K_LOSS, k_loss, dim3(1), dim3(1024), (const float*)terms, (const int*)nv, p->reduction, loss);
   return L.st;
 }

@@ -259,3 +259,31 @@ def test_a_device_without_room_for_the_wide_slabs_takes_the_least_workspace(monk
     assert asked[0] == big and asked[1] == least
     for a, b in zip(*grads):
         assert float((a - b).norm() / a.norm()) <= 1e-3 and bool(torch.isfinite(b).all())
+
+
+@pytest.mark.parametrize("n,d,v,nv", [(12289, 64, 3000, 1), (12289, 64, 3000, 700), (13000, 200, 49000, 64), (12500, 1536, 2000, 65),
+                                      (12288, 64, 3000, 700), (12289, 1544, 2000, 65), (12289, 64, 49153, 63)])
+def test_both_widths_of_the_partials_merge_match_the_oracle(n, d, v, nv):
+    # 64 tokens a workgroup from 12289 tokens on, up to 1536 wide and 128 tiles of 384 ids, and 16 just outside; 1
+    # to 65 valid tokens, and the least workspace's running pairs folded in first
+    import torch
+    rng = np.random.default_rng([n, d, nv])
+    t = np.full(n, -100, dtype=np.int32)
+    rows = np.sort(rng.choice(n, size=nv, replace=False))
+    t[rows] = rng.integers(0, v, size=nv, dtype=np.int32)
+    inp = WL.custom(n, d, v, seed=15, sigma_w=0.2, target_override=t)
+    print(f"case merge n={n} d={d} v={v} nv={nv}", flush=True)
+    h, w, tt = U.to_device(inp)
+    ref = O.lce(inp.h_bits, inp.w_bits, inp.targets, reduction="none", grad=np.ones(n))
+    p = B.problem(n, d, v, reduction="none")
+    scale = max(1.0, np.max(np.abs(ref["lse"])))
+    for nbytes in (B.lce_workspace_size(p)[0], B.lce_workspace_size_least(p)[0]):
+        loss, lse = (torch.full((n,), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+        cnt = torch.empty(1, dtype=torch.int32, device="cuda")
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        B.lce_forward(p, h.data_ptr(), w.data_ptr(), tt.data_ptr(), loss.data_ptr(), lse.data_ptr(), cnt.data_ptr(), 0,
+                      ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert int(cnt) == nv
+        assert np.max(np.abs(lse.cpu().numpy() - ref["lse"])) <= 1e-5 * scale
+        assert np.max(np.abs(loss.cpu().numpy() - ref["loss"])) <= 2e-5 * scale
