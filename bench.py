@@ -147,9 +147,13 @@ def _gemm_reference(args, wl, h, w, inp):
 
 
 def _source_hash():
+    # of the kernels and the index functions they share with the host
     import hashlib
-    src = os.path.join(ROOT, "paper_2605_21442_amd", "csrc", "lce.hip")
-    return hashlib.sha256(open(src, "rb").read()).hexdigest()
+    h = hashlib.sha256()
+    for name in ("lce.hip", "tiles.h"):
+        with open(os.path.join(ROOT, "paper_2605_21442_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def _kernel_breakdown(B, step, steps):

@@ -51,12 +51,17 @@
 
 #include "lce.h"
 
+#define LCE_HD __host__ __device__ __forceinline__
+#include "tiles.h"
+
 // Workspace of lce_forward_noalloc: device memory of the code object itself, one copy per GPU,
 // held until the process ends. In host code `scratch` is only a stand-in for the symbol; its
 // device address comes from hipGetSymbolAddress (see noalloc_scratch).
 static __device__ __align__(256) char scratch[LCE_NOALLOC_SCRATCH_BYTES];
 
 namespace {
+
+using namespace lce_tiles;
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -289,10 +294,7 @@ struct FragSet {
 };
 
 // chunk this lane loads for its even-numbered rows (odd rows: ^ 1), row-major operands
-__device__ __forceinline__ int lane_chunk_even() {
-  const int j = threadIdx.x & 63;
-  return (j & 7) ^ ((j >> 3) & 7);
-}
+__device__ __forceinline__ int lane_chunk_even() { return lane_chunk(threadIdx.x & 63); }
 
 // K-major swizzle: position in LDS of 16-byte chunk c (of kW / 8) of K-row k, and its inverse.
 //  kW = 256: c ^ (4 (k & 3) + 16 ((k >> 3) & 1));
@@ -394,13 +396,12 @@ __device__ __forceinline__ void mma_substep(f32x16_t (&acc)[BI][BJ], const FragS
 template <bool kAsm, int kKind, int kW, bool kMasked>
 __device__ __forceinline__ void load_operand(const Operand& op, const char* dstp, int dst, int k0, int K) {
   if constexpr (kKind != OP_KMAJOR) {
-    const int ce = lane_chunk_even();
     // dense: the odd-q offset of lane L is the even-q offset of lane L ^ 1 (same row, the chunk
     // with the other parity), fetched by a quad swap instead of held in a register
     const uint32_t odd = kKind == OP_DENSE ? (uint32_t)__builtin_amdgcn_mov_dpp((int)op.off[0], 0xB1, 0xF, 0xF, false) : 0u;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const bool ok = !kMasked || k0 + (ce ^ (q & 1)) * 8 < K;
+      const bool ok = !kMasked || chunk_exists(threadIdx.x & 63, q, k0, K);
       const uint32_t v = kKind == OP_DENSE ? ((q & 1) ? odd : op.off[0]) : op.off[q];
       const uint32_t so = (uint32_t)k0 * 2 + (kKind == OP_DENSE ? (uint32_t)q * op.qstride : 0u);
       dma16<kAsm>(op.rsrc, op.rwords, dstp + q * 1024, dst + q * 1024, ok ? v : kOobOffset, so);
@@ -428,10 +429,9 @@ __device__ __forceinline__ void load_operand(const Operand& op, const char* dstp
 template <int kKind>
 __device__ __forceinline__ void mask_tail(Operand& op, int k0, int K) {
   static_assert(kKind != OP_KMAJOR, "");
-  const int ce = lane_chunk_even();
 #pragma unroll
   for (int q = 0; q < (kKind == OP_DENSE ? 1 : 4); ++q)
-    if (k0 + (ce ^ (q & 1)) * 8 >= K) op.off[q] = kOobOffset;
+    if (!chunk_exists(threadIdx.x & 63, q, k0, K)) op.off[q] = kOobOffset;
 }
 
 // w: this wave's index in the workgroup, a wave-uniform (scalar) value
@@ -779,67 +779,6 @@ __device__ __forceinline__ void merge_weighted(float& m, float& s, float& q, flo
   m = mn;
 }
 
-// XCD-aware order of the tiles of a forward or G launch: `tiles` vocabulary tiles by nt token tiles,
-// workgroups dealt round-robin to the 8 XCDs (block b runs on XCD b mod 8). The first a = tiles & ~7
-// vocabulary tiles go in groups of gw tiles (a and gw multiples of 8; a last group may be narrower)
-// by all token tiles, vocabulary tiles fastest: XCD x then takes the tiles = x (mod 8) of each
-// group, and a round of its ~32 workgroups shares a few W tiles and a few H tiles, while the group's
-// W rows stay in the MALL as the token tiles pass. The last tiles - a (< 8) vocabulary tiles are
-// dealt by token tile instead: XCD x takes the token tiles = x (mod 8), each with all of them.
-// (Dealt the first way, a group whose width is not a multiple of 8 would give every XCD most of the
-// group's W tiles.) False for blocks past the last tile.
-__device__ __forceinline__ bool xcd_tile(int b, int tiles, int gw, int nt, int& tm, int& tn) {
-  const int a = tiles & ~7, ba = a * nt;
-  if (b < ba) {
-    const int full = a / gw, g = b / (gw * nt);
-    const int wl = g < full ? gw : a - full * gw, r = b - g * gw * nt;
-    tm = g * gw + r % wl;
-    tn = r / wl;
-    return true;
-  }
-  const int rem = tiles - a, r = b - ba, k = r >> 3;
-  if (rem == 0) return false;
-  tm = a + k % rem;
-  tn = (r & 7) + 8 * (k / rem);
-  return tn < nt;
-}
-
-// The tiles a forward or G launch leaves for its last, partial round of the 256 CUs (all of them in a small
-// launch) are cut into parts of 192 ids x 256 tokens (2 per tile, up to 128 tiles) or 192 x 128 (4 per tile,
-// up to 64), so that the round has two or four times the workgroups. A half tile takes about 0.73 and a
-// quarter 0.57 of a tile's time (less work per byte loaded), so that more tiles than that are left whole,
-// as is everything in launches of more than kSplitTiles tiles, where the last round is a small share.
-// Forward, before and after: 3276 x 8192 x 16032 (546 tiles) 784 -> 673 us; 900 x 2048 x 32000 (336) 140 ->
-// 122; 2549 x 1000 x 32003 (840) 174 -> 162; 230 x 512 x 4096 (11) 22 -> 12, its G 28 -> 14. `t` is the index
-// space of xcd_tile (a multiple of 8, so that all parts of a tile run on one XCD).
-constexpr int kSplitTiles = 2048;
-__host__ __device__ inline int tile_space(int tiles, int nt) {
-  const int a = tiles & ~7;
-  return a * nt + (tiles - a) * ((nt + 7) / 8 * 8);
-}
-__device__ __forceinline__ int tail_parts(int t, bool split) {   // parts of the tail tiles (1: no tail is cut)
-  const int rem = t & 255;
-  return !split || t > kSplitTiles || rem == 0 || rem > 128 ? 1 : rem > 64 ? 2 : 4;
-}
-struct TilePart {
-  int tm, tn;        // vocabulary tile, token tile
-  int parts, part;   // parts of the tile, this block's (bit 0: its ids, bit 1: its tokens)
-};
-__device__ __forceinline__ bool tile_part(int b, int tiles, int gw, int nt, bool split, TilePart& p) {
-  const int t = tile_space(tiles, nt), parts = tail_parts(t, split), whole = parts > 1 ? t & ~255 : t;
-  int l = b;
-  p.parts = 1;
-  p.part = 0;
-  if (b >= whole) {
-    if (parts == 1) return false;
-    const int j = b - whole;
-    l = whole + j / (8 * parts) * 8 + (j & 7);
-    p.parts = parts;
-    p.part = (j >> 3) % parts;
-  }
-  return l < t && xcd_tile(l, tiles, gw, nt, p.tm, p.tn);
-}
-
 // The forward statistics of one tile or part: ids of the vleft rows of W from wt on, the tleft tokens of Hv
 // from ht on; one partial pair per token to out_m / out_s.
 template <bool kTail, int BI, int BJ>
@@ -1148,69 +1087,6 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict_
     if (i < nv) v = *reinterpret_cast<const uint4*>(H + (int64_t)idx[i] * ldh + c * 8);
     *reinterpret_cast<uint4*>(Hv + i * d + c * 8) = v;
   }
-}
-
-// dH launches with fewer output tiles than CUs: K is split so that every CU has a block. The host
-// reserves kz_max accumulators (2 to 8); the parts taken follow from the live tile count t = ceil(Nv
-// / 384) x ceil(D / 256): the number whose rounds of 256 units take the least K together (64 tiles: 4
-// parts, one round; 144 tiles: 3 parts, two rounds of a third of K each). The t * parts units
-// (part-major) are cut into 8 equal shares, one per XCD, so that all XCDs work whatever the number of row tiles, and an XCD's
-// blocks walk one or two K ranges of G and W in step, which its L2 then reads once. (With whole row
-// tiles dealt to the XCDs instead, 4 row tiles kept 4 of the 8 XCDs busy: dH of 2048 x 4096 x 128256
-// with 1536 valid tokens 2500 us, now 1154; of 1948 x 3584 x 152064 2220 -> 1257; of 4096 x 2048 x
-// 128256, whose 64 tiles took 3 parts by N and take 4 by Nv, 1365 -> 1133.)
-__device__ __forceinline__ int dh_split_parts(int t, int kz_max) {
-  int best = 1, rounds = (t + 255) / 256;
-  for (int kz = 2; kz <= kz_max; ++kz) {
-    const int r = (t * kz + 255) / 256;
-    if (r * best < rounds * kz) {
-      best = kz;
-      rounds = r;
-    }
-  }
-  return best;
-}
-
-// dH launches whose K the host did not split. With T = tm_live x dt live output tiles (tm_live =
-// ceil(Nv / 384) row tiles of 384 tokens, dt column tiles of 256), XCD x takes the tiles [c0(x),
-// c0(x + 1)) of a balanced cut, c0(x) = floor(x T / 8), in an order that keeps consecutive tiles on
-// few operand tiles: bands of 4 row tiles, each walked column by column. An XCD runs its ~32
-// resident workgroups in rounds; the n_tail tiles of its last, partial round are split along K
-// into dh_tail_parts(n_tail) parts, so that they fill that round instead of leaving most of its
-// CUs idle. Part 0 of a tile accumulates into the tile's rows of the accumulator (row stride D);
-// part z >= 1 of tail tile t into slot dh_slot0(x) + (z - 1) * n_tail + t, a 384 x 256 fp32 block
-// (row stride 256) in the accumulator's rows at or past tm_live * 384, which hold no valid token.
-// When those rows cannot hold every slot, no tile is split. The finalise adds the parts in order.
-constexpr int kDhBand = 4;                       // row tiles per band
-constexpr int64_t kDhSlot = 384 * 256;           // floats per slot
-__device__ __forceinline__ int dh_c0(int x, int t) { return (int)(((int64_t)x * t) >> 3); }
-__device__ __forceinline__ int dh_tail_parts(int n_tail) {
-  return n_tail > 0 && n_tail <= 16 ? (32 / n_tail < 8 ? 32 / n_tail : 8) : 1;
-}
-// slots taken by the XCDs before x (the slots are numbered XCD by XCD, each XCD's in part-major
-// order); dh_slot0(8, t) is the total
-__device__ __forceinline__ int dh_slot0(int x, int t) {
-  int n = 0;
-  for (int y = 0; y < x; ++y) {
-    const int nt = (dh_c0(y + 1, t) - dh_c0(y, t)) & 31;
-    n += (dh_tail_parts(nt) - 1) * nt;
-  }
-  return n;
-}
-__device__ __forceinline__ bool dh_tail_fits(int t, int tm_live, int d, int acc_rows) {
-  return (int64_t)dh_slot0(8, t) * kDhSlot <= (int64_t)(acc_rows - tm_live * 384) * d;
-}
-__device__ __forceinline__ void dh_band_tile(int l, int tm_live, int dt, int& tm, int& tn) {
-  const int band = l / (kDhBand * dt), r0 = band * kDhBand;
-  const int rows = tm_live - r0 < kDhBand ? tm_live - r0 : kDhBand;
-  const int k = l - band * kDhBand * dt;
-  tm = r0 + k % rows;
-  tn = k / rows;
-}
-__device__ __forceinline__ int dh_band_index(int tm, int tn, int tm_live, int dt) {
-  const int band = tm / kDhBand, r0 = band * kDhBand;
-  const int rows = tm_live - r0 < kDhBand ? tm_live - r0 : kDhBand;
-  return band * kDhBand * dt + tn * rows + (tm - r0);
 }
 
 // scale c = g / n_norm (mean) or g (sum), 0 when the count is 0; for NONE the caller reads
@@ -1633,13 +1509,8 @@ __device__ __forceinline__ void dw_tile(char* smem, int blk, const uint16_t* __r
                                         int tm_count, uint16_t* __restrict__ dW, int64_t v0, const AdamWState& st,
                                         const AdamWConst& oc) {
   constexpr int TM = Geo<WM>::TM;
-  // the slab's T = tm_count x dt tiles in the balanced cut of the dH launches: XCD x takes
-  // [c0(x), c0(x + 1)), walked in bands of 4 row tiles, column by column
-  const int dt = (d + TILE - 1) / TILE, t = tm_count * dt, x = blk & 7, k = blk >> 3;
-  const int c0 = dh_c0(x, t);
-  if (k >= dh_c0(x + 1, t) - c0) return;
   int tm, tn;
-  dh_band_tile(c0 + k, tm_count, dt, tm, tn);
+  if (!dw_unit(blk, tm_count, d, tm, tn)) return;
   const int m0 = tm * TM, d0 = tn * TILE;
   const int nv = *nv_ptr;
   const int kpad = ((nv + KPAD - 1) / KPAD) * KPAD;
@@ -1772,62 +1643,27 @@ __device__ __forceinline__ void dh_tile(char* smem, int blk, const uint16_t* __r
   static_assert(Geo<WM>::TM == 384, "the tail slots and the finalise assume 384-row tiles");
   constexpr int TM = Geo<WM>::TM;
   const int nv = *nv_ptr;
-  const int dt = (d + TILE - 1) / TILE, tm_live = (nv + TM - 1) / TM;
-  // this block's tile, K part z of kzl, and the fp32 block it accumulates into (tile origin,
-  // row stride, column of the tile's first column)
-  int tm, tn, z, kzl;
+  DhUnit u;
+  if (!dh_unit(blk, nv, d, kz, acc_rows, u)) return;
+  const int tm = u.tm, tn = u.tn;
+  // the fp32 block that this unit accumulates into: tile origin, row stride, column of the tile's first column
   float* acc_tile;
   int ldacc, cb;
-  if (kz > 1) {
-    // every tile's K in kzl parts (launches with fewer tiles than CUs)
-    const int t = tm_live * dt;
-    if (t == 0) return;
-    kzl = dh_split_parts(t, kz);
-    const int u = t * kzl, x = blk & 7, l = dh_c0(x, u) + (blk >> 3);
-    if (l >= dh_c0(x + 1, u)) return;
-    z = l / t;
-    dh_band_tile(l - z * t, tm_live, dt, tm, tn);
-    acc_tile = (z ? dH32 + (int64_t)z * (dH32b - dH32) : dH32) + (int64_t)tm * TM * d;
+  if (u.slot < 0) {
+    acc_tile = (u.z ? dH32 + (int64_t)u.z * (dH32b - dH32) : dH32) + (int64_t)tm * TM * d;
     ldacc = d;
     cb = tn * TILE;
   } else {
-    const int t = tm_live * dt, x = blk & 7, k = blk >> 3;
-    const int c0 = dh_c0(x, t), n = dh_c0(x + 1, t) - c0, nmain = n & ~31, nt = n - nmain;
-    const int kzt = dh_tail_fits(t, tm_live, d, acc_rows) ? dh_tail_parts(nt) : 1;
-    int l, slot = 0;
-    if (k < nmain) {
-      l = c0 + k;
-      z = 0;
-      kzl = 1;
-    } else {
-      const int j = k - nmain;
-      if (j >= kzt * nt) return;
-      const int ti = j % nt;
-      z = j / nt;
-      kzl = kzt;
-      l = c0 + nmain + ti;
-      slot = dh_slot0(x, t) + (z - 1) * nt + ti;
-    }
-    dh_band_tile(l, tm_live, dt, tm, tn);
-    if (z == 0) {
-      acc_tile = dH32 + (int64_t)tm * TM * d;
-      ldacc = d;
-      cb = tn * TILE;
-    } else {
-      acc_tile = dH32 + (int64_t)tm_live * TM * d + (int64_t)slot * kDhSlot;
-      ldacc = TILE;
-      cb = 0;
-    }
+    acc_tile = dH32 + (int64_t)((nv + TM - 1) / TM) * TM * d + (int64_t)u.slot * kDhSlot;
+    ldacc = TILE;
+    cb = 0;
   }
   const int m0 = tm * TM, d0 = tn * TILE;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wr = wave >> 2, wc = wave & 3;
   // K = the slab's vs ids; the last slice of a slab whose width is not a multiple of 64 is masked
-  // (lanes past K load zeros), so no W row past the vocabulary is addressed. Half z covers
-  // [k0, k0 + kzn), the first half a whole number of 64-wide slices.
-  const int kt = (vs + KSLICE - 1) / KSLICE * KSLICE;
-  const int kh = ((kt + kzl - 1) / kzl + KSLICE - 1) / KSLICE * KSLICE;
-  const int k0 = z * kh;
-  const int kzn = vs - k0 < kh ? vs - k0 : kh;
+  // (lanes past K load zeros), so no W row past the vocabulary is addressed.
+  int k0;
+  const int kzn = dh_k_range(vs, u.kz, u.z, k0);
   f32x16_t acc[4][2];
   if (kzn > 0) {
     const Operand opa = dense_operand(G + (int64_t)m0 * vc + k0, nv - m0, vc);
@@ -1918,11 +1754,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_dhdw(const uint16_t* __
                                                              uint16_t* __restrict__ dW, int64_t v0) {
   static_assert(kMode != DW_ADAMW, "the optimizer step of dW updates the W rows that dH reads");
   __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
-  const int nv = *nv_ptr, t = (nv + Geo<WM>::TM - 1) / Geo<WM>::TM * ((d + TILE - 1) / TILE);
-  const bool dw_first = (int64_t)nv * (kz > 1 ? dh_split_parts(t, kz) : 1) > vs;
-  // (both counts are multiples of 8, so that either part's blocks keep their XCDs)
-  int b = (int)blockIdx.x;
-  if (dw_first) b = b < (int)gridDim.x - dh_blocks ? b + dh_blocks : b - ((int)gridDim.x - dh_blocks);
+  const int b = dhdw_block((int)blockIdx.x, dh_blocks, (int)gridDim.x - dh_blocks, dw_first(*nv_ptr, d, kz, vs));
   if (b < dh_blocks)
     dh_tile<WM>(smem, b, G, vc, vs, Ws, ldw, ws_rows, d, nv_ptr, dH32, accumulate, kz, dH32b, acc_rows);
   else
@@ -2146,19 +1978,6 @@ inline int group_tiles(int64_t tiles, int64_t tile_rows, int64_t d) {
   const int64_t bytes = tiles * tile_rows * d * 2;
   const int64_t groups = std::max<int64_t>(1, (bytes + kGroupBytes - 1) / kGroupBytes);
   return (int)std::max<int64_t>(1, (tiles + groups - 1) / groups);
-}
-
-// Grid and group width of a launch in the order of xcd_tile: `tiles` vocabulary tiles by nt token
-// tiles, in groups at most `width` tiles wide (rounded down to a multiple of 8). A split launch's parts
-// take at most a round of 256 blocks beside the whole tiles.
-struct TileOrder {
-  unsigned grid;
-  int gw;
-};
-inline TileOrder tile_order(int64_t tiles, int64_t nt, int64_t width, bool split = false) {
-  const int64_t a = tiles & ~(int64_t)7, rem = tiles - a;
-  return TileOrder{(unsigned)(a * nt + (rem ? 8 * rem * ((nt + 7) / 8) : 0) + (split ? 256 : 0)),
-                   (int)std::max<int64_t>(8, std::min(width, a) & ~(int64_t)7)};
 }
 
 // Workgroup rounds of the dW launches over the whole vocabulary with slabs of r 384-id row tiles:
@@ -2665,12 +2484,9 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
         (const uint16_t*)hv, (int64_t)d, targets, p->target_bytes, si.v_begin, (const int*)idx, (const int*)nv, lse,
         grad_loss, (const int*)n_valid, p->reduction, d, tmg, to.gw, 1, g, vc);
     }
-    // split launches: a block for each part the tiles may take; otherwise 8 XCDs x 32 CUs x (whole rounds of the
-    // largest per-XCD share + one round for the split tail)
-    const unsigned bdh = pl.dh_kz > 1 ? (unsigned)((pl.dh_kz * dh_tiles * dt + 7) / 8 * 8)
-                                      : (unsigned)(256 * (((int64_t)dh_tiles * dt + 7) / 8 / 32 + 1));
+    const unsigned bdh = (unsigned)dh_grid(pl.npad, d, pl.dh_kz);
     const int tmw = (vs + Geo<kDwWM>::TM - 1) / Geo<kDwWM>::TM;
-    const unsigned bdw = (unsigned)(8 * (((int64_t)tmw * dt + 7) / 8));
+    const unsigned bdw = (unsigned)dw_grid(tmw, d);
     // dH reads the slab's W rows before the dW launch, whose AdamW epilogue (in-backward step)
     // may update them; later slabs read only their own rows
     if (merge) {

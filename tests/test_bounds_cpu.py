@@ -6,23 +6,29 @@ each kernel's loads, stores and read-modify-writes can form and checks it agains
 the region (workspace) or of the caller's tensor it addresses. The arithmetic follows the
 kernels' index expressions:
 
-* tiles are 384 x 256 (D % 64 == 0: 12 waves) or 256 x 256 (other widths: 8 waves); the rows of
-  the last vocabulary tile past V are loaded through the out-of-range offset (zeros, no address),
-  so the W rows addressed are those below V;
+* forward and G tiles are 384 x 256 over the gathered rows Hv at every width, and the last round's
+  may be cut into 192 x 256 or 192 x 128 parts; the rows of the last vocabulary tile past V, and the
+  chunks of a row past D, are loaded through the out-of-range offset (zeros, no address), so the W
+  rows addressed are those below V;
 * K-major operands send the lanes whose columns lie past D (the hidden width) to the same offset;
 * dH runs K over the slab's vs ids (a ragged last slice masks the rest), split into 1 to 8 parts;
 * G and the dH accumulators hold rows_g rows, the 384-row tiles of the last token rows included;
 * the dW / AdamW epilogues touch only the rows of the slab that exist.
 
-Accesses sent to the out-of-range offset form no address and are not counted. No GPU is needed.
+Accesses sent to the out-of-range offset form no address and are not counted. Which workgroup takes
+which tile, part, K range or slot is asked of the functions that the kernels run (host_tiles). No GPU
+is needed.
 """
 import pytest
 
 from paper_2605_21442_amd import binding as B
+from tests import host_tiles as T
 
 HEADS = [(256, 512, 4096), (8192, 2048, 128256), (16384, 4096, 128256), (32768, 3584, 152064),
          (16384, 8192, 128256)]
-EDGES = [(1, 8, 5), (300, 264, 1000), (257, 64, 9000), (513, 520, 300), (300, 64, 12300), (200, 128, 12289),
+# launches that may be cut, and a ragged width among them
+CUT = [(2048, 2048, 128256), (2999, 1000, 32003), (4096, 8192, 16032), (513, 64, 40520), (100, 136, 57607), (709, 2048, 128256)]
+EDGES = CUT + [(1, 8, 5), (300, 264, 1000), (257, 64, 9000), (513, 520, 300), (300, 64, 12300), (200, 128, 12289),
          (768, 128, 1536), (520, 64, 40000), (33, 72, 1), (16385, 64, 383), (1000, 136, 385)]
 
 
@@ -49,35 +55,9 @@ class Extents:
 
 
 def dh_tail_parts(nv, d, acc_rows):
-    """The K parts z >= 1 of the tail tiles of a dH launch the host did not split, as the kernel
-    assigns them: (xcd, first row of the tile, z, parts of the tile, slot)."""
-    tm_live, dtc = cdiv(nv, 384), cdiv(d, 256)
-    t = tm_live * dtc
-
-    def c0(x):
-        return (x * t) >> 3
-
-    def parts(nt):
-        return min(8, 32 // nt) if 0 < nt <= 16 else 1
-
-    tails = [(c0(x + 1) - c0(x)) & 31 for x in range(8)]
-    if sum((parts(nt) - 1) * nt for nt in tails) * 384 * 256 > (acc_rows - tm_live * 384) * d:
-        return []
-    out, slot0 = [], 0
-    for x in range(8):
-        n = c0(x + 1) - c0(x)
-        nmain, nt = n & ~31, n & 31
-        kz = parts(nt)
-        for z in range(1, kz):
-            for ti in range(nt):
-                l = c0(x) + nmain + ti
-                band, = divmod(l, 4 * dtc)[:1]
-                r0 = band * 4
-                rows = min(4, tm_live - r0)
-                tm = r0 + (l - band * 4 * dtc) % rows
-                out.append((x, tm * 384, z, kz, slot0 + (z - 1) * nt + ti))
-        slot0 += (kz - 1) * nt
-    return out
+    """The K parts z >= 1 of the tail tiles of a dH launch the host did not split: (xcd, first row of
+    the tile, z, parts of the tile, slot)."""
+    return [(blk & 7, tm * 384, z, kz, slot) for blk, tm, _, z, kz, slot in T.dh_units(nv, nv, d, 1, acc_rows) if z]
 
 
 def walk(n, d, v, nv, ld_h=None, ld_w=None):
@@ -93,8 +73,7 @@ def walk(n, d, v, nv, ld_h=None, ld_w=None):
              "idx": 4 * npad, "pos": 4 * npad, "hv": 2 * npad * d,
              "pm": 4 * info["part_rows"] * npad, "ps": 4 * info["part_rows"] * npad, "terms": 4 * npad,
              "G": 2 * rows_g * vc, "dh32": 4 * rows_g * d * info["dh_kz"]}
-    twelve = d % 64 == 0
-    tm_rows = 384 if twelve else 256          # vocabulary (A) rows of a forward / G tile
+    nt, vt3 = cdiv(nv, 256), cdiv(v, 384)
 
     # compaction: idx[0..nv), pos[0..n), the targets
     if nv:
@@ -107,25 +86,47 @@ def walk(n, d, v, nv, ld_h=None, ld_w=None):
         last = min(v0 + rows, v) - 1
         e.touch("W", 2 * (last * ld_w + d))
 
+    def part_box(p):
+        """First id and token of a tile's part, relative to the launch, and its ids and tokens."""
+        tm, tn, parts, part = p
+        ih, th = (part & 1, part >> 1) if parts > 1 else (0, 0)
+        ids = 192 if parts > 1 else 384
+        n0 = tn * 256 + th * 128
+        wide = nv - tn * 256 > 128 and parts < 4
+        return tm * 384 + ih * 192, n0, ids, 256 if wide else 128
+
+    def hv_tile(n0, rows):
+        # a tile's dense rows, those past Nv included
+        e.touch("hv", 2 * (n0 + rows) * d)
+
     # forward statistics
     if nv:
-        if twelve and info["fwd_gathers"]:
-            e.touch("hv", 2 * rup(nv, 64) * d)                      # gather, zero rows to a multiple of 64
-            for n0 in range(0, nv, 256):
-                e.touch("hv", 2 * (n0 + 256) * d)                   # B: 256 dense rows of Hv
-            for v0 in range(0, v, 384):
-                w_rows(v0, 384)
-            vt3 = cdiv(v, 384)
-            if info["fwd_one_launch"]:
-                e.touch("pm", 4 * ((vt3 - 1) * npad + nv))
-            else:
-                gw = (info["part_rows"] - 1) // 2
-                e.touch("pm", 4 * (2 * gw * npad + nv))             # running pair after the two row sets
+        e.touch("H", 2 * ((n - 1) * ld_h + d))                      # rows gathered through idx (< n)
+        e.touch("hv", 2 * rup(nv, 64) * d)                          # gather, zero rows to a multiple of 64
+        if info["fwd_one_launch"]:
+            cut = vt3 * (npad // 256) <= 4096                       # the launch may be cut (of up to 2048 live tiles)
+            grid, gw = T.tile_order(vt3, npad // 256, vt3, cut)
+            second = T.tail_parts(T.tile_space(vt3, nt), cut) > 1   # a second row per tile
+            for b in range(grid) if vt3 * nt <= 4096 else ():
+                p = T.tile_part(b, vt3, gw, nt, cut)
+                if p is None:
+                    continue
+                v0, n0, ids, toks = part_box(p)
+                if n0 >= nv:
+                    continue
+                row = p[0] + (vt3 if p[2] > 1 and p[3] & 1 else 0)
+                if v0 < v:
+                    w_rows(v0, ids)
+                hv_tile(n0, toks)
+                e.touch("pm", 4 * (row * npad + min(n0 + toks, nv)))
+                if second and p[2] == 1:                            # an empty pair beside a whole tile's
+                    e.touch("pm", 4 * ((row + vt3) * npad + min(n0 + 256, nv)))
+            e.touch("pm", 4 * (((2 if second else 1) * vt3 - 1) * npad + nv))       # the merge reads these rows
         else:
-            e.touch("H", 2 * ((n - 1) * ld_h + d))                  # rows gathered through idx (< n)
-            for v0 in range(0, v, 256):
-                w_rows(v0, 256)
-            e.touch("pm", 4 * ((2 * min(cdiv(v, 256), 32) - 1) * npad + nv))
+            gw = (info["part_rows"] - 1) // 2
+            e.touch("pm", 4 * (2 * gw * npad + nv))                 # running pair after the two row sets
+        w_rows(0, vt3 * 384)
+        hv_tile(0, nt * 256)
         e.touch("ps", e.ends["pm"])
         e.touch("terms", 4 * nv)
         e.touch("lse", 4 * n)
@@ -139,38 +140,35 @@ def walk(n, d, v, nv, ld_h=None, ld_w=None):
         vs = min(vc, v - v0)
         if not nv:
             continue
-        # G tiles: W rows v0 + [vt0, vt0 + tm_rows) (masked past V), Hv / gathered H rows, G written whole
-        for vt0 in range(0, vs, tm_rows):
-            w_rows(v0 + vt0, tm_rows)
-            for n0 in range(0, nv, 256):
-                if twelve:
-                    e.touch("hv", 2 * (n0 + 256) * d)
-                e.touch("G", 2 * ((n0 + 255) * vc + vt0 + tm_rows))
+        # G: W rows v0 + [vt0, vt0 + ids) (masked past V), Hv rows; a tile or part is written whole
+        tmg = cdiv(vs, 384)
+        grid, gw = T.tile_order(tmg, npad // 256, tmg, True)
+        for b in range(grid) if tmg * nt <= 4096 else ():
+            p = T.tile_part(b, tmg, gw, nt)
+            if p is None:
+                continue
+            vt0, n0, ids, toks = part_box(p)
+            if n0 >= nv or vt0 >= vs:
+                continue
+            w_rows(v0 + vt0, ids)
+            hv_tile(n0, toks)
+            e.touch("G", 2 * ((n0 + toks - 1) * vc + vt0 + ids))
+        w_rows(v0, tmg * 384)
+        e.touch("G", 2 * ((nt * 256 - 1) * vc + tmg * 384))
         # dH: 384-row tiles of G rows, K over [k0, k0 + kzn), W slab rows v0 + k (< v0 + vs), columns < d
-        kt = rup(vs, 64)
-
-        def dh_part(m0, z, kz, acc_end):
-            kh = rup(cdiv(kt, kz), 64)
-            k0 = z * kh
-            kzn = min(vs - k0, kh)
-            e.touch("dh32", acc_end)            # read-modify-write of the part's accumulator block
+        seen = set()
+        for _, tm, _, z, kz, slot in T.dh_units(n, nv, d, dh_kz, rows_g):
+            if (tm, z, kz, slot) in seen:
+                continue
+            seen.add((tm, z, kz, slot))
+            k0, kzn = T.dh_k_range(vs, kz, z)
+            # read-modify-write of the block: rows of the tile in accumulator z (the parts follow each other), or
+            # a 384 x 256 slot past the live tiles' rows
+            e.touch("dh32", 4 * ((z * rows_g if slot < 0 else 0) + tm * 384 + 384) * d if slot < 0
+                    else 4 * (cdiv(nv, 384) * 384 * d + (slot + 1) * 384 * 256))
             if kzn > 0:
-                e.touch("G", 2 * ((m0 + 383) * vc + k0 + kzn))
+                e.touch("G", 2 * ((tm * 384 + 383) * vc + k0 + kzn))
                 w_rows(v0 + k0, kzn)
-
-        if dh_kz > 1:
-            for z in range(dh_kz):
-                for m0 in range(0, nv, 384):
-                    # the tile's rows in accumulator z (the parts follow each other)
-                    dh_part(m0, z, dh_kz, 4 * (z * rows_g + m0 + 384) * d)
-        else:
-            # device-side split of each XCD's last partial round (dh_tile): part 0 in the tile's rows,
-            # parts z >= 1 in 384 x 256 slots after row tm_live * 384
-            tm_live, dtc = cdiv(nv, 384), cdiv(d, 256)
-            for m0 in range(0, nv, 384):
-                dh_part(m0, 0, 1, 4 * (m0 + 384) * d)
-            for x, m0, z, kz, slot in dh_tail_parts(nv, d, rows_g):
-                dh_part(m0, z, kz, 4 * (tm_live * 384 * d + (slot + 1) * 384 * 256))
         # dW: G and Hv read K-major over round_up(Nv, 64) token rows; dW rows of the slab only
         kpad = rup(nv, 64)
         for m0 in range(0, vs, 384):
@@ -245,6 +243,18 @@ def test_the_walk_flags_regions_sized_to_npad_rows():
             e.check(short, "npad rows")
 
 
+@pytest.mark.parametrize("n,d,v,nv", [(1000, 1000, 32003, 900), (4096, 8192, 16032, 3276), (256, 512, 4096, 230),
+                                      (900, 2048, 32000, 900)])
+def test_the_walk_flags_partial_rows_without_the_second_set(n, d, v, nv):
+    # launches whose last tiles are cut write two partial rows per tile
+    e, sizes, info = walk(n, d, v, nv)
+    vt3 = cdiv(v, 384)
+    assert T.tail_parts(T.tile_space(vt3, cdiv(nv, 256))) > 1
+    for buf in ("pm", "ps"):
+        with pytest.raises(AssertionError, match=buf):
+            e.check(dict(sizes, **{buf: 4 * vt3 * info["npad"]}), "one row per tile")
+
+
 @pytest.mark.parametrize("n,d,v,nv", [(12288, 2048, 1000, 300), (12288, 2048, 1000, 1400), (12288, 2048, 1000, 3686),
                                       (12288, 2048, 1000, 4423), (8192, 4096, 1000, 6209),
                                       (32768, 3584, 152064, 22936), (16384, 8192, 128256, 13107)])
@@ -261,40 +271,22 @@ def test_split_dh_tails_stay_inside_the_accumulator(n, d, v, nv):
 
 @pytest.mark.parametrize("nv,d", [(300, 2048), (3686, 2048), (22936, 3584), (13107, 8192), (12288, 4096), (1, 64)])
 def test_split_dh_blocks_cover_every_tile_and_k_part_once(nv, d):
-    # the blocks of a launch the host did not split, as dh_tile maps them: every live tile once,
-    # with parts 0 .. kz - 1 of one kz
+    # the blocks of a launch the host did not split, with room for every slot: every live tile once, with parts
+    # 0 .. kz - 1 of one kz, whose K ranges are disjoint and cover the slab
     tm_live, dtc = cdiv(nv, 384), cdiv(d, 256)
-    t = tm_live * dtc
     rows_g = rup(rup(max(nv, 1), 256), 384) + 384 * 64
-    tails = {(p[1] // 384, p[2]): p[3] for p in dh_tail_parts(nv, d, rows_g)}
-    seen = {}
-    for x in range(8):
-        c0, c1 = (x * t) >> 3, ((x + 1) * t) >> 3
-        for l in range(c0, c1):
-            band = l // (4 * dtc)
-            rows = min(4, tm_live - band * 4)
-            k = l - band * 4 * dtc
-            seen.setdefault((band * 4 + k % rows, k // rows), set()).add(0)
-    assert sorted(seen) == sorted((tm, tn) for tm in range(tm_live) for tn in range(dtc))
-    for (tm, z), kz in tails.items():
-        assert 1 <= z < kz <= 8
-
-
-def dw_block_tile(blk, tm_count, d):
-    """The dW tile of block blk as dw_tile maps it (None: the block has no tile): the slab's
-    tm_count x ceil(D / 256) tiles cut evenly over the 8 XCDs, bands of 4 row tiles walked column
-    by column."""
-    dtc = cdiv(d, 256)
-    t = tm_count * dtc
-    x, k = blk & 7, blk >> 3
-    c0, c1 = (x * t) >> 3, ((x + 1) * t) >> 3
-    if k >= c1 - c0:
-        return None
-    l = c0 + k
-    band = l // (4 * dtc)
-    rows = min(4, tm_count - band * 4)
-    kk = l - band * 4 * dtc
-    return band * 4 + kk % rows, kk // rows
+    seen, slots = {}, []
+    for _, tm, tn, z, kz, slot in T.dh_units(nv, nv, d, 1, rows_g):
+        seen.setdefault((tm, tn, kz), []).append(z)
+        assert (slot >= 0) == (z > 0)
+        slots += [slot] if z else []
+    assert sorted(k[:2] for k in seen) == sorted((tm, tn) for tm in range(tm_live) for tn in range(dtc))
+    assert all(sorted(z) == list(range(k[2])) and k[2] <= 8 for k, z in seen.items())
+    assert sorted(slots) == list(range(len(slots)))
+    for kz in {k[2] for k in seen} | {1, 3, 8}:
+        for vs in (1, 63, 64, 1000, 16032, 18432):
+            ids = [i for z in range(kz) for k0, k in [T.dh_k_range(vs, kz, z)] for i in range(k0, k0 + max(k, 0))]
+            assert ids == list(range(vs))
 
 
 @pytest.mark.parametrize("tm_count,d", [(48, 4096), (54, 3584), (18, 3584), (64, 2048), (14, 2048), (96, 8192),
@@ -302,8 +294,8 @@ def dw_block_tile(blk, tm_count, d):
 def test_dw_blocks_cover_every_tile_once_in_balanced_xcd_shares(tm_count, d):
     dtc = cdiv(d, 256)
     t = tm_count * dtc
-    grid = 8 * cdiv(t, 8)                      # the host's dW grid
-    tiles = [dw_block_tile(b, tm_count, d) for b in range(grid)]
+    grid = T.dw_grid(tm_count, d)
+    tiles = [T.dw_unit(b, tm_count, d) for b in range(grid)]
     live = [tt for tt in tiles if tt is not None]
     assert sorted(live) == sorted((tm, tn) for tm in range(tm_count) for tn in range(dtc))
     per_xcd = [sum(tiles[b] is not None for b in range(x, grid, 8)) for x in range(8)]
@@ -335,36 +327,13 @@ def test_the_slab_width_gives_the_dw_launches_the_fewest_rounds_in_its_range(d, 
         assert dw_rounds(v, d, vc // 384) == cdiv(cdiv(v, 384) * cdiv(d, 256), 256) == 22
 
 
-def xcd_tile(b, tiles, gw, nt):
-    """The (vocabulary tile, token tile) of block b of a forward or G launch, as xcd_tile maps it."""
-    a = tiles & ~7
-    ba = a * nt
-    if b < ba:
-        full, g = a // gw, b // (gw * nt)
-        wl = gw if g < full else a - full * gw
-        r = b - g * gw * nt
-        return g * gw + r % wl, r // wl
-    rem, r = tiles - a, b - ba
-    if rem == 0:
-        return None
-    k = r >> 3
-    tn = (r & 7) + 8 * (k // rem)
-    return (a + k % rem, tn) if tn < nt else None
-
-
-def tile_order(tiles, nt, width):
-    a = tiles & ~7
-    rem = tiles - a
-    return a * nt + (8 * rem * cdiv(nt, 8) if rem else 0), max(8, min(width, a) & ~7)
-
-
 @pytest.mark.parametrize("tiles,nt,width", [(334, 48, 48), (54, 90, 54), (46, 48, 46), (96, 52, 24), (64, 24, 64),
                                             (12, 1, 12), (11, 2, 11), (3, 5, 3), (72, 64, 72), (17, 9, 17), (1, 1, 1),
                                             (8, 7, 8), (40, 33, 16)])
 def test_forward_and_g_blocks_cover_every_tile_once_and_keep_w_tiles_on_one_xcd(tiles, nt, width):
-    grid, gw = tile_order(tiles, nt, width)
+    grid, gw = T.tile_order(tiles, nt, width)
     assert gw % 8 == 0
-    got = [xcd_tile(b, tiles, gw, nt) for b in range(grid)]
+    got = [T.xcd_tile(b, tiles, gw, nt) for b in range(grid)]
     live = [t for t in got if t is not None]
     assert sorted(live) == [(tm, tn) for tm in range(tiles) for tn in range(nt)]
     a = tiles & ~7
@@ -400,19 +369,9 @@ def test_few_token_calls_take_the_fewest_equal_slabs_within_the_budget(n, d, v, 
 
 
 def dh_split_blocks(n, nv, d, kz_max):
-    """(row tile, column tile, K part, parts) of every block of a split dH launch, as dh_tile maps them."""
-    tm_live, dtc = cdiv(nv, 384), cdiv(d, 256)
-    t = tm_live * dtc
-    kz = min(range(1, kz_max + 1), key=lambda k: (cdiv(t * k, 256) / k, k))
-    u = t * kz
-    for blk in range(rup(kz_max * cdiv(rup(n, 256), 384) * dtc, 8)):          # the host's dH grid
-        x, l = blk & 7, ((blk & 7) * u >> 3) + (blk >> 3)
-        if l >= ((x + 1) * u) >> 3:
-            continue
-        z, l = divmod(l, t)
-        band, k = divmod(l, 4 * dtc)
-        rows = min(4, tm_live - band * 4)
-        yield x, band * 4 + k % rows, k // rows, z, kz
+    """(xcd, row tile, column tile, K part, parts) of every block of a split dH launch."""
+    for blk, tm, tn, z, kz, _ in T.dh_units(n, nv, d, kz_max, rup(rup(n, 256), 384)):
+        yield blk & 7, tm, tn, z, kz
 
 
 @pytest.mark.parametrize("n,d", [(256, 512), (1, 64), (700, 264), (2048, 4096), (1948, 3584), (4096, 2048), (4096, 4096),
@@ -432,24 +391,20 @@ def test_split_dh_launches_cover_every_tile_and_part_once_on_all_xcds(n, d):
 
 @pytest.mark.parametrize("d", [8, 56, 64, 72, 264, 1000, 1016])
 def test_the_tail_mask_keeps_row_major_loads_inside_their_rows(d):
-    # the last K slice of a width that is not a multiple of 64, as mask_tail and load_operand form it: lane j of
-    # a wave loads row j // 8 of each of 4 groups of 8 rows, chunk ce for even groups and ce ^ 1 for odd ones (a
-    # dense operand takes the odd one's offset, mask included, from lane j ^ 1); every chunk below d is loaded
-    # once per row and none at or past d
+    # the last K slice of a width that is not a multiple of 64: lane j of a wave loads row j // 8 of each of 4
+    # groups of 8 rows, chunk lane_chunk(j) for even groups and that ^ 1 for odd ones (a dense operand takes the odd
+    # one's offset, mask included, from lane j ^ 1); every chunk below d is loaded once per row and none past d
     k0 = (cdiv(d, 64) - 1) * 64
-
-    def ce(j):
-        return (j & 7) ^ ((j >> 3) & 7)
-
     for dense in (True, False):
         for q in range(4):
             got = {}
             for j in range(64):
-                src = j ^ (q & 1) if dense else j           # whose offset register is used
-                chunk = ce(src) if dense else ce(j) ^ (q & 1)
-                masked = k0 + chunk * 8 >= d
-                assert chunk == ce(j) ^ (q & 1) and src // 8 == j // 8
-                if not masked:
+                src, sq = (j ^ (q & 1), 0) if dense else (j, q)     # whose offset register is used, and its group
+                assert src // 8 == j // 8
+                chunk = T.lane_chunk(src) ^ (sq & 1)
+                assert chunk == T.lane_chunk(j) ^ (q & 1)
+                assert T.chunk_exists(src, sq, k0, d) == (k0 + 8 * chunk < d)
+                if T.chunk_exists(src, sq, k0, d):
                     got.setdefault(j // 8, []).append(chunk)
             for row in range(8):
                 assert sorted(got.get(row, [])) == list(range(cdiv(d - k0, 8)))
@@ -477,34 +432,13 @@ def test_a_workspace_of_the_former_ragged_width_size_still_serves_the_forward(n,
     assert e.value.code == B.LCE_ERR_WORKSPACE
 
 
-def tile_part(b, tiles, gw, nt, split=True):
-    """The (vocabulary tile, token tile, parts, part) of block b of a split forward or G launch, as tile_part maps
-    it: the last, partial round of 256 tiles in 2 parts per tile (up to 128 tiles) or 4 (up to 64)."""
-    a = tiles & ~7
-    t = a * nt + (tiles - a) * rup(nt, 8)
-    rem = t & 255
-    parts = 1 if not split or t > 2048 or rem == 0 or rem > 128 else (2 if rem > 64 else 4)
-    whole = t & ~255 if parts > 1 else t
-    part, n = 0, 1
-    l = b
-    if b >= whole:
-        if parts == 1:
-            return None
-        j = b - whole
-        l, n, part = whole + j // (8 * parts) * 8 + (j & 7), parts, (j >> 3) % parts
-    if l >= t:
-        return None
-    got = xcd_tile(l, tiles, gw, nt)
-    return None if got is None else (*got, n, part)
-
-
 @pytest.mark.parametrize("tiles,nt", [(1, 1), (3, 1), (7, 9), (8, 1), (11, 1), (42, 13), (64, 1), (65, 2), (84, 10), (128, 2),
                                       (129, 2), (167, 1), (334, 2), (334, 6), (17, 16), (256, 8), (333, 7)])
 def test_split_launches_cover_every_part_once_and_keep_a_tile_on_one_xcd(tiles, nt):
-    grid, gw = tile_order(tiles, nt, tiles)
+    grid, gw = T.tile_order(tiles, nt, tiles, True)
     seen, xcd = {}, {}
-    for b in range(grid + 256):
-        p = tile_part(b, tiles, gw, nt)
+    for b in range(grid):
+        p = T.tile_part(b, tiles, gw, nt)
         if p is None:
             continue
         tm, tn, parts, part = p
@@ -627,3 +561,19 @@ def test_distillation_workspaces_of_the_former_sizes_still_hold_every_call(dt):
         assert b <= bwd + p_bytes + hvt, (n, d, v)
         full = B.lce_kd_workspace_size(B.kd_problem(n, d, dt, v))
         assert f <= full[0] and b <= full[1] == B.lce_kd_workspace_size_fused(B.kd_problem(n, d, dt, v))
+
+
+@pytest.mark.parametrize("n,d,v,nv", [(16384, 256, 8192, 12288), (9000, 512, 3001, 420), (9000, 512, 20000, 420),
+                                      (2048, 4096, 64512, 1536), (16384, 4096, 18432, 12288), (300, 264, 1000, 300), (700, 64, 500, 0)])
+def test_the_merged_launch_runs_every_block_of_both_and_starts_the_longer_units(n, d, v, nv):
+    info = B.lce_plan_info(B.problem(n, d, v))
+    dh, dw = T.dh_grid(n, d, info["dh_kz"]), T.dw_grid(cdiv(v, 384), d)
+    first = T.dw_first(nv, d, info["dh_kz"], v)
+    got = [T.dhdw_block(b, dh, dw, first) for b in range(dh + dw)]
+    assert sorted(got) == list(range(dh + dw))
+    for b, g in enumerate(got):
+        assert (g if g < dh else g - dh) % 8 == b % 8              # each block of either launch keeps its XCD
+    units = [u for u in (T.dh_unit(b, nv, d, info["dh_kz"], info["rows_g"]) for b in range(dh)) if u]
+    parts = units[0][3] if units and info["dh_kz"] > 1 else 1
+    assert first == (nv * parts > v)                                # dW's K against that of a dH unit
+    assert (got[0] >= dh) == first
