@@ -161,7 +161,7 @@ typedef struct lce_plan_info {
   int64_t vc, nslab;        /* backward slab width (ids) and slab count */
   int64_t dh_kz;            /* most K parts of a dH launch: 1, or up to 8 for launches with few tiles */
   int64_t part_rows;        /* partial rows of the forward statistics */
-  int64_t fwd_gathers;      /* 1 if d % 64 == 0: the gathered rows the forward leaves in the prefix are whole K slices */
+  int64_t fwd_gathers;      /* 1: the forward leaves the gathered rows of H in the prefix (at every width) */
   int64_t fwd_one_launch;   /* 1 if the forward statistics run as one launch */
   int64_t o_idx, o_pos, o_nv, o_hv;
   int64_t o_pm, o_ps, o_terms, fwd_bytes;

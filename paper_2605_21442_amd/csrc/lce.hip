@@ -1317,9 +1317,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_kd_tile(const uint16_t* __r
   // block (i, j) is 1 KB, 16 bytes a lane. Producer and consumer move 16 bytes per lane and whole lines
   // (id-major rows of P took 4 bytes per lane and two 128-byte pieces per instruction).
   const int wr_u = __builtin_amdgcn_readfirstlane(wr), wc_u = __builtin_amdgcn_readfirstlane(wc);
-  float* punit = nullptr;
-  if constexpr (kMode == P_WRITE || kMode == Z_WRITE || kMode == G_SOFT || kMode == KD_STATS)
-    punit = P + ((int64_t)(vt0 / 128 + wr_u) * (ldt / 64) + (n0 / 64 + wc_u)) * (128 * 64);
+  float* punit = P + ((int64_t)(vt0 / 128 + wr_u) * (ldt / 64) + (n0 / 64 + wc_u)) * (128 * 64);
   // The student's epilogues take block b + 1's loads in flight while they use block b = 4 j + i (kF: no test
   // per element; else `absent` stands for ids past the slab and tokens past Nv).
   auto load_teacher = [&](float (&x)[16], int b, auto kFull, float absent) {
@@ -1442,7 +1440,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_kd_tile(const uint16_t* __r
   auto fill = [&](auto kFull) {
     constexpr bool kF = decltype(kFull)::value;
     float pt[2][16];
-    if constexpr (kMode == G_SOFT) load_teacher(pt[0], 0, kFull, 0.f);
+    load_teacher(pt[0], 0, kFull, 0.f);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const bool tok_ok = kF || tok[j] < nv;
@@ -1450,9 +1448,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_kd_tile(const uint16_t* __r
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int blk = 4 * j + i;
-        if constexpr (kMode == G_SOFT) {
-          if (blk < 7) load_teacher(pt[(blk + 1) & 1], blk + 1, kFull, 0.f);
-        }
+        if (blk < 7) load_teacher(pt[(blk + 1) & 1], blk + 1, kFull, 0.f);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           float gq[4];
@@ -2677,7 +2673,7 @@ lce_status_t lce_plan_info(const lce_problem_t* p, lce_plan_info_t* out) {
   out->nslab = pl.nslab;
   out->dh_kz = pl.dh_kz;
   out->part_rows = pl.part_rows;
-  out->fwd_gathers = pl.d % KSLICE == 0 ? 1 : 0;
+  out->fwd_gathers = 1;
   out->fwd_one_launch = pl.one_launch ? 1 : 0;
   out->o_idx = (int64_t)pl.o_idx;
   out->o_pos = (int64_t)pl.o_pos;

@@ -99,7 +99,7 @@ def test_the_forward_and_backward_share_the_prefix_the_reuse_flag_relies_on(n, d
     assert info["o_idx"] < info["o_pos"] < info["o_nv"] < info["o_hv"]
     prefix_end = info["o_hv"] + 2 * d * info["npad"]
     assert info["o_pm"] >= prefix_end and info["o_g"] >= prefix_end
-    assert info["fwd_gathers"] == (1 if d % 64 == 0 else 0)
+    assert info["fwd_gathers"] == 1                 # at every width
 
 
 def _fake(addr=0x100000):

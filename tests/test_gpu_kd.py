@@ -2,8 +2,7 @@
 
 Student and teacher heads of different hidden sizes over one vocabulary, ragged tiles, several
 vocabulary slabs, temperatures 1 and 2, every reduction, empty and fully masked batches. The
-heads' statistics run on 12-wave tiles (D % 64 == 0), 8-wave tiles, or one of each, and with
-D = 64 and 9000 ids in one launch per group of tiles (the student's layout serves both heads).
+teacher's tiles are 12-wave ones (Dt % 64 == 0) or 8-wave ones like the student's.
 Tolerances as for LCE: loss 1e-3 absolute (per token for "none"), lse 1e-3, relative Frobenius
 1e-2 on dHs and dWs.
 """

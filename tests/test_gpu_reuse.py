@@ -1,7 +1,7 @@
 """The backward with LCE_FLAG_REUSE_FORWARD (it takes the valid-row list and gathered rows of H that
 the preceding forward left in the shared workspace) gives the same bits as the backward that forms
-them itself, for the plain, vocabulary-shard and in-backward AdamW calls, at widths where the
-forward gathers the rows (D % 64 == 0) and where it does not."""
+them itself, for the plain, vocabulary-shard and in-backward AdamW calls, at widths of whole K
+slices (D % 64 == 0) and ragged ones."""
 import numpy as np
 import pytest
 
