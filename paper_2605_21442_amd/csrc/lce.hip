@@ -936,12 +936,12 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
 // ---------------------------------------------------------------------------------------------
 // K3: per valid token: merge the vocabulary partials into lse, take the target logit
 // s[n, t_n] = H[n] . W[t_n] in fp32, and the per-row loss l_n = lse_n - s[n, t_n].
-// A workgroup of 16 waves serves kTok consecutive tokens, 16 or 64. Its waves first take the target logits, a
-// wave-wide dot product each; then a wave's 64 / kTok groups of lanes fold a partial row each (reads along the
-// tokens), and the groups and the waves are merged in a fixed order. Bound by latency (few tokens) or by
-// the partials' bytes. With 64 tokens a workgroup, a wave folds a quarter as many rows in parallel and takes
-// four dot products in turn: 496 valid tokens of 2048 x 128256 are 8 workgroups, 40 us against 16; 12288
-// of 4096 x 128256 62 against 53. Many tokens of a narrow head with few rows to fold prefer it (wide_combine).
+// A workgroup of 16 waves serves kTok consecutive tokens, 16 or 64. Its waves first take the target logits of
+// kTok / 16 tokens each, wave-wide dot products; then a wave's 64 / kTok groups of lanes fold a partial row each
+// (reads along the tokens), and the groups and the waves are merged in a fixed order. Bound by latency (few
+// tokens) or by the partials' bytes. With 64 tokens a workgroup, a wave folds a quarter as many rows in
+// parallel: 496 valid tokens of 2048 x 128256 are 8 workgroups, 59 us against 20; 12288 of 4096 x 128256 73
+// against 56. Many tokens of a narrow head prefer it (wide_combine).
 // ---------------------------------------------------------------------------------------------
 template <int kTok>
 __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H, int64_t ldh,
@@ -961,28 +961,39 @@ __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H
   const int i0 = blockIdx.x * kTok;
   const int nv = *nv_ptr;
   if (i0 >= nv) return;
-  for (int w = wave; w < kTok && i0 + w < nv; w += 16) {
-    const int row = idx[i0 + w];
-    // target id relative to this W's first row (id0 > 0 only for a vocabulary shard, which may
-    // not hold the target: then its target logit is 0)
-    const int64_t tl = load_target(targets, tbytes, row) - id0;
-    float dot = 0.f;
-    if (tl >= 0 && tl < v_local) {
-      const uint4* hr = reinterpret_cast<const uint4*>(H + (int64_t)row * ldh);
-      const uint4* wt = reinterpret_cast<const uint4*>(W + tl * ldw);
-#pragma unroll 4
-      for (int c = lane; c < d / 8; c += 64) {
-        const uint4 a = hr[c], b = wt[c];
-        const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+  // this wave's kTok / 16 tokens side by side, so that their chains of loads (row, target, operands) overlap
+  constexpr int kPer = kTok / 16;
+  int row_p[kPer];
+  int64_t tl[kPer];
+  float dot_p[kPer];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          dot = fmaf(bf16_to_f32(av[q] & 0xFFFF), bf16_to_f32(bv[q] & 0xFFFF), dot);
-          dot = fmaf(bf16_to_f32(av[q] >> 16), bf16_to_f32(bv[q] >> 16), dot);
-        }
+  for (int p = 0; p < kPer; ++p) row_p[p] = i0 + wave * kPer + p < nv ? idx[i0 + wave * kPer + p] : -1;
+  // target id relative to this W's first row (id0 > 0 only for a vocabulary shard, which may
+  // not hold the target: then its target logit is 0)
+#pragma unroll
+  for (int p = 0; p < kPer; ++p) {
+    tl[p] = row_p[p] >= 0 ? load_target(targets, tbytes, row_p[p]) - id0 : -1;
+    dot_p[p] = 0.f;
+  }
+#pragma unroll kPer == 1 ? 4 : 1
+  for (int c = lane; c < d / 8; c += 64) {
+#pragma unroll
+    for (int p = 0; p < kPer; ++p) {
+      if (tl[p] < 0 || tl[p] >= v_local) continue;
+      const uint4 a = reinterpret_cast<const uint4*>(H + (int64_t)row_p[p] * ldh)[c];
+      const uint4 b = reinterpret_cast<const uint4*>(W + tl[p] * ldw)[c];
+      const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        dot_p[p] = fmaf(bf16_to_f32(av[q] & 0xFFFF), bf16_to_f32(bv[q] & 0xFFFF), dot_p[p]);
+        dot_p[p] = fmaf(bf16_to_f32(av[q] >> 16), bf16_to_f32(bv[q] >> 16), dot_p[p]);
       }
-      dot = wave_sum(dot);
     }
-    if (lane == 0) dots[w] = dot;
+  }
+#pragma unroll
+  for (int p = 0; p < kPer; ++p) {
+    const float dot = wave_sum(dot_p[p]);
+    if (lane == 0) dots[wave * kPer + p] = dot;
   }
   const int i = i0 + t;
   const int rows = tail_parts(tile_space(tiles, (nv + TILE - 1) / TILE), split) > 1 ? 2 * tiles : tiles;
@@ -2190,12 +2201,11 @@ unsigned adamw_grid(int64_t v, int64_t d) {
   return (unsigned)(blocks < 16384 ? blocks : 16384);
 }
 
-// k_combine with 64 tokens a workgroup: short dot products, few partial rows, and enough workgroups all the
-// same. 64 tokens against 16: 16384 tokens of 256 / 512 / 768 / 1024 x 8192 14 / 14 / 16 / 17 us against
-// 15 / 16 / 20 / 19, 32768 tokens 20 / 20 / 24 / 26 against 25 / 24 / 28 / 32, and x 32768 25 / 26 / 30 / 31
-// against 30 / 29 / 36 / 35; but 16384 tokens x 128256 30 / 29 / 36 / 38 against 28 / 27 / 33 / 41, 8192
-// tokens x 128256 29 to 35 against 20 to 24, and 24576 x 2048 x 32768 48 against 41.
-inline bool wide_combine(const Plan& pl) { return pl.n > 12288 && pl.d <= 1536 && pl.vt_count3 <= 128; }
+// k_combine with 64 tokens a workgroup: enough workgroups all the same, and dot products so short that four side by
+// side fill a wave's loads. 64 tokens against 16: 32768 tokens of 256 / 1024 / 2048 x 5000 ids 14 / 22 / 34 us
+// against 21 / 25 / 36, x 32768 17 / 26 / 44 against 23 / 29 / 46, x 128256 28 / 47 / 73 against 37 / 47 / 73; but
+// 16384 tokens of 256 / 1024 / 2048 x 128256 24 / 36 / 49 against 20 / 29 / 37, and fewer tokens more so.
+inline bool wide_combine(const Plan& pl) { return pl.n > 16384 && pl.d <= 1536; }
 
 struct Launcher {
   hipStream_t s;

@@ -261,11 +261,11 @@ def test_a_device_without_room_for_the_wide_slabs_takes_the_least_workspace(monk
         assert float((a - b).norm() / a.norm()) <= 1e-3 and bool(torch.isfinite(b).all())
 
 
-@pytest.mark.parametrize("n,d,v,nv", [(12289, 64, 3000, 1), (12289, 64, 3000, 700), (13000, 200, 49000, 64), (12500, 1536, 2000, 65),
-                                      (12288, 64, 3000, 700), (12289, 1544, 2000, 65), (12289, 64, 49153, 63)])
+@pytest.mark.parametrize("n,d,v,nv", [(16385, 64, 3000, 1), (16385, 64, 3000, 700), (17000, 200, 49000, 64), (16500, 1536, 2000, 65),
+                                      (16384, 64, 3000, 700), (16385, 1544, 2000, 65), (16385, 64, 60001, 63)])
 def test_both_widths_of_the_partials_merge_match_the_oracle(n, d, v, nv):
-    # 64 tokens a workgroup from 12289 tokens on, up to 1536 wide and 128 tiles of 384 ids, and 16 just outside; 1
-    # to 65 valid tokens, and the least workspace's running pairs folded in first
+    # 64 tokens a workgroup from 16385 tokens on, up to 1536 wide, and 16 just outside; 1 to 65 valid tokens, and
+    # the least workspace's running pairs folded in first
     import torch
     rng = np.random.default_rng([n, d, nv])
     t = np.full(n, -100, dtype=np.int32)
