@@ -90,12 +90,11 @@ typedef struct lce_problem {
  * lce_backward_adamw rejects it (one update per backward pass). */
 #define LCE_FLAG_ACCUMULATE_DW 1
 
-/* For lce_backward, lce_backward_select, lce_backward_adamw and lce_backward_shard: the workspace still holds what the
- * immediately preceding lce_forward (or lce_forward_shard, then lce_combine_shards) of the same
- * problem, H and targets left in it, on the same stream and with nothing else written to the
- * workspace in between. The backward then reuses that call's valid-row list and gathered valid
- * rows of H instead of forming them again: two fewer kernels
- * per step. Without the flag the backward depends on no earlier call. The forward and the
+/* For lce_backward, lce_backward_select, lce_backward_adamw and lce_backward_shard: the workspace
+ * still holds what the immediately preceding lce_forward (or lce_forward_shard, then
+ * lce_combine_shards) of the same problem, H and targets left in it, on the same stream and with
+ * nothing else written to the workspace in between. The backward then reuses that call's valid-row
+ * list and gathered valid rows of H instead of forming them again: two fewer kernels per step. Without the flag the backward depends on no earlier call. The forward and the
  * combine ignore the flag; the KD calls reject it (LCE_ERR_ARG). The workspace must hold
  * both calls' bytes (it is one buffer). */
 #define LCE_FLAG_REUSE_FORWARD 2
@@ -220,15 +219,15 @@ lce_status_t lce_backward_select(const lce_problem_t* p,
 /*
  * lce_forward for callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): the same computation and outputs as
- * lce_forward, bit for bit, with the workspace taken from a fixed device array inside the library
- * instead of from the caller. The array holds LCE_NOALLOC_SCRATCH_BYTES (256 MiB) on every GPU
+ * lce_forward in a workspace of the reported size, bit for bit, with the workspace taken from a
+ * fixed device array inside the library instead of from the caller. The array holds LCE_NOALLOC_SCRATCH_BYTES (256 MiB) on every GPU
  * the library runs on, from the first call on that GPU until the process ends; problems whose
  * forward workspace (lce_workspace_size's fwd_bytes) is larger are rejected with
  * LCE_ERR_WORKSPACE before anything is launched. (A problem that fits the array in the least
- * form of the forward only takes that form in lce_forward too, and reports its bytes.) The call itself allocates nothing. All calls on
- * one GPU share its array: calls that may overlap on one GPU (on different streams, or from
- * several threads onto different streams) race and must be ordered by the caller; calls on one
- * stream are ordered by it. `stream` must belong to the current device (else LCE_ERR_ARG). The
+ * form of the forward only takes that form in lce_forward too, and reports its bytes.) The call
+ * itself allocates nothing. All calls on one GPU share its array: calls that may overlap on one
+ * GPU (on different streams, or from several threads onto different streams) race and must be
+ * ordered by the caller; calls on one stream are ordered by it. `stream` must belong to the current device (else LCE_ERR_ARG). The
  * backward of a problem forwarded this way is lce_backward with a workspace of its own.
  */
 #define LCE_NOALLOC_SCRATCH_BYTES (256u * 1024u * 1024u)

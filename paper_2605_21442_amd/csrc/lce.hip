@@ -25,17 +25,18 @@
 // Every contraction C = A B^T (C [M, N], sum over K) runs one MFMA main loop: bf16
 // v_mfma_f32_32x32x16 with fp32 accumulation, waves of 128x64 outputs, K streamed through
 // two 64-wide LDS slices filled by direct-to-LDS buffer loads (XOR-swizzled 16-byte
-// chunks). Tiles are 384x256 with 12 waves (three per SIMD) for the LCE contractions, and
-// 256x256 with 8 waves for the distillation student and teachers with Dt % 64 != 0. Each operand is either K-contiguous (W and Hv in
-// the forward and G kernels; G in dH) or K-major (G and Hv in dW, the W slab in dH: the
-// MFMA fragments then come from transposing LDS reads), so G is written once, token-major,
-// and W is never copied.
+// chunks). Tiles are 384x256 with 12 waves (three per SIMD) for the LCE contractions (the last round of
+// a forward or G launch may take parts of them), and 256x256 with 8 waves for the distillation student
+// and teachers with Dt % 64 != 0. Each operand is either K-contiguous (W and Hv in the forward and G
+// kernels; G in dH) or K-major (G and Hv in dW, the W slab in dH: the MFMA fragments then come from
+// transposing LDS reads), so G is written once, token-major, and W is never copied.
 //
 // Launch shapes follow the 8 XCDs, each with its own L2 (workgroups are dealt to them round-
 // robin): the forward and G tiles go in vocabulary groups a multiple of 8 tiles wide, so that each
 // XCD keeps its own W tiles while the token tiles pass (xcd_tile); the dH and dW tiles are cut into
 // balanced per-XCD shares walked in bands of 4 row tiles; and the backward slab width is chosen so
-// that the dW launches fill whole rounds of the 256 CUs (whole_round_slab).
+// that the dW launches fill whole rounds of the 256 CUs (whole_round_slab). Which workgroup takes which
+// tile is in tiles.h.
 
 #include <hip/hip_runtime.h>
 
@@ -398,7 +399,8 @@ __device__ __forceinline__ void load_operand(const Operand& op, const char* dstp
   if constexpr (kKind != OP_KMAJOR) {
     // dense: the odd-q offset of lane L is the even-q offset of lane L ^ 1 (same row, the chunk
     // with the other parity), fetched by a quad swap instead of held in a register
-    const uint32_t odd = kKind == OP_DENSE ? (uint32_t)__builtin_amdgcn_mov_dpp((int)op.off[0], 0xB1, 0xF, 0xF, false) : 0u;
+    const uint32_t odd =
+        kKind == OP_DENSE ? (uint32_t)__builtin_amdgcn_mov_dpp((int)op.off[0], 0xB1, 0xF, 0xF, false) : 0u;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const bool ok = !kMasked || chunk_exists(threadIdx.x & 63, q, k0, K);
@@ -753,11 +755,11 @@ __global__ __launch_bounds__(1024) void k_compact(const void* targets, int tbyte
 // 1000 x 32003 (2549 valid) forward 237 -> 172 us against 256 x 256 tiles of 8 waves that gathered rows
 // in the loop.
 // ---------------------------------------------------------------------------------------------
-// Tiles are taken in the order of xcd_tile (below), in groups of gw vocabulary tiles (the slab
+// Tiles are taken in the order of xcd_tile (tiles.h), in groups of gw vocabulary tiles (the slab
 // rule's width, within the MALL cap, a multiple of 8) by all token tiles, ids fastest: the group's
 // W rows stay in the MALL while the token tiles pass, and the workgroups resident on one XCD share
-// their W and H tiles through its L2 as in the backward's G launches. One launch covers vt_launch tiles from tm0
-// on and writes one partial row per tile (row tm - tm0). When the rows of all tiles would take too
+// their W and H tiles through its L2 as in the backward's G launches. One launch covers vt_launch tiles from
+// tm0 on and writes one partial row per tile (row tm - tm0). When the rows of all tiles would take too
 // much space (plan_forward), the host launches one group at a time instead: group g writes to one of two
 // row sets (by the parity of g), and in launch g >= 1 the workgroup of the group's first tile of each token
 // tile first folds the other set (group g - 1, complete since launches on a stream run in order) into a
@@ -867,8 +869,8 @@ __device__ __forceinline__ void fwd_part(char* smem, const uint16_t* wt, int64_t
   }
 }
 
-// split: the last round's tiles may be cut; the partial rows are then two sets of vt_launch, tile tl writing row
-// tl (the first half of its ids, or all) and row vt_launch + tl (the second half, or an empty pair).
+// split: the last round's tiles may be cut; the partial rows are then two sets of vt_launch, tile tl writing
+// row tl (the first half of its ids, or all) and row vt_launch + tl (the second half, or an empty pair).
 template <bool kTail>
 __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __restrict__ W, int64_t ldw, int v,
                                                             const uint16_t* __restrict__ Hv, int64_t ldh,
@@ -909,9 +911,11 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
   // 190 and 238 -> 213)
   if (p.parts == 1) {
     if (nv - n0 > TILE / 2)
-      fwd_part<kTail, 4, 2>(smem, W + (int64_t)v0 * ldw, ldw, vleft, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os, scale2);
+      fwd_part<kTail, 4, 2>(smem, W + (int64_t)v0 * ldw, ldw, vleft, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os,
+                            scale2);
     else
-      fwd_part<kTail, 4, 1>(smem, W + (int64_t)v0 * ldw, ldw, vleft, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os, scale2);
+      fwd_part<kTail, 4, 1>(smem, W + (int64_t)v0 * ldw, ldw, vleft, Hv + (int64_t)n0 * ldh, ldh, nv - n0, d, om, os,
+                            scale2);
     if (tail_parts(tile_space(vt_launch, nt), split) > 1 && threadIdx.x < TILE && n0 + (int)threadIdx.x < nv) {
       om[(int64_t)vt_launch * npad + threadIdx.x] = -INFINITY;
       os[(int64_t)vt_launch * npad + threadIdx.x] = 0.f;
@@ -929,7 +933,8 @@ __global__ __launch_bounds__(Geo<3>::NT, 3) void k_fwd_tile(const uint16_t* __re
   } else {
     const int t0 = th * (TILE / 2);
     if (n0 + t0 >= nv) return;
-    fwd_part<kTail, 2, 1>(smem, wt, ldw, vl, Hv + (int64_t)(n0 + t0) * ldh, ldh, nv - n0 - t0, d, om + t0, os + t0, scale2);
+    fwd_part<kTail, 2, 1>(smem, wt, ldw, vl, Hv + (int64_t)(n0 + t0) * ldh, ldh, nv - n0 - t0, d, om + t0, os + t0,
+                          scale2);
   }
 }
 
@@ -1113,9 +1118,15 @@ __device__ __forceinline__ float grad_scale(const float* grad, const int* n_norm
 // ---------------------------------------------------------------------------------------------
 // K4: softmax-gradient tile for one vocabulary slab. Tile (vocabulary tile tm, token tile tn) of
 // S^T = W_slab Hv^T is recomputed and turned into G = c (exp(s - lse) - onehot), rounded to
-// bf16 and written as G[token][v] (row stride vc). Every tile is written whole: entries of tokens
-// at or beyond Nv and of ids at or beyond the slab width are zeros, so the two contractions that
-// read G (dH with K = ids, dW with K = tokens, G read K-major) need no masking of G.
+// bf16 and written as G[token][v] (row stride vc). A tile, or a part of one, is written whole: entries of
+// tokens at or beyond Nv and of ids at or beyond the slab width vs are zeros. Parts without such a token
+// or id at all, and the second half of a last token tile of at most 128 tokens, are not written; neither
+// contraction that reads G needs a mask for them:
+//  - dH (K = ids) takes the rows below Nv only, and along K the 16-byte chunks that start below vs; parts are
+//    192 ids, so the last chunk lies in a part that is written;
+//  - dW (K = tokens, G read K-major) takes the tokens below round_up(Nv, 64), which lie in the same 128 as
+//    token Nv - 1, and of the ids at or beyond vs it may read what is left there, but forms only rows of dW
+//    past the slab from it, which are not stored.
 // ---------------------------------------------------------------------------------------------
 // One tile or part of the LCE gradient: the vleft ids from W row wt on (target of a token: id tbase), the tleft
 // tokens of Hv / idx from ht / idx0 on, G from element (first token, first id) on (row stride vc).
@@ -1502,8 +1513,8 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_kd_tile(const uint16_t* __r
 
 // K5: dW[v0 + m][dd] = sum_k G[k][m] Hv[k][dd] over k < round_up(Nv, 64), G [Npad][vc] and the
 // gathered valid rows Hv [Npad][D] both read K-major (transposing LDS reads); tiles of (128 WM)
-// ids x 256 hidden columns. The epilogue either writes the block in bf16 (each element once), adds it to the bf16
-// values already there, or hands each bf16-rounded element straight to the AdamW update of W (the
+// ids x 256 hidden columns. The epilogue either writes the block in bf16 (each element once), adds it to the
+// bf16 values already there, or hands each bf16-rounded element straight to the AdamW update of W (the
 // in-backward step). Its accesses go through buffer resources over the tile's rows below the slab
 // width (rows past it read 0 and drop their stores): a per-lane 32-bit offset and a wave-uniform
 // row offset per element, so that the accumulators are nearly the only registers it holds.
@@ -1876,9 +1887,10 @@ __global__ __launch_bounds__(256) void k_adamw(int64_t v, int d, const uint16_t*
 // one row of values per token, written unless this is the last slab), and behind the last slab turned into
 // both log-sum-exps and the loss l = lse_s - sum_v p_t(v) zs(v); terms (compact order) feed the mean / sum,
 // per_token (row order) is the "none" output. So the values of one slab's tiles are held at a time, 20 bytes
-// per 256 ids and token. A workgroup of 16 waves serves 16 tokens: a wave's four groups of 16 lanes fold every 64th tile
-// (64-byte reads along the tokens), then the groups and the waves are merged in a fixed order. (One
-// thread per token and a serial fold left most CUs idle: 4096 tokens, 501 tiles: 417 us, now 31.)
+// per 256 ids and token. A workgroup of 16 waves serves 16 tokens: a wave's four groups of 16 lanes fold every
+// 64th tile (64-byte reads along the tokens), then the groups and the waves are merged in a fixed order. (One
+// thread per token and a serial fold left most CUs idle: 4096 tokens, 501 tiles: 417 us, now 20 in one slab and
+// 50 in five.)
 constexpr int kKdTok = 16;
 
 __global__ __launch_bounds__(1024) void k_kd_combine(const float* __restrict__ part, int tiles, int64_t ldp,
@@ -1941,10 +1953,10 @@ __global__ __launch_bounds__(1024) void k_kd_combine(const float* __restrict__ p
 // Host side: validation, plan, workspace carve-up, launches, optional timing.
 // ---------------------------------------------------------------------------------------------
 enum KernelId { K_COMPACT = 0, K_FWD_STATS, K_COMBINE, K_LOSS, K_GATHER_H, K_BWD_G,
-                K_BWD_DW, K_BWD_DH, K_BWD_DHDW, K_DH_FINAL, K_ADAMW, K_SHARD_COMBINE, K_KD_Z, K_KD_STATS, K_KD_COMBINE, K_KD_P, K_MISC,
-                K_COUNT };
-const char* const kKernelNames[K_COUNT] = {"compact", "fwd_stats", "combine", "loss", "gather_h",
-                                           "bwd_g", "bwd_dw", "bwd_dh", "bwd_dhdw", "dh_finalize", "adamw", "shard_combine",
+                K_BWD_DW, K_BWD_DH, K_BWD_DHDW, K_DH_FINAL, K_ADAMW, K_SHARD_COMBINE,
+                K_KD_Z, K_KD_STATS, K_KD_COMBINE, K_KD_P, K_MISC, K_COUNT };
+const char* const kKernelNames[K_COUNT] = {"compact", "fwd_stats", "combine", "loss", "gather_h", "bwd_g",
+                                           "bwd_dw", "bwd_dh", "bwd_dhdw", "dh_finalize", "adamw", "shard_combine",
                                            "kd_teacher_z", "kd_student_stats", "kd_combine", "kd_teacher_p", "misc"};
 
 struct Timing {
@@ -2346,7 +2358,8 @@ lce_status_t forward_impl(const lce_problem_t* p, const ShardInfo* shard, const 
   const int ctok = wide_combine(pl) ? 64 : 16;
   L(K_COMBINE, ctok == 64 ? k_combine<64> : k_combine<16>, dim3((unsigned)((pl.n + ctok - 1) / ctok)), dim3(1024), h,
     pl.ldh, w, pl.ldw, targets, p->target_bytes, si.v_begin, pl.v, (const int*)idx, (const int*)nv, (int)pl.d,
-    pr.count, pr.split, pr.m, pr.s, (int)pl.npad, pr.run_m, pr.run_s, lse, terms, none ? loss : (float*)nullptr, tgt_part);
+    pr.count, pr.split, pr.m, pr.s, (int)pl.npad, pr.run_m, pr.run_s, lse, terms, none ? loss : (float*)nullptr,
+    tgt_part);
   if (!none && !shard) L(K_LOSS, k_loss, dim3(1), dim3(1024), (const float*)terms, (const int*)nv, p->reduction, loss);
   return L.st;
 }
