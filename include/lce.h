@@ -141,8 +141,8 @@ lce_status_t lce_workspace_size(const lce_problem_t* p, size_t* fwd_bytes, size_
 lce_status_t lce_workspace_size_least(const lce_problem_t* p, size_t* fwd_bytes, size_t* bwd_bytes);
 
 /*
- * Layout of the workspace that lce_forward and lce_backward carve for problem p, for tests and
- * tools that check it (host only; nothing is launched). Offsets and sizes are in bytes from the
+ * Layout of the workspace that lce_forward and lce_backward carve for problem p when it holds the
+ * reported bytes, for tests and tools that check it (host only; nothing is launched). Offsets and sizes are in bytes from the
  * workspace start; rows in elements. A prefix is shared by both passes: the valid-row list idx
  * and inverse map pos ([npad] int32 each), the count Nv, and the gathered valid rows of H
  * ([npad][d] bf16). The forward then holds its vocabulary partial pairs (two [part_rows][npad]

@@ -2035,7 +2035,7 @@ int64_t whole_round_slab(int64_t v, int64_t d, int64_t vc) {
 // which the last, partial one costs most of a round, and every slab pays its launches and a pass over
 // the fp32 dH accumulators. When a slab has at most 1024 tiles of 384 ids x 256 tokens (4 rounds of 256
 // CUs), the vocabulary is cut into as few equal slabs as keep G within kFewTokenG, whatever V: one
-// where [N, V] itself is that small, 1984 tokens of a 131072-id vocabulary. Measured, the rule's slabs, these,
+// where [N, V] itself is that small, 1792 tokens of a 128256-id vocabulary. Measured, the rule's slabs, these,
 // and as few as 1280 MiB allow (a matrix as large as the bf16 logits; us per step and backward workspace):
 //   2048 x 4096 x 128256:        5490 us  313 MiB, 5200 us  516 MiB, 5180 us  796 MiB;
 //   1948 x 3584 x 152064:        5515 us  326 MiB, 5225 us  569 MiB, 5150 us  903 MiB;
@@ -2121,7 +2121,6 @@ void plan_backward(Plan* pl, bool least) {
   pl->o_dh32b = pl->dh_kz > 1 ? pl->o_dh32 + part : 0;
   pl->bwd_bytes = cur;
 }
-
 
 lce_status_t make_plan(const lce_problem_t* p, Plan* pl, bool wide_slabs = true) {
   if (!p) return LCE_ERR_NULL;
@@ -2478,9 +2477,10 @@ lce_status_t backward_impl(const lce_problem_t* p, const ShardInfo* shard, const
   // the W rows that dH reads) up to kMergeTiles dH tiles, 3 rounds of the CUs, of all N tokens. One launch
   // against two, dH + dW: 4096 tokens of a 16032 x 8192 shard (352 tiles) 1706 -> 1283 us; 8192 x 8192 x
   // 64000 (704) 11.5 -> 10.4 ms; 1948 x 3584 x 152064 (84) 2630 -> 2545 us; 256 x 512 x 4096 (2) 48 -> 25 us;
-  // 16384 x 4096 x 128256 (688) the same within 1 %; narrow heads with many tokens (256 to 1024 wide, 8192
-  // to 32768 tokens, 43 to 344 tiles) 1 to 25 % less; but 32768 x 3584 x 152064 (1204, several dH rounds
-  // anyway) 37.9 -> 38.3 ms.
+  // 16384 x 4096 x 128256 (688) the same within 1 %; 16384 x 4352 x 100000 (731) 21.0 -> 19.5 ms; 24576 x 3072
+  // x 32768 (768) 6050 -> 5580 us, x 128256 the same; narrow heads with many tokens (256 to 1024 wide, 8192 to
+  // 32768 tokens, 43 to 344 tiles) 1 to 25 % less; but 32768 x 3584 x 152064 (1204, several dH rounds anyway)
+  // 37.9 -> 38.3 ms.
   static_assert(kDhWM == kDwWM, "one launch runs both");
   constexpr int kMergeTiles = 768;
   const bool merge = !adamw && want == (WANT_DH | WANT_DW) && (int64_t)dh_tiles * dt <= kMergeTiles;
