@@ -1772,7 +1772,7 @@ __global__ __launch_bounds__(Geo<WM>::NT, WM) void k_bwd_dhdw(const uint16_t* __
                                                              uint16_t* __restrict__ dW, int64_t v0) {
   static_assert(kMode != DW_ADAMW, "the optimizer step of dW updates the W rows that dH reads");
   __shared__ __attribute__((aligned(16))) char smem[Geo<WM>::LDS];
-  const int b = dhdw_block((int)blockIdx.x, dh_blocks, (int)gridDim.x - dh_blocks, dw_first(*nv_ptr, d, kz, vs));
+  const int b = dhdw_block((int)blockIdx.x, dh_blocks, (int)gridDim.x - dh_blocks, dw_first(*nv_ptr, kz, vs));
   if (b < dh_blocks)
     dh_tile<WM>(smem, b, G, vc, vs, Ws, ldw, ws_rows, d, nv_ptr, dH32, accumulate, kz, dH32b, acc_rows);
   else

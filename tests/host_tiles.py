@@ -39,7 +39,7 @@ int t_dh_grid(int64_t npad, int d, int kz_max) { return dh_grid(npad, d, kz_max)
 int t_dw_grid(int tm_count, int d) { return dw_grid(tm_count, d); }
 int t_dh_k_range(int vs, int kz, int z, int* o) { o[1] = dh_k_range(vs, kz, z, o[0]); return 1; }
 int t_dw_unit(int blk, int tm_count, int d, int* o) { return dw_unit(blk, tm_count, d, o[0], o[1]); }
-int t_dw_first(int nv, int d, int kz_max, int vs) { return dw_first(nv, d, kz_max, vs); }
+int t_dw_first(int nv, int kz_max, int vs) { return dw_first(nv, kz_max, vs); }
 int t_dhdw_block(int b, int dh_blocks, int dw_blocks, int first) { return dhdw_block(b, dh_blocks, dw_blocks, first); }
 int t_lane_chunk(int lane) { return lane_chunk(lane); }
 int t_chunk_exists(int lane, int q, int k0, int K) { return chunk_exists(lane, q, k0, K); }
@@ -105,8 +105,8 @@ def dw_unit(blk, tm_count, d):
     return _call("t_dw_unit", 2, blk, tm_count, d)
 
 
-def dw_first(nv, d, kz_max, vs):
-    return bool(_lib().t_dw_first(nv, d, kz_max, vs))
+def dw_first(nv, kz_max, vs):
+    return bool(_lib().t_dw_first(nv, kz_max, vs))
 
 
 def dhdw_block(b, dh_blocks, dw_blocks, first):

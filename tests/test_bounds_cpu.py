@@ -568,12 +568,10 @@ def test_distillation_workspaces_of_the_former_sizes_still_hold_every_call(dt):
 def test_the_merged_launch_runs_every_block_of_both_and_starts_the_longer_units(n, d, v, nv):
     info = B.lce_plan_info(B.problem(n, d, v))
     dh, dw = T.dh_grid(n, d, info["dh_kz"]), T.dw_grid(cdiv(v, 384), d)
-    first = T.dw_first(nv, d, info["dh_kz"], v)
+    first = T.dw_first(nv, info["dh_kz"], v)
     got = [T.dhdw_block(b, dh, dw, first) for b in range(dh + dw)]
     assert sorted(got) == list(range(dh + dw))
     for b, g in enumerate(got):
         assert (g if g < dh else g - dh) % 8 == b % 8              # each block of either launch keeps its XCD
-    units = [u for u in (T.dh_unit(b, nv, d, info["dh_kz"], info["rows_g"]) for b in range(dh)) if u]
-    parts = units[0][3] if units and info["dh_kz"] > 1 else 1
-    assert first == (nv * parts > v)                                # dW's K against that of a dH unit
+    assert first == (nv * info["dh_kz"] > v)                        # dW's K against that of a dH unit's most parts
     assert (got[0] >= dh) == first
