@@ -969,29 +969,38 @@ __global__ __launch_bounds__(1024) void k_combine(const uint16_t* __restrict__ H
   // this wave's kTok / 16 tokens side by side, so that their chains of loads (row, target, operands) overlap
   constexpr int kPer = kTok / 16;
   int row_p[kPer];
-  int64_t tl[kPer];
   float dot_p[kPer];
 #pragma unroll
   for (int p = 0; p < kPer; ++p) row_p[p] = i0 + wave * kPer + p < nv ? idx[i0 + wave * kPer + p] : -1;
   // target id relative to this W's first row (id0 > 0 only for a vocabulary shard, which may
   // not hold the target: then its target logit is 0)
+  const uint4* hr[kPer];
+  const uint4* wt[kPer];
+  bool in[kPer], any = false;
 #pragma unroll
   for (int p = 0; p < kPer; ++p) {
-    tl[p] = row_p[p] >= 0 ? load_target(targets, tbytes, row_p[p]) - id0 : -1;
+    const int64_t tl = row_p[p] >= 0 ? load_target(targets, tbytes, row_p[p]) - id0 : -1;
+    in[p] = tl >= 0 && tl < v_local;
+    any |= in[p];
+    hr[p] = reinterpret_cast<const uint4*>(H + (int64_t)(in[p] ? row_p[p] : 0) * ldh);
+    wt[p] = reinterpret_cast<const uint4*>(W + (in[p] ? tl : 0) * ldw);
     dot_p[p] = 0.f;
   }
-#pragma unroll kPer == 1 ? 4 : 1
-  for (int c = lane; c < d / 8; c += 64) {
+  if (any) {
+    // two chunks in flight: with four, the registers leave one workgroup a CU (16384 x 1024 x 128256 39 us, so 29;
+    // 700 x 4096 x 5000 10.0 against 10.4)
+#pragma unroll kPer == 1 ? 2 : 1
+    for (int c = lane; c < d / 8; c += 64) {
 #pragma unroll
-    for (int p = 0; p < kPer; ++p) {
-      if (tl[p] < 0 || tl[p] >= v_local) continue;
-      const uint4 a = reinterpret_cast<const uint4*>(H + (int64_t)row_p[p] * ldh)[c];
-      const uint4 b = reinterpret_cast<const uint4*>(W + tl[p] * ldw)[c];
-      const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+      for (int p = 0; p < kPer; ++p) {
+        if (kPer > 1 && !in[p]) continue;
+        const uint4 a = hr[p][c], b = wt[p][c];
+        const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        dot_p[p] = fmaf(bf16_to_f32(av[q] & 0xFFFF), bf16_to_f32(bv[q] & 0xFFFF), dot_p[p]);
-        dot_p[p] = fmaf(bf16_to_f32(av[q] >> 16), bf16_to_f32(bv[q] >> 16), dot_p[p]);
+        for (int q = 0; q < 4; ++q) {
+          dot_p[p] = fmaf(bf16_to_f32(av[q] & 0xFFFF), bf16_to_f32(bv[q] & 0xFFFF), dot_p[p]);
+          dot_p[p] = fmaf(bf16_to_f32(av[q] >> 16), bf16_to_f32(bv[q] >> 16), dot_p[p]);
+        }
       }
     }
   }
